@@ -49,3 +49,25 @@ def test_volume_gradient_range_edges(sizes):
         want = gV[h].astype(np.float64) * dV + gA[h].astype(np.float64) * dA
         got = g[off[h]:off[h + 1]]
         assert np.linalg.norm(got - want) <= 1e-4 * np.linalg.norm(want)
+
+
+# an edge from a point to itself is its own twin; a third half-edge of an edge
+# is an error whichever arrives last; a table of one slot group
+@pytest.mark.parametrize("faces,want", [
+    ([[0, 0, 1]], [[0, 0, 0]]),
+    ([[0, 1, 2]], [[-1, -1, -1]]),
+    ([[0, 1, 2], [2, 1, 0]], [[1, 1, 1], [1 - 1, 0, 0]]),
+    ([[0, 1, 2], [1, 0, 3], [0, 1, 4]], None),
+    ([[0, 0, 1], [0, 0, 2]], None)])
+def test_adjacency_small_tables(faces, want):
+    import torch
+    from paper_1205_1171_amd import hull
+    f = torch.tensor(faces, dtype=torch.int32, device="cuda")
+    say("adjacency", faces)
+    if want is None:
+        with pytest.raises(hull.HullError):
+            hull.face_adjacency(f)
+        return
+    adj, open_edges = hull.face_adjacency(f)
+    assert adj.cpu().tolist() == want
+    assert open_edges == sum(x < 0 for row in want for x in row)
