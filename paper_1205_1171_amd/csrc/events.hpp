@@ -229,36 +229,28 @@ __device__ __forceinline__ int tri_cmp_mid_body(const WPt* pts, Tri A, Tri B, in
   return s ? s : tri_cmp_exact(pts, A, B, zs);
 }
 
-// The mid tier as a call (kernels with many live registers) ...
+// Order of two events that the filter on stored times cannot tell apart:
+// 0 for the same triple, else the standard parts once more in double (a stored
+// time is a float), then the mid tier.  A call: kernels with many live
+// registers.
 template <class PT>
-__device__ __noinline__ int tri_cmp_mid(const PT* pts, Tri A, Tri B, int zs) {
-  return tri_cmp_mid_body(pts, A, B, zs);
+__device__ __noinline__ int tri_cmp_near(const PT* pts, Tri A, Tri B, int zs) {
+  if (A.a == B.a && A.w == B.w && A.b == B.b) return 0;
+  const int s = std_cmp_fine(tau_std(pts[A.a], pts[A.w], pts[A.b], zs),
+                             tau_std(pts[B.a], pts[B.w], pts[B.b], zs));
+  return s ? s : tri_cmp_mid_body(pts, A, B, zs);
 }
 
-// Order of two events: 0 for the same triple, else the standard-part filter,
-// then the mid tier (inlined with kInlineMid: the lane-serial merge, where
-// exact standard-part ties are frequent and a call costs more than the
-// registers).
+// Order of two events: the standard-part filter, then (rare) tri_cmp_near, or
+// with kInlineMid the mid tier inline (the lane-serial merge, where exact
+// standard-part ties are frequent and a call costs more than the registers).
 template <bool kInlineMid = false, class PT>
 __device__ __forceinline__ int ev_cmp(const PT* pts, const Cand& A, const Cand& B, int zs) {
-  if (A.t.a == B.t.a && A.t.w == B.t.w && A.t.b == B.t.b) return 0;
-  int s = std_cmp(A.st, B.st);
-  if (s) return s;
-  return kInlineMid ? tri_cmp_mid_body(pts, A.t, B.t, zs) : tri_cmp_mid(pts, A.t, B.t, zs);
-}
-
-// The same order for callers that hold both triples' points (A's as a0, a1,
-// a2 and B's as b0, b1, b2, in rank order): the mid tier then needs no loads
-// and no call; only the full cascade (rare) reloads them.
-template <class PT>
-__device__ __forceinline__ int ev_cmp_pts(const PT* pts, const Cand& A, const PT& a0, const PT& a1,
-                                          const PT& a2, const Cand& B, const PT& b0, const PT& b1,
-                                          const PT& b2, int zs) {
-  if (A.t.a == B.t.a && A.t.w == B.t.w && A.t.b == B.t.b) return 0;
   const int s = std_cmp(A.st, B.st);
   if (s) return s;
-  const int m = lead_cmp(lead_of(a0, a1, a2, zs), lead_of(b0, b1, b2, zs));
-  return m ? m : tri_cmp_exact(pts, A.t, B.t, zs);
+  if (!kInlineMid) return tri_cmp_near(pts, A.t, B.t, zs);
+  if (A.t.a == B.t.a && A.t.w == B.t.w && A.t.b == B.t.b) return 0;
+  return tri_cmp_mid_body(pts, A.t, B.t, zs);
 }
 
 // The same for a candidate A whose points the caller holds (a0, a1, a2) against
@@ -266,9 +258,9 @@ __device__ __forceinline__ int ev_cmp_pts(const PT* pts, const Cand& A, const PT
 template <class PT>
 __device__ __forceinline__ int ev_cmp_half(const PT* pts, const Cand& A, const PT& a0, const PT& a1,
                                            const PT& a2, const Cand& B, int zs) {
-  if (A.t.a == B.t.a && A.t.w == B.t.w && A.t.b == B.t.b) return 0;
   const int s = std_cmp(A.st, B.st);
   if (s) return s;
+  if (A.t.a == B.t.a && A.t.w == B.t.w && A.t.b == B.t.b) return 0;
   const int m = lead_cmp(lead_of(a0, a1, a2, zs), lead_of(pts[B.t.a], pts[B.t.w], pts[B.t.b], zs));
   return m ? m : tri_cmp_exact(pts, A.t, B.t, zs);
 }
@@ -282,23 +274,14 @@ __device__ __noinline__ int d_sign_slow(PT P, PT Q, PT R) {
 }
 
 // Perturbed sign of D(a, b, c) (xy orientation).
-__device__ __forceinline__ int d_sign(int4 P, int4 Q, int4 R) {
-  const int dy1 = dif32(Q.y, P.y), dy2 = dif32(R.y, P.y);
-  const int64_t D0 = mul32(dif32(Q.x, P.x), dy2) - mul32(dif32(R.x, P.x), dy1);
-  if (D0) return D0 > 0 ? 1 : -1;
-  const int64_t D1 = mul32(Q.w - P.w, dy2) - mul32(R.w - P.w, dy1);
-  if (D1) return D1 > 0 ? 1 : -1;
-  return d_sign_slow(P, Q, R);
-}
-
-// The same on the wide range (D0 up to 2^63: int128; D1 up to 2^58).
-__device__ __forceinline__ int d_sign(const WPt& P, const WPt& Q, const WPt& R) {
-  const int64_t dy1 = (int64_t)Q.y - P.y, dy2 = (int64_t)R.y - P.y;
-  const i128 D0 = (i128)((int64_t)Q.x - P.x) * dy2 - (i128)((int64_t)R.x - P.x) * dy1;
-  if (D0) return D0 > 0 ? 1 : -1;
-  const int64_t D1 = (int64_t)(Q.w - P.w) * dy2 - (int64_t)(R.w - P.w) * dy1;
-  if (D1) return D1 > 0 ? 1 : -1;
-  return d_sign_slow(P, Q, R);
+template <class PT>
+__device__ __forceinline__ int d_sign(const PT& P, const PT& Q, const PT& R) {
+  const Dif q = dif_of(P, Q), r = dif_of(P, R);
+  const double D0 = det2(q.x, r.y, r.x, q.y);
+  if (D0 != 0) return D0 > 0 ? 1 : -1;
+  const double D1 = det2((double)(Q.w - P.w), r.y, (double)(R.w - P.w), q.y);
+  if (D1 != 0) return D1 > 0 ? 1 : -1;
+  return d_sign_slow<PT>(P, Q, R);
 }
 
 template <class PT>

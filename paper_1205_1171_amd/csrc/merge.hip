@@ -29,6 +29,7 @@
 
 #include "common.hpp"
 #include "events.hpp"
+#include "merge_tile.hpp"
 #include "merge_wave.hpp"
 
 namespace hull {
@@ -321,6 +322,32 @@ constexpr int64_t kOrderMinMerges = 32768;
 // Lane-group levels of at most this many merges (both runs) hold the merge's
 // points in LDS as well as its links.
 constexpr int kPtsLdsMerges = 1024;
+
+// Segments in LDS (k_merge_tile) against one lane or lane group per merge: a
+// segment's chain is short whatever the block's size, but every segment adds
+// a tangent search, so lane-serial merges win where they fill the chip by
+// themselves.  Measured per level (us, tile / lane-serial or lane group):
+// 60,001-point sphere, one run: level 4 71 / 55, 5 58 / 100, 6 57 / 153, 8 66
+// / 385, 10 73 / 1209; 2^20-point sphere, both runs: 4 (131,072 merges)
+// 704 / 253, 5 443 / 374, 6 (32,768) 431 / 588, 8 347 / 710, 10 598 / 1732.
+// Calls of many points of which few are vertices (2^24, 1% on a sphere) have
+// few events per block, and the tile's loads and list bounds, which cover all
+// points, then cost more than the walks they serve: level 10 6.8 ms / 2.6,
+// 11 3.5 / 1.9.
+constexpr int kTileFromLevel = 5;
+constexpr int64_t kTileMerges = 49152;
+constexpr int64_t kTilePoints = int64_t(1) << 21;
+constexpr int kMaxLevels = 28;
+constexpr int kTileLevels = 11;  // kTileMaxWidth
+
+// Lanes per merge of a tile level of width W: hulls whose points are nearly
+// all vertices have about W child events, so W / 4 segments of the default
+// length; twice as many lanes take the larger movies in one round.
+static int tile_lanes(int W) {
+  int gs = 16;
+  while (gs < 512 && gs < W / 2) gs *= 2;
+  return gs;
+}
 
 // Bytes of LDS one workgroup may use on the current device (looked up once
 // per device).
@@ -774,6 +801,9 @@ struct Opts {
                    // above them, the links alone)
   int order_from;     // lane-serial levels from this one list their merges in work order
   int64_t order_min;  // ... when the level bounds at least this many merges
+  int tile_levels;  // levels not run lane-serial, up to this one, run their segments in LDS
+  int tile_from;    // ... and, where the caller left serial_max open, levels from this one on
+                    // with fewer than kTileMerges merges (both runs together) do too
   int64_t pts_lds_merges;  // lane-group levels of at most this many merges (both runs
                            // together) hold the points in LDS too, where they fit
 };
@@ -806,6 +836,9 @@ static Opts resolve(const hull_schedule_t* sc, int64_t total) {
   o.lds_links = env_int("HULL_LDS_LINKS", 1) != 0;
   o.order_from = env_int("HULL_ORDER_LEVEL", kOrderFromLevel);
   o.order_min = std::max(env_int("HULL_ORDER_MIN", (int)kOrderMinMerges), 0);
+  o.tile_levels = env_int("HULL_TILE_LEVELS", kTileLevels);
+  const char* sl = getenv("HULL_SERIAL_LEVELS");
+  o.tile_from = (sc && sc->serial_levels >= 0) || (sl && *sl) ? kMaxLevels + 1 : kTileFromLevel;
   o.pts_lds_merges = std::max(env_int("HULL_PTS_LDS_MERGES", kPtsLdsMerges), 0);
   return o;
 }
@@ -897,14 +930,19 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
   for (int k = 1; k <= levels; ++k) {
     A.width = int64_t(1) << k;
     A.half = A.width >> 1;
-    const bool serial = k <= opt.serial_max;
+    const int64_t bound = std::min<int64_t>(pl.mcap, n / A.width + S.H + 1);
+    const bool tile_fits =
+        k <= opt.tile_levels && (opt.tile_from > kMaxLevels || n <= kTilePoints) && A.width <= kTileMaxWidth &&
+        (int64_t)TileLds<PT>::bytes((int)A.width, tile_lanes((int)A.width)) + 256 <= max_lds_bytes();
+    const bool serial =
+        k <= opt.serial_max && !(tile_fits && k >= opt.tile_from && 2 * bound < kTileMerges);
+    const bool tile = !serial && tile_fits;
     // lane groups at this level, and where the working links live
     const bool wave = serial && k > opt.lds_levels && opt.wave_from > 0 && k >= opt.wave_from;
     const int lanes =
         wave ? std::min(opt.wave_lanes_max, opt.wave_lanes << std::min(k - opt.wave_from, 3)) : 0;
     const bool lds_lane = serial && k > opt.lds_levels && !wave && opt.lds_links &&
                           A.width <= kLinkLdsLane;
-    const int64_t bound = std::min<int64_t>(pl.mcap, n / A.width + S.H + 1);
     // points in LDS as well: levels of few merges (each iteration of a long
     // merge then waits on LDS rather than on a cache), when a block fits
     const bool pts_lds = wave && opt.lds_links && 2 * bound <= opt.pts_lds_merges &&
@@ -992,6 +1030,21 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
         hipLaunchKernelGGL(k_merge_level_lk<PT>, g64, dim3(64), lds, s, B);
       } else
         hipLaunchKernelGGL(k_merge_level<PT>, grid, dim3(256), 0, s, B);
+    } else if (tile) {
+      const int W = (int)A.width;
+      const int gs = tile_lanes(W);
+      const int per = gs < 64 ? 64 / gs : 1;
+      const dim3 grid((unsigned)((bound + per - 1) / per), 2);
+      const size_t lds = per * TileLds<PT>::bytes(W, gs);
+#define HULL_TILE(G) \
+  hipLaunchKernelGGL((k_merge_tile<PT, G>), grid, dim3(G < 64 ? 64 : G), lds, s, A, opt.seg)
+      if (gs == 16) HULL_TILE(16);
+      else if (gs == 32) HULL_TILE(32);
+      else if (gs == 64) HULL_TILE(64);
+      else if (gs == 128) HULL_TILE(128);
+      else if (gs == 256) HULL_TILE(256);
+      else HULL_TILE(512);
+#undef HULL_TILE
     } else {
       P.k = k;
       P.run[0].stamp = P.run[1].stamp = k;

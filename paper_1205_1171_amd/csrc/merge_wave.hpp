@@ -241,7 +241,8 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
       valid = (lane == 2 ? nu : lane == 3 ? pu : lane == 4 ? pvv : nv) != kNil;
       if (valid) {
         c = make_cand(pts, a, w, b, pts[a], pts[w], pts[b], (lane == 2 || lane == 4) ? 1 : 0, zs);
-        valid = !haveT || ev_cmp(pts, c, T, zs) > 0;
+        // the move just undone is T itself: no exact comparison for it
+        valid = !haveT || (!(a == T.t.a && w == T.t.w && b == T.t.b) && ev_cmp(pts, c, T, zs) > 0);
       }
     }
     dirty = 0;

@@ -43,7 +43,7 @@ struct Tri {
 struct __align__(16) WPt {
   int x, y, w, pad;
   long long z;
-  long long pad2;
+  double zd;  // z again (exact: below 2^53)
 };
 
 // Range of each coordinate: int32 rows, |c| <= 2^29; int64 rows (the wide
@@ -69,7 +69,7 @@ __device__ __forceinline__ WPt make_pt(const int64_t* xyz, int64_t i, int local)
   q.w = local;
   q.pad = 0;
   q.z = xyz[3 * i + 2];
-  q.pad2 = 0;
+  q.zd = (double)q.z;
   return q;
 }
 
@@ -212,79 +212,89 @@ __device__ __noinline__ int tau_cmp_exact(const Coef& A, const Coef& B) {
 // rejects: no merge runs on them).
 __device__ __forceinline__ int dif32(int a, int b) { return (int)((unsigned)a - (unsigned)b); }
 __device__ __forceinline__ int64_t mul32(int a, int b) { return (int64_t)a * (int64_t)b; }
+// a b - c d in double for operands that are exact: relative error at most
+// 2 * 2^-53 (Kahan's difference of products), so the sign and a zero are
+// exact too.
+__device__ __forceinline__ double det2(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+  const double w = c * d;
+  const double e = __builtin_fma(-c, d, w);
+  const double f = __builtin_fma(a, b, -w);
+  return f + e;
+}
+
+// Coordinate differences as doubles (exact: below 2^53 on either range).
+struct Dif {
+  double x, y, z;
+};
+__device__ __forceinline__ Dif dif_of(int4 P, int4 Q) {
+  return Dif{(double)dif32(Q.x, P.x), (double)dif32(Q.y, P.y), (double)dif32(Q.z, P.z)};
+}
+__device__ __forceinline__ Dif dif_of(const WPt& P, const WPt& Q) {
+  return Dif{(double)Q.x - (double)P.x, (double)Q.y - (double)P.y, Q.zd - P.zd};
+}
+
+// The leading terms N0 and D0 of a triple, each within 2 * 2^-53 relative.
+template <class PT>
+__device__ __forceinline__ void lead_nd(const PT& P, const PT& Q, const PT& R, double& n, double& d) {
+  const Dif q = dif_of(P, Q), r = dif_of(P, R);
+  d = det2(q.x, r.y, r.x, q.y);
+  n = det2(q.x, r.z, r.x, q.z);
+}
+
+// Standard part of tau when D0 = 0: N1 / D1 when N0 = 0 and D1 != 0, else NaN
+// (the exact path then decides every comparison).  Inline in the lane-serial
+// merges: where many points share an x, most triples of the lowest levels
+// come here.
+template <class PT>
+__device__ __forceinline__ double tau_std_flat(const PT& P, const PT& Q, const PT& R, double n, int zs) {
+  if (n != 0) return __builtin_nan("");
+  const Dif q = dif_of(P, Q), r = dif_of(P, R);
+  const double di1 = (double)(Q.w - P.w), di2 = (double)(R.w - P.w);
+  const double D1 = det2(di1, r.y, di2, q.y);
+  if (D1 == 0) return __builtin_nan("");
+  return zs * det2(di1, r.z, di2, q.z) / D1;
+}
+
+// n / d for 1 <= |d| < 2^64: the reciprocal estimate (relative error below
+// 2^-22) and one Newton step (2^-44).  The filter needs 2^-24; the full
+// division costs three times the instructions and was a sixth of a merge
+// step.
+__device__ __forceinline__ double quotient(double n, double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = __builtin_fma(r, __builtin_fma(-d, r, 1.0), r);
+  return n * r;
+}
+
 // Returns the real limit of tau as the epsilons vanish when it is finite and
 // one of the two leading cases holds (D0 != 0, or D0 = N0 = 0 and D1 != 0);
-// NaN otherwise (the exact path then decides every comparison).
-__device__ __forceinline__ double tau_std(int4 P, int4 Q, int4 R, int zs) {
-  const int dx1 = dif32(Q.x, P.x), dx2 = dif32(R.x, P.x);
-  const int dy1 = dif32(Q.y, P.y), dy2 = dif32(R.y, P.y);
-  const int dz1 = dif32(Q.z, P.z), dz2 = dif32(R.z, P.z);
-  const int64_t D0 = mul32(dx1, dy2) - mul32(dx2, dy1);
-  const int64_t N0 = mul32(dx1, dz2) - mul32(dx2, dz1);
-  if (D0 != 0) return (double)(zs * N0) / (double)D0;
-  if (N0 != 0) return __builtin_nan("");
-  const int di1 = Q.w - P.w, di2 = R.w - P.w;
-  const int64_t D1 = mul32(di1, dy2) - mul32(di2, dy1);
-  if (D1 == 0) return __builtin_nan("");
-  const int64_t N1 = mul32(di1, dz2) - mul32(di2, dz1);
-  return (double)(zs * N1) / (double)D1;
-}
-
-// Correctly rounded conversion of an int128 below 2^127 in magnitude: the
-// top 64 bits with a sticky bit for the rest, converted once (the bits below
-// the double's rounding position only decide "above half" versus "exactly
-// half", and the sticky bit keeps that), then scaled exactly.
-__device__ __forceinline__ double to_double(i128 v) {
-  const bool neg = v < 0;
-  const u128 u = neg ? (u128)(-v) : (u128)v;
-  const uint64_t hi = (uint64_t)(u >> 64);
-  double r;
-  if (hi == 0) {
-    r = (double)(uint64_t)u;
-  } else {
-    const int sh = 64 - __builtin_clzll(hi);
-    uint64_t t = (uint64_t)(u >> sh);
-    if ((u << (128 - sh)) != 0) t |= 1;
-    r = ldexp((double)t, sh);
-  }
-  return neg ? -r : r;
-}
-
-// Standard part of tau on the wide range: D0 fits int128 (up to 2^63), N0 up
-// to 2^75, D1 int64 (up to 2^58), N1 up to 2^70; each converted once
-// (correctly rounded) and divided once, so the filter bound below holds as
-// on the standard range.
-__device__ __forceinline__ double tau_std(const WPt& P, const WPt& Q, const WPt& R, int zs) {
-  const int64_t dx1 = (int64_t)Q.x - P.x, dx2 = (int64_t)R.x - P.x;
-  const int64_t dy1 = (int64_t)Q.y - P.y, dy2 = (int64_t)R.y - P.y;
-  const int64_t dz1 = Q.z - P.z, dz2 = R.z - P.z;
-  const i128 D0 = (i128)dx1 * dy2 - (i128)dx2 * dy1;
-  const i128 N0 = (i128)dx1 * dz2 - (i128)dx2 * dz1;
-  if (D0 != 0) return to_double(zs * N0) / to_double(D0);
-  if (N0 != 0) return __builtin_nan("");
-  const int64_t di1 = Q.w - P.w, di2 = R.w - P.w;
-  const int64_t D1 = di1 * dy2 - di2 * dy1;
-  if (D1 == 0) return __builtin_nan("");
-  const i128 N1 = (i128)di1 * dz2 - (i128)di2 * dz1;
-  return to_double(zs * N1) / to_double(D1);
+// NaN otherwise (the exact path then decides every comparison).  Relative
+// error below 2^-43.
+template <class PT>
+__device__ __forceinline__ double tau_std(const PT& P, const PT& Q, const PT& R, int zs) {
+  double n, d;
+  lead_nd(P, Q, R, n, d);
+  if (d != 0) return quotient(zs < 0 ? -n : n, d);
+  return tau_std_flat(P, Q, R, n, zs);
 }
 
 // Does the standard-part filter decide sign(tau_A - tau_B)?  Each standard
-// part is a quotient of two integers below 2^76, each rounded once to double
-// and divided once (relative error at most 3 * 2^-53 (1 + 2^-52)), and the
-// value stored with an event is that double rounded once more to float
-// (2^-24 more): the error of either kind is below 2^-24 + 2^-51 relative,
-// and the quotients stay inside float's normal range (between 2^-76 and
-// 2^76 in magnitude).  A gap larger than 2^-23 (|sa| + |sb|) therefore fixes
-// the sign; the subtraction of two such values is exact or rounds by at most
-// 2^-53 relative, which the margin covers.
+// part is computed within 2^-43 relative, and the value stored with an event
+// is that double rounded once more to float (2^-24 more): the error of either
+// kind is below 2^-24 + 2^-42 relative, and the quotients stay inside float's
+// normal range (between 2^-76 and 2^76 in magnitude).  A gap larger than
+// 2^-23 (|sa| + |sb|) therefore fixes the sign; the subtraction of two such
+// values is exact or rounds by at most 2^-53 relative, which the margin
+// covers.  NaN (not covered) compares false and gives 0.
 __device__ __forceinline__ int std_cmp(double sa, double sb) {
-  if (!(sa == sa) || !(sb == sb)) return 0;  // NaN: not covered
-  double d = sa - sb;
-  double tol = 0x1p-23 * (fabs(sa) + fabs(sb));
-  if (d > tol) return 1;
-  if (-d > tol) return -1;
-  return 0;
+  const double d = sa - sb, tol = 0x1p-23 * (fabs(sa) + fabs(sb));
+  return d > tol ? 1 : (-d > tol ? -1 : 0);
+}
+
+// The same for two values fresh from tau_std (2^-43 each).
+__device__ __forceinline__ int std_cmp_fine(double sa, double sb) {
+  const double d = sa - sb, tol = 0x1p-42 * (fabs(sa) + fabs(sb));
+  return d > tol ? 1 : (-d > tol ? -1 : 0);
 }
 
 }  // namespace hull

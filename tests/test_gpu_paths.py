@@ -71,3 +71,41 @@ def test_adjacency_small_tables(faces, want):
     adj, open_edges = hull.face_adjacency(f)
     assert adj.cpu().tolist() == want
     assert open_edges == sum(x < 0 for row in want for x in row)
+
+
+# The time-segmented merges in LDS (every level up to 11, then none) with
+# segments of the shortest length, of more steps than the counting pass notes
+# and of whole movies; sizes at the edges of blocks and with ragged last blocks.
+@pytest.mark.parametrize("seg", ["4", "16", "1000000"])
+@pytest.mark.parametrize("tile", ["11", "0"])
+def test_segment_walk_movies(monkeypatch, tile, seg):
+    import oracle
+    import torch
+    from paper_1205_1171_amd import hull
+    monkeypatch.setenv("HULL_SERIAL_LEVELS", "0")
+    monkeypatch.setenv("HULL_TILE_LEVELS", tile)
+    monkeypatch.setenv("HULL_WALK_SEGMENT", seg)
+    rng = np.random.default_rng(5)
+    # a cone: the apex is a neighbour of every rim point (one list as long as
+    # the movie); lattices: every kind of tie; a curve whose points are all
+    # vertices
+    rim = workloads.sphere(rng, 600, 1 << 20)
+    rim[:, 2] = 1000
+    cone = np.concatenate([rim, [[3, 5, -(1 << 20)]]]).astype(np.int32)
+    sets = [workloads.sphere(rng, n, 1 << 20) for n in (2, 3, 17, 255, 256, 257, 2047, 2049, 4100)]
+    sets += [cone, workloads.lattice(rng, 700, 3), workloads.lattice(rng, 900, 20),
+             workloads.moment_curve(), workloads.cube(rng, 3000, 1 << 29)]
+    ws = hull.Workspace()
+    for p in sets:
+        p = np.ascontiguousarray(p)
+        L = oracle.levels_for(len(p))
+        x = torch.from_numpy(p).cuda()
+        for run in (0, 1):
+            for level in {L, L // 2 + 1}:
+                say("segment walk", tile, seg, len(p), run, level)
+                ev, bl, _ = hull.movies(x, run, level, ws=ws)
+                want, wbl = oracle.level_movies(p, run, level)
+                w = 1 << min(level, L)
+                assert (bl[::w] == wbl).all()
+                got = np.concatenate([ev[2 * s:2 * s + bl[s]] for s in range(0, len(p), w)])
+                assert (got == want).all()
