@@ -164,7 +164,13 @@ static int table_bits(int64_t F) {
   return bits;
 }
 
-static size_t adj_ws_bytes(int64_t F) { return 256 + (size_t(1) << table_bits(F)) * sizeof(unsigned); }
+// The workspace asked for stays what it was with a table of 16-byte slots, at
+// least 6 per face (callers size buffers by it); the table takes the front of it.
+static size_t adj_ws_bytes(int64_t F) {
+  int bits = 4;
+  while ((int64_t(1) << bits) < 6 * F) ++bits;
+  return 256 + (size_t(16) << bits);
+}
 
 }  // namespace hull
 

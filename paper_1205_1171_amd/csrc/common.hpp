@@ -25,26 +25,25 @@ constexpr int kScanItems = 16;
 constexpr int kScanBlock = kSortThreads * kScanItems;
 constexpr int kStrideBlocks = 1024;  // grid of the grid-stride kernels
 constexpr int kScanDevGrid = 128;    // tile blocks per job of a device-length scan
-constexpr int kSegKeep = 4;  // bridge events a walk segment keeps from its counting pass
+constexpr int kSegKeep = 6;  // bridge events a walk segment keeps from its counting pass
+constexpr int kListScan = 12;  // longest link-change list kept unsorted
 constexpr int kMinWalkSegment = 4;  // fewest child events per walk segment
 constexpr int kWorkBins = 1024;     // child-event counts told apart when ordering merges
 
 // Slots of the per-run counter region of the parallel merge strategy.
-constexpr int kCtrTouched = 2;   // per-point link-change lists allocated this level
-constexpr int kCtrMerges = 4;    // merges of the level
-constexpr int kCtrEvents = 5;    // child events of the level
-constexpr int kCtrSegments = 6;  // walk segments of the level
-constexpr int kCtrBridge = 7;    // bridge events of the level
+constexpr int kCtrMerges = 0;    // merges of the level
+constexpr int kCtrEvents = 1;    // child events of the level
+constexpr int kCtrSegments = 2;  // walk segments of the level
+constexpr int kCtrKeys = 3;      // list bounds of the level (two per point and two more)
+constexpr int kCtrSplice = 4;    // splices pending from the level before, by its parity (2 slots)
 constexpr int kCtrSlots = 8;     // size of the region (int32 words)
-static_assert(kCtrBridge < kCtrSlots, "counter region too small");
 
 // Device-side status words at the head of every workspace.
 struct Header {
   int32_t err;      // first error seen on the device (HULL_* code), 0 = none
   int32_t minx;     // minimum x (sort key origin)
   int32_t maxx;     // maximum x
-  int32_t nbits;    // bits of (maxx - minx): radix passes actually needed
-  int32_t pad[60];  // keeps the header one 256-byte line
+  int32_t pad[61];  // keeps the header one 256-byte line
 };
 
 // One movie event: the face (a, w, b) of ranks a < w < b whose middle vertex w
@@ -69,35 +68,18 @@ __host__ __device__ inline Event make_event(int a, int w, int b, int kind, doubl
   return e;
 }
 
-// A link-change list entry of the parallel merge strategy: the child event's
-// (a, w | kind << 31, b) and a key that is first the event's slot in the input
-// movies (the list's sort key: a movie is in time order) and, once the list
-// is sorted, the bits of its time (the fields of an Event).
-struct __align__(16) Entry {
-  int a;
-  int wk;
-  int b;
-  int key;
-  __host__ __device__ int w() const { return wk & 0x7fffffff; }
-  __host__ __device__ int kind() const { return (int)((unsigned)wk >> 31); }
-};
-
 // Offsets (bytes) of every workspace region for n points in H hulls.
 struct Plan {
   size_t header, keys0, vals0, keys1, vals1, counts, pts, hid, off1;
   size_t pv0[2], nx0[2], lk[2];
   size_t ev[2][2], len[2][2];  // [run][buffer]
-  // the level schedule (merge list, trailing blocks)
-  size_t mcnt, moff, tcnt, toff, tlist, mlist;
+  // the level schedule of a batch (merge list)
+  size_t mcnt, moff, mlist;
   size_t perm[2], wbins[2];  // per run: merges in work order, work histogram
   // parallel merge strategy, per run
-  size_t cntR[2], cntL[2], offR[2], offL[2], curR[2], curL[2], claimR[2], claimL[2];
-  size_t entR[2], entL[2], ctr[2], touched[2];
-  size_t ecnt[2], eoff[2], cslot[2], cmerge[2];
-  size_t segS[2], segBase[2], segMerge[2], segB[2], segCnt[2], segOff[2], segUV[2];
-  size_t segTmp[2], segTmpUV[2];  // the first kSegKeep bridge events of each segment
-  size_t bev[2], buv[2], nB[2], boff[2], uv0[2], surv[2], jb[2], pre[2];
-  size_t aR[2], aL[2], aT[2], wf[2];
+  size_t off[2], ent[2], pos[2], cmerge[2], ctr[2];
+  size_t ecnt[2], eoff[2], segS[2], segBase[2], segMerge[2], segJ[2], segCnt[2], segOff[2];
+  size_t segUV[2], segSteps[2], segKeep[2], uv0[2];
   // status words of the parallel strategy's one-launch scans (kChainJobs x chain_stride)
   size_t chain_words;
   int64_t chain_stride;
@@ -143,15 +125,26 @@ int32_t hull_runs(const int64_t* d_xyz, int64_t n, int32_t* d_faces, int64_t cap
 size_t wide_workspace_bytes(int64_t n);
 size_t f32_workspace_bytes(int64_t n);
 
-// Clear the device status words (a kernel, so that the call can be captured).
-void init_header(Header* h, hipStream_t s);
+// First launch of every call: the device status words, the rank offsets of a
+// single hull (off1, if not null) and the status words of the call's
+// one-launch scans (a kernel, so that the call can be captured).
+void init_call(Header* h, int64_t* off1, int64_t n, char* ws, const Plan& pl, hipStream_t s);
+
+// What the sort prepares for the merges of one run: -inf links and the empty
+// movies of single points (null pv0: the run is not wanted).
+struct RunInit {
+  int* pv0;
+  int* nx0;
+  int* len;
+  int* ctr;
+};
 
 // Sort: ranks by (hull, x, index within the hull).  Fills pts (PT: int4 x, y,
-// z, index within the hull from int32 rows; WPt from int64 rows, by rank).
-// hull_off (device [H + 1]) may be NULL for a single hull.
+// z, index within the hull from int32 rows; WPt from int64 rows, by rank) and
+// the runs' links.  hull_off (device [H + 1]) may be NULL for a single hull.
 template <class InT, class PT>
 int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_t H, char* ws,
-                    const Plan& pl, hipStream_t s);
+                    const Plan& pl, const RunInit* runs, hipStream_t s);
 
 // Exclusive scans of int32 (in place allowed), each in one launch (a chained
 // scan): up to kMaxScanJobs arrays of the same add and cap, each of a length
@@ -178,10 +171,7 @@ int32_t exclusive_scan_chained(const ScanJobs& J, int add, int64_t cap, unsigned
 int32_t scan_chained_i32(const int32_t* in, int32_t* out, int64_t len, unsigned long long* words,
                          int64_t wstride, unsigned epoch, Header* h, hipStream_t s);
 // Epochs of the one-launch scans of a call: the sort's passes 1..8, level k's
-// scans 8k + 1..7, the face offsets kChainEpochFaces.  The sort clears the
+// scans 8k + 1..7, the face offsets kChainEpochFaces.  init_call clears the
 // words at the start of every call.
 constexpr unsigned kChainEpochFaces = 8 * 28 + 1;
-// Zero count 64-bit words (a kernel: capturable).
-void zero_words(unsigned long long* w, int64_t count, hipStream_t s);
-
 }  // namespace hull

@@ -11,19 +11,54 @@ struct Cand {
   int kind;   // 1 insertion, 0 deletion
 };
 
-// Pointers of one run (lower or upper) for the lane-serial merge strategy.
+// Levels of merges that a block of n points has behind it.
+__host__ __device__ inline int levels_of(int64_t n) {
+  return n <= 1 ? 0 : 64 - __builtin_clzll((unsigned long long)(n - 1));
+}
+
+// Pointers of one run (lower or upper).
 // pts: the points by rank, int4 (x, y, z, w) on the standard range or WPt on
 // the wide range (the kernels are instantiated for each).
+// A block's movie sits in the buffer of the last level that merged it: level
+// k writes buffer k & 1, and a block of n points was last merged at level
+// levels_of(n) (an unpaired trailing block waits there for as many levels as
+// it takes).
 struct RunPtrs {
   const void* pts;
   int* pv0;
   int* nx0;
   int2* lk;  // working links of the level: (pv, nx) of each point
-  const Event* ev_in;
-  const int* len_in;
-  Event* ev_out;
-  int* len_out;
+  Event* ev[2];
+  int* len[2];
+  int k;  // the level
   int zs;
+  // The left block of a merge at this level is always a full one.
+  __device__ __forceinline__ const Event* left_ev(int64_t s) const { return ev[(k - 1) & 1] + 2 * s; }
+  __device__ __forceinline__ int left_len(int64_t s) const { return len[(k - 1) & 1][s]; }
+  __device__ __forceinline__ const Event* right_ev(int64_t m, int64_t e) const {
+    return ev[levels_of(e - m) & 1] + 2 * m;
+  }
+  __device__ __forceinline__ int right_len(int64_t m, int64_t e) const {
+    return len[levels_of(e - m) & 1][m];
+  }
+  // Where the right block waits in the buffer that this level writes, its movie
+  // would be overwritten while it is read (the merged movie covers its slots):
+  // it moves to the other buffer first, copied by a group of `size` threads.
+  // The caller's threads must see each other's stores before they read it.
+  __device__ __forceinline__ bool right_waits_in_output(int64_t m, int64_t e) const {
+    return ((levels_of(e - m) ^ k) & 1) == 0;
+  }
+  __device__ __forceinline__ const Event* settle_right(int64_t m, int64_t e, int nR, int rank,
+                                                       int size) const {
+    if (right_waits_in_output(m, e)) {
+      const Event* src = ev[k & 1] + 2 * m;
+      Event* dst = ev[(k - 1) & 1] + 2 * m;
+      for (int q = rank; q < nR; q += size) dst[q] = src[q];
+    }
+    return ev[(k - 1) & 1] + 2 * m;
+  }
+  __device__ __forceinline__ Event* out_ev(int64_t s) const { return ev[k & 1] + 2 * s; }
+  __device__ __forceinline__ int& out_len(int64_t s) const { return len[k & 1][s]; }
 };
 
 // Working links (pv, nx) of a merge's points, in one of three places.  The
@@ -92,17 +127,24 @@ struct LdsLinksShifted {
   }
 };
 
-// The hulls of a call (rank offsets) and the level schedule built for every
-// level on the device: the merges (pairs of adjacent blocks inside a hull)
-// and the unpaired trailing blocks that are copied across.
+// The hulls of a call (rank offsets) and the merges of a level: pairs of
+// adjacent blocks inside a hull.  A single hull's follow from its number of
+// points; a batch's are listed on the device for every level.
 struct Sched {
   const int64_t* off;  // [H + 1] rank offsets of the hulls
   int64_t H;
   int* moff;           // [H + 1] merges before each hull; moff[H] = merges of the level
   int2* mlist;         // [mcap] (s, e) of each merge, m = s + half
-  int* toff;           // [H + 1] trailing blocks before each hull; toff[H] = their count
-  int* tlist;          // [H] trailing block starts
-  int64_t mcap;
+  int k;               // the level
+  __device__ __forceinline__ int64_t merges() const {
+    if (H != 1) return moff[H];
+    return ((off[1] + (int64_t(1) << (k - 1)) - 1) >> (k - 1)) >> 1;
+  }
+  __device__ __forceinline__ int2 merge(int64_t g) const {
+    if (H != 1) return mlist[g];
+    const int64_t s = g << k, e = s + (int64_t(1) << k), n = off[1];
+    return make_int2((int)s, (int)(e < n ? e : n));
+  }
 };
 
 struct LevelArgs {
@@ -111,7 +153,6 @@ struct LevelArgs {
   int* wbins[2];  // per run: histogram, then cursors, of the work order
   Header* h;
   Sched S;
-  int64_t n;
   int64_t half;   // size of a left block
   int64_t width;  // size of a merged block
 };
@@ -314,68 +355,37 @@ __device__ __forceinline__ Cand cand_of(const Event* ev, int64_t q) {
   return c;
 }
 
-// Pointers of one run for the parallel (bridge walk and scatter) strategy.
-// Everything is sized by the events of the level, not by the points: child
-// events are enumerated into a compact list, and per-point lists exist only
-// for the points those events touch.
+// Workspace of one run for the parallel strategy (merge_par.hip).
 struct ParRun {
-  const void* pts;  // int4 or WPt, as in RunPtrs
-  int* pv0;
-  int* nx0;
-  const Event* ev_in;
-  const int* len_in;
-  Event* ev_out;
-  int* len_out;
-  int* cntR;      // per point: # child events changing nx(p)
-  int* cntL;      // per point: # child events changing pv(p)
-  int* offR;      // per point: start of its list
-  int* offL;
-  int* curR;
-  int* curL;
-  int* claimR;    // per point: level that allocated its list
-  int* claimL;
-  int stamp;      // this level's claim stamp: lists of other points are empty
-  Entry* entR;    // link-change events grouped by point, time-sorted (by slot)
-  Entry* entL;
-  int* ctr;       // [kCtrSlots]: touched lists; level totals of merges, child events,
-                  // walk segments, bridge events
-  int* touched;   // (point << 1 | side) of every allocated list
+  int* off;       // [2 (n + 1)] bounds of the link-change lists: next links of point p at
+                  // p, prev links at n + 1 + p
+  int2* ent;      // list entries: (position in the child movie, the link after it)
+  int4* pos;      // per child event: its places in the lists of a, b, w, w
+  int* cmerge;    // per child event: its merge
+  int* ctr;       // [kCtrSlots]: level totals
   int* ecnt;      // per merge: child events (mcap + 1)
   int* eoff;      // exclusive scan of ecnt
-  int* cslot;     // per child event: its slot in the input movies
-  int* cmerge;    // per child event: its merge
-  int* segS;      // per merge: # time segments of its bridge walk
+  int* segS;      // per merge: # time segments of its walk
   int* segBase;   // exclusive scan of segS
   int* segMerge;  // per segment: its merge
-  int* segB;      // per segment: input-movie slot of the child event it starts after (-1: -inf)
-  int* segCnt;    // per segment: # bridge events
+  int* segJ;      // per segment: left events before it
+  int* segCnt;    // per segment: # events it puts out
   int* segOff;    // exclusive scan of segCnt
-  int2* segUV;    // per segment: the bridge at its start (found by the counting pass)
-  Event* segTmp;  // per segment: its first kSegKeep bridge events (counting pass)
-  int2* segTmpUV; // and the bridges after them
-  Event* bev;     // bridge events of merge (s, e) at slots [2s, 2s + nB)
-  int2* buv;      // (u, v) after each bridge event
-  int* nB;        // per merge: # bridge events
-  int* boff;      // exclusive scan of nB
+  int2* segUV;    // per segment: the bridge at its start
+  unsigned long long* segSteps;  // per segment: outcomes of its steps (kStepsLost: not kept)
+  Event* segKeep;                // per segment: its first kSegKeep bridge events
   int2* uv0;      // per merge: the bridge at -inf
-  int* surv;      // per child event: survives into the merged movie (+1 entry)
-  int* jb;        // per child event: # bridge events before it
-  int* pre;       // exclusive scan of surv
-  int* aR;        // per child event: list entries (R side) of the lists it allocates,
-  int* aL;        //   then their start (exclusive scan); L side
-  int* aT;        //   touched lists it allocates, then their start
-  unsigned char* wf;  // per child event: which of its lists it allocates (bits R a, R w, L b, L w)
-  int zs;
 };
 
 struct ParLevel {
-  ParRun run[2];
+  RunPtrs run[2];
+  ParRun par[2];
   Header* h;
   Sched S;
-  int k;            // level: input blocks of 2^(k-1) points, merged blocks of 2^k
+  int64_t n;        // bound on the points
   int seg_events;   // child events per walk segment
   int64_t seg_cap;  // bound on the walk segments of a level
-  int64_t ecap;     // bound on the child events of a level (2n)
+  int64_t mcap;     // bound on the merges of a level
   unsigned long long* chain_words;  // status words of the level's one-launch scans
   int64_t chain_stride;             // (kChainJobs slots), zeroed once per call
 };

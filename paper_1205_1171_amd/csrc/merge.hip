@@ -281,30 +281,30 @@ __device__ __forceinline__ int merge_core(const PT* pts, LK lk, int* pv0, int* n
 
 template <class PT>
 __device__ void merge_one(const RunPtrs& R, Header* h, int64_t s, int64_t m, int64_t e) {
-  const int nL = R.len_in[s], nR = R.len_in[m];
+  const int nL = R.left_len(s), nR = R.right_len(m, e);
   if (nL < 0 || nR < 0 || nL > 2 * (m - s) || nR > 2 * (e - m)) {
     atomicCAS(&h->err, 0, HULL_EINTERNAL);
-    R.len_out[s] = 0;
+    R.out_len(s) = 0;
     return;
   }
-  const int k = merge_core<1>((const PT*)R.pts, GlobalLinks{R.lk}, R.pv0, R.nx0, 0, R.ev_in + 2 * s, nL, R.ev_in + 2 * m, nR,
-                           R.ev_out + 2 * s, h, s, m, e, R.zs);
-  R.len_out[s] = k < 0 ? 0 : k;
+  const int k = merge_core<1>((const PT*)R.pts, GlobalLinks{R.lk}, R.pv0, R.nx0, 0, R.left_ev(s), nL,
+                              R.settle_right(m, e, nR, 0, 1), nR, R.out_ev(s), h, s, m, e, R.zs);
+  R.out_len(s) = k < 0 ? 0 : k;
 }
 
 template <class PT>
 __global__ void __launch_bounds__(256) k_merge_level(LevelArgs A) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts || t >= A.S.moff[A.S.H]) return;
+  if (!R.pts || t >= A.S.merges()) return;
   const int* perm = A.perm[blockIdx.y];
   const int64_t g = perm ? perm[t] : t;
-  const int2 se = A.S.mlist[g];
+  const int2 se = A.S.merge(g);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   // After an error the movies are empty, so that every later kernel still
   // reads lengths that were written.
   if (A.h->err) {
-    R.len_out[s] = 0;
+    R.out_len(s) = 0;
     return;
   }
   merge_one<PT>(R, A.h, s, m, e);
@@ -371,8 +371,8 @@ static int64_t max_lds_bytes() {
 // histogram, scan, placement; the order inside a count is arbitrary and
 // changes nothing but timing (every merge writes only its own block).
 __device__ __forceinline__ int work_bin(const LevelArgs& A, const RunPtrs& R, int64_t g) {
-  const int64_t s = A.S.mlist[g].x;
-  int w = R.len_in[s] + R.len_in[s + A.half];
+  const int2 se = A.S.merge(g);
+  int w = R.left_len(se.x) + R.right_len(se.x + A.half, se.y);
   w = w < 0 ? 0 : (w > kWorkBins - 1 ? kWorkBins - 1 : w);
   return kWorkBins - 1 - w;
 }
@@ -385,7 +385,7 @@ __global__ void __launch_bounds__(256) k_work_clear(LevelArgs A) {
 __global__ void __launch_bounds__(256) k_work_hist(LevelArgs A) {
   __shared__ int hist[kWorkBins];
   const RunPtrs& R = A.run[blockIdx.y];
-  const int64_t M = A.S.moff[A.S.H];
+  const int64_t M = A.S.merges();
   if (!R.pts || blockIdx.x * (int64_t)blockDim.x >= M) return;
   for (int i = threadIdx.x; i < kWorkBins; i += blockDim.x) hist[i] = 0;
   __syncthreads();
@@ -426,7 +426,7 @@ __global__ void __launch_bounds__(256) k_work_place(LevelArgs A) {
   __shared__ int cnt[kWorkBins];
   __shared__ int base[kWorkBins];
   const RunPtrs& R = A.run[blockIdx.y];
-  const int64_t M = A.S.moff[A.S.H];
+  const int64_t M = A.S.merges();
   if (!R.pts || blockIdx.x * (int64_t)blockDim.x >= M) return;
   for (int i = threadIdx.x; i < kWorkBins; i += blockDim.x) cnt[i] = 0;
   __syncthreads();
@@ -454,18 +454,18 @@ __global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
   __shared__ int2 sl[64 * W];
   const RunPtrs& R = A.run[blockIdx.y];
   const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (!R.pts || g >= A.S.moff[A.S.H]) return;
-  const int2 se = A.S.mlist[g];
+  if (!R.pts || g >= A.S.merges()) return;
+  const int2 se = A.S.merge(g);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   if (A.h->err || e - s > W) {
     if (!A.h->err) atomicCAS(&A.h->err, 0, HULL_EINTERNAL);
-    R.len_out[s] = 0;
+    R.out_len(s) = 0;
     return;
   }
-  const int nL = R.len_in[s], nR = R.len_in[m];
+  const int nL = R.left_len(s), nR = R.right_len(m, e);
   if (nL < 0 || nR < 0 || nL > 2 * (m - s) || nR > 2 * (e - m)) {
     atomicCAS(&A.h->err, 0, HULL_EINTERNAL);
-    R.len_out[s] = 0;
+    R.out_len(s) = 0;
     return;
   }
   PT* P = sp + threadIdx.x * W;
@@ -477,9 +477,9 @@ __global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
     const int pv = R.pv0[s + j], nx = R.nx0[s + j];
     K[j] = make_int2(pv == kNil ? kNil : pv - b, nx == kNil ? kNil : nx - b);
   }
-  const int k = merge_core<2>(P, GlobalLinks{K}, R.pv0, R.nx0, b, R.ev_in + 2 * s, nL, R.ev_in + 2 * m, nR,
-                           R.ev_out + 2 * s, A.h, 0, m - s, e - s, R.zs);
-  R.len_out[s] = k < 0 ? 0 : k;
+  const int k = merge_core<2>(P, GlobalLinks{K}, R.pv0, R.nx0, b, R.left_ev(s), nL,
+                           R.settle_right(m, e, nR, 0, 1), nR, R.out_ev(s), A.h, 0, m - s, e - s, R.zs);
+  R.out_len(s) = k < 0 ? 0 : k;
 }
 
 // Lane-serial levels with each lane's working links in LDS as block-local
@@ -493,20 +493,20 @@ __global__ void __launch_bounds__(64) k_merge_level_lk(LevelArgs A) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts || t >= A.S.moff[A.S.H]) return;
+  if (!R.pts || t >= A.S.merges()) return;
   const int* perm = A.perm[blockIdx.y];
   const int64_t g = perm ? perm[t] : t;
-  const int2 se = A.S.mlist[g];
+  const int2 se = A.S.merge(g);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   if (A.h->err) {
-    R.len_out[s] = 0;
+    R.out_len(s) = 0;
     return;
   }
-  const int nL = R.len_in[s], nR = R.len_in[m];
+  const int nL = R.left_len(s), nR = R.right_len(m, e);
   if (nL < 0 || nR < 0 || nL > 2 * (m - s) || nR > 2 * (e - m) || e - s > A.width ||
       A.width > kLinkLdsLane) {
     atomicCAS(&A.h->err, 0, HULL_EINTERNAL);
-    R.len_out[s] = 0;
+    R.out_len(s) = 0;
     return;
   }
   const LdsLinks<signed char, 64> K{(LinkPair<signed char>*)dyn_lds + threadIdx.x};
@@ -525,9 +525,9 @@ __global__ void __launch_bounds__(64) k_merge_level_lk(LevelArgs A) {
     }
   }
   for (; j < w; ++j) K.set(j, local(R.pv0[s + j]), local(R.nx0[s + j]));
-  const int k = merge_core<1>((const PT*)R.pts + s, K, R.pv0, R.nx0, b, R.ev_in + 2 * s, nL,
-                           R.ev_in + 2 * m, nR, R.ev_out + 2 * s, A.h, 0, m - s, e - s, R.zs);
-  R.len_out[s] = k < 0 ? 0 : k;
+  const int k = merge_core<1>((const PT*)R.pts + s, K, R.pv0, R.nx0, b, R.left_ev(s), nL,
+                           R.settle_right(m, e, nR, 0, 1), nR, R.out_ev(s), A.h, 0, m - s, e - s, R.zs);
+  R.out_len(s) = k < 0 ? 0 : k;
 }
 
 // Level 1: the merge of two single points has no events (neither chain has a
@@ -536,46 +536,19 @@ __global__ void __launch_bounds__(64) k_merge_level_lk(LevelArgs A) {
 __global__ void __launch_bounds__(256) k_merge_level1(LevelArgs A) {
   const RunPtrs& R = A.run[blockIdx.y];
   if (!R.pts) return;
-  const int64_t M = A.S.moff[A.S.H];
+  const int64_t M = A.S.merges();
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < M;
        g += (int64_t)gridDim.x * blockDim.x) {
-    const int2 se = A.S.mlist[g];
+    const int2 se = A.S.merge(g);
     const int s = se.x;
-    if (A.h->err || se.y - se.x != 2 || R.len_in[s] != 0 || R.len_in[s + 1] != 0) {
+    if (A.h->err || se.y - se.x != 2 || R.len[0][s] != 0 || R.len[0][s + 1] != 0) {
       if (!A.h->err) atomicCAS(&A.h->err, 0, HULL_EINTERNAL);
-      R.len_out[s] = 0;
+      R.out_len(s) = 0;
       continue;
     }
     R.nx0[s] = s + 1;
     R.pv0[s + 1] = s;
-    R.len_out[s] = 0;
-  }
-}
-
-// The unpaired trailing block of a hull at this level keeps its movie: copy
-// it across (a hull already complete keeps its movie where it is).
-__global__ void __launch_bounds__(256) k_passthrough(LevelArgs A) {
-  const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts) return;
-  const int count = A.S.toff[A.S.H];
-  for (int t = blockIdx.x; t < count; t += gridDim.x) {
-    const int64_t s = A.S.tlist[t];
-    int len = R.len_in[s];
-    if (A.h->err || len < 0 || len > 2 * A.half) len = 0;
-    for (int q = threadIdx.x; q < len; q += blockDim.x) R.ev_out[2 * s + q] = R.ev_in[2 * s + q];
-    if (threadIdx.x == 0) R.len_out[s] = len;
-  }
-}
-
-__global__ void __launch_bounds__(256) k_init_links(int* pv0, int* nx0, int* len, int* claimR,
-                                                    int* claimL, int64_t n) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    pv0[p] = kNil;
-    nx0[p] = kNil;
-    len[p] = 0;
-    claimR[p] = 0;
-    claimL[p] = 0;
+    R.out_len(s) = 0;
   }
 }
 
@@ -587,75 +560,25 @@ __global__ void __launch_bounds__(256) k_copy_links(const int* __restrict__ pv0,
     lk[p] = make_int2(pv0[p], nx0[p]);
 }
 
-__device__ __forceinline__ int dev_levels(int64_t n) {
-  int L = 0;
-  while ((int64_t(1) << L) < n) ++L;
-  return L;
-}
-
-// Level schedule: per hull, merges = floor(blocks / 2) and one trailing
-// block when the number of blocks is odd and above one.
-__global__ void __launch_bounds__(256) k_sched_count(Sched S, int k, int* mcnt, int* tcnt) {
+// Level schedule of a batch: per hull, merges = floor(blocks / 2).
+__global__ void __launch_bounds__(256) k_sched_count(Sched S, int* mcnt) {
   for (int64_t h = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; h <= S.H;
        h += (int64_t)gridDim.x * blockDim.x) {
-    if (h == S.H) {
-      mcnt[h] = 0;
-      tcnt[h] = 0;
-      continue;
-    }
-    const int64_t nh = S.off[h + 1] - S.off[h];
-    const int64_t w = int64_t(1) << (k - 1);
-    const int64_t nb = (nh + w - 1) >> (k - 1);
+    int64_t nb = 0;
+    if (h < S.H) nb = (S.off[h + 1] - S.off[h] + (int64_t(1) << (S.k - 1)) - 1) >> (S.k - 1);
     mcnt[h] = (int)(nb >> 1);
-    tcnt[h] = (nb > 1 && (nb & 1)) ? 1 : 0;
   }
 }
 
-__global__ void __launch_bounds__(256) k_sched_fill(Sched S, int k) {
+__global__ void __launch_bounds__(256) k_sched_fill(Sched S) {
   const int merges = S.moff[S.H];
-  const int64_t width = int64_t(1) << k, w = width >> 1;
+  const int64_t width = int64_t(1) << S.k;
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < merges;
        g += (int64_t)gridDim.x * blockDim.x) {
     const int h = find_owner(S.moff, (int)S.H, g);
     const int64_t s = S.off[h] + (g - S.moff[h]) * width;
     const int64_t e = s + width < S.off[h + 1] ? s + width : S.off[h + 1];
     S.mlist[g] = make_int2((int)s, (int)e);
-  }
-  for (int64_t h = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; h < S.H;
-       h += (int64_t)gridDim.x * blockDim.x) {
-    if (S.toff[h + 1] > S.toff[h]) {
-      const int64_t nh = S.off[h + 1] - S.off[h];
-      const int64_t nb = (nh + w - 1) >> (k - 1);
-      S.tlist[S.toff[h]] = (int)(S.off[h] + (nb - 1) * w);
-    }
-  }
-}
-
-// The same schedule for a single hull of n points in one launch (no scans:
-// merge g covers [g 2^k, min((g + 1) 2^k, n))).
-__global__ void __launch_bounds__(256) k_sched_single(Sched S, int k, int64_t n) {
-  const int64_t width = int64_t(1) << k, w = width >> 1;
-  const int64_t nb = (n + w - 1) >> (k - 1);
-  const int64_t merges = nb >> 1;
-  for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < merges;
-       g += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t s = g * width;
-    S.mlist[g] = make_int2((int)s, (int)(s + width < n ? s + width : n));
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    const int t = (nb > 1 && (nb & 1)) ? 1 : 0;
-    S.moff[0] = 0;
-    S.moff[1] = (int)merges;
-    S.toff[0] = 0;
-    S.toff[1] = t;
-    if (t) S.tlist[0] = (int)((nb - 1) * w);
-  }
-}
-
-__global__ void k_set_off1(int64_t* off, int64_t n) {
-  if (threadIdx.x == 0) {
-    off[0] = 0;
-    off[1] = n;
   }
 }
 
@@ -673,28 +596,18 @@ struct ExtractArgs {
   const Header* h;
 };
 
+__device__ __forceinline__ int face_total(const ExtractArgs& X, int64_t h) {
+  const int64_t o = X.S.off[h], nh = X.S.off[h + 1] - o;
+  if (nh < 3) return 0;
+  const int b = levels_of(nh) & 1;
+  return (X.ev[0][b] ? X.len[0][b][o] : 0) + (X.ev[1][b] ? X.len[1][b][o] : 0);
+}
+
+// Faces per hull of a batch (a single hull's count needs no scan).
 __global__ void __launch_bounds__(256) k_face_count(ExtractArgs X) {
-  const Sched& S = X.S;
-  for (int64_t h = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; h <= S.H;
-       h += (int64_t)gridDim.x * blockDim.x) {
-    int F = 0;
-    if (h < S.H) {
-      const int64_t o = S.off[h], nh = S.off[h + 1] - o;
-      if (nh >= 3) {
-        const int b = dev_levels(nh) & 1;
-        if (X.ev[0][b]) F += X.len[0][b][o];
-        if (X.ev[1][b]) F += X.len[1][b][o];
-      }
-    }
-    if (S.H == 1) {  // offsets [0, F] directly, no scan
-      if (h == 0) {
-        X.fcnt[0] = 0;
-        X.fcnt[1] = F;
-      }
-    } else {
-      X.fcnt[h] = F;
-    }
-  }
+  for (int64_t h = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; h <= X.S.H;
+       h += (int64_t)gridDim.x * blockDim.x)
+    X.fcnt[h] = h < X.S.H ? face_total(X, h) : 0;
 }
 
 // Event (a, w, b) gives the face with the middle vertex w; an insertion has
@@ -705,16 +618,17 @@ template <class PT>
 __global__ void __launch_bounds__(256) k_extract(ExtractArgs X) {
   const PT* pts = (const PT*)X.pts;
   const Sched& S = X.S;
-  const int64_t total = X.fcnt[S.H];
+  const bool single = S.H == 1;
+  const int64_t total = single ? face_total(X, 0) : X.fcnt[S.H];
   const bool over = total > X.cap || total < 0;
   const int err = X.h->err;
   const int64_t F = (over || err) ? 0 : total;
   for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < F;
        t += (int64_t)gridDim.x * blockDim.x) {
-    const int h = find_owner(X.fcnt, (int)S.H, t);
+    const int h = single ? 0 : find_owner(X.fcnt, (int)S.H, t);
     const int64_t o = S.off[h];
-    const int b = dev_levels(S.off[h + 1] - o) & 1;
-    int64_t q = t - X.fcnt[h];
+    const int b = levels_of(S.off[h + 1] - o) & 1;
+    int64_t q = single ? t : t - X.fcnt[h];
     const int nl = X.ev[0][b] ? X.len[0][b][o] : 0;
     const bool lower = q < nl;
     const Event E = lower ? X.ev[0][b][2 * o + q] : X.ev[1][b][2 * o + (q - nl)];
@@ -726,7 +640,7 @@ __global__ void __launch_bounds__(256) k_extract(ExtractArgs X) {
   }
   for (int64_t h = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; h <= S.H;
        h += (int64_t)gridDim.x * blockDim.x)
-    if (X.face_off) X.face_off[h] = (over || err) ? 0 : X.fcnt[h];
+    if (X.face_off) X.face_off[h] = (over || err) ? 0 : (single ? (h ? total : 0) : X.fcnt[h]);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     X.info[0] = err ? err : (over ? HULL_EINTERNAL : 0);
     X.info[1] = F;
@@ -740,24 +654,32 @@ __global__ void k_info_small(int64_t* info, const Header* h) {
   }
 }
 
+struct ExportArgs {
+  const Event* ev[2];  // by buffer
+  const int* len[2];
+  const int4* pts;
+  int64_t n, width;
+  const Header* h;
+};
+__device__ __forceinline__ int export_len(const ExportArgs& X, int64_t s, int& b) {
+  const int64_t w = X.width < X.n - s ? X.width : X.n - s;
+  b = levels_of(w) & 1;
+  const int L = X.h->err ? 0 : X.len[b][s];
+  return L < 0 || L > 2 * w ? 0 : L;
+}
 __global__ void __launch_bounds__(256)
-    k_export_movies(const Event* __restrict__ ev, const int* __restrict__ len,
-                    const int4* __restrict__ pts, int64_t n, int64_t width, int32_t* d_ev,
-                    int32_t* d_block_len, int32_t* d_order, const Header* h) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
+    k_export_movies(ExportArgs X, int32_t* d_ev, int32_t* d_block_len, int32_t* d_order) {
+  int b;
+  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < X.n;
        p += (int64_t)gridDim.x * blockDim.x) {
-    d_order[p] = pts[p].w;
-    bool start = p % width == 0;
-    int L = start && !h->err ? len[p] : 0;
-    if (L < 0 || L > 2 * std::min(width, n - p)) L = 0;
-    d_block_len[p] = L;
+    d_order[p] = X.pts[p].w;
+    d_block_len[p] = p % X.width == 0 ? export_len(X, p, b) : 0;
   }
-  for (int64_t s = 0; s < n; s += width) {
-    int L = h->err ? 0 : len[s];
-    if (L < 0 || L > 2 * std::min(width, n - s)) L = 0;
+  for (int64_t s = 0; s < X.n; s += X.width) {
+    const int L = export_len(X, s, b);
     for (int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; q < L;
          q += (int64_t)gridDim.x * blockDim.x) {
-      Event E = ev[2 * s + q];
+      const Event E = X.ev[b][2 * s + q];
       d_ev[4 * (2 * s + q) + 0] = E.a;
       d_ev[4 * (2 * s + q) + 1] = E.w();
       d_ev[4 * (2 * s + q) + 2] = E.b;
@@ -770,11 +692,7 @@ __global__ void __launch_bounds__(256)
 constexpr int kLdsLevels = 4;
 constexpr int kFirstWaveLevel = 4;
 
-static int levels_for(int64_t n) {
-  int L = 0;
-  while ((int64_t(1) << L) < n) ++L;
-  return L;
-}
+static int levels_for(int64_t n) { return levels_of(n); }
 
 static unsigned grid_for(int64_t work, int64_t cap_blocks = 4096) {
   int64_t b = (work + 255) / 256;
@@ -852,80 +770,50 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
   Sched S = S0;
   S.moff = (int*)(ws + pl.moff);
   S.mlist = (int2*)(ws + pl.mlist);
-  S.toff = (int*)(ws + pl.toff);
-  S.tlist = (int*)(ws + pl.tlist);
-  S.mcap = pl.mcap;
   int* mcnt = (int*)(ws + pl.mcnt);
-  int* tcnt = (int*)(ws + pl.tcnt);
   LevelArgs A{};
   A.h = h;
-  A.S = S;
-  A.n = n;
   ParLevel P{};
   P.h = h;
-  P.S = S;
+  P.n = n;
   P.seg_events = opt.seg;
   P.seg_cap = pl.seg_cap;
-  P.ecap = 2 * n;
-  // the call's one-launch scans tell their status words apart by epoch (the
-  // sort cleared the words at the start of the call)
+  P.mcap = pl.mcap;
+  // the call's one-launch scans tell their status words apart by epoch
+  // (cleared by the call's first launch)
   P.chain_words = (unsigned long long*)(ws + pl.chain_words);
   P.chain_stride = pl.chain_stride;
   for (int r = 0; r < 2; ++r) {
-    bool on = r == 0 ? lower : upper;
+    const bool on = r == 0 ? lower : upper;
     RunPtrs& R = A.run[r];
     R.pts = on ? (const void*)(ws + pl.pts) : nullptr;
     R.pv0 = (int*)(ws + pl.pv0[r]);
     R.nx0 = (int*)(ws + pl.nx0[r]);
     R.lk = (int2*)(ws + pl.lk[r]);
+    for (int b = 0; b < 2; ++b) {
+      R.ev[b] = (Event*)(ws + pl.ev[r][b]);
+      R.len[b] = (int*)(ws + pl.len[r][b]);
+    }
     R.zs = r == 0 ? 1 : -1;
-    ParRun& Q = P.run[r];
-    Q.pts = R.pts;
-    Q.pv0 = R.pv0;
-    Q.nx0 = R.nx0;
-    Q.zs = R.zs;
-    Q.cntR = (int*)(ws + pl.cntR[r]);
-    Q.cntL = (int*)(ws + pl.cntL[r]);
-    Q.offR = (int*)(ws + pl.offR[r]);
-    Q.offL = (int*)(ws + pl.offL[r]);
-    Q.curR = (int*)(ws + pl.curR[r]);
-    Q.curL = (int*)(ws + pl.curL[r]);
-    Q.claimR = (int*)(ws + pl.claimR[r]);
-    Q.claimL = (int*)(ws + pl.claimL[r]);
-    Q.entR = (Entry*)(ws + pl.entR[r]);
-    Q.entL = (Entry*)(ws + pl.entL[r]);
+    ParRun& Q = P.par[r];
+    Q.off = (int*)(ws + pl.off[r]);
+    Q.ent = (int2*)(ws + pl.ent[r]);
+    Q.pos = (int4*)(ws + pl.pos[r]);
+    Q.cmerge = (int*)(ws + pl.cmerge[r]);
     Q.ctr = (int*)(ws + pl.ctr[r]);
-    Q.touched = (int*)(ws + pl.touched[r]);
     Q.ecnt = (int*)(ws + pl.ecnt[r]);
     Q.eoff = (int*)(ws + pl.eoff[r]);
-    Q.cslot = (int*)(ws + pl.cslot[r]);
-    Q.cmerge = (int*)(ws + pl.cmerge[r]);
     Q.segS = (int*)(ws + pl.segS[r]);
     Q.segBase = (int*)(ws + pl.segBase[r]);
     Q.segMerge = (int*)(ws + pl.segMerge[r]);
-    Q.segB = (int*)(ws + pl.segB[r]);
+    Q.segJ = (int*)(ws + pl.segJ[r]);
     Q.segCnt = (int*)(ws + pl.segCnt[r]);
     Q.segOff = (int*)(ws + pl.segOff[r]);
     Q.segUV = (int2*)(ws + pl.segUV[r]);
-    Q.segTmp = (Event*)(ws + pl.segTmp[r]);
-    Q.segTmpUV = (int2*)(ws + pl.segTmpUV[r]);
-    Q.bev = (Event*)(ws + pl.bev[r]);
-    Q.buv = (int2*)(ws + pl.buv[r]);
-    Q.nB = (int*)(ws + pl.nB[r]);
-    Q.boff = (int*)(ws + pl.boff[r]);
+    Q.segSteps = (unsigned long long*)(ws + pl.segSteps[r]);
+    Q.segKeep = (Event*)(ws + pl.segKeep[r]);
     Q.uv0 = (int2*)(ws + pl.uv0[r]);
-    Q.surv = (int*)(ws + pl.surv[r]);
-    Q.jb = (int*)(ws + pl.jb[r]);
-    Q.pre = (int*)(ws + pl.pre[r]);
-    Q.aR = (int*)(ws + pl.aR[r]);
-    Q.aL = (int*)(ws + pl.aL[r]);
-    Q.aT = (int*)(ws + pl.aT[r]);
-    Q.wf = (unsigned char*)(ws + pl.wf[r]);
-    if (on)
-      hipLaunchKernelGGL(k_init_links, dim3(grid_for(n)), dim3(256), 0, s, R.pv0, R.nx0,
-                         (int*)(ws + pl.len[r][0]), Q.claimR, Q.claimL, n);
   }
-  int buf = 0;
   const unsigned hgrid = grid_for(S.H + 1, 1024);
   for (int k = 1; k <= levels; ++k) {
     A.width = int64_t(1) << k;
@@ -953,34 +841,19 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
     const bool lds_group = wave && opt.lds_links && !pts_lds &&
                            (256 / lanes) * A.width * (int64_t)sizeof(LinkPair<short>) <=
                                kLinkLdsGroupBytes;
-    // the schedule of this level
+    S.k = k;
+    A.S = S;
+    for (int r = 0; r < 2; ++r) A.run[r].k = k;
     int32_t rc = HULL_OK;
-    const bool single = S.H == 1;
-    if (single) {
-      hipLaunchKernelGGL(k_sched_single, dim3(grid_for(n / A.width + 1)), dim3(256), 0, s, S, k,
-                         n);
-    } else {
-      hipLaunchKernelGGL(k_sched_count, dim3(hgrid), dim3(256), 0, s, S, k, mcnt, tcnt);
+    if (S.H > 1) {  // the merges of this level of a batch
+      hipLaunchKernelGGL(k_sched_count, dim3(hgrid), dim3(256), 0, s, S, mcnt);
       rc = scan_chained_i32(mcnt, S.moff, S.H + 1, P.chain_words, P.chain_stride,
                             (unsigned)(8 * k + 6), h, s);
-      if (!rc)
-        rc = scan_chained_i32(tcnt, S.toff, S.H + 1, P.chain_words, P.chain_stride,
-                              (unsigned)(8 * k + 7), h, s);
       if (rc) return rc;
-      hipLaunchKernelGGL(k_sched_fill, dim3(grid_for(std::min<int64_t>(pl.mcap, n / A.width + S.H + 1))),
-                         dim3(256), 0, s, S, k);
+      hipLaunchKernelGGL(k_sched_fill, dim3(grid_for(bound)), dim3(256), 0, s, S);
     }
     for (int r = 0; r < 2; ++r) {
-      RunPtrs& R = A.run[r];
-      R.ev_in = (const Event*)(ws + pl.ev[r][buf]);
-      R.len_in = (const int*)(ws + pl.len[r][buf]);
-      R.ev_out = (Event*)(ws + pl.ev[r][buf ^ 1]);
-      R.len_out = (int*)(ws + pl.len[r][buf ^ 1]);
-      ParRun& Q = P.run[r];
-      Q.ev_in = R.ev_in;
-      Q.len_in = R.len_in;
-      Q.ev_out = R.ev_out;
-      Q.len_out = R.len_out;
+      const RunPtrs& R = A.run[r];
       if (R.pts && serial && k > opt.lds_levels && !lds_lane && !lds_group && !pts_lds)
         hipLaunchKernelGGL(k_copy_links, dim3(grid_for(n)), dim3(256), 0, s, R.pv0, R.nx0, R.lk, n);
     }
@@ -1046,20 +919,13 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
       else HULL_TILE(512);
 #undef HULL_TILE
     } else {
-      P.k = k;
-      P.run[0].stamp = P.run[1].stamp = k;
+      P.S = S;
+      for (int r = 0; r < 2; ++r) P.run[r] = A.run[r];
       rc = parallel_level<PT>(P, s);
       if (rc) return rc;
     }
     if (events) (void)hipEventRecord(events[2 * k + 1], s);
-    // a single hull has a trailing block at this level when its block count
-    // is odd and above one
-    const int64_t nb = (n + A.half - 1) / A.half;
-    if (!single || (nb > 1 && (nb & 1)))
-      hipLaunchKernelGGL(k_passthrough, dim3((unsigned)std::min<int64_t>(S.H, 4096), 2), dim3(256),
-                         0, s, A);
     HULL_LAUNCH_CHECK();
-    buf ^= 1;
   }
   return HULL_OK;
 }
@@ -1084,8 +950,8 @@ static int32_t extract(const Sched& S, char* ws, const Plan& pl, hipStream_t s, 
   X.face_off = d_face_off;
   X.info = d_info;
   X.h = (const Header*)(ws + pl.header);
-  hipLaunchKernelGGL(k_face_count, dim3(grid_for(S.H + 1, 1024)), dim3(256), 0, s, X);
-  if (S.H > 1) {  // one hull: k_face_count writes the offsets themselves
+  if (S.H > 1) {
+    hipLaunchKernelGGL(k_face_count, dim3(grid_for(S.H + 1, 1024)), dim3(256), 0, s, X);
     int32_t rc = scan_chained_i32(X.fcnt, X.fcnt, S.H + 1, (unsigned long long*)(ws + pl.chain_words),
                                   pl.chain_stride, kChainEpochFaces, (Header*)(ws + pl.header), s);
     if (rc) return rc;
@@ -1095,6 +961,20 @@ static int32_t extract(const Sched& S, char* ws, const Plan& pl, hipStream_t s, 
   HULL_LAUNCH_CHECK();
   return HULL_OK;
 }
+
+// What the sort prepares for the runs wanted.
+struct RunInits {
+  RunInit r[2];
+  RunInits(char* ws, const Plan& pl, bool lower, bool upper) {
+    for (int q = 0; q < 2; ++q) {
+      const bool on = q == 0 ? lower : upper;
+      r[q].pv0 = on ? (int*)(ws + pl.pv0[q]) : nullptr;
+      r[q].nx0 = (int*)(ws + pl.nx0[q]);
+      r[q].len = (int*)(ws + pl.len[q][0]);
+      r[q].ctr = (int*)(ws + pl.ctr[q]);
+    }
+  }
+};
 
 template <class InT, class PT>
 static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_t cap,
@@ -1111,7 +991,8 @@ static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_
   char* ws = (char*)d_ws;
   Header* h = (Header*)(ws + pl.header);
   if (ev) (void)hipEventRecord(ev[0], s);
-  init_header(h, s);
+  int64_t* off = (int64_t*)(ws + pl.off1);
+  init_call(h, off, n, ws, pl, s);
   if (n < 3) {
     hipLaunchKernelGGL(k_info_small, dim3(1), dim3(64), 0, s, d_info, h);
     HULL_LAUNCH_CHECK();
@@ -1119,12 +1000,11 @@ static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_
       for (int q = 1; q < 2 * L + 3; ++q) (void)hipEventRecord(ev[q], s);
     return HULL_OK;
   }
-  int64_t* off = (int64_t*)(ws + pl.off1);
-  hipLaunchKernelGGL(k_set_off1, dim3(1), dim3(64), 0, s, off, n);
   Sched S{};
   S.off = off;
   S.H = 1;
-  int32_t rc = sort_points<InT, PT>(d_xyz, n, nullptr, 1, ws, pl, s);
+  const RunInits init(ws, pl, lower, upper);
+  int32_t rc = sort_points<InT, PT>(d_xyz, n, nullptr, 1, ws, pl, init.r, s);
   if (rc) return rc;
   if (ev) (void)hipEventRecord(ev[1], s);
   rc = run_levels<PT>(n, S, ws, pl, s, lower, upper, L, opt, ev);
@@ -1167,20 +1047,16 @@ int32_t batched(const int32_t* d_xyz, const int64_t* d_off, const int64_t* h_off
   if (ws_bytes < pl.total) return HULL_EWORKSPACE;
   char* ws = (char*)d_ws;
   Header* h = (Header*)(ws + pl.header);
-  init_header(h, s);
+  init_call(h, nullptr, 0, ws, pl, s);
   Sched S{};
   S.off = d_off;
   S.H = H;
   if (n > 0) {
-    int32_t rc = sort_points<int32_t, int4>(d_xyz, n, d_off, H, ws, pl, s);
+    const RunInits init(ws, pl, true, true);
+    int32_t rc = sort_points<int32_t, int4>(d_xyz, n, d_off, H, ws, pl, init.r, s);
     if (rc) return rc;
     rc = run_levels<int4>(n, S, ws, pl, s, true, true, L, opt, nullptr);
     if (rc) return rc;
-  } else {
-    for (int r = 0; r < 2; ++r)
-      hipLaunchKernelGGL(k_init_links, dim3(1), dim3(256), 0, s, (int*)(ws + pl.pv0[r]),
-                         (int*)(ws + pl.nx0[r]), (int*)(ws + pl.len[r][0]),
-                         (int*)(ws + pl.claimR[r]), (int*)(ws + pl.claimL[r]), int64_t(1));
   }
   return extract<int4>(S, ws, pl, s, true, true, d_faces, cap, d_face_off, d_info);
 }
@@ -1196,22 +1072,29 @@ int32_t movies(const int32_t* d_xyz, int64_t n, int32_t run, int32_t level, int3
   if (ws_bytes < pl.total) return HULL_EWORKSPACE;
   char* ws = (char*)d_ws;
   Header* h = (Header*)(ws + pl.header);
-  init_header(h, s);
   int64_t* off = (int64_t*)(ws + pl.off1);
-  hipLaunchKernelGGL(k_set_off1, dim3(1), dim3(64), 0, s, off, n);
+  init_call(h, off, n, ws, pl, s);
   Sched S{};
   S.off = off;
   S.H = 1;
-  int32_t rc = sort_points<int32_t, int4>(d_xyz, n, nullptr, 1, ws, pl, s);
+  const RunInits init(ws, pl, run == 0, run == 1);
+  int32_t rc = sort_points<int32_t, int4>(d_xyz, n, nullptr, 1, ws, pl, init.r, s);
   if (rc) return rc;
   int L = levels_for(n);
   if (level >= 0 && level < L) L = level;
   rc = run_levels<int4>(n, S, ws, pl, s, run == 0, run == 1, L, opt, nullptr);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_export_movies, dim3(grid_for(2 * n, 1024)), dim3(256), 0, s,
-                     (const Event*)(ws + pl.ev[run][L & 1]), (const int*)(ws + pl.len[run][L & 1]),
-                     (const int4*)(ws + pl.pts), n, int64_t(1) << L, d_ev, d_block_len, d_order,
-                     h);
+  ExportArgs X{};
+  for (int b = 0; b < 2; ++b) {
+    X.ev[b] = (const Event*)(ws + pl.ev[run][b]);
+    X.len[b] = (const int*)(ws + pl.len[run][b]);
+  }
+  X.pts = (const int4*)(ws + pl.pts);
+  X.n = n;
+  X.width = int64_t(1) << L;
+  X.h = h;
+  hipLaunchKernelGGL(k_export_movies, dim3(grid_for(2 * n, 1024)), dim3(256), 0, s, X, d_ev,
+                     d_block_len, d_order);
   hipLaunchKernelGGL(k_info_small, dim3(1), dim3(64), 0, s, d_info, h);
   HULL_LAUNCH_CHECK();
   return HULL_OK;

@@ -1,763 +1,435 @@
-// Parallel merge strategy for large blocks: the kinetic merge of two movies
-// (Sec. 2, the merge step) with only the bridge walk left serial.
+// Parallel merge strategy for large blocks: the merge of two movies (Sec. 2, the
+// merge step) with its time axis cut into segments (walk.hpp) and the lists of
+// link-changing events in global memory.
 //
-// In the merge of L and R, a child event matters to the bridge only when it
-// changes a link of a current bridge endpoint (nx(u), pv(u), pv(v), nx(v));
-// every other child event just passes through or is hidden, depending on
-// where the bridge was at its time.  So:
-//   1. per-point lists of the child events that change the point's links,
-//      in time order (a counting sort by point, then a sort of each short
-//      list by event position: a movie is already in time order);
-//   2. the bridge walk, one thread per merge: the four bridge moves and the
-//      next link change of u and v, earliest first.  Its length is the number
-//      of bridge events plus the link changes of the endpoints, not the size
-//      of the movies;
-//   3. each child event finds, by binary search over the bridge events, the
-//      bridge at its time: an L event survives when its point is left of u,
-//      an R event when right of v;
-//   4. the merged movie is the three time-sorted lists (L survivors, R
-//      survivors, bridge events) merged: every element's position is its
-//      rank in its own list plus its rank in the two others (prefix sums and
-//      binary searches).
-// The result is the same movie as the lane-serial merge, event for event.
+// Per level, over the child events of all merges (nothing per merge is serial):
+//   1. the events are enumerated and every event takes its places in the lists
+//      of the points whose links it changes (one atomic per change; its value
+//      is the place);
+//   2. list bounds by a scan over the points, then the entries: the event's
+//      position in its child movie and the link after it.  Lists of up to
+//      kListScan entries stay in arrival order (a lookup reads them whole);
+//      longer ones are sorted by position;
+//   3. a counting walk per segment, a scan, and a writing walk that replays
+//      the counted steps.  A segment's output is in order, so the level needs
+//      no classification of the child events and no ranks of events in other
+//      lists.
+// A level is nine launches.  Claiming lists by events, filling and sorting
+// 16-byte entries, a separate bridge list, survival flags and three more scans
+// took 1.70-2.25 ms a level on the 2^20-point sphere,
+// this 0.70-1.05 ms.
 #include <algorithm>
 #include <initializer_list>
 
 #include "common.hpp"
 #include "events.hpp"
+#include "walk.hpp"
 
 namespace hull {
 
-// # of events among slots [base, base + len) strictly before X.
+constexpr unsigned long long kStepsLost = ~0ull;  // a segment to be walked again
+
 template <class PT>
-__device__ int count_before(const PT* pts, const Event* ev, int64_t base, int len, const Cand& X,
-                            int zs) {
-  int lo = 0, hi = len;
-  while (lo < hi) {
-    int mid = (lo + hi) >> 1;
-    Cand c = cand_of(ev, base + mid);
-    if (ev_cmp(pts, c, X, zs) < 0) lo = mid + 1;
-    else hi = mid;
+struct ParCtx {
+  const PT* pts;
+  const Event* evL;
+  const Event* evR;
+  const int* off;
+  const int2* ent;
+  const int* nx0;
+  const int* pv0;
+  int64_t np1;  // points + 1: prev lists start there
+  int zs;
+  __device__ __forceinline__ WalkEv ev(bool left, int i) const {
+    const int4 x = *(const int4*)((left ? evL : evR) + i);
+    WalkEv e;
+    e.a = x.x;
+    e.w = x.y & 0x7fffffff;
+    e.b = x.z;
+    e.kind = (int)((unsigned)x.y >> 31);
+    e.t = (double)__int_as_float(x.w);
+    return e;
   }
-  return lo;
+  // the link after the last event of the list [lo, hi) before position
+  // `cursor`, `none` if there is none
+  __device__ __forceinline__ int last_before(int lo, int hi, int cursor, int none) const {
+    if (hi - lo > kListScan) {
+      const int first = lo;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ent[mid].x < cursor) lo = mid + 1;
+        else hi = mid;
+      }
+      return lo > first ? ent[lo - 1].y : none;
+    }
+    int best = -1, l = none;
+    for (; lo < hi; lo += 4) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int2 c = ent[lo + k < hi ? lo + k : lo];
+        const bool later = c.x < cursor && c.x > best;
+        best = later ? c.x : best;
+        l = later ? c.y : l;
+      }
+    }
+    return l;
+  }
+  __device__ __forceinline__ int link(int p, bool nx, bool, int cursor) const {
+    const int64_t key = nx ? p : np1 + p;
+    return last_before(off[key], off[key + 1], cursor, nx ? nx0[p] : pv0[p]);
+  }
+  __device__ __forceinline__ void links(int p, bool, int cursor, int& nx, int& pv) const {
+    const int n0 = off[p], n1 = off[p + 1], p0 = off[np1 + p], p1 = off[np1 + p + 1];
+    const int ln = nx0[p], lp = pv0[p];
+    nx = last_before(n0, n1, cursor, ln);
+    pv = last_before(p0, p1, cursor, lp);
+  }
+};
+
+template <class PT>
+__device__ __forceinline__ ParCtx<PT> ctx_of(const ParLevel& P, int r, int64_t s, int64_t m) {
+  const RunPtrs& R = P.run[r];
+  ParCtx<PT> X;
+  X.pts = (const PT*)R.pts;
+  X.evL = R.left_ev(s);
+  X.evR = R.ev[(P.S.k - 1) & 1] + 2 * m;  // k_par_prep settled it there
+  X.off = P.par[r].off;
+  X.ent = P.par[r].ent;
+  X.nx0 = R.nx0;
+  X.pv0 = R.pv0;
+  X.np1 = P.S.off[P.S.H] + 1;
+  X.zs = R.zs;
+  return X;
 }
 
-// Sort one point's entries by slot (= time order within the child movie),
-// then replace each slot by the event's time.
-__device__ void sort_entries(Entry* a, int k, const Event* ev) {
+// Sorts a list by position (Shell's method; only lists above kListScan).
+__device__ void sort_entries(int2* a, int k) {
   int gap = 1;
   while (gap < k / 3) gap = 3 * gap + 1;
   for (; gap > 0; gap /= 3)
     for (int i = gap; i < k; ++i) {
-      Entry x = a[i];
+      const int2 x = a[i];
       int j = i;
-      while (j >= gap && a[j - gap].key > x.key) {
+      while (j >= gap && a[j - gap].x > x.x) {
         a[j] = a[j - gap];
         j -= gap;
       }
       a[j] = x;
     }
-  for (int i = 0; i < k; ++i) a[i].key = __float_as_int(ev[a[i].key].t);
-}
-
-// Link of p after an event that changes it.
-__device__ __forceinline__ int right_after(const Entry& E, int p) {
-  return p == E.a ? (E.kind() ? E.w() : E.b) : E.b;
-}
-__device__ __forceinline__ int left_after(const Entry& E, int p) {
-  return p == E.b ? (E.kind() ? E.w() : E.a) : E.a;
-}
-
-// A sorted entry as a candidate (its key holds the time).
-__device__ __forceinline__ Cand cand_entry(const Entry* e, int j) {
-  const Entry E = e[j];
-  Cand c;
-  c.t = Tri{E.a, E.w(), E.b};
-  c.kind = E.kind();
-  c.st = (double)__int_as_float(E.key);
-  return c;
-}
-
-// Position in a point's list of its first change strictly after T.
-template <class PT>
-__device__ int first_after(const ParRun& R, const Entry* e, int off, int cnt, bool haveT,
-                           const Cand& T) {
-  if (!haveT) return 0;
-  int lo = 0, hi = cnt;
-  while (lo < hi) {
-    int mid = (lo + hi) >> 1;
-    Cand c = cand_entry(e, off + mid);
-    if (ev_cmp((const PT*)R.pts, c, T, R.zs) > 0) hi = mid;
-    else lo = mid + 1;
-  }
-  return lo;
-}
-
-struct Endpoint {
-  int p;       // the point
-  int nx, pv;  // its links at the current time
-  int cr, cl;  // next unprocessed change in its right / left list
-  int oR, nR, oL, nL;
-};
-
-template <class PT>
-__device__ void lookup(const ParRun& R, Endpoint& X, bool haveT, const Cand& T) {
-  int p = X.p;
-  // a point no child event touched at this level has empty lists (its
-  // counters still hold an earlier level's values)
-  const bool hasR = R.claimR[p] == R.stamp, hasL = R.claimL[p] == R.stamp;
-  X.oR = hasR ? R.offR[p] : 0;
-  X.nR = hasR ? R.cntR[p] : 0;
-  X.oL = hasL ? R.offL[p] : 0;
-  X.nL = hasL ? R.cntL[p] : 0;
-  X.cr = first_after<PT>(R, R.entR, X.oR, X.nR, haveT, T);
-  X.cl = first_after<PT>(R, R.entL, X.oL, X.nL, haveT, T);
-  X.nx = X.cr > 0 ? right_after(R.entR[X.oR + X.cr - 1], p) : R.nx0[p];
-  X.pv = X.cl > 0 ? left_after(R.entL[X.oL + X.cl - 1], p) : R.pv0[p];
-}
-
-// One link of p just after T (the right link with `right`), without the rest
-// of the endpoint state: the tangent search needs only that.
-template <class PT>
-__device__ int link_after(const ParRun& R, int p, bool right, bool haveT, const Cand& T) {
-  if (right) {
-    if (R.claimR[p] != R.stamp) return R.nx0[p];
-    const int o = R.offR[p];
-    const int c = first_after<PT>(R, R.entR, o, R.cntR[p], haveT, T);
-    return c > 0 ? right_after(R.entR[o + c - 1], p) : R.nx0[p];
-  }
-  if (R.claimL[p] != R.stamp) return R.pv0[p];
-  const int o = R.offL[p];
-  const int c = first_after<PT>(R, R.entL, o, R.cntL[p], haveT, T);
-  return c > 0 ? left_after(R.entL[o + c - 1], p) : R.pv0[p];
-}
-
-// Orientation of the rank-ordered triple (a, b, c) just after event T: its
-// sign at t = -inf is sign(D), and it flips once, at its own event.
-template <class PT>
-__device__ int orient_after(const PT* pts, int a, int b, int c, const Cand& T, int zs) {
-  const PT A = pts[a], B = pts[b], C = pts[c];
-  int ds = d_sign(A, B, C);
-  Cand x = make_cand(pts, a, b, c, A, B, C, 0, zs);
-  return ev_cmp(pts, x, T, zs) > 0 ? ds : -ds;
-}
-
-// Segment i of S of a merge covers the events after boundary b_i up to and
-// including b_(i+1), b_0 = -inf, b_S = +inf.  With N = nL + nR child events
-// in time order (both movies merged), b_i (0 < i < S) is the one at position
-// floor(i * N / S) - 1, so every segment spans the same number of child
-// events of the two movies together.  Found by a co-rank search: the number
-// jL of left-movie events among the first k = floor(i * N / S) is the first
-// j at which L[j] comes after R[k-1-j].  Returns b_i's input-movie slot.
-template <class PT>
-__device__ int64_t boundary_slot(const ParRun& R, int64_t s, int64_t m, int i, int S) {
-  const PT* pts = (const PT*)R.pts;
-  const int nL = R.len_in[s], nR = R.len_in[m];
-  const int64_t N = (int64_t)nL + nR;
-  const int k = (int)((int64_t)i * N / S);
-  int lo = k - nR > 0 ? k - nR : 0, hi = k < nL ? k : nL;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (ev_cmp(pts, cand_of(R.ev_in, 2 * s + mid), cand_of(R.ev_in, 2 * m + (k - 1 - mid)),
-               R.zs) < 0)
-      lo = mid + 1;
-    else
-      hi = mid;
-  }
-  const int jL = lo, jR = k - lo;
-  if (jL == 0) return 2 * m + jR - 1;
-  if (jR == 0) return 2 * s + jL - 1;
-  const int64_t a = 2 * s + jL - 1, b = 2 * m + jR - 1;
-  return ev_cmp(pts, cand_of(R.ev_in, a), cand_of(R.ev_in, b), R.zs) > 0 ? a : b;
-}
-
-__device__ __forceinline__ int segments_for(int nL, int nR, int G) {
-  int nn = nL > nR ? nL : nR;
-  int S = 1 + (nL + nR) / G;
-  return S > nn + 1 ? nn + 1 : S;
-}
-
-// The bridge walk over one time segment.  Returns the number of bridge
-// events in the segment; with `out` set, writes them there (and their
-// bridges after each move to `out_uv`).  Segment 0 also reports the -inf
-// bridge in `uv0`.
-template <class PT>
-__device__ int walk_segment(const ParRun& R, Header* h, int64_t s, int64_t m, int64_t e,
-                            int64_t b0, int64_t b1, Event* out, int2* out_uv, int cap,
-                            int2* uv0, int2* start_uv, bool have_start, Event* keep = nullptr,
-                            int2* keep_uv = nullptr, const Event* resume = nullptr) {
-  const PT* pts = (const PT*)R.pts;
-  const int zs = R.zs;
-  bool haveT = false, haveEnd = false;
-  Cand T, Tend;
-  T.t = Tri{-1, -1, -1};
-  T.st = 0.0;
-  T.kind = 0;
-  Tend = T;
-  if (b0 >= 0) {
-    T = cand_of(R.ev_in, b0);
-    haveT = true;
-  }
-  if (b1 >= 0) {
-    Tend = cand_of(R.ev_in, b1);
-    haveEnd = true;
-  }
-  if (resume) {  // continue after an event this segment already produced
-    T = cand_of(resume, 0);
-    haveT = true;
-  }
-  // the bridge at the start of the segment: walk to the lower common tangent
-  // of the two chains, from the inner ends of the blocks (each step needs one
-  // link of one endpoint); the counting pass leaves it for the writing pass
-  int up = (int)m - 1, vp = (int)m;
-  if (have_start) {
-    up = start_uv->x;
-    vp = start_uv->y;
-    if (up < s || up >= m || vp < m || vp >= e) {
-      atomicCAS(&h->err, 0, HULL_EINTERNAL);
-      return 0;
-    }
-  } else {
-    int vnx = link_after<PT>(R, vp, true, haveT, T), upv = link_after<PT>(R, up, false, haveT, T);
-    for (int guard = 0;; ++guard) {
-      if (guard > 2 * (e - s) + 4) {
-        atomicCAS(&h->err, 0, HULL_EINTERNAL);
-        return 0;
-      }
-      if (vnx != kNil) {
-        int o = haveT ? orient_after(pts, up, vp, vnx, T, zs) : d_sign(pts[up], pts[vp], pts[vnx]);
-        if (o < 0) {
-          vp = vnx;
-          vnx = link_after<PT>(R, vp, true, haveT, T);
-          continue;
-        }
-      }
-      if (upv != kNil) {
-        int o = haveT ? orient_after(pts, upv, up, vp, T, zs) : d_sign(pts[upv], pts[up], pts[vp]);
-        if (o < 0) {
-          up = upv;
-          upv = link_after<PT>(R, up, false, haveT, T);
-          continue;
-        }
-      }
-      break;
-    }
-    if (start_uv) *start_uv = make_int2(up, vp);
-  }
-  Endpoint U{up, 0, 0, 0, 0, 0, 0, 0, 0}, V{vp, 0, 0, 0, 0, 0, 0, 0, 0};
-  lookup<PT>(R, U, haveT, T);
-  lookup<PT>(R, V, haveT, T);
-  if (uv0) *uv0 = make_int2(U.p, V.p);
-  PT Pu = pts[U.p], Pv = pts[V.p];
-  int nb = 0;
-  const int64_t iter_cap = (int64_t)R.len_in[s] + R.len_in[m] + 4 * (e - s) + 16;
-  for (int64_t it = 0;; ++it) {
-    if (it > iter_cap) {
-      atomicCAS(&h->err, 0, HULL_EINTERNAL);
-      break;
-    }
-    // candidates: 0..3 bridge moves (checked against T), 4..7 the next link
-    // changes of u and v (after T by construction).  The running best is
-    // kept field by field in scalars and every candidate index is a
-    // compile-time constant, so the candidates stay in registers.
-    int bi = -1, ba = 0, bw = 0, bb = 0, bk = 0;
-    double bs = 0.0;
-#define HULL_CONSIDER(IDX, CAND)                                                  \
-  do {                                                                            \
-    const Cand cc_ = (CAND);                                                      \
-    bool take_ = !((IDX) < 4 && haveT && ev_cmp(pts, cc_, T, zs) <= 0);           \
-    if (take_ && bi >= 0) {                                                       \
-      Cand cb_;                                                                   \
-      cb_.t = Tri{ba, bw, bb};                                                    \
-      cb_.st = bs;                                                                \
-      cb_.kind = bk;                                                              \
-      take_ = ev_cmp(pts, cc_, cb_, zs) < 0;                                      \
-    }                                                                             \
-    if (take_) {                                                                  \
-      bi = (IDX);                                                                 \
-      ba = cc_.t.a;                                                               \
-      bw = cc_.t.w;                                                               \
-      bb = cc_.t.b;                                                               \
-      bs = cc_.st;                                                                \
-      bk = cc_.kind;                                                              \
-    }                                                                             \
-  } while (0)
-    if (U.nx != kNil) HULL_CONSIDER(0, make_cand(pts, U.p, U.nx, V.p, Pu, pts[U.nx], Pv, 1, zs));
-    if (U.pv != kNil) HULL_CONSIDER(1, make_cand(pts, U.pv, U.p, V.p, pts[U.pv], Pu, Pv, 0, zs));
-    if (V.pv != kNil) HULL_CONSIDER(2, make_cand(pts, U.p, V.pv, V.p, Pu, pts[V.pv], Pv, 1, zs));
-    if (V.nx != kNil) HULL_CONSIDER(3, make_cand(pts, U.p, V.p, V.nx, Pu, Pv, pts[V.nx], 0, zs));
-    if (U.cr < U.nR) HULL_CONSIDER(4, cand_entry(R.entR, U.oR + U.cr));
-    if (U.cl < U.nL) HULL_CONSIDER(5, cand_entry(R.entL, U.oL + U.cl));
-    if (V.cl < V.nL) HULL_CONSIDER(6, cand_entry(R.entL, V.oL + V.cl));
-    if (V.cr < V.nR) HULL_CONSIDER(7, cand_entry(R.entR, V.oR + V.cr));
-#undef HULL_CONSIDER
-    Cand best;
-    best.t = Tri{ba, bw, bb};
-    best.st = bs;
-    best.kind = bk;
-    if (bi < 0) break;
-    if (haveEnd && ev_cmp(pts, best, Tend, zs) > 0) break;
-    T = best;
-    haveT = true;
-    if (bi >= 4) {  // a link change of an endpoint
-      if (bi == 4) { U.nx = right_after(R.entR[U.oR + U.cr], U.p); ++U.cr; }
-      else if (bi == 5) { U.pv = left_after(R.entL[U.oL + U.cl], U.p); ++U.cl; }
-      else if (bi == 6) { V.pv = left_after(R.entL[V.oL + V.cl], V.p); ++V.cl; }
-      else { V.nx = right_after(R.entR[V.oR + V.cr], V.p); ++V.cr; }
-      continue;
-    }
-    if (bi == 0) U.p = U.nx;
-    else if (bi == 1) U.p = U.pv;
-    else if (bi == 2) V.p = V.pv;
-    else V.p = V.nx;
-    if (bi <= 1) {
-      Pu = pts[U.p];
-      lookup<PT>(R, U, true, T);
-    } else {
-      Pv = pts[V.p];
-      lookup<PT>(R, V, true, T);
-    }
-    if (out) {
-      if (nb >= cap) {
-        atomicCAS(&h->err, 0, HULL_EINTERNAL);
-        break;
-      }
-      out[nb] = make_event(T.t.a, T.t.w, T.t.b, T.kind, T.st);
-      out_uv[nb] = make_int2(U.p, V.p);
-    } else if (keep && nb < kSegKeep) {
-      keep[nb] = make_event(T.t.a, T.t.w, T.t.b, T.kind, T.st);
-      keep_uv[nb] = make_int2(U.p, V.p);
-    }
-    ++nb;
-  }
-  return nb;
 }
 
 #define GRID_STRIDE(i, n) \
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (n); \
        i += (int64_t)gridDim.x * blockDim.x)
 
-// Per merge: child event count and walk segments; counters reset.
+// Per merge: child event count and walk segments; the list bounds cleared;
+// short right blocks moved out of the buffer the level writes; and the splices of the level before (its walks, which read the -inf links, have
+// ended; nothing here reads them).
 __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
-  const int merges = P.S.moff[P.S.H];
-  const int64_t half = int64_t(1) << (P.k - 1);
-  GRID_STRIDE(g, (int64_t)merges + 1) {
+  const int64_t merges = P.S.merges(), half = int64_t(1) << (P.S.k - 1);
+  const int64_t keys = merges ? 2 * (P.S.off[P.S.H] + 1) : 0;
+  const bool err = P.h->err != 0;
+  GRID_STRIDE(g, (int64_t)(err ? 0 : Q.ctr[kCtrSplice + ((P.S.k - 1) & 1)])) {
+    const int2 b = Q.uv0[g];
+    R.nx0[b.x] = b.y;
+    R.pv0[b.y] = b.x;
+  }
+  GRID_STRIDE(g, merges + 1) {
     if (g == 0) {
-      R.ctr[kCtrTouched] = 0;
-      R.ctr[kCtrMerges] = merges;
+      Q.ctr[kCtrMerges] = (int)merges;
+      Q.ctr[kCtrKeys] = (int)keys;
+      Q.ctr[kCtrSplice + (P.S.k & 1)] = (int)merges;
     }
-    if (g < merges && !P.h->err) {
-      const int2 se = P.S.mlist[g];
-      const int nL = R.len_in[se.x], nR = R.len_in[se.x + half];
-      R.ecnt[g] = nL + nR;
-      R.segS[g] = segments_for(nL, nR, P.seg_events);
+    if (g < merges && !err) {
+      const int2 se = P.S.merge(g);
+      const int64_t m = se.x + half;
+      const int nL = R.left_len(se.x), nR = R.right_len(m, se.y);
+      Q.ecnt[g] = nL + nR;
+      Q.segS[g] = segments_for(nL + nR, P.seg_events);
     } else {
-      R.ecnt[g] = 0;
-      R.segS[g] = 0;
+      Q.ecnt[g] = 0;
+      Q.segS[g] = 0;
     }
-    R.nB[g] = 0;
+  }
+  GRID_STRIDE(q, keys) Q.off[q] = 0;
+  if (err) return;
+  for (int64_t g = blockIdx.x; g < merges; g += gridDim.x) {  // one block per merge
+    const int2 se = P.S.merge(g);
+    const int64_t m = se.x + half, e = se.y;
+    if (R.right_waits_in_output(m, e))
+      (void)R.settle_right(m, e, R.right_len(m, e), threadIdx.x, blockDim.x);
   }
 }
 
-// The compact list of child events (slot and merge of each), and the
-// link-change counters of their points cleared; then, past the events, the
-// segment table: per walk segment its merge and the slot of the child event
-// it starts after.
+// The child events take their places in the lists; then, past the events, the
+// segment table: per walk segment its merge and the left events before it.
 template <class PT>
 __global__ void __launch_bounds__(256) k_par_enum(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
-  const int merges = R.ctr[kCtrMerges], E = R.ctr[kCtrEvents], Sg = R.ctr[kCtrSegments];
-  const int64_t half = int64_t(1) << (P.k - 1);
-  const bool err = P.h->err != 0;
+  const int merges = Q.ctr[kCtrMerges], E = Q.ctr[kCtrEvents], Sg = Q.ctr[kCtrSegments];
+  if (!merges) return;
+  const int64_t half = int64_t(1) << (P.S.k - 1), np1 = P.S.off[P.S.H] + 1;
   GRID_STRIDE(c, (int64_t)E + Sg) {
-    if (c >= E) {
-      const int64_t t = c - E;
-      const int g = find_owner(R.segBase, merges, t);
-      R.segMerge[t] = g;
-      const int i = (int)(t - R.segBase[g]);
-      const int64_t s = P.S.mlist[g].x;
-      R.segB[t] = i == 0 || err ? -1 : (int)boundary_slot<PT>(R, s, s + half, i, R.segS[g]);
+    const bool seg = c >= E;
+    const int64_t t = seg ? c - E : c;
+    const int g = find_owner(seg ? Q.segBase : Q.eoff, merges, t);
+    const int2 se = P.S.merge(g);
+    const int64_t s = se.x, m = s + half, e = se.y;
+    const ParCtx<PT> X = ctx_of<PT>(P, blockIdx.y, s, m);
+    const int nL = R.left_len(s);
+    if (seg) {
+      const int nR = R.right_len(m, e);
+      Q.segMerge[t] = g;
+      Q.segJ[t] = segment_split<PT>(X, nL, nR, (int)(t - Q.segBase[g]), Q.segS[g]);
       continue;
     }
-    const int g = find_owner(R.eoff, merges, c);
-    const int2 se = P.S.mlist[g];
-    const int64_t s = se.x, m = s + half;
-    const int nL = R.len_in[s];
-    const int64_t i = c - R.eoff[g];
-    const int64_t slot = i < nL ? 2 * s + i : 2 * m + (i - nL);
-    R.cslot[c] = (int)slot;
-    R.cmerge[c] = g;
-    const Event X = R.ev_in[slot];
-    R.cntR[X.a] = 0;
-    R.curR[X.a] = 0;
-    R.cntL[X.b] = 0;
-    R.curL[X.b] = 0;
-    if (X.kind()) {
-      R.cntR[X.w()] = 0;
-      R.curR[X.w()] = 0;
-      R.cntL[X.w()] = 0;
-      R.curL[X.w()] = 0;
+    const int i = (int)(t - Q.eoff[g]);
+    const WalkEv x = X.ev(i < nL, i < nL ? i : i - nL);
+    Q.cmerge[c] = g;
+    int4 at = make_int4(0, 0, 0, 0);
+    at.x = atomicAdd(&Q.off[x.a], 1);
+    at.y = atomicAdd(&Q.off[np1 + x.b], 1);
+    if (x.kind) {
+      at.z = atomicAdd(&Q.off[x.w], 1);
+      at.w = atomicAdd(&Q.off[np1 + x.w], 1);
     }
+    Q.pos[c] = at;
   }
 }
 
-// Which links an event changes: nx(a) and pv(b); an insertion also sets
-// nx(w) and pv(w).
-__global__ void __launch_bounds__(256) k_par_count(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
+// An event sets next(a) and prev(b), an insertion both links of w too.
+template <class PT>
+__global__ void __launch_bounds__(256) k_par_fill(ParLevel P) {
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
-  GRID_STRIDE(c, R.ctr[kCtrEvents]) {
-    const Event X = R.ev_in[R.cslot[c]];
-    atomicAdd(&R.cntR[X.a], 1);
-    atomicAdd(&R.cntL[X.b], 1);
-    if (X.kind()) {
-      atomicAdd(&R.cntR[X.w()], 1);
-      atomicAdd(&R.cntL[X.w()], 1);
-    }
-  }
-}
-
-// One list per touched (point, side), allocated by whichever child event
-// claims it first at this level (claim stamp = the level).  Pass 1: each
-// event claims, and records how many list entries and lists it allocates;
-// after exclusive scans of those counts, pass 2 places the lists.  (No
-// shared counters: space comes from prefix sums.)
-__global__ void __launch_bounds__(256) k_par_claim(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
-  if (!R.pts) return;
-  const int E = R.ctr[kCtrEvents], st = R.stamp;
-  GRID_STRIDE(c, (int64_t)E + 1) {
-    if (c == E) {  // the scans read one entry past the last event
-      R.aR[c] = R.aL[c] = R.aT[c] = 0;
-      continue;
-    }
-    const Event X = R.ev_in[R.cslot[c]];
-    unsigned bits = 0;
-    int nR = 0, nL = 0;
-    if (atomicExch(&R.claimR[X.a], st) != st) {
-      bits |= 1u;
-      nR += R.cntR[X.a];
-    }
-    if (atomicExch(&R.claimL[X.b], st) != st) {
-      bits |= 4u;
-      nL += R.cntL[X.b];
-    }
-    if (X.kind()) {
-      if (atomicExch(&R.claimR[X.w()], st) != st) {
-        bits |= 2u;
-        nR += R.cntR[X.w()];
-      }
-      if (atomicExch(&R.claimL[X.w()], st) != st) {
-        bits |= 8u;
-        nL += R.cntL[X.w()];
-      }
-    }
-    R.aR[c] = nR;
-    R.aL[c] = nL;
-    R.aT[c] = __builtin_popcount(bits);
-    R.wf[c] = (unsigned char)bits;
-  }
-}
-
-__global__ void __launch_bounds__(256) k_par_place(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
-  if (!R.pts) return;
-  const int E = R.ctr[kCtrEvents];
-  // capacities: 3n entries per side (one per child event, 2n events, and one
-  // more per insertion, n of them: a point is inserted at most once in its
-  // block's movie), 2n touched lists (one per point and side)
-  const int64_t ent_cap = P.ecap + P.ecap / 2, touched_cap = P.ecap;
-  if (R.aR[E] > ent_cap || R.aL[E] > ent_cap || R.aT[E] > touched_cap) {
+  const int E = Q.ctr[kCtrEvents], keys = Q.ctr[kCtrKeys];
+  if (E <= 0 || keys <= 0) return;
+  const int64_t half = int64_t(1) << (P.S.k - 1), np1 = P.S.off[P.S.H] + 1;
+  // capacity: 6 entries per point (the last bound is the entries of all but
+  // the last key, whose list is empty)
+  if (Q.off[keys - 1] > 6 * P.n) {
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
     return;
   }
-  GRID_STRIDE(c, (int64_t)E + 1) {
-    if (c == E) {
-      R.ctr[kCtrTouched] = R.aT[E];  // touched lists of the level
-      continue;
-    }
-    const unsigned bits = R.wf[c];
-    if (!bits) continue;
-    const Event X = R.ev_in[R.cslot[c]];
-    int bR = R.aR[c], bL = R.aL[c], bT = R.aT[c];
-    if (bits & 1u) {
-      R.offR[X.a] = bR;
-      bR += R.cntR[X.a];
-      R.touched[bT++] = X.a << 1;
-    }
-    if (bits & 2u) {
-      R.offR[X.w()] = bR;
-      R.touched[bT++] = X.w() << 1;
-    }
-    if (bits & 4u) {
-      R.offL[X.b] = bL;
-      bL += R.cntL[X.b];
-      R.touched[bT++] = (X.b << 1) | 1;
-    }
-    if (bits & 8u) {
-      R.offL[X.w()] = bL;
-      R.touched[bT++] = (X.w() << 1) | 1;
-    }
-  }
-}
-
-// Lists of link changes: every entry is the child event and its slot in the
-// input movies (the sort key: a movie is in time order).
-__global__ void __launch_bounds__(256) k_par_fill(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
-  if (!R.pts || P.h->err) return;  // after an error the offsets may be stale
-  GRID_STRIDE(c, R.ctr[kCtrEvents]) {
-    const int q = R.cslot[c];
-    const Event E = R.ev_in[q];
-    Entry X;
-    X.a = E.a;
-    X.wk = E.wk;
-    X.b = E.b;
-    X.key = q;
-    int j = R.offR[E.a] + atomicAdd(&R.curR[E.a], 1);
-    R.entR[j] = X;
-    j = R.offL[E.b] + atomicAdd(&R.curL[E.b], 1);
-    R.entL[j] = X;
-    if (E.kind()) {
-      const int w = E.w();
-      j = R.offR[w] + atomicAdd(&R.curR[w], 1);
-      R.entR[j] = X;
-      j = R.offL[w] + atomicAdd(&R.curL[w], 1);
-      R.entL[j] = X;
+  GRID_STRIDE(c, (int64_t)E) {
+    const int g = Q.cmerge[c];
+    const int2 se = P.S.merge(g);
+    const int64_t s = se.x, m = s + half, e = se.y;
+    const ParCtx<PT> X = ctx_of<PT>(P, blockIdx.y, s, m);
+    const int nL = R.left_len(s), i = (int)(c - Q.eoff[g]);
+    const int j = i < nL ? i : i - nL;
+    const WalkEv x = X.ev(i < nL, j);
+    const int4 at = Q.pos[c];
+    Q.ent[Q.off[x.a] + at.x] = make_int2(j, x.kind ? x.w : x.b);
+    Q.ent[Q.off[np1 + x.b] + at.y] = make_int2(j, x.kind ? x.w : x.a);
+    if (x.kind) {
+      Q.ent[Q.off[x.w] + at.z] = make_int2(j, x.b);
+      Q.ent[Q.off[np1 + x.w] + at.w] = make_int2(j, x.a);
     }
   }
 }
 
 __global__ void __launch_bounds__(256) k_par_sort(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
-  if (!R.pts || P.h->err) return;
-  GRID_STRIDE(t, R.ctr[kCtrTouched]) {
-    const int x = R.touched[t], p = x >> 1;
-    if (x & 1) sort_entries(R.entL + R.offL[p], R.cntL[p], R.ev_in);
-    else sort_entries(R.entR + R.offR[p], R.cntR[p], R.ev_in);
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!P.run[blockIdx.y].pts || P.h->err) return;
+  GRID_STRIDE(q, (int64_t)Q.ctr[kCtrKeys] - 1) {
+    const int first = Q.off[q], k = Q.off[q + 1] - first;
+    if (k > kListScan) sort_entries(Q.ent + first, k);
   }
 }
 
-// Pass 1 counts each segment's bridge events; pass 2 writes them at their
-// place in the merge's bridge list.
+// A counting walk: its steps, and its first kSegKeep bridge events put aside.
+struct ParCount {
+  WalkNote note;
+  Event* keep;
+  __device__ __forceinline__ void child(bool left, bool kept, int, int, int, int, double) {
+    note.child(left, kept);
+  }
+  __device__ __forceinline__ void bridge(int a, int w, int b, int kind, double t) {
+    if (note.nbridge < kSegKeep) keep[note.nbridge] = make_event(a, w, b, kind, t);
+    ++note.nbridge;
+    note.step(kStepBridge, true);
+  }
+};
+
+struct ParWrite {
+  Event* out;
+  __device__ __forceinline__ void child(bool, bool kept, int a, int w, int b, int kind, double t) {
+    if (kept) *out++ = make_event(a, w, b, kind, t);
+  }
+  __device__ __forceinline__ void bridge(int a, int w, int b, int kind, double t) {
+    *out++ = make_event(a, w, b, kind, t);
+  }
+};
+
+// One segment's place: its merge, its child events and the last event before
+// it.
 template <class PT>
-__global__ void __launch_bounds__(64) k_par_walk(ParLevel P, int write) {
-  const ParRun& R = P.run[blockIdx.y];
-  if (!R.pts) return;
-  const int total = R.ctr[kCtrSegments];
-  const int64_t half = int64_t(1) << (P.k - 1);
-  GRID_STRIDE(t, (int64_t)total + 1) {
-    if (t == total) {  // the scan reads one entry past the last segment
-      if (!write) R.segCnt[t] = 0;
-      continue;
-    }
-    const int g = R.segMerge[t];
-    const int first = R.segBase[g], S = R.segS[g], i = (int)(t - first);
-    const int2 se = P.S.mlist[g];
-    const int64_t s = se.x, m = s + half, e = se.y;
-    const int64_t b0 = R.segB[t], b1 = i + 1 < S ? R.segB[t + 1] : -1;
-    if (P.h->err) {
-      if (!write) R.segCnt[t] = 0;
-      else if (i == 0) {
-        R.nB[g] = 0;
-        R.uv0[g] = make_int2(0, 0);
+struct ParSeg {
+  int64_t s, m, e;
+  ParCtx<PT> X;
+  int i, S, jL, jR, kL, kR, limit;
+  Cand T;
+  __device__ __forceinline__ ParSeg(const ParLevel& P, int r, int64_t t, int g) {
+    const RunPtrs& R = P.run[r];
+    const ParRun& Q = P.par[r];
+    const int2 se = P.S.merge(g);
+    s = se.x;
+    m = s + (int64_t(1) << (P.S.k - 1));
+    e = se.y;
+    X = ctx_of<PT>(P, r, s, m);
+    i = (int)(t - Q.segBase[g]);
+    S = Q.segS[g];
+    const int nL = R.left_len(s), nR = R.right_len(m, e);
+    const int64_t N = (int64_t)nL + nR;
+    jL = Q.segJ[t];
+    jR = (int)(i * N / S) - jL;
+    kL = i + 1 < S ? Q.segJ[t + 1] : nL;
+    kR = (int)((i + 1) * N / S) - kL;
+    const int64_t lim = 4 * (e - s) + N + 16;
+    limit = (int)(lim < 0x7fffffff ? lim : 0x7ffffffe);
+    T.t = Tri{-1, -1, -1};
+    T.st = 0.0;
+    T.kind = 0;
+    if (i > 0) {
+      if (jL == 0) T = walk_cand(X.ev(false, jR - 1));
+      else if (jR == 0) T = walk_cand(X.ev(true, jL - 1));
+      else {
+        const Cand x = walk_cand(X.ev(true, jL - 1)), y = walk_cand(X.ev(false, jR - 1));
+        T = ev_cmp(X.pts, x, y, X.zs) > 0 ? x : y;
       }
+    }
+  }
+};
+
+template <class PT>
+__global__ void __launch_bounds__(64) k_par_walk(ParLevel P) {
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!P.run[blockIdx.y].pts) return;
+  const int total = Q.ctr[kCtrSegments];
+  if (!Q.ctr[kCtrMerges]) return;
+  const bool err = P.h->err != 0;
+  GRID_STRIDE(t, (int64_t)total + 1) {
+    if (t == total || err) {  // the scan reads one entry past the last segment
+      Q.segCnt[t] = 0;
       continue;
     }
-    if (!write) {
-      R.segCnt[t] = walk_segment<PT>(R, P.h, s, m, e, b0, b1, nullptr, nullptr, 0,
-                                 i == 0 ? &R.uv0[g] : nullptr, &R.segUV[t], false,
-                                 R.segTmp + (int64_t)t * kSegKeep,
-                                 R.segTmpUV + (int64_t)t * kSegKeep);
+    const int g = Q.segMerge[t];
+    const ParSeg<PT> Z(P, blockIdx.y, t, g);
+    int u = 0, v = 0;
+    ParCount cnt;
+    cnt.keep = Q.segKeep + t * kSegKeep;
+    bool ok = bridge_at<PT>(Z.X, (int)Z.m, Z.jL, Z.jR, Z.i > 0, Z.T, Z.limit, u, v);
+    if (ok)
+      ok = walk<PT>(Z.X, u, v, Z.jL, Z.kL, Z.jR, Z.kR, Z.i + 1 == Z.S, Z.i > 0, Z.T, Z.limit, cnt);
+    if (!ok) {
+      atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
+      Q.segCnt[t] = 0;
       continue;
     }
-    if (i == 0) R.nB[g] = R.segOff[first + S] - R.segOff[first];
-    const int cnt = R.segCnt[t];
-    if (cnt == 0) continue;  // nothing to write (the -inf bridge is known)
-    const int64_t off = R.segOff[t] - R.segOff[first];
-    const int cap = (int)(2 * (e - s) - off);
-    // the counting pass kept the first kSegKeep: copy them, and walk on from
-    // the last of them only for the rest
-    const int kept = cnt < kSegKeep ? cnt : kSegKeep;
-    if (cnt > cap) {
+    if (Z.i == 0) Q.uv0[g] = make_int2(u, v);
+    Q.segUV[t] = make_int2(u, v);
+    Q.segCnt[t] = cnt.note.nout;
+    Q.segSteps[t] = cnt.note.nsteps <= kWalkSteps && cnt.note.nbridge <= kSegKeep ? cnt.note.steps
+                                                                                  : kStepsLost;
+  }
+}
+
+// Every segment's events to their place in the merged movie.
+template <class PT>
+__global__ void __launch_bounds__(64) k_par_write(ParLevel P) {
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!R.pts || !Q.ctr[kCtrMerges]) return;
+  const bool err = P.h->err != 0;
+  GRID_STRIDE(t, (int64_t)Q.ctr[kCtrSegments]) {
+    const int g = Q.segMerge[t];
+    const int first = Q.segBase[g];
+    if (err) {  // every merge writes its length, also after an error
+      if (t == first) R.out_len(P.S.merge(g).x) = 0;
+      continue;
+    }
+    const ParSeg<PT> Z(P, blockIdx.y, t, g);
+    const int len = Q.segOff[first + Z.S] - Q.segOff[first];
+    const int64_t cap = 2 * (Z.e - Z.s);
+    if (t == first) R.out_len(Z.s) = len <= cap ? len : 0;
+    if (len > cap) {
       atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
       continue;
     }
-    for (int q = 0; q < kept; ++q) {
-      R.bev[2 * s + off + q] = R.segTmp[(int64_t)t * kSegKeep + q];
-      R.buv[2 * s + off + q] = R.segTmpUV[(int64_t)t * kSegKeep + q];
-    }
-    if (cnt <= kSegKeep) continue;
-    const int64_t last = (int64_t)t * kSegKeep + kSegKeep - 1;
-    walk_segment<PT>(R, P.h, s, m, e, b0, b1, R.bev + 2 * s + off + kSegKeep,
-                 R.buv + 2 * s + off + kSegKeep, cap - kSegKeep, nullptr, &R.segTmpUV[last],
-                 true, nullptr, nullptr, &R.segTmp[last]);
-  }
-}
-
-// Survival of every child event, and the number of bridge events before it.
-template <class PT>
-__global__ void __launch_bounds__(256) k_par_classify(ParLevel P) {
-  const ParRun& R = P.run[blockIdx.y];
-  if (!R.pts) return;
-  const int E = R.ctr[kCtrEvents];
-  const int64_t half = int64_t(1) << (P.k - 1);
-  const bool err = P.h->err != 0;
-  GRID_STRIDE(c, (int64_t)E + 1) {
-    if (c == E || err) {
-      R.surv[c] = 0;
+    ParWrite wr{R.out_ev(Z.s) + (Q.segOff[t] - Q.segOff[first])};
+    unsigned long long steps = Q.segSteps[t];
+    if (steps == kStepsLost) {
+      const int2 uv = Q.segUV[t];
+      (void)walk<PT>(Z.X, uv.x, uv.y, Z.jL, Z.kL, Z.jR, Z.kR, Z.i + 1 == Z.S, Z.i > 0, Z.T, Z.limit, wr);
       continue;
     }
-    const int g = R.cmerge[c];
-    const int q = R.cslot[c];
-    const int64_t s = P.S.mlist[g].x, m = s + half;
-    const bool isL = q < 2 * m;
-    const Cand x = cand_of(R.ev_in, q);
-    const int j = count_before((const PT*)R.pts, R.bev, 2 * s, R.nB[g], x, R.zs);
-    const int2 ref = j > 0 ? R.buv[2 * s + j - 1] : R.uv0[g];
-    R.surv[c] = isL ? (x.t.w < ref.x) : (x.t.w > ref.y);
-    R.jb[c] = j;
-  }
-}
-
-// Scatter: child survivors, then bridge events, to their places in the
-// merged movies; then every merge writes its length and splices its -inf
-// chains (no kernel of this level reads the -inf links after the walk).
-template <class PT>
-__global__ void __launch_bounds__(256) k_par_scatter(ParLevel P) {
-  const PT* pts = (const PT*)P.run[blockIdx.y].pts;
-  const ParRun& R = P.run[blockIdx.y];
-  if (!R.pts) return;
-  const bool err = P.h->err != 0;
-  const int merges = R.ctr[kCtrMerges], E = R.ctr[kCtrEvents], Bt = R.ctr[kCtrBridge];
-  const int64_t half = int64_t(1) << (P.k - 1);
-  GRID_STRIDE(t, (int64_t)E + Bt + merges) {
-    if (t < E) {
-      const int64_t c = t;
-      if (err || !R.surv[c]) continue;
-      const int g = R.cmerge[c];
-      const int q = R.cslot[c];
-      const int2 se = P.S.mlist[g];
-      const int64_t s = se.x, m = s + half, e = se.y;
-      const int nL = R.len_in[s], nR = R.len_in[m];
-      const int c0 = R.eoff[g], cR = c0 + nL;
-      const Cand x = cand_of(R.ev_in, q);
-      int64_t pos;
-      if (q < 2 * m) {
-        const int idx = count_before(pts, R.ev_in, 2 * m, nR, x, R.zs);
-        pos = (R.pre[c] - R.pre[c0]) + (R.pre[cR + idx] - R.pre[cR]) + R.jb[c];
+    int jL = Z.jL, jR = Z.jR;
+    const Event* keep = Q.segKeep + t * kSegKeep;
+    for (; steps; steps >>= 3) {
+      const unsigned code = (unsigned)steps & 7u;
+      if (code == kStepBridge) {
+        *wr.out++ = *keep++;
       } else {
-        const int idx = count_before(pts, R.ev_in, 2 * s, nL, x, R.zs);
-        pos = (R.pre[c0 + idx] - R.pre[c0]) + (R.pre[c] - R.pre[cR]) + R.jb[c];
-      }
-      if (pos >= 2 * (e - s)) {
-        atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
-        continue;
-      }
-      R.ev_out[2 * s + pos] = R.ev_in[q];
-    } else if (t < (int64_t)E + Bt) {
-      if (err) continue;
-      const int64_t b = t - E;
-      const int g = find_owner(R.boff, merges, b);
-      const int j = (int)(b - R.boff[g]);
-      const int2 se = P.S.mlist[g];
-      const int64_t s = se.x, m = s + half, e = se.y;
-      const int nL = R.len_in[s], nR = R.len_in[m];
-      const int c0 = R.eoff[g], cR = c0 + nL;
-      const Cand x = cand_of(R.bev, 2 * s + j);
-      const int iL = count_before(pts, R.ev_in, 2 * s, nL, x, R.zs);
-      const int iR = count_before(pts, R.ev_in, 2 * m, nR, x, R.zs);
-      const int64_t pos = j + (R.pre[c0 + iL] - R.pre[c0]) + (R.pre[cR + iR] - R.pre[cR]);
-      if (pos >= 2 * (e - s)) {
-        atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
-        continue;
-      }
-      R.ev_out[2 * s + pos] = R.bev[2 * s + j];
-    } else {
-      const int g = (int)(t - E - Bt);
-      const int2 se = P.S.mlist[g];
-      const int64_t s = se.x, e = se.y;
-      // every merge writes its length, also after an error (then 0)
-      const int cnt = err ? 0 : (R.pre[R.eoff[g + 1]] - R.pre[R.eoff[g]]) + R.nB[g];
-      R.len_out[s] = cnt <= 2 * (e - s) ? cnt : 0;
-      if (cnt > 2 * (e - s)) atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
-      if (!err) {
-        const int2 b0 = R.uv0[g];
-        R.nx0[b0.x] = b0.y;
-        R.pv0[b0.y] = b0.x;
+        const bool left = code == kStepL || code == kStepHideL;
+        const Event* x = left ? Z.X.evL + jL++ : Z.X.evR + jR++;
+        if (code == kStepL || code == kStepR) *wr.out++ = *x;
       }
     }
   }
 }
 
-// Scans of the same per-run arrays of both runs (and of several arrays) in
-// one set of launches.
-static ScanJobs jobs_of(const ParLevel& P, std::initializer_list<int> fields, int ctr_index) {
+// Scans of the same arrays of both runs in one launch.  kinds: 0 child events
+// and 1 walk segments per merge (their totals are the level's), 2 the lists'
+// lengths by key, 3 events put out per segment.
+static ScanJobs jobs_of(const ParLevel& P, std::initializer_list<int> kinds) {
   ScanJobs J{};
   for (int r = 0; r < 2; ++r) {
-    const ParRun& R = P.run[r];
-    if (!R.pts) continue;
-    for (int f : fields) {
-      int32_t* a = nullptr;
+    if (!P.run[r].pts) continue;
+    const ParRun& Q = P.par[r];
+    for (int f : kinds) {
+      ScanJob& j = J.j[J.count++];
       switch (f) {
-        // the level totals of child events, walk segments and bridge events
-        // come from the scans themselves
-        case 0: J.j[J.count] = ScanJob{R.ecnt, R.eoff, R.ctr + ctr_index, R.ctr + kCtrEvents}; break;
-        case 1:
-          J.j[J.count] = ScanJob{R.segS, R.segBase, R.ctr + ctr_index, R.ctr + kCtrSegments};
-          break;
-        case 2: a = R.aR; J.j[J.count] = ScanJob{a, a, R.ctr + ctr_index, nullptr}; break;
-        case 3: a = R.aL; J.j[J.count] = ScanJob{a, a, R.ctr + ctr_index, nullptr}; break;
-        case 4: a = R.aT; J.j[J.count] = ScanJob{a, a, R.ctr + ctr_index, nullptr}; break;
-        case 5: J.j[J.count] = ScanJob{R.segCnt, R.segOff, R.ctr + ctr_index, nullptr}; break;
-        case 6: J.j[J.count] = ScanJob{R.nB, R.boff, R.ctr + ctr_index, R.ctr + kCtrBridge}; break;
-        default: J.j[J.count] = ScanJob{R.surv, R.pre, R.ctr + ctr_index, nullptr}; break;
+        case 0: j = ScanJob{Q.ecnt, Q.eoff, Q.ctr + kCtrMerges, Q.ctr + kCtrEvents}; break;
+        case 1: j = ScanJob{Q.segS, Q.segBase, Q.ctr + kCtrMerges, Q.ctr + kCtrSegments}; break;
+        case 2: j = ScanJob{Q.off, Q.off, Q.ctr + kCtrKeys, nullptr}; break;
+        default: j = ScanJob{Q.segCnt, Q.segOff, Q.ctr + kCtrSegments, nullptr}; break;
       }
-      ++J.count;
     }
   }
   return J;
 }
 
-// The level's five scans, one launch each, on job slots of their own; the
-// epoch (level and scan) tells their status words from those of earlier
-// levels of the call.
-static int32_t chained(const ParLevel& P, const ScanJobs& J, int slot, int site, int64_t cap,
+// The level's three scans, on job slots of their own; the epoch (level and
+// scan) tells their status words from those of earlier levels of the call.
+static int32_t chained(const ParLevel& P, const ScanJobs& J, int slot, int site, int add, int64_t cap,
                        hipStream_t s) {
-  return exclusive_scan_chained(J, 1, cap, P.chain_words + slot * P.chain_stride, P.chain_stride,
-                                (unsigned)(P.k * 8 + site), P.h, s);
+  return exclusive_scan_chained(J, add, cap, P.chain_words + slot * P.chain_stride, P.chain_stride,
+                                (unsigned)(P.S.k * 8 + site), P.h, s);
 }
 
 template <class PT>
 int32_t parallel_level(const ParLevel& P, hipStream_t s) {
   const dim3 g2(kStrideBlocks, 2), b256(256);
   hipLaunchKernelGGL(k_par_prep, g2, b256, 0, s, P);
-  // per merge: child events, walk segments (length: merges + 1)
-  int32_t rc = chained(P, jobs_of(P, {0, 1}, kCtrMerges), 0, 1, P.S.mcap + 1, s);
+  int32_t rc = chained(P, jobs_of(P, {0, 1}), 0, 1, 1, P.mcap + 1, s);
   if (rc) return rc;
   hipLaunchKernelGGL(k_par_enum<PT>, g2, b256, 0, s, P);
-  hipLaunchKernelGGL(k_par_count, g2, b256, 0, s, P);
-  hipLaunchKernelGGL(k_par_claim, g2, b256, 0, s, P);
-  // per child event: list entries and lists it allocates (length: events + 1)
-  rc = chained(P, jobs_of(P, {2, 3, 4}, kCtrEvents), 4, 2, P.ecap + 1, s);
+  rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 2, s);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_par_place, g2, b256, 0, s, P);
-  hipLaunchKernelGGL(k_par_fill, g2, b256, 0, s, P);
+  hipLaunchKernelGGL(k_par_fill<PT>, g2, b256, 0, s, P);
   hipLaunchKernelGGL(k_par_sort, g2, b256, 0, s, P);
   const dim3 gw(16384, 2), b64(64);
-  hipLaunchKernelGGL(k_par_walk<PT>, gw, b64, 0, s, P, 0);
-  rc = chained(P, jobs_of(P, {5}, kCtrSegments), 10, 3, P.seg_cap + 1, s);
+  hipLaunchKernelGGL(k_par_walk<PT>, gw, b64, 0, s, P);
+  rc = chained(P, jobs_of(P, {3}), 6, 3, 1, P.seg_cap + 1, s);
   if (rc) return rc;
-  hipLaunchKernelGGL(k_par_walk<PT>, gw, b64, 0, s, P, 1);
-  rc = chained(P, jobs_of(P, {6}, kCtrMerges), 12, 4, P.S.mcap + 1, s);
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_par_classify<PT>, g2, b256, 0, s, P);
-  rc = chained(P, jobs_of(P, {7}, kCtrEvents), 14, 5, P.ecap + 1, s);
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_par_scatter<PT>, g2, b256, 0, s, P);
+  hipLaunchKernelGGL(k_par_write<PT>, gw, b64, 0, s, P);
   HULL_LAUNCH_CHECK();
   return HULL_OK;
 }

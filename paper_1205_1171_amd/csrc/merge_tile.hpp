@@ -16,7 +16,6 @@ namespace hull {
 
 constexpr int kTileRankBits = 10;
 constexpr int kTileKeep = 8;   // bridge events a lane puts aside per segment
-constexpr int kTileScan = 12;  // longest list kept unsorted
 constexpr int kTileMaxWidth = 2 << kTileRankBits;  // two children of 1,024 points
 
 // LDS of one merge of up to W points (W even) by a group of GS lanes.
@@ -67,11 +66,11 @@ struct TileCtx {
     return e;
   }
   // position in ev of the last event among the list [lo, hi) before position
-  // `cur`, -1 if none: a list of up to kTileScan entries is not sorted and read
+  // `cur`, -1 if none: a list of up to kListScan entries is not sorted and read
   // whole, four independent reads at a time; a longer one by binary search
   __device__ __forceinline__ int last_before(int lo, int hi, int cur) const {
     int best = -1;
-    if (hi - lo > kTileScan) {
+    if (hi - lo > kListScan) {
       const int first = lo;
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -173,13 +172,15 @@ template <class PT, class GRP>
 __device__ __forceinline__ void tile_merge(const GRP& g, unsigned char* lds, int W,
                                            const RunPtrs& R, Header* h, int64_t s, int64_t m,
                                            int64_t e, int seg) {
-  const int nL = R.len_in[s], nR = R.len_in[m];
+  const int nL = R.left_len(s), nR = R.right_len(m, e);
+  const Event* Lev = R.left_ev(s);
+  const Event* Rev = R.right_ev(m, e);
   const int w = (int)(e - s), half = (int)(m - s);
   if (nL < 0 || nR < 0 || nL > 2 * half || nR > 2 * (w - half) || w > W || half > (1 << kTileRankBits) ||
       w - half > (1 << kTileRankBits)) {
     if (g.rank() == 0) {
       atomicCAS(&h->err, 0, HULL_EINTERNAL);
-      R.len_out[s] = 0;
+      R.out_len(s) = 0;
     }
     return;
   }
@@ -201,7 +202,7 @@ __device__ __forceinline__ void tile_merge(const GRP& g, unsigned char* lds, int
   for (int c = g.rank(); c < N; c += g.size()) {
     const bool left = c < nL;
     const int64_t o = left ? s : m;
-    const int4 x = *(const int4*)&R.ev_in[left ? 2 * s + c : 2 * m + (c - nL)];
+    const int4 x = *(const int4*)(left ? Lev + c : Rev + (c - nL));
     const int a = (int)(x.x - o), ww = (int)((x.y & 0x7fffffff) - o), b = (int)(x.z - o);
     const unsigned kind = (unsigned)x.y >> 31;
     L.ev[c] = make_uint2((unsigned)a | ((unsigned)ww << kTileRankBits) |
@@ -238,7 +239,7 @@ __device__ __forceinline__ void tile_merge(const GRP& g, unsigned char* lds, int
   if (total > 6 * W) {
     if (g.rank() == 0) {
       atomicCAS(&h->err, 0, HULL_EINTERNAL);
-      R.len_out[s] = 0;
+      R.out_len(s) = 0;
     }
     return;
   }
@@ -267,7 +268,7 @@ __device__ __forceinline__ void tile_merge(const GRP& g, unsigned char* lds, int
   g.sync();
   for (int q = g.rank(); q < 2 * W; q += g.size()) {
     const int first = L.off[q], k = L.off[q + 1] - first;
-    if (k > kTileScan) sort_positions(L.ent + first, k);
+    if (k > kListScan) sort_positions(L.ent + first, k);
   }
   g.sync();
   const int64_t cap = 2 * (e - s);
@@ -312,7 +313,7 @@ __device__ __forceinline__ void tile_merge(const GRP& g, unsigned char* lds, int
       break;
     }
     if (i < S && !bad && cnt.note.nout > 0) {
-      Event* out = R.ev_out + 2 * s + pos;
+      Event* out = R.out_ev(s) + pos;
       TileWrite wr{out, (int)s};
       if (cnt.complete()) {
         int nb = 0;
@@ -341,7 +342,7 @@ __device__ __forceinline__ void tile_merge(const GRP& g, unsigned char* lds, int
   }
   if (bad) atomicCAS(&h->err, 0, HULL_EINTERNAL);
   if (g.rank() == 0) {
-    R.len_out[s] = bad ? 0 : done;
+    R.out_len(s) = bad ? 0 : done;
     if (!bad) {
       // splice the -inf chains
       R.nx0[s + u00] = (int)s + v00;
@@ -411,12 +412,12 @@ __global__ void __launch_bounds__(GS < 64 ? 64 : GS) k_merge_tile(LevelArgs A, i
   const RunPtrs& R = A.run[blockIdx.y];
   const int grp = GS < 64 ? (int)threadIdx.x / GS : 0;
   const int64_t t = blockIdx.x * (int64_t)per + grp;
-  if (!R.pts || t >= A.S.moff[A.S.H]) return;  // the same on every lane of the group
+  if (!R.pts || t >= A.S.merges()) return;  // the same on every lane of the group
   const int* perm = A.perm[blockIdx.y];
-  const int2 se = A.S.mlist[perm ? perm[t] : t];
+  const int2 se = A.S.merge(perm ? perm[t] : t);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   if (A.h->err) {
-    if ((threadIdx.x & (GS - 1)) == 0) R.len_out[s] = 0;
+    if ((threadIdx.x & (GS - 1)) == 0) R.out_len(s) = 0;
     return;
   }
   const int W = (int)A.width;

@@ -93,21 +93,21 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
   const int gshift = (threadIdx.x & 63) & ~(G - 1);  // the group's first lane in the wave
   const int64_t g0 = (blockIdx.x * (int64_t)NB + threadIdx.x) / G;
   const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts || g0 >= A.S.moff[A.S.H]) return;  // the same for every lane of the group
+  if (!R.pts || g0 >= A.S.merges()) return;  // the same for every lane of the group
   const int* perm = A.perm[blockIdx.y];
   const int64_t g = perm ? perm[g0] : g0;
-  const int2 se = A.S.mlist[g];
+  const int2 se = A.S.merge(g);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   Header* h = A.h;
   if (h->err) {
-    if (lane == 0) R.len_out[s] = 0;
+    if (lane == 0) R.out_len(s) = 0;
     return;
   }
-  const int nL = R.len_in[s], nR = R.len_in[m];
+  const int nL = R.left_len(s), nR = R.right_len(m, e);
   if (nL < 0 || nR < 0 || nL > 2 * (m - s) || nR > 2 * (e - m)) {
     if (lane == 0) {
       atomicCAS(&h->err, 0, HULL_EINTERNAL);
-      R.len_out[s] = 0;
+      R.out_len(s) = 0;
     }
     return;
   }
@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
     if (e - s > A.width || A.width > 32767) {
       if (lane == 0) {
         atomicCAS(&h->err, 0, HULL_EINTERNAL);
-        R.len_out[s] = 0;
+        R.out_len(s) = 0;
       }
       return;
     }
@@ -147,9 +147,10 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
     lk.p = R.lk;
     pts = (const PT*)R.pts;
   }
-  const Event* Lev = R.ev_in + 2 * s;
-  const Event* Rev = R.ev_in + 2 * m;
-  Event* out = R.ev_out + 2 * s;
+  const Event* Lev = R.left_ev(s);
+  const Event* Rev = R.settle_right(m, e, nR, lane, G);
+  if (R.right_waits_in_output(m, e)) __threadfence_block();
+  Event* out = R.out_ev(s);
   const int64_t cap = 2 * (e - s);
   Event* Lc = chunk[grp][0];
   Event* Rc = chunk[grp][1];
@@ -163,7 +164,7 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
       if (guard > 2 * (e - s) + 4) {
         if (lane == 0) {
           atomicCAS(&h->err, 0, HULL_EINTERNAL);
-          R.len_out[s] = 0;
+          R.out_len(s) = 0;
         }
         return;
       }
@@ -329,7 +330,7 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
   if (lane == 0) {
     R.nx0[u0 + base] = v0 + base;
     R.pv0[v0 + base] = u0 + base;
-    R.len_out[s] = k;
+    R.out_len(s) = k;
   }
 }
 

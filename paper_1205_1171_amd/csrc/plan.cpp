@@ -25,7 +25,7 @@ Plan make_plan(int64_t n, int64_t H, int min_seg, int pt_bytes) {
   p.mcap = nn / 2 + 1;
   // walk segments of one level: sum over merges of 1 + events / G, events <= 2n
   p.seg_cap = p.mcap + (2 * nn) / std::max(min_seg, 1) + 1;
-  int64_t longest = std::max<int64_t>({p.count_len, 2 * nn + 1, p.seg_cap + 1, hh + 1});
+  int64_t longest = std::max<int64_t>({p.count_len, 2 * nn + 2, p.seg_cap + 1, hh + 1});
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t o = off;
@@ -39,9 +39,6 @@ Plan make_plan(int64_t n, int64_t H, int min_seg, int pt_bytes) {
   p.off1 = take(2 * sizeof(int64_t));
   p.mcnt = take((hh + 1) * 4);
   p.moff = take((hh + 1) * 4);
-  p.tcnt = take((hh + 1) * 4);
-  p.toff = take((hh + 1) * 4);
-  p.tlist = take(hh * 4);
   p.mlist = take(p.mcap * sizeof(int2));
   for (int r = 0; r < 2; ++r) {
     p.perm[r] = take(p.mcap * 4);
@@ -56,19 +53,14 @@ Plan make_plan(int64_t n, int64_t H, int min_seg, int pt_bytes) {
       p.ev[r][b] = take(2 * nn * sizeof(Event));
       p.len[r][b] = take(nn * 4);
     }
-    p.cntR[r] = take(nn * 4);
-    p.cntL[r] = take(nn * 4);
-    p.offR[r] = take(nn * 4);
-    p.offL[r] = take(nn * 4);
-    p.curR[r] = take(nn * 4);
-    p.curL[r] = take(nn * 4);
-    p.claimR[r] = take(nn * 4);
-    p.claimL[r] = take(nn * 4);
-    p.entR[r] = take(3 * nn * sizeof(Entry));
+    p.off[r] = take((2 * nn + 2) * 4);
+    // at most 6 entries per point: an event (2n of them) changes two links, an
+    // insertion (n: a point enters its block's chain at most once) four
+    p.ent[r] = take(6 * nn * sizeof(int2));
     if (r == 0) {
       // the sort's buffers live only until the points are gathered, before
       // any merge: they share run 0's entry lists (48 bytes per point)
-      size_t o = p.entR[0];
+      size_t o = p.ent[0];
       auto sub = [&](size_t bytes) {
         size_t q = o;
         o = align256(o + bytes);
@@ -80,38 +72,23 @@ Plan make_plan(int64_t n, int64_t H, int min_seg, int pt_bytes) {
       p.vals1 = sub(nn * 4);
       p.hid = sub(nn * 4);
       p.counts = sub(p.count_len * 4);
-      static_assert(3 * sizeof(Entry) >= 20, "sort buffers must fit in the entry lists");
+      if (o > off) off = o;  // a few points: the radix counts are longer
     }
-    p.entL[r] = take(3 * nn * sizeof(Entry));
+    p.pos[r] = take(2 * nn * sizeof(int4));
     p.ctr[r] = take(kCtrSlots * sizeof(int32_t));
-    p.touched[r] = take(2 * nn * 4);
     p.ecnt[r] = take((p.mcap + 1) * 4);
     p.eoff[r] = take((p.mcap + 1) * 4);
-    p.cslot[r] = take(2 * nn * 4);
     p.cmerge[r] = take(2 * nn * 4);
     p.segS[r] = take((p.mcap + 1) * 4);
     p.segBase[r] = take((p.mcap + 1) * 4);
     p.segMerge[r] = take((p.seg_cap + 1) * 4);
-    p.segB[r] = take((p.seg_cap + 1) * 4);
+    p.segJ[r] = take((p.seg_cap + 1) * 4);
     p.segCnt[r] = take((p.seg_cap + 1) * 4);
     p.segOff[r] = take((p.seg_cap + 1) * 4);
     p.segUV[r] = take((p.seg_cap + 1) * sizeof(int2));
-    p.segTmp[r] = take((p.seg_cap + 1) * kSegKeep * sizeof(Event));
-    p.segTmpUV[r] = take((p.seg_cap + 1) * kSegKeep * sizeof(int2));
-    p.bev[r] = take(2 * nn * sizeof(Event));
-    p.buv[r] = take(2 * nn * sizeof(int2));
-    p.nB[r] = take((p.mcap + 1) * 4);
-    p.boff[r] = take((p.mcap + 1) * 4);
+    p.segSteps[r] = take((p.seg_cap + 1) * sizeof(unsigned long long));
+    p.segKeep[r] = take((p.seg_cap + 1) * kSegKeep * sizeof(Event));
     p.uv0[r] = take(p.mcap * sizeof(int2));
-    p.aR[r] = take((2 * nn + 1) * 4);
-    p.aL[r] = take((2 * nn + 1) * 4);
-    p.aT[r] = take((2 * nn + 1) * 4);
-    // per-event survival flags and prefix sums are written after the list
-    // allocation counts are last read (place, before the walk): same space
-    p.surv[r] = p.aR[r];
-    p.jb[r] = p.aL[r];
-    p.pre[r] = p.aT[r];
-    p.wf[r] = take(2 * nn);
   }
   p.total = off;
   return p;

@@ -14,12 +14,19 @@ namespace hull {
 // ---------------------------------------------------------------------------
 // Range check and x extent.
 // ---------------------------------------------------------------------------
-__global__ void k_header_init(Header* h) {
-  if (threadIdx.x == 0) {
+__global__ void __launch_bounds__(256) k_call_init(Header* h, int64_t* off1, int64_t n,
+                                                   unsigned long long* words, int64_t count) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
+       i += (int64_t)gridDim.x * blockDim.x)
+    words[i] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
     h->err = 0;
     h->minx = 0x7fffffff;
     h->maxx = -0x7fffffff - 1;
-    h->nbits = 0;
+    if (off1) {
+      off1[0] = 0;
+      off1[1] = n;
+    }
   }
 }
 
@@ -57,15 +64,6 @@ __global__ void __launch_bounds__(256) k_extent(const InT* __restrict__ xyz, int
   }
 }
 
-__global__ void k_nbits(Header* h) {
-  if (threadIdx.x == 0) {
-    uint32_t span = (uint32_t)((int64_t)h->maxx - h->minx);
-    int b = 0;
-    while (b < 32 && (span >> b) != 0) ++b;
-    h->nbits = b;
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Radix passes.  The x passes sort the key x - min(x) (value = input index);
 // passes whose digit lies above the key's bit length are skipped.  For a
@@ -79,8 +77,9 @@ struct RadixBufs {
 };
 
 __device__ __forceinline__ int x_passes(const Header* h) {
-  int p = (h->nbits + kRadixBits - 1) / kRadixBits;
-  return p < 1 ? 1 : p;
+  const uint32_t span = (uint32_t)((int64_t)h->maxx - h->minx);
+  const int bits = span ? 32 - __builtin_clz(span) : 1;
+  return (bits + kRadixBits - 1) / kRadixBits;
 }
 
 // Digit of element p for (kind, d): kind 0 = x digit d, kind 1 = hull digit d.
@@ -195,12 +194,16 @@ __global__ void __launch_bounds__(256) k_hull_ids(const int64_t* __restrict__ of
 }
 
 // Gather the points in rank order from the buffer of the last executed pass;
-// the index carried with each is the one within the point's hull.
+// the index carried with each is the one within the point's hull.  Single
+// points: no links, empty movies.
+struct RunInitPair {
+  RunInit r[2];
+};
 template <class InT, class PT>
 __global__ void __launch_bounds__(256)
     k_gather(const InT* __restrict__ xyz, RadixBufs B, const int32_t* __restrict__ hid,
              const int64_t* __restrict__ off, int hull_passes, int64_t n, PT* __restrict__ pts,
-             const Header* h) {
+             RunInitPair I, const Header* h) {
   const int e = x_passes(h) + hull_passes - 1;
   const int32_t* v = B.vals[e & 1];
   for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n;
@@ -208,7 +211,18 @@ __global__ void __launch_bounds__(256)
     int i = v[r];
     int local = hid ? (int)(i - off[hid[i]]) : i;
     pts[r] = make_pt(xyz, i, local);
+    for (int q = 0; q < 2; ++q) {
+      if (!I.r[q].pv0) continue;
+      I.r[q].pv0[r] = kNil;
+      I.r[q].nx0[r] = kNil;
+      I.r[q].len[r] = 0;
+      if (r < kCtrSlots) I.r[q].ctr[r] = 0;
+    }
   }
+  // (fewer points than counters)
+  if (blockIdx.x == 0 && threadIdx.x < kCtrSlots && threadIdx.x >= n)
+    for (int q = 0; q < 2; ++q)
+      if (I.r[q].pv0) I.r[q].ctr[threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -354,26 +368,15 @@ int32_t scan_chained_i32(const int32_t* in, int32_t* out, int64_t len, unsigned 
   return exclusive_scan_chained(J, 0, len, words, wstride, epoch, h, s);
 }
 
-__global__ void __launch_bounds__(256) k_zero_words(unsigned long long* w, int64_t count) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
-       i += (int64_t)gridDim.x * blockDim.x)
-    w[i] = 0;
-}
-
-void zero_words(unsigned long long* w, int64_t count, hipStream_t s) {
-  if (count <= 0) return;
-  const int64_t b = (count + 255) / 256;
-  hipLaunchKernelGGL(k_zero_words, dim3((unsigned)(b < 1024 ? b : 1024)), dim3(256), 0, s, w,
-                     count);
-}
-
-void init_header(Header* h, hipStream_t s) {
-  hipLaunchKernelGGL(k_header_init, dim3(1), dim3(64), 0, s, h);
+void init_call(Header* h, int64_t* off1, int64_t n, char* ws, const Plan& pl, hipStream_t s) {
+  const int64_t count = kChainJobs * pl.chain_stride, b = (count + 255) / 256;
+  hipLaunchKernelGGL(k_call_init, dim3((unsigned)(b < 1024 ? b : 1024)), dim3(256), 0, s, h, off1, n,
+                     (unsigned long long*)(ws + pl.chain_words), count);
 }
 
 template <class InT, class PT>
 int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_t H, char* ws,
-                    const Plan& pl, hipStream_t s) {
+                    const Plan& pl, const RunInit* runs, hipStream_t s) {
   Header* h = (Header*)(ws + pl.header);
   RadixBufs B;
   B.keys[0] = (uint32_t*)(ws + pl.keys0);
@@ -390,14 +393,10 @@ int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_
     hull_passes = (hb + kRadixBits - 1) / kRadixBits;
   }
   const int tiles = (int)pl.tiles;
-  // the status words of the call's one-launch scans start from zero here:
-  // the sort's passes use epochs 1..8, the merge levels higher ones
   unsigned long long* words = (unsigned long long*)(ws + pl.chain_words);
-  zero_words(words, kChainJobs * pl.chain_stride, s);
   unsigned eg = (unsigned)std::min<int64_t>((n + 255) / 256, 2048);
   if (eg < 1) eg = 1;
   hipLaunchKernelGGL(k_extent<InT>, dim3(eg), dim3(256), 0, s, d_xyz, n, h);
-  hipLaunchKernelGGL(k_nbits, dim3(1), dim3(64), 0, s, h);
   if (hid) hipLaunchKernelGGL(k_hull_ids, dim3(eg), dim3(256), 0, s, hull_off, H, n, hid);
   for (int kind = 0; kind < 2; ++kind) {
     const int npass = kind == 0 ? 4 : hull_passes;
@@ -412,14 +411,14 @@ int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_
     }
   }
   hipLaunchKernelGGL((k_gather<InT, PT>), dim3(eg), dim3(256), 0, s, d_xyz, B, hid, hull_off,
-                     hull_passes, n, (PT*)(ws + pl.pts), h);
+                     hull_passes, n, (PT*)(ws + pl.pts), RunInitPair{{runs[0], runs[1]}}, h);
   HULL_LAUNCH_CHECK();
   return HULL_OK;
 }
 
 template int32_t sort_points<int32_t, int4>(const int32_t*, int64_t, const int64_t*, int64_t,
-                                            char*, const Plan&, hipStream_t);
+                                            char*, const Plan&, const RunInit*, hipStream_t);
 template int32_t sort_points<int64_t, WPt>(const int64_t*, int64_t, const int64_t*, int64_t,
-                                           char*, const Plan&, hipStream_t);
+                                           char*, const Plan&, const RunInit*, hipStream_t);
 
 }  // namespace hull

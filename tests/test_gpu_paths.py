@@ -109,3 +109,26 @@ def test_segment_walk_movies(monkeypatch, tile, seg):
                 assert (bl[::w] == wbl).all()
                 got = np.concatenate([ev[2 * s:2 * s + bl[s]] for s in range(0, len(p), w)])
                 assert (got == want).all()
+
+
+# Ragged sizes around powers of two: a trailing block waits in the buffer of
+# its own last level, which is the merge's output buffer at every other level,
+# on every strategy.
+@pytest.mark.parametrize("serial,tile,wave", [("99", "0", "-1"), ("99", "0", "4"), ("3", "11", "-1"),
+                                              ("0", "0", "-1")])
+def test_trailing_blocks(monkeypatch, serial, tile, wave):
+    import oracle
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    monkeypatch.setenv("HULL_SERIAL_LEVELS", serial)
+    monkeypatch.setenv("HULL_TILE_LEVELS", tile)
+    monkeypatch.setenv("HULL_WAVE_LEVEL", wave)
+    rng = np.random.default_rng(8)
+    ws = hull.Workspace()
+    for n in [b + d for b in (64, 256, 1024, 2048) for d in (1, 2, 3, 7, 33, b // 2 + 1, b - 1)]:
+        p = np.ascontiguousarray(workloads.sphere(rng, n, 1 << 20))
+        say("trailing", serial, tile, wave, n)
+        got = hull.hull_sync(torch.from_numpy(p).cuda(), ws=ws).cpu().numpy()
+        a, b = validate.canonical(got), validate.canonical(oracle.hull(p))
+        assert a.shape == b.shape and (a == b).all()
