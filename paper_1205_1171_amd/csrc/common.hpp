@@ -41,10 +41,15 @@ constexpr int kCtrSlots = 8;     // size of the region (int32 words)
 // Device-side status words at the head of every workspace.
 struct Header {
   int32_t err;      // first error seen on the device (HULL_* code), 0 = none
-  int32_t minx;     // minimum x (sort key origin)
-  int32_t maxx;     // maximum x
-  int32_t pad[61];  // keeps the header one 256-byte line
+  int32_t kept;     // points left by the filter
+  int32_t radix_len;    // radix counts in use (256 per tile of the sort)
+  uint32_t rho[2];      // radius of the filter's ball by its coarse and fine cells (float bits)
+  int32_t pad0;
+  long long lo[3], hi[3];  // extent of the coordinates (x: the sort key's origin and length)
+  double csum[3];          // sums of 256 sample points
+  int32_t pad[40];  // keeps the header one 256-byte line
 };
+static_assert(sizeof(Header) == 256, "one line");
 
 // One movie event: the face (a, w, b) of ranks a < w < b whose middle vertex w
 // enters (kind = 1) or leaves (kind = 0) the kinetic chain, and the standard
@@ -112,13 +117,15 @@ inline void clear_stale_hip_error() { (void)hipGetLastError(); }
 
 // One hull (lower and/or upper run) of n points: sort, every merge level,
 // faces (the body of hull_lower / hull_full).  int32 rows: the standard
-// range; int64 rows: the wide range (hull_full_wide and friends).
+// range; int64 rows: the wide range (hull_full_wide and friends).  filter: let
+// interior points go first (calls of kFilterMin points and more).
+constexpr int64_t kFilterMin = 1024;
 int32_t hull_runs(const int32_t* d_xyz, int64_t n, int32_t* d_faces, int64_t cap, int64_t* d_info,
                   void* d_ws, size_t ws_bytes, hipStream_t s, bool lower, bool upper,
-                  void* const* events, int32_t nevents);
+                  void* const* events, int32_t nevents, bool filter = true);
 int32_t hull_runs(const int64_t* d_xyz, int64_t n, int32_t* d_faces, int64_t cap, int64_t* d_info,
                   void* d_ws, size_t ws_bytes, hipStream_t s, bool lower, bool upper,
-                  void* const* events, int32_t nevents);
+                  void* const* events, int32_t nevents, bool filter = true);
 
 // Workspace bytes of the wide-range entry points (int64 rows) and of the
 // float entry points (the wide hull plus the snapped rows), for n points.
@@ -139,12 +146,20 @@ struct RunInit {
   int* ctr;
 };
 
-// Sort: ranks by (hull, x, index within the hull).  Fills pts (PT: int4 x, y,
+// Extent and range check of the input (into the header) and, if asked for, the
+// interior points taken out (filter.hip): the kept points' keys and indices go
+// to the sort's second buffer and their number to off1[1].
+template <class InT>
+int32_t extent_and_filter(const InT* d_xyz, int64_t n, bool filter, char* ws, const Plan& pl,
+                          hipStream_t s);
+
+// Sort: ranks by (hull, x, index within the hull), of the points that
+// extent_and_filter listed (from_list) or of all n.  Fills pts (PT: int4 x, y,
 // z, index within the hull from int32 rows; WPt from int64 rows, by rank) and
 // the runs' links.  hull_off (device [H + 1]) may be NULL for a single hull.
 template <class InT, class PT>
 int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_t H, char* ws,
-                    const Plan& pl, const RunInit* runs, hipStream_t s);
+                    const Plan& pl, const RunInit* runs, bool from_list, hipStream_t s);
 
 // Exclusive scans of int32 (in place allowed), each in one launch (a chained
 // scan): up to kMaxScanJobs arrays of the same add and cap, each of a length
@@ -174,4 +189,5 @@ int32_t scan_chained_i32(const int32_t* in, int32_t* out, int64_t len, unsigned 
 // scans 8k + 1..7, the face offsets kChainEpochFaces.  init_call clears the
 // words at the start of every call.
 constexpr unsigned kChainEpochFaces = 8 * 28 + 1;
+constexpr unsigned kChainEpochFilter = 8 * 28 + 2;
 }  // namespace hull

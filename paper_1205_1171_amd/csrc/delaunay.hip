@@ -70,7 +70,7 @@ int32_t hull_delaunay(const int32_t* d_xy, int64_t n, int32_t* d_tris, int64_t c
     hipLaunchKernelGGL(hull::k_lift, dim3(g), dim3(256), 0, s, d_xy, n, xyz);
   }
   int32_t rc = hull::hull_runs(n > 0 ? xyz : (const int64_t*)nullptr, n, d_tris, cap, d_info, d_ws, head, s, true,
-                               false, nullptr, 0);
+                               false, nullptr, 0, false);  // no lifted point is interior
   if (rc) return rc;
   hipLaunchKernelGGL(hull::k_ccw, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((cap + 255) / 256, 4096))),
                      dim3(256), 0, s, d_tris, d_info);

@@ -147,6 +147,20 @@ struct Sched {
   }
 };
 
+// A level's merges run either way (kernels' `sel`: 1, only if the level counts as
+// many merges; 2, only if it does not; 0, always).  The host cannot tell once
+// interior points have been taken out, so both kernels are launched and the
+// device's number of points decides.  Many: enough merges to fill the chip one
+// lane or lane group each, or a block's points mostly not vertices.
+constexpr int64_t kTileMerges = 49152;
+constexpr int64_t kTilePoints = int64_t(1) << 21;
+__host__ __device__ inline bool many_merges(int64_t merges, int64_t n) {
+  return 2 * merges >= kTileMerges || n > kTilePoints;
+}
+__device__ __forceinline__ bool selected(const Sched& S, int sel) {
+  return sel == 0 || many_merges(S.merges(), S.off[S.H]) == (sel == 1);
+}
+
 struct LevelArgs {
   RunPtrs run[2];
   int* perm[2];   // per run: merge of each lane (nullptr: lane g takes merge g)
@@ -155,6 +169,7 @@ struct LevelArgs {
   Sched S;
   int64_t half;   // size of a left block
   int64_t width;  // size of a merged block
+  int sel;
 };
 // Exact (time, rank triple) order of two events (cold path).  Arguments
 // go by value so that callers keep their candidates in registers.
@@ -383,6 +398,7 @@ struct ParLevel {
   Header* h;
   Sched S;
   int64_t n;        // bound on the points
+  int sel;
   int seg_events;   // child events per walk segment
   int64_t seg_cap;  // bound on the walk segments of a level
   int64_t mcap;     // bound on the merges of a level

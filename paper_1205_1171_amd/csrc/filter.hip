@@ -1,0 +1,447 @@
+// Interior points leave before the sort.  A point strictly inside the hull of
+// other input points is no vertex of the hull, whatever the symbolic
+// perturbation (it moves points by infinitesimals), and taking it away
+// changes neither the faces nor their order (ranks keep their order, and the
+// perturbation goes by the input index a point carries).
+//
+// The certificate is a star of tetrahedra around a centre c, the mean of 256
+// input points (so c lies in their hull):
+//   - directions from c are cut into G x G cells (the octahedral map: the
+//     sphere's directions unfolded onto a square); every cell's representative
+//     is its point farthest from c;
+//   - the representatives of four adjacent cells give two triangles, and with c
+//     two tetrahedra of points of the hull;
+//   - a point strictly inside one of the eight tetrahedra around its cell (which
+//     hold the cell's directions whatever the representatives' places in their
+//     cells) is dropped.
+// A tetrahedron that is flat or misses a corner drops nothing, so any input is
+// safe.  Most points need no tetrahedron: when every one of a grid's is
+// positively oriented, their triangles are a closed surface around c that
+// meets every direction (its signed solid angles are all positive, so it winds
+// around c at least once), and the ball up to its nearest plane lies inside.
+// Kept: 13,400 of 2^20 points of a ball (whose hull has 4,600 vertices), 13,700
+// of a cube, all of a sphere; of 2^24 points, 1% on a sphere around a Gaussian,
+// the sphere's.  That cloud's hull took 26.6 ms with every point, 3.1 with the
+// filter (0.28 of them the filter's).
+//
+// Arithmetic: coordinates relative to c, each axis scaled by a power of two to
+// |q| <= 1 (exact in double: 256 samples add 8 bits to at most 43), rounded to
+// float.  Every tetrahedron is stored as four planes with unit normals, made in
+// double and rounded to float; a dot product of such a normal with q is
+// within 2^-21 |q|_1 (2^-24 each for the normal, for q and for three products
+// and sums), and the tests ask for a margin of 2^-20 |q|_1.  A tetrahedron's
+// orientation is taken from a determinant in double, and those below 2^-24 (in
+// units where |q| <= 1) are not used.
+#include <algorithm>
+#include <limits>
+
+#include "common.hpp"
+#include "predicates.hpp"
+
+namespace hull {
+
+constexpr int kCoarse = 8;       // cells per side of the first test (its tetrahedra in LDS)
+constexpr int kFilterTile = 1024;  // points per block of the mask and the compaction
+constexpr double kMinDet = 0x1p-24;
+
+struct FilterArgs {
+  int64_t n;
+  Header* h;
+  unsigned long long* reps;  // [G * G] (|q|^2 as float bits, point), 0: empty
+  float4* quads;             // [(kCoarse + 1)^2 + (G + 1)^2] x 8
+  unsigned long long* mask;  // [ceil(n / 1024) * 16] points kept
+  int32_t* tcnt;             // [ceil(n / 1024)] points kept per tile, then their offsets
+  uint32_t* keys;            // kept points: x - min x
+  int32_t* vals;             //              index
+  int64_t* off1;             // [1] receives the number of points kept
+  int G;
+};
+
+struct Frame {
+  double c[3], s[3];
+};
+__device__ __forceinline__ Frame frame_of(const Header* h) {
+  Frame f;
+  for (int a = 0; a < 3; ++a) {
+    f.c[a] = h->csum[a] * (1.0 / 256.0);
+    const double span = (double)(h->hi[a] - h->lo[a]);
+    int e = 0;
+    (void)frexp(span > 1.0 ? span : 1.0, &e);  // span <= 2^e
+    f.s[a] = ldexp(1.0, -e);
+  }
+  return f;
+}
+template <class InT>
+__device__ __forceinline__ void rel(const Frame& f, const InT* xyz, int64_t i, double q[3]) {
+  for (int a = 0; a < 3; ++a) q[a] = ((double)xyz[3 * i + a] - f.c[a]) * f.s[a];
+}
+__device__ __forceinline__ float abs1(float x, float y, float z) { return fabsf(x) + fabsf(y) + fabsf(z); }
+
+// The direction of q on the unit square (any rounding will do: the square only
+// says which tetrahedra to try).
+__device__ __forceinline__ void square_of(float x, float y, float z, float& u, float& v) {
+  const float l = 1.0f / fmaxf(abs1(x, y, z), 1e-30f);
+  u = x * l;
+  v = y * l;
+  if (z < 0) {
+    const float a = copysignf(1.0f - fabsf(v), u), b = copysignf(1.0f - fabsf(u), v);
+    u = a;
+    v = b;
+  }
+  u = u * 0.5f + 0.5f;
+  v = v * 0.5f + 0.5f;
+}
+__device__ __forceinline__ int cell_at(float u, int G) {
+  const int i = (int)(u * (float)G);
+  return i < 0 ? 0 : (i > G - 1 ? G - 1 : i);
+}
+
+// Extent of each axis, the range check, and (block 0) the sum of 256 samples.
+// Clears the representatives.
+template <class InT>
+__global__ void __launch_bounds__(256) k_extent(const InT* __restrict__ xyz, int64_t n, Header* h,
+                                                unsigned long long* reps, int nreps) {
+  __shared__ long long smin[3][256], smax[3][256];
+  __shared__ int sbad[256];
+  const int t = threadIdx.x;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + t; i < nreps; i += (int64_t)gridDim.x * blockDim.x)
+    reps[i] = 0;
+  InT lo[3], hi[3];
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = std::numeric_limits<InT>::max();
+    hi[a] = std::numeric_limits<InT>::lowest();
+  }
+  int bad = 0;
+  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + t; p < n; p += (int64_t)gridDim.x * blockDim.x) {
+    const InT c[3] = {xyz[3 * p], xyz[3 * p + 1], xyz[3 * p + 2]};
+    const bool b = pt_out_of_range(c[0], c[1], c[2]);
+    bad |= b;
+    for (int a = 0; a < 3; ++a) {  // rows out of range count as zero
+      const InT v = b ? 0 : c[a];
+      lo[a] = v < lo[a] ? v : lo[a];
+      hi[a] = v > hi[a] ? v : hi[a];
+    }
+  }
+  for (int a = 0; a < 3; ++a) {
+    smin[a][t] = lo[a];
+    smax[a][t] = hi[a];
+  }
+  sbad[t] = bad;
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (t < s) {
+      for (int a = 0; a < 3; ++a) {
+        smin[a][t] = min(smin[a][t], smin[a][t + s]);
+        smax[a][t] = max(smax[a][t], smax[a][t + s]);
+      }
+      sbad[t] |= sbad[t + s];
+    }
+    __syncthreads();
+  }
+  if (t < 3) {
+    // the device's rows only narrow an extent that others have widened
+    atomicMin(&h->lo[t], smin[t][0]);
+    atomicMax(&h->hi[t], smax[t][0]);
+  }
+  if (t == 0 && sbad[0]) atomicCAS(&h->err, 0, HULL_ERANGE);
+  if (blockIdx.x != 0) return;
+  __syncthreads();
+  for (int a = 0; a < 3; ++a) smin[a][t] = (long long)xyz[3 * ((int64_t)t * n / 256) + a];
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (t < s)
+      for (int a = 0; a < 3; ++a) smin[a][t] += smin[a][t + s];
+    __syncthreads();
+  }
+  if (t < 3) h->csum[t] = (double)smin[t][0];
+}
+
+template <class InT>
+__global__ void __launch_bounds__(256) k_reps(const InT* __restrict__ xyz, FilterArgs F) {
+  extern __shared__ unsigned long long best[];
+  const int cells = F.G * F.G;
+  if (F.h->err) return;
+  for (int q = threadIdx.x; q < cells; q += blockDim.x) best[q] = 0;
+  __syncthreads();
+  const Frame f = frame_of(F.h);
+  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < F.n;
+       p += (int64_t)gridDim.x * blockDim.x) {
+    double q[3];
+    rel(f, xyz, p, q);
+    const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
+    float u, v;
+    square_of(x, y, z, u, v);
+    const int c = cell_at(v, F.G) * F.G + cell_at(u, F.G);
+    const unsigned long long key =
+        ((unsigned long long)__float_as_uint(x * x + y * y + z * z) << 32) | (unsigned)p;
+    if (key > best[c]) atomicMax(&best[c], key);
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < cells; q += blockDim.x)
+    if (best[q] > __hip_atomic_load(&F.reps[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&F.reps[q], best[q]);
+}
+
+// Cells across the edges of the square: the octahedron's edges there fold onto
+// themselves.
+__device__ __forceinline__ void wrap_cell(int& i, int& j, int G) {
+  if (i < 0) { i = 0; j = G - 1 - j; }
+  else if (i >= G) { i = G - 1; j = G - 1 - j; }
+  if (j < 0) { j = 0; i = G - 1 - i; }
+  else if (j >= G) { j = G - 1; i = G - 1 - i; }
+}
+
+__device__ double det3(const double* a, const double* b, const double* d) {
+  return (a[1] * b[2] - a[2] * b[1]) * d[0] + (a[2] * b[0] - a[0] * b[2]) * d[1] +
+         (a[0] * b[1] - a[1] * b[0]) * d[2];
+}
+
+// The tetrahedron (c, a, b, d) as three planes through c and the outer one;
+// left zero when it is flat.  Returns the outer plane's distance from c, 0
+// unless the tetrahedron is positively oriented.
+__device__ float tetra(const double* a, const double* b, const double* d, float4* out) {
+  auto cross = [](const double* p, const double* q, double* r) {
+    r[0] = p[1] * q[2] - p[2] * q[1];
+    r[1] = p[2] * q[0] - p[0] * q[2];
+    r[2] = p[0] * q[1] - p[1] * q[0];
+  };
+  auto unit = [](double* r, double sg) {
+    const double l = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
+    for (int k = 0; k < 3; ++k) r[k] = l > 0 ? r[k] * (sg / l) : 0.0;
+  };
+  double ab[3], bd[3], da[3], n[3], e[3], g[3];
+  cross(a, b, ab);
+  const double det = ab[0] * d[0] + ab[1] * d[1] + ab[2] * d[2];
+  if (!(fabs(det) > kMinDet)) {
+    for (int k = 0; k < 4; ++k) out[k] = make_float4(0, 0, 0, 0);
+    return 0.0f;
+  }
+  const double sg = det > 0 ? 1.0 : -1.0;
+  cross(b, d, bd);
+  cross(d, a, da);
+  for (int k = 0; k < 3; ++k) {
+    e[k] = b[k] - a[k];
+    g[k] = d[k] - a[k];
+  }
+  cross(e, g, n);
+  unit(ab, sg);
+  unit(bd, sg);
+  unit(da, sg);
+  unit(n, sg);
+  const double h = n[0] * a[0] + n[1] * a[1] + n[2] * a[2];
+  out[0] = make_float4((float)ab[0], (float)ab[1], (float)ab[2], (float)n[0]);
+  out[1] = make_float4((float)bd[0], (float)bd[1], (float)bd[2], (float)n[1]);
+  out[2] = make_float4((float)da[0], (float)da[1], (float)da[2], (float)n[2]);
+  const float dist = (float)(h * (1.0 - 0x1p-22));
+  out[3] = make_float4(dist, 0, 0, 0);
+  return det > 0 ? dist : 0.0f;
+}
+
+// The two tetrahedra of every 2 x 2 block of adjacent cells, at kCoarse cells
+// per side (a coarse cell's representative: the farthest of its cells') and at G.
+template <class InT>
+__global__ void __launch_bounds__(64) k_mesh(const InT* __restrict__ xyz, FilterArgs F) {
+  if (F.h->err) return;
+  const int nc = (kCoarse + 1) * (kCoarse + 1), nf = (F.G + 1) * (F.G + 1);
+  int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= nc + nf) return;
+  float4* out = F.quads + 8 * (int64_t)t;
+  const int grid = t >= nc;  // 0: the coarse cells, 1: the fine ones
+  const int g = grid ? F.G : kCoarse, per = F.G / g;
+  if (grid) t -= nc;
+  const int qi = t % (g + 1), qj = t / (g + 1);
+  const Frame f = frame_of(F.h);
+  double v[4][3];
+  int cell[4];
+  bool ok = true;
+  for (int k = 0; k < 4; ++k) {
+    int i = qi - (k == 0 || k == 3), j = qj - (k < 2);
+    wrap_cell(i, j, g);
+    cell[k] = j * g + i;
+    unsigned long long key = 0;
+    for (int y = 0; y < per; ++y)
+      for (int x = 0; x < per; ++x) {
+        const unsigned long long c = F.reps[(j * per + y) * F.G + i * per + x];
+        key = c > key ? c : key;
+      }
+    ok = ok && key != 0;
+    rel(f, xyz, (int64_t)(unsigned)key, v[k]);
+  }
+  if (!ok)
+    for (int k = 0; k < 3; ++k) v[1][k] = v[3][k] = 0.0;
+  // the diagonal that leaves both triangles positively oriented, if one does
+  const double d02 = fmin(det3(v[0], v[1], v[2]), det3(v[0], v[2], v[3]));
+  const double d13 = fmin(det3(v[1], v[2], v[3]), det3(v[1], v[3], v[0]));
+  const bool swap = d13 > d02;
+  const double *a = swap ? v[1] : v[0], *b = swap ? v[2] : v[1], *c = swap ? v[3] : v[2],
+               *d = swap ? v[0] : v[3];
+  const float r0 = tetra(a, b, c, out), r1 = tetra(a, c, d, out + 4);
+  // in the middle of the square's edges a block folds onto one edge of the
+  // surface
+  if (cell[0] != cell[2] && cell[1] != cell[3])
+    atomicMin(&F.h->rho[grid], __float_as_uint(fminf(r0, r1)));
+}
+
+__device__ __forceinline__ bool inside(const float4* T, float x, float y, float z, float l1) {
+  const float tol = 0x1p-20f * l1;
+  bool in = false;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const float4 a = T[4 * k], b = T[4 * k + 1], c = T[4 * k + 2];
+    const float d = T[4 * k + 3].x;
+    const float p = a.x * x + a.y * y + a.z * z, q = b.x * x + b.y * y + b.z * z,
+                r = c.x * x + c.y * y + c.z * z, o = a.w * x + b.w * y + c.w * z;
+    in = in || (p > tol && q > tol && r > tol && o < d - tol);
+  }
+  return in;
+}
+
+// The tetrahedra at the four corners of the cell of (u, v).
+__device__ __forceinline__ bool inside_around(const float4* quads, int G, float u, float v, float x,
+                                              float y, float z, float l1) {
+  const int i = cell_at(u, G), j = cell_at(v, G);
+  bool in = false;
+  for (int k = 0; k < 4 && !in; ++k)
+    in = inside(quads + 8 * ((j + (k >> 1)) * (G + 1) + i + (k & 1)), x, y, z, l1);
+  return in;
+}
+
+// Points kept, as bits, and their number per tile.  The ball decides most; the
+// others are listed in LDS, so that the tetrahedra are tested by full wavefronts.
+template <class InT>
+__global__ void __launch_bounds__(256) k_mask(const InT* __restrict__ xyz, FilterArgs F) {
+  constexpr int nc = (kCoarse + 1) * (kCoarse + 1);
+  __shared__ float4 coarse[8 * nc];
+  __shared__ unsigned short list[kFilterTile];
+  __shared__ unsigned mask[kFilterTile / 32];
+  __shared__ int listed, count;
+  if (F.h->err) return;
+  const int t = threadIdx.x;
+  for (int q = t; q < 8 * nc; q += 256) coarse[q] = F.quads[q];
+  if (t < kFilterTile / 32) mask[t] = 0;
+  if (t == 0) listed = count = 0;
+  __syncthreads();
+  const Frame f = frame_of(F.h);
+  const float rho = fmaxf(__uint_as_float(F.h->rho[0]), __uint_as_float(F.h->rho[1]));
+  const float rr = rho * rho * (1.0f - 0x1p-18f);
+  const int64_t base = (int64_t)blockIdx.x * kFilterTile;
+  const int64_t left = F.n - base;
+  for (int j = t; j < kFilterTile && j < left; j += 256) {
+    double q[3];
+    rel(f, xyz, base + j, q);
+    const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
+    if (!(x * x + y * y + z * z < rr)) list[atomicAdd(&listed, 1)] = (unsigned short)j;
+  }
+  __syncthreads();
+  int kept = 0;
+  for (int k = t; k < listed; k += 256) {
+    const int j = list[k];
+    double q[3];
+    rel(f, xyz, base + j, q);
+    const float x = (float)q[0], y = (float)q[1], z = (float)q[2], l1 = abs1(x, y, z);
+    float u, v;
+    square_of(x, y, z, u, v);
+    if (inside_around(coarse, kCoarse, u, v, x, y, z, l1)) continue;
+    if (F.G > kCoarse && inside_around(F.quads + 8 * nc, F.G, u, v, x, y, z, l1)) continue;
+    atomicOr(&mask[j >> 5], 1u << (j & 31));
+    ++kept;
+  }
+  if (kept) atomicAdd(&count, kept);
+  __syncthreads();
+  if (t < kFilterTile / 64)
+    F.mask[(base >> 6) + t] = mask[2 * t] | ((unsigned long long)mask[2 * t + 1] << 32);
+  if (t == 0) F.tcnt[blockIdx.x] = count;
+}
+
+// The kept points in input order: keys and indices for the sort.
+template <class InT>
+__global__ void __launch_bounds__(256) k_compact(const InT* __restrict__ xyz, FilterArgs F) {
+  constexpr int words = kFilterTile / 64;
+  __shared__ int before[words];
+  const int t = threadIdx.x;
+  if (F.h->err) {  // no merge runs
+    if (blockIdx.x == 0 && t == 0) {
+      F.off1[1] = 0;
+      F.h->radix_len = 0;
+    }
+    return;
+  }
+  const int64_t base = (int64_t)blockIdx.x * kFilterTile;
+  if (t < words) {
+    const int c = __popcll(F.mask[(base >> 6) + t]);
+    int incl = c;
+    for (int o = 1; o < words; o <<= 1) {
+      const int y = __shfl_up(incl, o, words);
+      if (t >= o) incl += y;
+    }
+    before[t] = F.tcnt[blockIdx.x] + incl - c;
+  }
+  __syncthreads();
+  const long long minx = F.h->lo[0];
+  for (int j = 0; j < kFilterTile / 256; ++j) {
+    const int w = j * 4 + (t >> 6);
+    const unsigned long long m = F.mask[(base >> 6) + w];
+    if (!((m >> (t & 63)) & 1)) continue;
+    const int64_t p = base + j * 256 + t;
+    const int at = before[w] + __popcll(m & ((1ull << (t & 63)) - 1));
+    F.keys[at] = (uint32_t)((long long)xyz[3 * p] - minx);
+    F.vals[at] = (int32_t)p;
+  }
+  if (blockIdx.x == 0 && t == 0) {
+    F.off1[1] = F.h->kept;
+    F.h->radix_len = (F.h->kept + kTile - 1) / kTile * kBuckets;
+  }
+}
+
+// Cells per side: finer cells follow the surface closer but take more
+// representatives, and a cell should hold tens of points for its farthest to
+// be near the surface.
+static int filter_cells(int64_t n) { return n >= (1 << 17) ? 32 : (n >= (1 << 13) ? 16 : kCoarse); }
+
+template <class InT>
+int32_t extent_and_filter(const InT* d_xyz, int64_t n, bool filter, char* ws, const Plan& pl,
+                          hipStream_t s) {
+  Header* h = (Header*)(ws + pl.header);
+  FilterArgs F{};
+  F.n = n;
+  F.h = h;
+  F.G = filter_cells(n);
+  // in the space of the merge levels' event places (32 bytes per point)
+  char* o = ws + pl.pos[0];
+  auto take = [&](size_t bytes) {
+    char* q = o;
+    o += (bytes + 255) & ~(size_t)255;
+    return q;
+  };
+  const int64_t tiles = (n + kFilterTile - 1) / kFilterTile;
+  const int quads = (kCoarse + 1) * (kCoarse + 1) + (F.G + 1) * (F.G + 1);
+  F.reps = (unsigned long long*)take((size_t)F.G * F.G * 8);
+  F.quads = (float4*)take((size_t)quads * 8 * sizeof(float4));
+  F.mask = (unsigned long long*)take((size_t)tiles * (kFilterTile / 64) * 8);
+  F.tcnt = (int32_t*)take((size_t)(tiles + 1) * 4);
+  if (filter && (size_t)(o - (ws + pl.pos[0])) > 2 * (size_t)n * sizeof(int4)) filter = false;
+  F.keys = (uint32_t*)(ws + pl.keys1);
+  F.vals = (int32_t*)(ws + pl.vals1);
+  F.off1 = (int64_t*)(ws + pl.off1);
+  const unsigned eg = (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 1024));
+  hipLaunchKernelGGL(k_extent<InT>, dim3(eg), dim3(256), 0, s, d_xyz, n, h, F.reps,
+                     filter ? F.G * F.G : 0);
+  if (!filter) return HULL_OK;
+  hipLaunchKernelGGL(k_reps<InT>, dim3(std::min(eg, 512u)), dim3(256), (size_t)F.G * F.G * 8, s, d_xyz, F);
+  hipLaunchKernelGGL(k_mesh<InT>, dim3((quads + 63) / 64), dim3(64), 0, s, d_xyz, F);
+  hipLaunchKernelGGL(k_mask<InT>, dim3((unsigned)tiles), dim3(256), 0, s, d_xyz, F);
+  ScanJobs J{};
+  J.j[0] = ScanJob{F.tcnt, F.tcnt, nullptr, &h->kept};
+  J.count = 1;
+  const int32_t rc = exclusive_scan_chained(J, 0, tiles, (unsigned long long*)(ws + pl.chain_words),
+                                            pl.chain_stride, kChainEpochFilter, h, s);
+  if (rc) return rc;
+  hipLaunchKernelGGL(k_compact<InT>, dim3((unsigned)tiles), dim3(256), 0, s, d_xyz, F);
+  HULL_LAUNCH_CHECK();
+  return HULL_OK;
+}
+
+template int32_t extent_and_filter<int32_t>(const int32_t*, int64_t, bool, char*, const Plan&, hipStream_t);
+template int32_t extent_and_filter<int64_t>(const int64_t*, int64_t, bool, char*, const Plan&, hipStream_t);
+
+}  // namespace hull

@@ -294,20 +294,19 @@ __device__ void merge_one(const RunPtrs& R, Header* h, int64_t s, int64_t m, int
 
 template <class PT>
 __global__ void __launch_bounds__(256) k_merge_level(LevelArgs A) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts || t >= A.S.merges()) return;
+  if (!R.pts || !selected(A.S, A.sel)) return;
   const int* perm = A.perm[blockIdx.y];
-  const int64_t g = perm ? perm[t] : t;
-  const int2 se = A.S.merge(g);
-  const int64_t s = se.x, m = s + A.half, e = se.y;
-  // After an error the movies are empty, so that every later kernel still
-  // reads lengths that were written.
-  if (A.h->err) {
-    R.out_len(s) = 0;
-    return;
+  const int64_t M = A.S.merges();
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < M;
+       t += (int64_t)gridDim.x * blockDim.x) {
+    const int2 se = A.S.merge(perm ? perm[t] : t);
+    const int64_t s = se.x, m = s + A.half, e = se.y;
+    // After an error the movies are empty, so that every later kernel still
+    // reads lengths that were written.
+    if (A.h->err) R.out_len(s) = 0;
+    else merge_one<PT>(R, A.h, s, m, e);
   }
-  merge_one<PT>(R, A.h, s, m, e);
 }
 
 // Lane-serial levels from this one on list their merges in work order; below
@@ -334,9 +333,7 @@ constexpr int kPtsLdsMerges = 1024;
 // few events per block, and the tile's loads and list bounds, which cover all
 // points, then cost more than the walks they serve: level 10 6.8 ms / 2.6,
 // 11 3.5 / 1.9.
-constexpr int kTileFromLevel = 5;
-constexpr int64_t kTileMerges = 49152;
-constexpr int64_t kTilePoints = int64_t(1) << 21;
+constexpr int kTileFromLevel = 5;  // (kTileMerges and kTilePoints: events.hpp)
 constexpr int kMaxLevels = 28;
 constexpr int kTileLevels = 11;  // kTileMaxWidth
 
@@ -449,12 +446,7 @@ __global__ void __launch_bounds__(256) k_work_place(LevelArgs A) {
 // (global memory serves only the sequential child events and the output).
 // One wavefront per workgroup; a lane touches only its own LDS slice.
 template <class PT, int W>
-__global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
-  __shared__ PT sp[64 * W];
-  __shared__ int2 sl[64 * W];
-  const RunPtrs& R = A.run[blockIdx.y];
-  const int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (!R.pts || g >= A.S.merges()) return;
+__device__ __forceinline__ void merge_lds_one(const LevelArgs& A, const RunPtrs& R, int64_t g, PT* P, int2* K) {
   const int2 se = A.S.merge(g);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   if (A.h->err || e - s > W) {
@@ -468,9 +460,7 @@ __global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
     R.out_len(s) = 0;
     return;
   }
-  PT* P = sp + threadIdx.x * W;
   const PT* pts = (const PT*)R.pts;
-  int2* K = sl + threadIdx.x * W;
   const int w = (int)(e - s), b = (int)s;
   for (int j = 0; j < w; ++j) {
     P[j] = pts[s + j];
@@ -482,6 +472,17 @@ __global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
   R.out_len(s) = k < 0 ? 0 : k;
 }
 
+template <class PT, int W>
+__global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
+  __shared__ PT sp[64 * W];
+  __shared__ int2 sl[64 * W];
+  const RunPtrs& R = A.run[blockIdx.y];
+  if (!R.pts) return;
+  const int64_t M = A.S.merges();
+  for (int64_t g = blockIdx.x * (int64_t)64 + threadIdx.x; g < M; g += (int64_t)gridDim.x * 64)
+    merge_lds_one<PT, W>(A, R, g, sp + threadIdx.x * W, sl + threadIdx.x * W);
+}
+
 // Lane-serial levels with each lane's working links in LDS as block-local
 // int8 ranks (blocks of up to kLinkLdsLane points, the lanes of a wave
 // interleaved): the merge's scattered link reads and writes stay on chip, and
@@ -489,13 +490,8 @@ __global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
 // Points, child events and the merged movie stay in global memory.  Dynamic
 // LDS: width x 64 link pairs of 2 bytes.
 template <class PT>
-__global__ void __launch_bounds__(64) k_merge_level_lk(LevelArgs A) {
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts || t >= A.S.merges()) return;
-  const int* perm = A.perm[blockIdx.y];
-  const int64_t g = perm ? perm[t] : t;
+__device__ __forceinline__ void merge_lk_one(const LevelArgs& A, const RunPtrs& R, int64_t g,
+                                             unsigned char* dyn_lds) {
   const int2 se = A.S.merge(g);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   if (A.h->err) {
@@ -528,6 +524,17 @@ __global__ void __launch_bounds__(64) k_merge_level_lk(LevelArgs A) {
   const int k = merge_core<1>((const PT*)R.pts + s, K, R.pv0, R.nx0, b, R.left_ev(s), nL,
                            R.settle_right(m, e, nR, 0, 1), nR, R.out_ev(s), A.h, 0, m - s, e - s, R.zs);
   R.out_len(s) = k < 0 ? 0 : k;
+}
+
+template <class PT>
+__global__ void __launch_bounds__(64) k_merge_level_lk(LevelArgs A) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  const RunPtrs& R = A.run[blockIdx.y];
+  if (!R.pts || !selected(A.S, A.sel)) return;
+  const int* perm = A.perm[blockIdx.y];
+  const int64_t M = A.S.merges();
+  for (int64_t t = blockIdx.x * (int64_t)64 + threadIdx.x; t < M; t += (int64_t)gridDim.x * 64)
+    merge_lk_one<PT>(A, R, perm ? perm[t] : t, dyn_lds);
 }
 
 // Level 1: the merge of two single points has no events (neither chain has a
@@ -721,7 +728,7 @@ struct Opts {
   int64_t order_min;  // ... when the level bounds at least this many merges
   int tile_levels;  // levels not run lane-serial, up to this one, run their segments in LDS
   int tile_from;    // ... and, where the caller left serial_max open, levels from this one on
-                    // with fewer than kTileMerges merges (both runs together) do too
+                    // that do not count as many merges do too
   int64_t pts_lds_merges;  // lane-group levels of at most this many merges (both runs
                            // together) hold the points in LDS too, where they fit
 };
@@ -761,11 +768,19 @@ static Opts resolve(const hull_schedule_t* sc, int64_t total) {
   return o;
 }
 
-// Runs `levels` merge levels of the selected runs over the hulls of S.
+// Blocks per run of a merge kernel (its merges stride over them): the device
+// may have far fewer merges than the host's bound, and an empty block still
+// costs its dispatch.
+static unsigned merge_grid(int64_t merges, int per) {
+  return (unsigned)std::min<int64_t>((merges + per - 1) / per, 8192);
+}
+
+// Runs `levels` merge levels of the selected runs over the hulls of S, n points
+// (device_n: at most n, the device knows how many).
 template <class PT>
 static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, hipStream_t s,
                           bool lower, bool upper, int levels, const Opts& opt,
-                          hipEvent_t* events) {
+                          hipEvent_t* events, bool device_n = false) {
   Header* h = (Header*)(ws + pl.header);
   Sched S = S0;
   S.moff = (int*)(ws + pl.moff);
@@ -820,11 +835,17 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
     A.half = A.width >> 1;
     const int64_t bound = std::min<int64_t>(pl.mcap, n / A.width + S.H + 1);
     const bool tile_fits =
-        k <= opt.tile_levels && (opt.tile_from > kMaxLevels || n <= kTilePoints) && A.width <= kTileMaxWidth &&
+        k <= opt.tile_levels && A.width <= kTileMaxWidth &&
         (int64_t)TileLds<PT>::bytes((int)A.width, tile_lanes((int)A.width)) + 256 <= max_lds_bytes();
-    const bool serial =
-        k <= opt.serial_max && !(tile_fits && k >= opt.tile_from && 2 * bound < kTileMerges);
-    const bool tile = !serial && tile_fits;
+    const bool open = tile_fits && k >= opt.tile_from;  // the number of merges decides
+    const bool few = !many_merges(bound, n);            // (of the host's bound; the device may have fewer)
+    // what runs: k <= serial_max lane-serial or lane groups, above that tiles
+    // where they fit, else the parallel strategy; and tiles instead of either
+    // where the choice is open
+    const bool tile = open ? few || device_n : tile_fits && k > opt.serial_max;
+    const bool serial = k <= opt.serial_max && !(open && few);
+    const bool par = k > opt.serial_max && (!tile_fits || (open && !few));
+    const int sel_tile = open && !few ? 2 : 0, sel_other = open && device_n ? 1 : 0;
     // lane groups at this level, and where the working links live
     const bool wave = serial && k > opt.lds_levels && opt.wave_from > 0 && k >= opt.wave_from;
     const int lanes =
@@ -861,15 +882,15 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
     if (serial && k == 1) {
       hipLaunchKernelGGL(k_merge_level1, dim3(grid_for(bound), 2), dim3(256), 0, s, A);
     } else if (serial && k <= opt.lds_levels) {
-      const dim3 grid((unsigned)((bound + 63) / 64), 2);
-      if (k == 1) hipLaunchKernelGGL((k_merge_level_lds<PT, 2>), grid, dim3(64), 0, s, A);
-      else if (k == 2) hipLaunchKernelGGL((k_merge_level_lds<PT, 4>), grid, dim3(64), 0, s, A);
+      const dim3 grid(merge_grid(bound, 64), 2);
+      if (k == 2) hipLaunchKernelGGL((k_merge_level_lds<PT, 4>), grid, dim3(64), 0, s, A);
       else if (k == 3) hipLaunchKernelGGL((k_merge_level_lds<PT, 8>), grid, dim3(64), 0, s, A);
       else hipLaunchKernelGGL((k_merge_level_lds<PT, 16>), grid, dim3(64), 0, s, A);
     } else if (serial) {
-      const dim3 grid((unsigned)((bound + 255) / 256), 2);
       LevelArgs B = A;
+      B.sel = sel_other;
       if (k >= opt.order_from && bound >= opt.order_min) {
+        const dim3 grid((unsigned)((bound + 255) / 256), 2);
         for (int r = 0; r < 2; ++r) {
           B.perm[r] = (int*)(ws + pl.perm[r]);
           B.wbins[r] = (int*)(ws + pl.wbins[r]);
@@ -884,7 +905,7 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
         // every lane-group level keeps about the same number of waves
         const int nb = pts_lds ? 64 : 256;  // lanes per block
         const int per = nb / lanes;          // merges per block
-        const dim3 wg((unsigned)((bound + per - 1) / per), 2);
+        const dim3 wg(merge_grid(bound, per), 2);
         const size_t lds =
             pts_lds ? (size_t)per * A.width * (sizeof(LinkPair<short>) + sizeof(PT))
                     : (lds_group ? (size_t)per * A.width * sizeof(LinkPair<short>) : 0);
@@ -898,19 +919,28 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
         else { HULL_WAVE(8) }
 #undef HULL_WAVE
       } else if (lds_lane) {
-        const dim3 g64((unsigned)((bound + 63) / 64), 2);
         const size_t lds = (size_t)A.width * 64 * sizeof(LinkPair<signed char>);
-        hipLaunchKernelGGL(k_merge_level_lk<PT>, g64, dim3(64), lds, s, B);
+        hipLaunchKernelGGL(k_merge_level_lk<PT>, dim3(merge_grid(bound, 64), 2), dim3(64), lds, s, B);
       } else
-        hipLaunchKernelGGL(k_merge_level<PT>, grid, dim3(256), 0, s, B);
-    } else if (tile) {
+        hipLaunchKernelGGL(k_merge_level<PT>, dim3(merge_grid(bound, 256), 2), dim3(256), 0, s, B);
+    }
+    if (par) {
+      P.S = S;
+      P.sel = sel_other;
+      for (int r = 0; r < 2; ++r) P.run[r] = A.run[r];
+      rc = parallel_level<PT>(P, s);
+      if (rc) return rc;
+    }
+    if (tile) {
+      LevelArgs B = A;
+      B.sel = sel_tile;
       const int W = (int)A.width;
       const int gs = tile_lanes(W);
       const int per = gs < 64 ? 64 / gs : 1;
-      const dim3 grid((unsigned)((bound + per - 1) / per), 2);
+      const dim3 grid(merge_grid(bound, per), 2);
       const size_t lds = per * TileLds<PT>::bytes(W, gs);
 #define HULL_TILE(G) \
-  hipLaunchKernelGGL((k_merge_tile<PT, G>), grid, dim3(G < 64 ? 64 : G), lds, s, A, opt.seg)
+  hipLaunchKernelGGL((k_merge_tile<PT, G>), grid, dim3(G < 64 ? 64 : G), lds, s, B, opt.seg)
       if (gs == 16) HULL_TILE(16);
       else if (gs == 32) HULL_TILE(32);
       else if (gs == 64) HULL_TILE(64);
@@ -918,11 +948,6 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
       else if (gs == 256) HULL_TILE(256);
       else HULL_TILE(512);
 #undef HULL_TILE
-    } else {
-      P.S = S;
-      for (int r = 0; r < 2; ++r) P.run[r] = A.run[r];
-      rc = parallel_level<PT>(P, s);
-      if (rc) return rc;
     }
     if (events) (void)hipEventRecord(events[2 * k + 1], s);
     HULL_LAUNCH_CHECK();
@@ -979,7 +1004,7 @@ struct RunInits {
 template <class InT, class PT>
 static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_t cap,
                            int64_t* d_info, void* d_ws, size_t ws_bytes, hipStream_t s, bool lower,
-                           bool upper, void* const* events, int32_t nevents) {
+                           bool upper, void* const* events, int32_t nevents, bool filter) {
   if (n < 0 || n > kMaxN || !d_info || (n > 0 && !d_xyz) || !d_faces || cap < 2 * n || !d_ws)
     return HULL_EINVAL;
   const int L = levels_for(n);
@@ -1004,10 +1029,13 @@ static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_
   S.off = off;
   S.H = 1;
   const RunInits init(ws, pl, lower, upper);
-  int32_t rc = sort_points<InT, PT>(d_xyz, n, nullptr, 1, ws, pl, init.r, s);
+  filter = filter && n >= kFilterMin;
+  int32_t rc = extent_and_filter<InT>(d_xyz, n, filter, ws, pl, s);
+  if (rc) return rc;
+  rc = sort_points<InT, PT>(d_xyz, n, nullptr, 1, ws, pl, init.r, filter, s);
   if (rc) return rc;
   if (ev) (void)hipEventRecord(ev[1], s);
-  rc = run_levels<PT>(n, S, ws, pl, s, lower, upper, L, opt, ev);
+  rc = run_levels<PT>(n, S, ws, pl, s, lower, upper, L, opt, ev, filter);
   if (rc) return rc;
   S.moff = (int*)(ws + pl.moff);
   rc = extract<PT>(S, ws, pl, s, lower, upper, d_faces, cap, nullptr, d_info);
@@ -1017,16 +1045,16 @@ static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_
 
 int32_t hull_runs(const int32_t* d_xyz, int64_t n, int32_t* d_faces, int64_t cap, int64_t* d_info,
                   void* d_ws, size_t ws_bytes, hipStream_t s, bool lower, bool upper,
-                  void* const* events, int32_t nevents) {
+                  void* const* events, int32_t nevents, bool filter) {
   return hull_runs_t<int32_t, int4>(d_xyz, n, d_faces, cap, d_info, d_ws, ws_bytes, s, lower,
-                                    upper, events, nevents);
+                                    upper, events, nevents, filter);
 }
 
 int32_t hull_runs(const int64_t* d_xyz, int64_t n, int32_t* d_faces, int64_t cap, int64_t* d_info,
                   void* d_ws, size_t ws_bytes, hipStream_t s, bool lower, bool upper,
-                  void* const* events, int32_t nevents) {
+                  void* const* events, int32_t nevents, bool filter) {
   return hull_runs_t<int64_t, WPt>(d_xyz, n, d_faces, cap, d_info, d_ws, ws_bytes, s, lower, upper,
-                                   events, nevents);
+                                   events, nevents, filter);
 }
 
 int32_t batched(const int32_t* d_xyz, const int64_t* d_off, const int64_t* h_off, int64_t H,
@@ -1053,7 +1081,9 @@ int32_t batched(const int32_t* d_xyz, const int64_t* d_off, const int64_t* h_off
   S.H = H;
   if (n > 0) {
     const RunInits init(ws, pl, true, true);
-    int32_t rc = sort_points<int32_t, int4>(d_xyz, n, d_off, H, ws, pl, init.r, s);
+    int32_t rc = extent_and_filter<int32_t>(d_xyz, n, false, ws, pl, s);
+    if (rc) return rc;
+    rc = sort_points<int32_t, int4>(d_xyz, n, d_off, H, ws, pl, init.r, false, s);
     if (rc) return rc;
     rc = run_levels<int4>(n, S, ws, pl, s, true, true, L, opt, nullptr);
     if (rc) return rc;
@@ -1078,7 +1108,9 @@ int32_t movies(const int32_t* d_xyz, int64_t n, int32_t run, int32_t level, int3
   S.off = off;
   S.H = 1;
   const RunInits init(ws, pl, run == 0, run == 1);
-  int32_t rc = sort_points<int32_t, int4>(d_xyz, n, nullptr, 1, ws, pl, init.r, s);
+  int32_t rc = extent_and_filter<int32_t>(d_xyz, n, false, ws, pl, s);
+  if (rc) return rc;
+  rc = sort_points<int32_t, int4>(d_xyz, n, nullptr, 1, ws, pl, init.r, false, s);
   if (rc) return rc;
   int L = levels_for(n);
   if (level >= 0 && level < L) L = level;

@@ -129,7 +129,7 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
   const RunPtrs& R = P.run[blockIdx.y];
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
-  const int64_t merges = P.S.merges(), half = int64_t(1) << (P.S.k - 1);
+  const int64_t merges = selected(P.S, P.sel) ? P.S.merges() : 0, half = int64_t(1) << (P.S.k - 1);
   const int64_t keys = merges ? 2 * (P.S.off[P.S.H] + 1) : 0;
   const bool err = P.h->err != 0;
   GRID_STRIDE(g, (int64_t)(err ? 0 : Q.ctr[kCtrSplice + ((P.S.k - 1) & 1)])) {

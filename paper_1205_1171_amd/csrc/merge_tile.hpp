@@ -408,24 +408,37 @@ template <class PT, int GS>
 __global__ void __launch_bounds__(GS < 64 ? 64 : GS) k_merge_tile(LevelArgs A, int seg) {
   extern __shared__ __align__(16) unsigned char dyn_lds[];
   __shared__ int wsum[GS > 64 ? GS / 64 : 1];
+  __shared__ int stop;
   constexpr int per = GS < 64 ? 64 / GS : 1;
   const RunPtrs& R = A.run[blockIdx.y];
+  if (!R.pts || !selected(A.S, A.sel)) return;
   const int grp = GS < 64 ? (int)threadIdx.x / GS : 0;
-  const int64_t t = blockIdx.x * (int64_t)per + grp;
-  if (!R.pts || t >= A.S.merges()) return;  // the same on every lane of the group
-  const int* perm = A.perm[blockIdx.y];
-  const int2 se = A.S.merge(perm ? perm[t] : t);
-  const int64_t s = se.x, m = s + A.half, e = se.y;
-  if (A.h->err) {
-    if ((threadIdx.x & (GS - 1)) == 0) R.out_len(s) = 0;
-    return;
-  }
   const int W = (int)A.width;
+  const int64_t M = A.S.merges();
   unsigned char* lds = dyn_lds + grp * TileLds<PT>::bytes(W, GS);
-  if constexpr (GS <= 64) {
-    tile_merge<PT>(LaneGroup<GS>{}, lds, W, R, A.h, s, m, e, seg);
-  } else {
-    tile_merge<PT>(BlockGroup<GS>{wsum}, lds, W, R, A.h, s, m, e, seg);
+  // t is the same on every lane of the group
+  for (int64_t t = blockIdx.x * (int64_t)per + grp; t < M; t += (int64_t)gridDim.x * per) {
+    const int2 se = A.S.merge(t);
+    const int64_t s = se.x, m = s + A.half, e = se.y;
+    if constexpr (GS <= 64) {
+      const LaneGroup<GS> g;
+      g.sync();  // the merge before still reads the group's LDS
+      if (A.h->err) {
+        if (g.rank() == 0) R.out_len(s) = 0;
+        continue;
+      }
+      tile_merge<PT>(g, lds, W, R, A.h, s, m, e, seg);
+    } else {
+      const BlockGroup<GS> g{wsum};
+      g.sync();
+      if (g.rank() == 0) stop = A.h->err;  // one reading for the whole group
+      g.sync();
+      if (stop) {
+        if (g.rank() == 0) R.out_len(s) = 0;
+        continue;
+      }
+      tile_merge<PT>(g, lds, W, R, A.h, s, m, e, seg);
+    }
   }
 }
 #endif

@@ -81,21 +81,16 @@ __device__ __forceinline__ Event shift_event(Event E, int base) {
 // out); blocks of 64 lanes, for levels of few, long merges whose iterations
 // wait on point loads (dynamic LDS: 64 / G merges x width x (4 + point
 // size) bytes).
+constexpr int wave_block(int mode) { return mode == 2 ? 64 : 256; }  // lanes per block
+
 template <class PT, int G, int MODE>
-__global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
+__device__ __forceinline__ void merge_wave_one(const LevelArgs& A, const RunPtrs& R, int64_t g,
+                                               unsigned char* dyn_lds, Event* Lc, Event* Rc) {
   static_assert(G == 8 || G == 16 || G == 32 || G == 64, "lanes per merge");
   static_assert(MODE >= 0 && MODE <= 2, "link and point placement");
-  constexpr int NB = MODE == 2 ? 64 : 256;  // lanes per block
-  extern __shared__ __align__(16) unsigned char dyn_lds[];
-  // per group of the block: G events of each child movie
-  __shared__ Event chunk[NB / G][2][G];
+  constexpr int NB = wave_block(MODE);
   const int lane = threadIdx.x & (G - 1), grp = threadIdx.x / G;
   const int gshift = (threadIdx.x & 63) & ~(G - 1);  // the group's first lane in the wave
-  const int64_t g0 = (blockIdx.x * (int64_t)NB + threadIdx.x) / G;
-  const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts || g0 >= A.S.merges()) return;  // the same for every lane of the group
-  const int* perm = A.perm[blockIdx.y];
-  const int64_t g = perm ? perm[g0] : g0;
   const int2 se = A.S.merge(g);
   const int64_t s = se.x, m = s + A.half, e = se.y;
   Header* h = A.h;
@@ -152,8 +147,6 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
   if (R.right_waits_in_output(m, e)) __threadfence_block();
   Event* out = R.out_ev(s);
   const int64_t cap = 2 * (e - s);
-  Event* Lc = chunk[grp][0];
-  Event* Rc = chunk[grp][1];
 
   // 1. bridge at t = -inf: every lane takes the same walk (the working links
   // hold the -inf links at the start of the merge)
@@ -331,6 +324,24 @@ __global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
     R.nx0[u0 + base] = v0 + base;
     R.pv0[v0 + base] = u0 + base;
     R.out_len(s) = k;
+  }
+}
+
+template <class PT, int G, int MODE>
+__global__ void __launch_bounds__(256) k_merge_wave(LevelArgs A) {
+  constexpr int NB = wave_block(MODE);
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  // per group of the block: G events of each child movie
+  __shared__ Event chunk[NB / G][2][G];
+  const RunPtrs& R = A.run[blockIdx.y];
+  if (!R.pts || !selected(A.S, A.sel)) return;
+  const int* perm = A.perm[blockIdx.y];
+  const int grp = threadIdx.x / G;
+  const int64_t M = A.S.merges();
+  // t is the same for every lane of the group
+  for (int64_t t = (blockIdx.x * (int64_t)NB + threadIdx.x) / G; t < M; t += (int64_t)gridDim.x * (NB / G)) {
+    merge_wave_one<PT, G, MODE>(A, R, perm ? perm[t] : t, dyn_lds, chunk[grp][0], chunk[grp][1]);
+    __builtin_amdgcn_wave_barrier();
   }
 }
 

@@ -11,56 +11,23 @@
 namespace hull {
 
 
-// ---------------------------------------------------------------------------
-// Range check and x extent.
-// ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_call_init(Header* h, int64_t* off1, int64_t n,
-                                                   unsigned long long* words, int64_t count) {
+                                                   unsigned long long* words, int64_t count, int radix_len) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count;
        i += (int64_t)gridDim.x * blockDim.x)
     words[i] = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     h->err = 0;
-    h->minx = 0x7fffffff;
-    h->maxx = -0x7fffffff - 1;
+    h->radix_len = radix_len;
+    h->rho[0] = h->rho[1] = 0x7f7fffffu;
+    for (int a = 0; a < 3; ++a) {
+      h->lo[a] = 0x7fffffffffffffffll;
+      h->hi[a] = -0x7fffffffffffffffll - 1;
+    }
     if (off1) {
       off1[0] = 0;
       off1[1] = n;
     }
-  }
-}
-
-template <class InT>
-__global__ void __launch_bounds__(256) k_extent(const InT* __restrict__ xyz, int64_t n,
-                                                Header* h) {
-  __shared__ int smin[256], smax[256], sbad[256];
-  int lo = 0x7fffffff, hi = -0x7fffffff - 1, bad = 0;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < n;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    const InT x = xyz[3 * p], y = xyz[3 * p + 1], z = xyz[3 * p + 2];
-    const bool b = pt_out_of_range(x, y, z);
-    // x of a row in range fits int32 on either range
-    const int xi = b ? 0 : (int)x;
-    lo = min(lo, xi);
-    hi = max(hi, xi);
-    bad |= b;
-  }
-  smin[threadIdx.x] = lo;
-  smax[threadIdx.x] = hi;
-  sbad[threadIdx.x] = bad;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      smin[threadIdx.x] = min(smin[threadIdx.x], smin[threadIdx.x + s]);
-      smax[threadIdx.x] = max(smax[threadIdx.x], smax[threadIdx.x + s]);
-      sbad[threadIdx.x] |= sbad[threadIdx.x + s];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    atomicMin(&h->minx, smin[0]);
-    atomicMax(&h->maxx, smax[0]);
-    if (sbad[0]) atomicCAS(&h->err, 0, HULL_ERANGE);
   }
 }
 
@@ -74,10 +41,12 @@ __global__ void __launch_bounds__(256) k_extent(const InT* __restrict__ xyz, int
 struct RadixBufs {
   uint32_t* keys[2];
   int32_t* vals[2];
+  const int64_t* n;  // the number of points
+  bool from_list;    // pass 0 reads buffer 1 (the filter's list) rather than xyz
 };
 
 __device__ __forceinline__ int x_passes(const Header* h) {
-  const uint32_t span = (uint32_t)((int64_t)h->maxx - h->minx);
+  const uint32_t span = (uint32_t)(h->hi[0] - h->lo[0]);
   const int bits = span ? 32 - __builtin_clz(span) : 1;
   return (bits + kRadixBits - 1) / kRadixBits;
 }
@@ -86,9 +55,9 @@ __device__ __forceinline__ int x_passes(const Header* h) {
 template <class InT>
 __device__ __forceinline__ uint32_t radix_key(const InT* xyz, const RadixBufs& B,
                                               const int32_t* hid, int64_t p, int e, int kind,
-                                              int minx, int32_t* val) {
+                                              int64_t minx, int32_t* val) {
   if (kind == 0) {
-    if (e == 0) {
+    if (e == 0 && !B.from_list) {
       *val = (int32_t)p;
       return (uint32_t)((int64_t)xyz[3 * p] - minx);
     }
@@ -103,15 +72,17 @@ __device__ __forceinline__ uint32_t radix_key(const InT* xyz, const RadixBufs& B
 template <class InT>
 __global__ void __launch_bounds__(kSortThreads)
     k_radix_hist(const InT* __restrict__ xyz, RadixBufs B, const int32_t* __restrict__ hid,
-                 int64_t n, int kind, int d, int tiles, int32_t* __restrict__ counts,
-                 const Header* h) {
+                 int kind, int d, int32_t* __restrict__ counts, const Header* h) {
+  const int64_t n = *B.n;
+  const int tiles = (int)((n + kTile - 1) / kTile);
+  if ((int)blockIdx.x >= tiles) return;
   const int xp = x_passes(h);
   if (kind == 0 && d >= xp) return;
   const int e = kind == 0 ? d : xp + d;
   __shared__ int hist[kBuckets];
   hist[threadIdx.x] = 0;
   __syncthreads();
-  const int minx = h->minx;
+  const int64_t minx = h->lo[0];
   const int64_t base = (int64_t)blockIdx.x * kTile;
   for (int j = 0; j < kSortItems; ++j) {
     int64_t p = base + j * kSortThreads + threadIdx.x;
@@ -128,8 +99,10 @@ __global__ void __launch_bounds__(kSortThreads)
 template <class InT>
 __global__ void __launch_bounds__(kSortThreads)
     k_radix_scatter(const InT* __restrict__ xyz, RadixBufs B, const int32_t* __restrict__ hid,
-                    int64_t n, int kind, int d, int tiles, const int32_t* __restrict__ offsets,
-                    const Header* h) {
+                    int kind, int d, const int32_t* __restrict__ offsets, const Header* h) {
+  const int64_t n = *B.n;
+  const int tiles = (int)((n + kTile - 1) / kTile);
+  if ((int)blockIdx.x >= tiles) return;
   const int xp = x_passes(h);
   if (kind == 0 && d >= xp) return;
   const int e = kind == 0 ? d : xp + d;
@@ -138,7 +111,7 @@ __global__ void __launch_bounds__(kSortThreads)
   __shared__ int wcnt[kWaves][kBuckets];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   base[tid] = offsets[(int64_t)tid * tiles + blockIdx.x];
-  const int minx = h->minx;
+  const int64_t minx = h->lo[0];
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   const int64_t tbase = (int64_t)blockIdx.x * kTile;
   uint32_t* kout = B.keys[e & 1];
@@ -202,8 +175,9 @@ struct RunInitPair {
 template <class InT, class PT>
 __global__ void __launch_bounds__(256)
     k_gather(const InT* __restrict__ xyz, RadixBufs B, const int32_t* __restrict__ hid,
-             const int64_t* __restrict__ off, int hull_passes, int64_t n, PT* __restrict__ pts,
+             const int64_t* __restrict__ off, int hull_passes, PT* __restrict__ pts,
              RunInitPair I, const Header* h) {
+  const int64_t n = *B.n;
   const int e = x_passes(h) + hull_passes - 1;
   const int32_t* v = B.vals[e & 1];
   for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n;
@@ -371,18 +345,20 @@ int32_t scan_chained_i32(const int32_t* in, int32_t* out, int64_t len, unsigned 
 void init_call(Header* h, int64_t* off1, int64_t n, char* ws, const Plan& pl, hipStream_t s) {
   const int64_t count = kChainJobs * pl.chain_stride, b = (count + 255) / 256;
   hipLaunchKernelGGL(k_call_init, dim3((unsigned)(b < 1024 ? b : 1024)), dim3(256), 0, s, h, off1, n,
-                     (unsigned long long*)(ws + pl.chain_words), count);
+                     (unsigned long long*)(ws + pl.chain_words), count, (int)pl.count_len);
 }
 
 template <class InT, class PT>
 int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_t H, char* ws,
-                    const Plan& pl, const RunInit* runs, hipStream_t s) {
+                    const Plan& pl, const RunInit* runs, bool from_list, hipStream_t s) {
   Header* h = (Header*)(ws + pl.header);
   RadixBufs B;
   B.keys[0] = (uint32_t*)(ws + pl.keys0);
   B.keys[1] = (uint32_t*)(ws + pl.keys1);
   B.vals[0] = (int32_t*)(ws + pl.vals0);
   B.vals[1] = (int32_t*)(ws + pl.vals1);
+  B.n = hull_off ? hull_off + H : (const int64_t*)(ws + pl.off1) + 1;
+  B.from_list = from_list;
   int32_t* counts = (int32_t*)(ws + pl.counts);
   int32_t* hid = nullptr;
   int hull_passes = 0;
@@ -396,29 +372,31 @@ int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_
   unsigned long long* words = (unsigned long long*)(ws + pl.chain_words);
   unsigned eg = (unsigned)std::min<int64_t>((n + 255) / 256, 2048);
   if (eg < 1) eg = 1;
-  hipLaunchKernelGGL(k_extent<InT>, dim3(eg), dim3(256), 0, s, d_xyz, n, h);
   if (hid) hipLaunchKernelGGL(k_hull_ids, dim3(eg), dim3(256), 0, s, hull_off, H, n, hid);
   for (int kind = 0; kind < 2; ++kind) {
     const int npass = kind == 0 ? 4 : hull_passes;
     for (int d = 0; d < npass; ++d) {
-      hipLaunchKernelGGL(k_radix_hist<InT>, dim3(tiles), dim3(kSortThreads), 0, s, d_xyz, B, hid, n,
-                         kind, d, tiles, counts, h);
-      int32_t rc = scan_chained_i32(counts, counts, pl.count_len, words, pl.chain_stride,
-                                    (unsigned)(1 + kind * 4 + d), h, s);
+      hipLaunchKernelGGL(k_radix_hist<InT>, dim3(tiles), dim3(kSortThreads), 0, s, d_xyz, B, hid,
+                         kind, d, counts, h);
+      ScanJobs J{};
+      J.j[0] = ScanJob{counts, counts, &h->radix_len, nullptr};
+      J.count = 1;
+      const int32_t rc = exclusive_scan_chained(J, 0, pl.count_len, words, pl.chain_stride,
+                                                (unsigned)(1 + kind * 4 + d), h, s);
       if (rc) return rc;
-      hipLaunchKernelGGL(k_radix_scatter<InT>, dim3(tiles), dim3(kSortThreads), 0, s, d_xyz, B, hid, n,
-                         kind, d, tiles, counts, h);
+      hipLaunchKernelGGL(k_radix_scatter<InT>, dim3(tiles), dim3(kSortThreads), 0, s, d_xyz, B, hid,
+                         kind, d, counts, h);
     }
   }
   hipLaunchKernelGGL((k_gather<InT, PT>), dim3(eg), dim3(256), 0, s, d_xyz, B, hid, hull_off,
-                     hull_passes, n, (PT*)(ws + pl.pts), RunInitPair{{runs[0], runs[1]}}, h);
+                     hull_passes, (PT*)(ws + pl.pts), RunInitPair{{runs[0], runs[1]}}, h);
   HULL_LAUNCH_CHECK();
   return HULL_OK;
 }
 
 template int32_t sort_points<int32_t, int4>(const int32_t*, int64_t, const int64_t*, int64_t,
-                                            char*, const Plan&, const RunInit*, hipStream_t);
+                                            char*, const Plan&, const RunInit*, bool, hipStream_t);
 template int32_t sort_points<int64_t, WPt>(const int64_t*, int64_t, const int64_t*, int64_t,
-                                           char*, const Plan&, const RunInit*, hipStream_t);
+                                           char*, const Plan&, const RunInit*, bool, hipStream_t);
 
 }  // namespace hull

@@ -132,3 +132,49 @@ def test_trailing_blocks(monkeypatch, serial, tile, wave):
         got = hull.hull_sync(torch.from_numpy(p).cuda(), ws=ws).cpu().numpy()
         a, b = validate.canonical(got), validate.canonical(oracle.hull(p))
         assert a.shape == b.shape and (a == b).all()
+
+
+# Interior points taken out before the sort: the faces are those of all points.
+# Shapes with many and few interior points, points on the facets and edges of
+# a lattice hull, flat and thin clouds, one outlier, duplicates; sizes around the
+# filter's smallest and its changes of grid.
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 8191, 8192, 131073])
+def test_interior_filter(n):
+    import oracle
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    rng = np.random.default_rng(n)
+    r = 1 << 20
+    ball = workloads.ball(rng, n, r)
+    sets = {"ball": ball, "cube": workloads.cube(rng, n, r),
+            "gaussian": workloads.gaussian(rng, n)}
+    if n <= 8192:
+        sets["sphere"] = workloads.sphere(rng, n, r)
+        out = ball // 1024
+        out[n // 2] = [r, -r, r // 2]
+        thin = ball.copy()
+        thin[:, 1] //= 1 << 18
+        flat = ball.copy()
+        flat[:, 2] = 7
+        skew = ball // 64
+        skew[:, 2] += 9 * skew[:, 0] - 5 * skew[:, 1]
+        sets.update({"lattice": workloads.lattice(rng, n, 9), "outlier": out, "thin": thin,
+                     "flat": flat, "skew": skew, "far": ball // 8 + (1 << 28),
+                     "full": workloads.cube(rng, n, 1 << 29),
+                     "corners": np.concatenate([workloads.cube_corners(r), ball[8:] // 2]),
+                     "same": np.repeat(ball[:4], (n + 3) // 4, axis=0)[:n]})
+    ws = hull.Workspace()
+    for name, p in sets.items():
+        p = np.ascontiguousarray(p, dtype=np.int32)
+        for lower in (False, True) if n <= 1025 else (n % 2 == 0,):
+            say("filter", n, name, lower)
+            got = hull.hull_sync(torch.from_numpy(p).cuda(), lower_only=lower, ws=ws).cpu().numpy()
+            a = validate.canonical(got)
+            b = validate.canonical(oracle.hull(p, lower_only=lower))
+            assert a.shape == b.shape and (a == b).all(), name
+    p = (ball.astype(np.int64) * 512)
+    p[:, 2] *= 1 << 12
+    say("filter wide", n)
+    a = validate.canonical(hull.hull_wide(torch.from_numpy(p).cuda()).cpu().numpy())
+    assert (a == validate.canonical(oracle.hull_wide(p))).all()
