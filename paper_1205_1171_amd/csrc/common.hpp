@@ -26,7 +26,6 @@ constexpr int kScanBlock = kSortThreads * kScanItems;
 constexpr int kStrideBlocks = 1024;  // grid of the grid-stride kernels
 constexpr int kScanDevGrid = 128;    // tile blocks per job of a device-length scan
 constexpr int kSegKeep = 6;  // bridge events a walk segment keeps from its counting pass
-constexpr int kListScan = 12;  // longest link-change list kept unsorted
 constexpr int kMinWalkSegment = 4;  // fewest child events per walk segment
 constexpr int kWorkBins = 1024;     // child-event counts told apart when ordering merges
 

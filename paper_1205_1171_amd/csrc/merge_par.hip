@@ -8,7 +8,7 @@
 //      is the place);
 //   2. list bounds by a scan over the points, then the entries: the event's
 //      position in its child movie and the link after it.  Lists of up to
-//      kListScan entries stay in arrival order (a lookup reads them whole);
+//      kParScan entries stay in arrival order (a lookup reads them whole);
 //      longer ones are sorted by position;
 //   3. a counting walk per segment, a scan, and a writing walk that replays
 //      the counted steps.  A segment's output is in order, so the level needs
@@ -27,6 +27,10 @@
 
 namespace hull {
 
+// Longest list kept unsorted.  Sorting is one thread's chain of dependent global
+// accesses: with 12, k_par_sort took 170 us a level on the 2^20-point sphere
+// (mean length 3, a few lists of 13-25), 6 with 32.
+constexpr int kParScan = 32;
 constexpr unsigned long long kStepsLost = ~0ull;  // a segment to be walked again
 
 template <class PT>
@@ -53,7 +57,7 @@ struct ParCtx {
   // the link after the last event of the list [lo, hi) before position
   // `cursor`, `none` if there is none
   __device__ __forceinline__ int last_before(int lo, int hi, int cursor, int none) const {
-    if (hi - lo > kListScan) {
+    if (hi - lo > kParScan) {
       const int first = lo;
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
@@ -102,7 +106,7 @@ __device__ __forceinline__ ParCtx<PT> ctx_of(const ParLevel& P, int r, int64_t s
   return X;
 }
 
-// Sorts a list by position (Shell's method; only lists above kListScan).
+// Sorts a list by position (Shell's method; only lists above kParScan).
 __device__ void sort_entries(int2* a, int k) {
   int gap = 1;
   while (gap < k / 3) gap = 3 * gap + 1;
@@ -240,7 +244,7 @@ __global__ void __launch_bounds__(256) k_par_sort(ParLevel P) {
   if (!P.run[blockIdx.y].pts || P.h->err) return;
   GRID_STRIDE(q, (int64_t)Q.ctr[kCtrKeys] - 1) {
     const int first = Q.off[q], k = Q.off[q + 1] - first;
-    if (k > kListScan) sort_entries(Q.ent + first, k);
+    if (k > kParScan) sort_entries(Q.ent + first, k);
   }
 }
 

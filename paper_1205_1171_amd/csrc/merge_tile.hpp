@@ -15,6 +15,7 @@
 namespace hull {
 
 constexpr int kTileRankBits = 10;
+constexpr int kListScan = 12;  // longest list kept unsorted
 constexpr int kTileKeep = 8;   // bridge events a lane puts aside per segment
 constexpr int kTileMaxWidth = 2 << kTileRankBits;  // two children of 1,024 points
 
