@@ -74,7 +74,7 @@ __host__ __device__ inline Event make_event(int a, int w, int b, int kind, doubl
 
 // Offsets (bytes) of every workspace region for n points in H hulls.
 struct Plan {
-  size_t header, keys0, vals0, keys1, vals1, counts, pts, hid, off1;
+  size_t header, keys0, vals0, keys1, vals1, counts, pts, hid, off1, off2;
   size_t pv0[2], nx0[2], lk[2];
   size_t ev[2][2], len[2][2];  // [run][buffer]
   // the level schedule of a batch (merge list)
@@ -152,8 +152,16 @@ template <class InT>
 int32_t extent_and_filter(const InT* d_xyz, int64_t n, bool filter, char* ws, const Plan& pl,
                           hipStream_t s);
 
+// The same per cloud of a batch, after extent_and_filter without its filter: the
+// clouds' new offsets to off2.  longest: points of the largest cloud, from
+// kCloudsFrom to kCloudMax.
+constexpr int64_t kCloudsFrom = 256;
+constexpr int64_t kCloudMax = int64_t(1) << 18;
+int32_t filter_clouds(const int32_t* d_xyz, int64_t n, const int64_t* d_off, int64_t H, int64_t longest,
+                      char* ws, const Plan& pl, hipStream_t s);
+
 // Sort: ranks by (hull, x, index within the hull), of the points that
-// extent_and_filter listed (from_list) or of all n.  Fills pts (PT: int4 x, y,
+// a filter listed (from_list) or of all n.  Fills pts (PT: int4 x, y,
 // z, index within the hull from int32 rows; WPt from int64 rows, by rank) and
 // the runs' links.  hull_off (device [H + 1]) may be NULL for a single hull.
 template <class InT, class PT>

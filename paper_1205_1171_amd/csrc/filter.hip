@@ -60,14 +60,17 @@ struct FilterArgs {
 struct Frame {
   double c[3], s[3];
 };
+// A power of two that takes a span to 1 at most.
+__device__ __forceinline__ double scale_of(double span) {
+  int e = 0;
+  (void)frexp(span > 1.0 ? span : 1.0, &e);  // span <= 2^e
+  return ldexp(1.0, -e);
+}
 __device__ __forceinline__ Frame frame_of(const Header* h) {
   Frame f;
   for (int a = 0; a < 3; ++a) {
     f.c[a] = h->csum[a] * (1.0 / 256.0);
-    const double span = (double)(h->hi[a] - h->lo[a]);
-    int e = 0;
-    (void)frexp(span > 1.0 ? span : 1.0, &e);  // span <= 2^e
-    f.s[a] = ldexp(1.0, -e);
+    f.s[a] = scale_of((double)(h->hi[a] - h->lo[a]));
   }
   return f;
 }
@@ -237,20 +240,12 @@ __device__ float tetra(const double* a, const double* b, const double* d, float4
   return det > 0 ? dist : 0.0f;
 }
 
-// The two tetrahedra of every 2 x 2 block of adjacent cells, at kCoarse cells
-// per side (a coarse cell's representative: the farthest of its cells') and at G.
-template <class InT>
-__global__ void __launch_bounds__(64) k_mesh(const InT* __restrict__ xyz, FilterArgs F) {
-  if (F.h->err) return;
-  const int nc = (kCoarse + 1) * (kCoarse + 1), nf = (F.G + 1) * (F.G + 1);
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nc + nf) return;
-  float4* out = F.quads + 8 * (int64_t)t;
-  const int grid = t >= nc;  // 0: the coarse cells, 1: the fine ones
-  const int g = grid ? F.G : kCoarse, per = F.G / g;
-  if (grid) t -= nc;
-  const int qi = t % (g + 1), qj = t / (g + 1);
-  const Frame f = frame_of(F.h);
+// The two tetrahedra of the 2 x 2 block of adjacent cells at corner (qi, qj) of a
+// grid of g cells per side, from the cells' representatives rep(i, j) (0: none).
+// Returns the distance of their nearest outer plane, 0 if one is not positively
+// oriented, and a large number for a block that folds onto one edge.
+template <class InT, class REP>
+__device__ float quad(const InT* xyz, const Frame& f, int g, int qi, int qj, const REP& rep, float4* out) {
   double v[4][3];
   int cell[4];
   bool ok = true;
@@ -258,12 +253,7 @@ __global__ void __launch_bounds__(64) k_mesh(const InT* __restrict__ xyz, Filter
     int i = qi - (k == 0 || k == 3), j = qj - (k < 2);
     wrap_cell(i, j, g);
     cell[k] = j * g + i;
-    unsigned long long key = 0;
-    for (int y = 0; y < per; ++y)
-      for (int x = 0; x < per; ++x) {
-        const unsigned long long c = F.reps[(j * per + y) * F.G + i * per + x];
-        key = c > key ? c : key;
-      }
+    const unsigned long long key = rep(i, j);
     ok = ok && key != 0;
     rel(f, xyz, (int64_t)(unsigned)key, v[k]);
   }
@@ -278,8 +268,33 @@ __global__ void __launch_bounds__(64) k_mesh(const InT* __restrict__ xyz, Filter
   const float r0 = tetra(a, b, c, out), r1 = tetra(a, c, d, out + 4);
   // in the middle of the square's edges a block folds onto one edge of the
   // surface
-  if (cell[0] != cell[2] && cell[1] != cell[3])
-    atomicMin(&F.h->rho[grid], __float_as_uint(fminf(r0, r1)));
+  return cell[0] != cell[2] && cell[1] != cell[3] ? fminf(r0, r1) : 3e38f;
+}
+
+// Every block's tetrahedra, at kCoarse cells per side (a coarse cell's
+// representative: the farthest of its cells') and at G.
+template <class InT>
+__global__ void __launch_bounds__(64) k_mesh(const InT* __restrict__ xyz, FilterArgs F) {
+  if (F.h->err) return;
+  const int nc = (kCoarse + 1) * (kCoarse + 1), nf = (F.G + 1) * (F.G + 1);
+  int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= nc + nf) return;
+  float4* out = F.quads + 8 * (int64_t)t;
+  const int grid = t >= nc;  // 0: the coarse cells, 1: the fine ones
+  const int g = grid ? F.G : kCoarse, per = F.G / g;
+  if (grid) t -= nc;
+  const Frame f = frame_of(F.h);
+  const auto rep = [&](int i, int j) {
+    unsigned long long key = 0;
+    for (int y = 0; y < per; ++y)
+      for (int x = 0; x < per; ++x) {
+        const unsigned long long c = F.reps[(j * per + y) * F.G + i * per + x];
+        key = c > key ? c : key;
+      }
+    return key;
+  };
+  const float r = quad(xyz, f, g, t % (g + 1), t / (g + 1), rep, out);
+  atomicMin(&F.h->rho[grid], __float_as_uint(r));
 }
 
 __device__ __forceinline__ bool inside(const float4* T, float x, float y, float z, float l1) {
@@ -393,6 +408,152 @@ __global__ void __launch_bounds__(256) k_compact(const InT* __restrict__ xyz, Fi
   }
 }
 
+// ---------------------------------------------------------------------------
+// Batches: the same, one workgroup per cloud, with the grid in LDS.
+// ---------------------------------------------------------------------------
+struct CloudArgs {
+  const int64_t* off;  // [H + 1] the clouds' points
+  int64_t H;
+  const Header* h;
+  int32_t* list;       // [n] cloud h's kept points from off[h] on
+  int32_t* kept;       // [H + 1] their number
+  int64_t lo, hi;      // clouds of lo <= points < hi
+};
+
+constexpr int kCloudThreads = 512;
+constexpr int64_t kCloudMin = 256;  // smaller clouds keep every point
+
+// Sum, minimum or maximum over the block (every thread gets it).
+template <class T, class OP>
+__device__ __forceinline__ T block_all(T x, T* lds, const OP& op) {
+  for (int o = 32; o > 0; o >>= 1) x = op(x, (T)__shfl_xor(x, o));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
+  __syncthreads();
+  x = lds[0];
+  for (int w = 1; w < kCloudThreads / 64; ++w) x = op(x, lds[w]);
+  return x;
+}
+
+template <class InT, int G>
+__global__ void __launch_bounds__(kCloudThreads) k_cloud_filter(const InT* __restrict__ xyz, CloudArgs A) {
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  constexpr int nq = (G + 1) * (G + 1), T = kCloudThreads;
+  float4* quads = (float4*)dyn_lds;                                    // [8 nq]
+  unsigned long long* reps = (unsigned long long*)(quads + 8 * nq);    // [G * G]
+  __shared__ long long red[T / 64];
+  __shared__ unsigned rho;
+  __shared__ int wcnt[2][T / 64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  for (int64_t h = blockIdx.x; h < A.H; h += gridDim.x) {
+    const int64_t o = A.off[h];
+    const int64_t n64 = A.off[h + 1] - o;
+    if (n64 < A.lo || n64 >= A.hi) continue;  // the same for the whole block
+    const int n = (int)n64;
+    const InT* P = xyz + 3 * o;
+    int32_t* list = A.list + o;
+    // (A.h->err was settled by an earlier launch: the same for the whole block)
+    if (A.h->err || n < kCloudMin) {
+      for (int p = t; p < n; p += T) list[p] = (int32_t)(o + p);
+      if (t == 0) A.kept[h] = n;
+      continue;
+    }
+    InT lo[3] = {P[0], P[1], P[2]}, hi[3] = {P[0], P[1], P[2]};
+    for (int p = t; p < n; p += T)
+      for (int a = 0; a < 3; ++a) {
+        const InT c = P[3 * (int64_t)p + a];
+        lo[a] = c < lo[a] ? c : lo[a];
+        hi[a] = c > hi[a] ? c : hi[a];
+      }
+    Frame f;
+    for (int a = 0; a < 3; ++a) {
+      const long long mn = block_all((long long)lo[a], red, [](long long x, long long y) { return x < y ? x : y; });
+      const long long mx = block_all((long long)hi[a], red, [](long long x, long long y) { return x > y ? x : y; });
+      const long long sample = t < 256 ? (long long)P[3 * ((int64_t)t * n / 256) + a] : 0;
+      const long long sum = block_all(sample, red, [](long long x, long long y) { return x + y; });
+      f.c[a] = (double)sum * (1.0 / 256.0);
+      f.s[a] = scale_of((double)(mx - mn));
+    }
+    for (int q = t; q < G * G; q += T) reps[q] = 0;
+    if (t == 0) rho = 0x7f7fffffu;
+    __syncthreads();
+    for (int p = t; p < n; p += T) {
+      double q[3];
+      rel(f, P, p, q);
+      const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
+      float u, v;
+      square_of(x, y, z, u, v);
+      const int c = cell_at(v, G) * G + cell_at(u, G);
+      const unsigned long long key =
+          ((unsigned long long)__float_as_uint(x * x + y * y + z * z) << 32) | (unsigned)p;
+      if (key > reps[c]) atomicMax(&reps[c], key);
+    }
+    __syncthreads();
+    for (int k = t; k < nq; k += T) {
+      const float r = quad(P, f, G, k % (G + 1), k / (G + 1),
+                           [&](int i, int j) { return reps[j * G + i]; }, quads + 8 * k);
+      atomicMin(&rho, __float_as_uint(r));
+    }
+    __syncthreads();
+    const float radius = __uint_as_float(rho), rr = radius * radius * (1.0f - 0x1p-18f);
+    // kept points in input order
+    int done = 0;
+    for (int p0 = 0, turn = 0; p0 < n; p0 += T, turn ^= 1) {
+      const int p = p0 + t;
+      bool keep = false;
+      if (p < n) {
+        double q[3];
+        rel(f, P, p, q);
+        const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
+        keep = !(x * x + y * y + z * z < rr);
+        if (keep) {
+          float u, v;
+          square_of(x, y, z, u, v);
+          keep = !inside_around(quads, G, u, v, x, y, z, abs1(x, y, z));
+        }
+      }
+      const unsigned long long m = __ballot(keep);
+      if (lane == 0) wcnt[turn][wave] = __popcll(m);
+      __syncthreads();  // (two sets of counts: one barrier a turn)
+      int before = 0, all = 0;
+      for (int w = 0; w < T / 64; ++w) {
+        const int c = wcnt[turn][w];
+        before += w < wave ? c : 0;
+        all += c;
+      }
+      if (keep) list[done + before + __popcll(m & ((1ull << lane) - 1))] = (int32_t)(o + p);
+      done += all;
+    }
+    if (t == 0) A.kept[h] = done;
+    __syncthreads();  // the next cloud rewrites the grid
+  }
+}
+
+// The clouds' kept points one after the other: their offsets, and the sort's
+// list (key, index) with the hull of each.
+template <class InT>
+__global__ void __launch_bounds__(256) k_cloud_list(const InT* __restrict__ xyz, CloudArgs A,
+                                                    const int32_t* __restrict__ before, Header* h,
+                                                    int64_t* off2, uint32_t* keys, int32_t* vals, int32_t* hid) {
+  const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t q = i0; q <= A.H; q += step) off2[q] = before[q];
+  const int total = before[A.H];
+  const long long minx = h->lo[0];
+  for (int64_t r = i0; r < total; r += step) {
+    int64_t lo = 0, hi = A.H;  // largest cloud with before <= r
+    while (hi - lo > 1) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (before[mid] <= r) lo = mid;
+      else hi = mid;
+    }
+    const int32_t p = A.list[A.off[lo] + (r - before[lo])];
+    keys[r] = (uint32_t)((long long)xyz[3 * (int64_t)p] - minx);
+    vals[r] = p;
+    hid[p] = (int32_t)lo;
+  }
+  if (i0 == 0) h->radix_len = (int32_t)(((int64_t)total + kTile - 1) / kTile * kBuckets);
+}
+
 // Cells per side: finer cells follow the surface closer but take more
 // representatives, and a cell should hold tens of points for its farthest to
 // be near the surface.
@@ -437,6 +598,44 @@ int32_t extent_and_filter(const InT* d_xyz, int64_t n, bool filter, char* ws, co
                                             pl.chain_stride, kChainEpochFilter, h, s);
   if (rc) return rc;
   hipLaunchKernelGGL(k_compact<InT>, dim3((unsigned)tiles), dim3(256), 0, s, d_xyz, F);
+  HULL_LAUNCH_CHECK();
+  return HULL_OK;
+}
+
+// Clouds by size: 8, 16 or 32 cells per side (10, 39 or 148 KB of LDS).  The
+// clouds of a batch are small enough for one workgroup each (kCloudMax).
+int32_t filter_clouds(const int32_t* d_xyz, int64_t n, const int64_t* d_off, int64_t H, int64_t longest,
+                      char* ws, const Plan& pl, hipStream_t s) {
+  Header* h = (Header*)(ws + pl.header);
+  CloudArgs A{};
+  A.off = d_off;
+  A.H = H;
+  A.h = h;
+  A.list = (int32_t*)(ws + pl.pos[0]);
+  A.kept = (int32_t*)(ws + pl.mcnt);
+  const unsigned grid = (unsigned)std::min<int64_t>(H, 16384);
+  const auto lds = [](int G) { return (size_t)(G + 1) * (G + 1) * 8 * sizeof(float4) + (size_t)G * G * 8; };
+  A.lo = 0;
+  A.hi = 2048;
+  hipLaunchKernelGGL((k_cloud_filter<int32_t, 8>), dim3(grid), dim3(kCloudThreads), lds(8), s, d_xyz, A);
+  A.lo = 2048;
+  A.hi = 8192;
+  if (longest >= A.lo)
+    hipLaunchKernelGGL((k_cloud_filter<int32_t, 16>), dim3(grid), dim3(kCloudThreads), lds(16), s, d_xyz, A);
+  A.lo = 8192;
+  A.hi = INT64_MAX;
+  if (longest >= A.lo)
+    hipLaunchKernelGGL((k_cloud_filter<int32_t, 32>), dim3(grid), dim3(kCloudThreads), lds(32), s, d_xyz, A);
+  int32_t* before = (int32_t*)(ws + pl.moff);
+  ScanJobs J{};  // entry H is not a cloud: the scan only writes its place
+  J.j[0] = ScanJob{A.kept, before, nullptr, nullptr};
+  J.count = 1;
+  const int32_t rc = exclusive_scan_chained(J, 0, H + 1, (unsigned long long*)(ws + pl.chain_words),
+                                            pl.chain_stride, kChainEpochFilter, h, s);
+  if (rc) return rc;
+  hipLaunchKernelGGL(k_cloud_list<int32_t>, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 4096)), dim3(256),
+                     0, s, d_xyz, A, before, h, (int64_t*)(ws + pl.off2), (uint32_t*)(ws + pl.keys1),
+                     (int32_t*)(ws + pl.vals1), (int32_t*)(ws + pl.hid));
   HULL_LAUNCH_CHECK();
   return HULL_OK;
 }

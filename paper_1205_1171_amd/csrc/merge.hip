@@ -1065,27 +1065,38 @@ int32_t batched(const int32_t* d_xyz, const int64_t* d_off, const int64_t* h_off
   if (h_off[0] != 0 || n < 0 || n > kMaxTotal || (n > 0 && !d_xyz) || cap < 2 * n)
     return HULL_EINVAL;
   const Opts opt = resolve(sched, n);
-  int L = 0;
+  int64_t longest = 0;
   for (int64_t q = 0; q < H; ++q) {
     const int64_t nh = h_off[q + 1] - h_off[q];
     if (nh < 0 || nh > kMaxN) return HULL_EINVAL;
-    L = std::max(L, levels_for(nh));
+    longest = std::max(longest, nh);
   }
+  const int L = levels_for(longest);
   Plan pl = make_plan(n, H, opt.seg);
   if (ws_bytes < pl.total) return HULL_EWORKSPACE;
   char* ws = (char*)d_ws;
   Header* h = (Header*)(ws + pl.header);
-  init_call(h, nullptr, 0, ws, pl, s);
+  init_call(h, (int64_t*)(ws + pl.off1), n, ws, pl, s);
   Sched S{};
   S.off = d_off;
   S.H = H;
   if (n > 0) {
     const RunInits init(ws, pl, true, true);
-    int32_t rc = extent_and_filter<int32_t>(d_xyz, n, false, ws, pl, s);
+    const bool single = H == 1;
+    bool filter = single ? n >= kFilterMin : longest >= kCloudsFrom && longest <= kCloudMax;
+    int32_t rc = extent_and_filter<int32_t>(d_xyz, n, single && filter, ws, pl, s);
     if (rc) return rc;
-    rc = sort_points<int32_t, int4>(d_xyz, n, d_off, H, ws, pl, init.r, false, s);
+    if (single) {
+      S.off = (const int64_t*)(ws + pl.off1);
+    } else if (filter) {
+      rc = filter_clouds(d_xyz, n, d_off, H, longest, ws, pl, s);
+      if (rc) return rc;
+      S.off = (const int64_t*)(ws + pl.off2);
+    }
+    rc = sort_points<int32_t, int4>(d_xyz, n, single ? nullptr : d_off, H, ws, pl, init.r, filter, s);
     if (rc) return rc;
-    rc = run_levels<int4>(n, S, ws, pl, s, true, true, L, opt, nullptr);
+    // (the bound on a level's merges counts every cloud: the device knows better)
+    rc = run_levels<int4>(n, S, ws, pl, s, true, true, L, opt, nullptr, filter || !single);
     if (rc) return rc;
   }
   return extract<int4>(S, ws, pl, s, true, true, d_faces, cap, d_face_off, d_info);

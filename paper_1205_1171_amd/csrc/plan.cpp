@@ -37,6 +37,7 @@ Plan make_plan(int64_t n, int64_t H, int min_seg, int pt_bytes) {
   p.chain_words = take(kChainJobs * p.chain_stride * sizeof(unsigned long long));
   p.pts = take(nn * (size_t)pt_bytes);
   p.off1 = take(2 * sizeof(int64_t));
+  p.off2 = take((hh + 1) * sizeof(int64_t));
   p.mcnt = take((hh + 1) * 4);
   p.moff = take((hh + 1) * 4);
   p.mlist = take(p.mcap * sizeof(int2));

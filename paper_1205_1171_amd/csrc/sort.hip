@@ -357,7 +357,8 @@ int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_
   B.keys[1] = (uint32_t*)(ws + pl.keys1);
   B.vals[0] = (int32_t*)(ws + pl.vals0);
   B.vals[1] = (int32_t*)(ws + pl.vals1);
-  B.n = hull_off ? hull_off + H : (const int64_t*)(ws + pl.off1) + 1;
+  B.n = !hull_off ? (const int64_t*)(ws + pl.off1) + 1
+                  : (from_list ? (const int64_t*)(ws + pl.off2) : hull_off) + H;
   B.from_list = from_list;
   int32_t* counts = (int32_t*)(ws + pl.counts);
   int32_t* hid = nullptr;
@@ -372,7 +373,7 @@ int32_t sort_points(const InT* d_xyz, int64_t n, const int64_t* hull_off, int64_
   unsigned long long* words = (unsigned long long*)(ws + pl.chain_words);
   unsigned eg = (unsigned)std::min<int64_t>((n + 255) / 256, 2048);
   if (eg < 1) eg = 1;
-  if (hid) hipLaunchKernelGGL(k_hull_ids, dim3(eg), dim3(256), 0, s, hull_off, H, n, hid);
+  if (hid && !from_list) hipLaunchKernelGGL(k_hull_ids, dim3(eg), dim3(256), 0, s, hull_off, H, n, hid);
   for (int kind = 0; kind < 2; ++kind) {
     const int npass = kind == 0 ? 4 : hull_passes;
     for (int d = 0; d < npass; ++d) {

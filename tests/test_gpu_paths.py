@@ -178,3 +178,39 @@ def test_interior_filter(n):
     say("filter wide", n)
     a = validate.canonical(hull.hull_wide(torch.from_numpy(p).cuda()).cpu().numpy())
     assert (a == validate.canonical(oracle.hull_wide(p))).all()
+
+
+# The filter of a batch: clouds at the edges of its three grids, clouds too small
+# for it, empty ones, spheres that keep everything next to balls; eager and
+# captured.
+def test_batch_filter():
+    import oracle
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    rng = np.random.default_rng(4)
+    sizes = [0, 1, 2, 3, 255, 256, 257, 0, 2047, 2048, 2049, 8191, 8192, 8193, 1000, 30000, 0]
+    parts = []
+    for k, n in enumerate(sizes):
+        make = [workloads.ball, workloads.sphere, workloads.cube][k % 3]
+        parts.append(make(rng, n, 1 << 20) if n else np.zeros((0, 3), np.int32))
+    parts[8][:, 2] = 5  # flat: nothing is interior
+    parts[10] //= 1 << 17  # a lattice of many duplicates
+    off = np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)
+    x = torch.from_numpy(np.ascontiguousarray(np.concatenate(parts), dtype=np.int32)).cuda()
+    say("batch filter eager")
+    f, fo = hull.hull_batched_sync(x, off)
+    bh = hull.BatchedHull(x, off)
+    say("batch filter captured")
+    bh.capture()
+    for _ in range(3):
+        bh.faces.zero_()
+        bh.replay()
+        g, go = bh.result()
+        assert torch.equal(f, g) and torch.equal(fo, go)
+    f, fo = f.cpu().numpy(), fo.cpu().numpy()
+    for k, p in enumerate(parts):
+        got = validate.canonical(f[fo[k]:fo[k + 1]])
+        want = validate.canonical(oracle.hull(np.ascontiguousarray(p, dtype=np.int32))) if len(p) >= 3 \
+            else np.zeros((0, 3))
+        assert got.shape == want.shape and (got == want).all(), (k, len(p))
