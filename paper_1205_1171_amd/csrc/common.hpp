@@ -145,6 +145,17 @@ struct RunInit {
   int* ctr;
 };
 
+struct RunInitPair {
+  RunInit r[2];
+};
+
+// init_call, the filter (if asked for) and the sort of a single hull of at most
+// kSmallMax points, in one launch.
+constexpr int64_t kSmallMax = 8192;
+template <class InT, class PT>
+int32_t small_setup_and_sort(const InT* d_xyz, int64_t n, bool filter, char* ws, const Plan& pl,
+                             const RunInit* runs, hipStream_t s);
+
 // Extent and range check of the input (into the header) and, if asked for, the
 // interior points taken out (filter.hip): the kept points' keys and indices go
 // to the sort's second buffer and their number to off1[1].

@@ -75,6 +75,10 @@ __device__ __forceinline__ Frame frame_of(const Header* h) {
   return f;
 }
 template <class InT>
+__device__ __forceinline__ void rel(const Frame& f, const InT c[3], double q[3]) {
+  for (int a = 0; a < 3; ++a) q[a] = ((double)c[a] - f.c[a]) * f.s[a];
+}
+template <class InT>
 __device__ __forceinline__ void rel(const Frame& f, const InT* xyz, int64_t i, double q[3]) {
   for (int a = 0; a < 3; ++a) q[a] = ((double)xyz[3 * i + a] - f.c[a]) * f.s[a];
 }
@@ -208,9 +212,14 @@ __device__ float tetra(const double* a, const double* b, const double* d, float4
     r[1] = p[2] * q[0] - p[0] * q[2];
     r[2] = p[0] * q[1] - p[1] * q[0];
   };
+  // (the normals are not zero: the determinant is not; two Newton steps on the
+  // estimate of the reciprocal root, relative error below 2^-44)
   auto unit = [](double* r, double sg) {
-    const double l = sqrt(r[0] * r[0] + r[1] * r[1] + r[2] * r[2]);
-    for (int k = 0; k < 3; ++k) r[k] = l > 0 ? r[k] * (sg / l) : 0.0;
+    const double l2 = r[0] * r[0] + r[1] * r[1] + r[2] * r[2];
+    double y = __builtin_amdgcn_rsq(l2);
+    y = y * (1.5 - 0.5 * l2 * y * y);
+    y = y * (1.5 - 0.5 * l2 * y * y) * sg;
+    for (int k = 0; k < 3; ++k) r[k] *= y;
   };
   double ab[3], bd[3], da[3], n[3], e[3], g[3];
   cross(a, b, ab);
@@ -423,16 +432,136 @@ struct CloudArgs {
 constexpr int kCloudThreads = 512;
 constexpr int64_t kCloudMin = 256;  // smaller clouds keep every point
 
-// Sum, minimum or maximum over the block (every thread gets it).
-template <class T, class OP>
-__device__ __forceinline__ T block_all(T x, T* lds, const OP& op) {
-  for (int o = 32; o > 0; o >>= 1) x = op(x, (T)__shfl_xor(x, o));
+// The points of a cloud for a block of NT threads: point p = threadIdx.x + j NT of
+// every pass is read from memory, or (PER > 0, at most PER NT points) was
+// loaded into registers once, all loads in flight together.
+template <int NT, int PER, class InT>
+struct CloudPoints {
+  const InT* P;
+  int n;
+  InT c[PER > 0 ? PER : 1][3];
+  __device__ __forceinline__ CloudPoints(const InT* points, int count) : P(points), n(count) {
+    if constexpr (PER > 0) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const int p = threadIdx.x + j * NT;
+        for (int a = 0; a < 3; ++a) c[j][a] = p < n ? P[3 * (int64_t)p + a] : 0;
+      }
+    }
+  }
+  template <class FN>
+  __device__ __forceinline__ void each(const FN& fn) const {
+    if constexpr (PER > 0) {
+#pragma unroll
+      for (int j = 0; j < PER; ++j) {
+        const int p = threadIdx.x + j * NT;
+        if (p < n) fn(p, c[j]);
+      }
+    } else {
+      for (int p = threadIdx.x; p < n; p += NT) {
+        const InT x[3] = {P[3 * (int64_t)p], P[3 * (int64_t)p + 1], P[3 * (int64_t)p + 2]};
+        fn(p, x);
+      }
+    }
+  }
+};
+
+// Extent, range check and frame of a cloud (red: 10 words).
+template <int NT, class PTS, class InT>
+__device__ __forceinline__ Frame cloud_frame(const PTS& pts, const InT* P, int n, long long* red, long long& minx,
+                                             bool& bad) {
+  const int t = threadIdx.x;
+  __syncthreads();  // earlier readers of red
+  if (t < 10) red[t] = t < 3 ? 0x7fffffffffffffffll : (t < 6 ? -0x7fffffffffffffffll - 1 : 0);
+  InT lo[3], hi[3], sample[3];
+  for (int a = 0; a < 3; ++a) {
+    lo[a] = std::numeric_limits<InT>::max();
+    hi[a] = std::numeric_limits<InT>::lowest();
+    sample[a] = t < 256 ? P[3 * ((int64_t)t * n / 256) + a] : 0;
+  }
+  int out = 0;
+  pts.each([&](int, const InT* c) {
+    for (int a = 0; a < 3; ++a) {
+      lo[a] = c[a] < lo[a] ? c[a] : lo[a];
+      hi[a] = c[a] > hi[a] ? c[a] : hi[a];
+    }
+    out |= pt_out_of_range(c[0], c[1], c[2]);
+  });
   __syncthreads();
-  if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
+  // by wavefront first: atomics of many lanes on one word take their turns
+  long long sum[3] = {sample[0], sample[1], sample[2]};
+  for (int a = 0; a < 3; ++a) {
+    for (int o = 32; o > 0; o >>= 1) {
+      const InT l = __shfl_xor(lo[a], o), u = __shfl_xor(hi[a], o);
+      lo[a] = l < lo[a] ? l : lo[a];
+      hi[a] = u > hi[a] ? u : hi[a];
+    }
+    if (t < 256)
+      for (int o = 32; o > 0; o >>= 1) sum[a] += __shfl_xor(sum[a], o);
+  }
+  const bool any = __ballot(out) != 0;
+  if ((t & 63) == 0 && t < n) {
+    for (int a = 0; a < 3; ++a) {
+      atomicMin(&red[a], (long long)lo[a]);
+      atomicMax(&red[3 + a], (long long)hi[a]);
+    }
+    if (any) atomicOr((unsigned long long*)&red[9], 1ull);
+  }
+  if ((t & 63) == 0 && t < 256)
+    for (int a = 0; a < 3; ++a) atomicAdd((unsigned long long*)&red[6 + a], (unsigned long long)sum[a]);
   __syncthreads();
-  x = lds[0];
-  for (int w = 1; w < kCloudThreads / 64; ++w) x = op(x, lds[w]);
-  return x;
+  Frame f;
+  for (int a = 0; a < 3; ++a) {
+    f.c[a] = (double)red[6 + a] * (1.0 / 256.0);
+    f.s[a] = scale_of((double)(red[3 + a] - red[a]));
+  }
+  minx = red[0];
+  bad = red[9] != 0;
+  return f;
+}
+
+// Representatives and tetrahedra of a cloud in LDS; returns the square of the
+// ball's radius.
+template <int NT, int G, class PTS, class InT>
+__device__ __forceinline__ float cloud_grid(const PTS& pts, const InT* P, const Frame& f, unsigned long long* reps,
+                                            float4* quads, unsigned* rho) {
+  constexpr int nq = (G + 1) * (G + 1);
+  const int t = threadIdx.x;
+  for (int q = t; q < G * G; q += NT) reps[q] = 0;
+  if (t == 0) *rho = 0x7f7fffffu;
+  __syncthreads();
+  pts.each([&](int p, const InT* xyz) {
+    double q[3];
+    rel(f, xyz, q);
+    const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
+    float u, v;
+    square_of(x, y, z, u, v);
+    const int c = cell_at(v, G) * G + cell_at(u, G);
+    const unsigned long long key =
+        ((unsigned long long)__float_as_uint(x * x + y * y + z * z) << 32) | (unsigned)p;
+    if (key > reps[c]) atomicMax(&reps[c], key);
+  });
+  __syncthreads();
+  for (int k = t; k < nq; k += NT) {
+    const float r = quad(P, f, G, k % (G + 1), k / (G + 1), [&](int i, int j) { return reps[j * G + i]; },
+                         quads + 8 * k);
+    atomicMin(rho, __float_as_uint(r));
+  }
+  __syncthreads();
+  const float radius = __uint_as_float(*rho);
+  return radius * radius * (1.0f - 0x1p-18f);
+}
+
+// May a point be a vertex, as far as the grid can tell?
+template <int G, class InT>
+__device__ __forceinline__ bool cloud_keeps(const InT* xyz, const Frame& f, const float4* quads, float rr) {
+  double q[3];
+  rel(f, xyz, q);
+  const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
+  if (x * x + y * y + z * z < rr) return false;
+  float u, v;
+  square_of(x, y, z, u, v);
+  return !inside_around(quads, G, u, v, x, y, z, abs1(x, y, z));
 }
 
 template <class InT, int G>
@@ -441,7 +570,7 @@ __global__ void __launch_bounds__(kCloudThreads) k_cloud_filter(const InT* __res
   constexpr int nq = (G + 1) * (G + 1), T = kCloudThreads;
   float4* quads = (float4*)dyn_lds;                                    // [8 nq]
   unsigned long long* reps = (unsigned long long*)(quads + 8 * nq);    // [G * G]
-  __shared__ long long red[T / 64];
+  __shared__ long long red[10];
   __shared__ unsigned rho;
   __shared__ int wcnt[2][T / 64];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -458,60 +587,16 @@ __global__ void __launch_bounds__(kCloudThreads) k_cloud_filter(const InT* __res
       if (t == 0) A.kept[h] = n;
       continue;
     }
-    InT lo[3] = {P[0], P[1], P[2]}, hi[3] = {P[0], P[1], P[2]};
-    for (int p = t; p < n; p += T)
-      for (int a = 0; a < 3; ++a) {
-        const InT c = P[3 * (int64_t)p + a];
-        lo[a] = c < lo[a] ? c : lo[a];
-        hi[a] = c > hi[a] ? c : hi[a];
-      }
-    Frame f;
-    for (int a = 0; a < 3; ++a) {
-      const long long mn = block_all((long long)lo[a], red, [](long long x, long long y) { return x < y ? x : y; });
-      const long long mx = block_all((long long)hi[a], red, [](long long x, long long y) { return x > y ? x : y; });
-      const long long sample = t < 256 ? (long long)P[3 * ((int64_t)t * n / 256) + a] : 0;
-      const long long sum = block_all(sample, red, [](long long x, long long y) { return x + y; });
-      f.c[a] = (double)sum * (1.0 / 256.0);
-      f.s[a] = scale_of((double)(mx - mn));
-    }
-    for (int q = t; q < G * G; q += T) reps[q] = 0;
-    if (t == 0) rho = 0x7f7fffffu;
-    __syncthreads();
-    for (int p = t; p < n; p += T) {
-      double q[3];
-      rel(f, P, p, q);
-      const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
-      float u, v;
-      square_of(x, y, z, u, v);
-      const int c = cell_at(v, G) * G + cell_at(u, G);
-      const unsigned long long key =
-          ((unsigned long long)__float_as_uint(x * x + y * y + z * z) << 32) | (unsigned)p;
-      if (key > reps[c]) atomicMax(&reps[c], key);
-    }
-    __syncthreads();
-    for (int k = t; k < nq; k += T) {
-      const float r = quad(P, f, G, k % (G + 1), k / (G + 1),
-                           [&](int i, int j) { return reps[j * G + i]; }, quads + 8 * k);
-      atomicMin(&rho, __float_as_uint(r));
-    }
-    __syncthreads();
-    const float radius = __uint_as_float(rho), rr = radius * radius * (1.0f - 0x1p-18f);
+    long long minx;
+    bool bad;  // (the range was checked by an earlier launch)
+    const CloudPoints<T, 0, InT> pts(P, n);
+    const Frame f = cloud_frame<T>(pts, P, n, red, minx, bad);
+    const float rr = cloud_grid<T, G>(pts, P, f, reps, quads, &rho);
     // kept points in input order
     int done = 0;
     for (int p0 = 0, turn = 0; p0 < n; p0 += T, turn ^= 1) {
       const int p = p0 + t;
-      bool keep = false;
-      if (p < n) {
-        double q[3];
-        rel(f, P, p, q);
-        const float x = (float)q[0], y = (float)q[1], z = (float)q[2];
-        keep = !(x * x + y * y + z * z < rr);
-        if (keep) {
-          float u, v;
-          square_of(x, y, z, u, v);
-          keep = !inside_around(quads, G, u, v, x, y, z, abs1(x, y, z));
-        }
-      }
+      const bool keep = p < n && cloud_keeps<G>(P + 3 * (int64_t)p, f, quads, rr);
       const unsigned long long m = __ballot(keep);
       if (lane == 0) wcnt[turn][wave] = __popcll(m);
       __syncthreads();  // (two sets of counts: one barrier a turn)
@@ -601,6 +686,131 @@ int32_t extent_and_filter(const InT* d_xyz, int64_t n, bool filter, char* ws, co
   HULL_LAUNCH_CHECK();
   return HULL_OK;
 }
+
+// ---------------------------------------------------------------------------
+// Small single hulls: the call's setup, the filter and the sort in one launch of
+// one workgroup.
+// ---------------------------------------------------------------------------
+// Nineteen launches (six of them the filter's) took 61 us for 97 points and 93 for
+// 4,096 cube points, 7 and 37 in this one.  The kept points' (x, index) pairs are
+// sorted in LDS: chunks of 128 by counting smaller keys (one barrier), then merged
+// pair by pair, every key finding its place in the other chunk by binary search
+// (a bitonic network takes 28 barriers for 97 points, 78 for 4,096).  The order
+// is total, so the points need not arrive in order.
+constexpr int kSmallChunk = 128;
+constexpr int kSmallGrid = 8;
+constexpr size_t kSmallQuads = (size_t)(kSmallGrid + 1) * (kSmallGrid + 1) * 8 * sizeof(float4);
+
+template <class InT, class PT, int T, int PER>
+__global__ void __launch_bounds__(T)
+    k_small_sort(const InT* __restrict__ xyz, int n, int filter, int cap, Header* h, int64_t* off1,
+                 unsigned long long* words, int64_t nwords, PT* __restrict__ out, RunInitPair I) {
+  constexpr int G = kSmallGrid, C = kSmallChunk;
+  extern __shared__ __align__(16) unsigned char dyn_lds[];
+  unsigned long long* keys = (unsigned long long*)dyn_lds;  // [cap], cap >= n + 1, even
+  unsigned long long* ordered = keys + cap;                 // [cap] the same, sorted by chunk
+  float4* quads = (float4*)(ordered + cap);                 // the filter's grid, if wanted
+  unsigned long long* reps = (unsigned long long*)((unsigned char*)quads + kSmallQuads);
+  __shared__ long long red[10];
+  __shared__ unsigned rho;
+  __shared__ int kept;
+  const int t = threadIdx.x;
+  for (int64_t q = t; q < nwords; q += T) words[q] = 0;
+  if (t == 0) kept = 0;
+  long long minx;
+  bool bad;
+  const CloudPoints<T, PER, InT> pts(xyz, n);
+  const Frame f = cloud_frame<T>(pts, xyz, n, red, minx, bad);
+  if (t == 0) {
+    h->err = bad ? HULL_ERANGE : 0;
+    off1[0] = 0;
+    off1[1] = n;
+  }
+  for (int q = t; q < kCtrSlots; q += T)
+    for (int r = 0; r < 2; ++r)
+      if (I.r[r].pv0) I.r[r].ctr[q] = 0;
+  if (bad) return;
+  if (filter) {
+    const float rr = cloud_grid<T, G>(pts, xyz, f, reps, quads, &rho);
+    pts.each([&](int p, const InT* c) {
+      if (cloud_keeps<G>(c, f, quads, rr))
+        keys[atomicAdd(&kept, 1)] = ((unsigned long long)((long long)c[0] - minx) << 32) | (unsigned)p;
+    });
+    __syncthreads();
+  } else {
+    pts.each([&](int p, const InT* c) {
+      keys[p] = ((unsigned long long)((long long)c[0] - minx) << 32) | (unsigned)p;
+    });
+  }
+  const int m = filter ? kept : n;
+  if (t == 0) keys[m] = ~0ull;  // chunks are read in pairs
+  __syncthreads();
+  for (int p = t; p < m; p += T) {
+    const unsigned long long key = keys[p];
+    const int base = p / C * C, pairs = (min(C, m - base) + 1) / 2;
+    const ulonglong2* c = (const ulonglong2*)(keys + base);
+    int r = 0;
+#pragma unroll 8
+    for (int q = 0; q < pairs; ++q) {
+      const ulonglong2 x = c[q];
+      r += (x.x < key) + (x.y < key);
+    }
+    ordered[base + r] = key;
+  }
+  __syncthreads();
+  for (int run = C; run < m; run *= 2) {
+    for (int p = t; p < m; p += T) {
+      const unsigned long long key = ordered[p];
+      const int mine = p / run * run, pair = mine & ~run, other = pair + (mine == pair ? run : 0);
+      int lo = 0, hi = max(0, min(run, m - other));
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ordered[other + mid] < key) lo = mid + 1;
+        else hi = mid;
+      }
+      keys[pair + (p - mine) + lo] = key;
+    }
+    __syncthreads();
+    unsigned long long* x = keys;
+    keys = ordered;
+    ordered = x;
+  }
+  for (int r = t; r < m; r += T) {
+    const unsigned long long key = ordered[r];
+    const int i = (int)(unsigned)key;
+    out[r] = make_pt(xyz, i, i);
+    for (int q = 0; q < 2; ++q) {
+      if (!I.r[q].pv0) continue;
+      I.r[q].pv0[r] = kNil;
+      I.r[q].nx0[r] = kNil;
+      I.r[q].len[r] = 0;
+    }
+  }
+  if (t == 0) off1[1] = m;
+}
+
+template <class InT, class PT>
+int32_t small_setup_and_sort(const InT* d_xyz, int64_t n, bool filter, char* ws, const Plan& pl,
+                             const RunInit* runs, hipStream_t s) {
+  const int cap = (int)(n + 2) & ~1;
+  const size_t lds = (size_t)cap * 16 + (filter ? kSmallQuads + (size_t)kSmallGrid * kSmallGrid * 8 : 0);
+#define HULL_SMALL(T, PER)                                                                                 \
+  hipLaunchKernelGGL((k_small_sort<InT, PT, T, PER>), dim3(1), dim3(T), lds, s, d_xyz, (int)n, (int)filter, cap, \
+                     (Header*)(ws + pl.header), (int64_t*)(ws + pl.off1),                               \
+                     (unsigned long long*)(ws + pl.chain_words), kChainJobs * pl.chain_stride,          \
+                     (PT*)(ws + pl.pts), RunInitPair{{runs[0], runs[1]}})
+  if (n <= 512) HULL_SMALL(256, 2);
+  else if (n <= 4096) HULL_SMALL(1024, 4);
+  else HULL_SMALL(1024, 8);
+#undef HULL_SMALL
+  HULL_LAUNCH_CHECK();
+  return HULL_OK;
+}
+
+template int32_t small_setup_and_sort<int32_t, int4>(const int32_t*, int64_t, bool, char*, const Plan&,
+                                                     const RunInit*, hipStream_t);
+template int32_t small_setup_and_sort<int64_t, WPt>(const int64_t*, int64_t, bool, char*, const Plan&,
+                                                    const RunInit*, hipStream_t);
 
 // Clouds by size: 8, 16 or 32 cells per side (10, 39 or 148 KB of LDS).  The
 // clouds of a batch are small enough for one workgroup each (kCloudMax).

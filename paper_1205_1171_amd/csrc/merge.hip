@@ -333,16 +333,35 @@ constexpr int kPtsLdsMerges = 1024;
 // few events per block, and the tile's loads and list bounds, which cover all
 // points, then cost more than the walks they serve: level 10 6.8 ms / 2.6,
 // 11 3.5 / 1.9.
-constexpr int kTileFromLevel = 5;  // (kTileMerges and kTilePoints: events.hpp)
-constexpr int kMaxLevels = 28;
+constexpr int kTileFromLevel = 5;  // (one earlier for calls of few points, two for the smallest;
+                                   // kTileMerges and kTilePoints: events.hpp)
 constexpr int kTileLevels = 11;  // kTileMaxWidth
+constexpr int kMaxLevels = 28;
 
-// Lanes per merge of a tile level of width W: hulls whose points are nearly
-// all vertices have about W child events, so W / 4 segments of the default
-// length; twice as many lanes take the larger movies in one round.
-static int tile_lanes(int W) {
+static int env_int(const char* name, int dflt) {
+  const char* e = getenv(name);
+  return (e && *e) ? atoi(e) : dflt;
+}
+
+// Child events per segment of a tile level and lanes per merge.  Hulls whose
+// points are nearly all vertices have about W child events in a block of W
+// points.  Calls of few points have lanes to spare: the shortest segments, and
+// tiles from one level earlier (60,001-point sphere, levels 4-9: 53-68 us with
+// four events and W / 2 lanes, 42-55 with two and W).  Otherwise three events, so
+// that W / 2 lanes take a movie in one round (2^20 sphere, levels 6-9: 426-547 us
+// with four, 388-486 with three; with W lanes 577-754).  At the widest blocks the
+// lanes are capped and the segments grow to fit.  A caller's own segment length
+// (not the default's) is taken as it is.
+constexpr int64_t kTileSparePoints = int64_t(1) << 17;
+constexpr int kWalkSegment = 4;
+static int tile_segment(int W, int64_t n, int seg) {
+  if (seg != kWalkSegment) return seg;
+  return W >= 2048 ? 4 : (W >= 1024 || n > kTileSparePoints ? 3 : 2);
+}
+static int tile_lanes(int W, int64_t n) {
+  const int most = n > kTileSparePoints ? W / 2 : W;
   int gs = 16;
-  while (gs < 512 && gs < W / 2) gs *= 2;
+  while (gs < 512 && gs < most) gs *= 2;
   return gs;
 }
 
@@ -708,10 +727,6 @@ static unsigned grid_for(int64_t work, int64_t cap_blocks = 4096) {
   return (unsigned)b;
 }
 
-static int env_int(const char* name, int dflt) {
-  const char* e = getenv(name);
-  return (e && *e) ? atoi(e) : dflt;
-}
 
 // The merge schedule: which levels run lane-serial and the walk segment
 // length.  Unset fields take the environment (HULL_SERIAL_LEVELS,
@@ -747,7 +762,7 @@ static int default_wave_level(int64_t total) {
 static Opts resolve(const hull_schedule_t* sc, int64_t total) {
   Opts o;
   o.serial_max = sc && sc->serial_levels >= 0 ? sc->serial_levels : env_int("HULL_SERIAL_LEVELS", 10);
-  o.seg = sc && sc->walk_segment > 0 ? sc->walk_segment : env_int("HULL_WALK_SEGMENT", 4);
+  o.seg = sc && sc->walk_segment > 0 ? sc->walk_segment : env_int("HULL_WALK_SEGMENT", kWalkSegment);
   if (o.seg < kMinWalkSegment) o.seg = kMinWalkSegment;
   o.lds_levels = std::min(std::max(env_int("HULL_LDS_LEVELS", 3), 0), kLdsLevels);
   const int wf = sc && sc->wave_from != 0 ? sc->wave_from
@@ -763,7 +778,8 @@ static Opts resolve(const hull_schedule_t* sc, int64_t total) {
   o.order_min = std::max(env_int("HULL_ORDER_MIN", (int)kOrderMinMerges), 0);
   o.tile_levels = env_int("HULL_TILE_LEVELS", kTileLevels);
   const char* sl = getenv("HULL_SERIAL_LEVELS");
-  o.tile_from = (sc && sc->serial_levels >= 0) || (sl && *sl) ? kMaxLevels + 1 : kTileFromLevel;
+  o.tile_from = (sc && sc->serial_levels >= 0) || (sl && *sl) ? kMaxLevels + 1
+                                                             : kTileFromLevel - (total <= kTileSparePoints) - (total <= kSmallMax);
   o.pts_lds_merges = std::max(env_int("HULL_PTS_LDS_MERGES", kPtsLdsMerges), 0);
   return o;
 }
@@ -836,7 +852,7 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
     const int64_t bound = std::min<int64_t>(pl.mcap, n / A.width + S.H + 1);
     const bool tile_fits =
         k <= opt.tile_levels && A.width <= kTileMaxWidth &&
-        (int64_t)TileLds<PT>::bytes((int)A.width, tile_lanes((int)A.width)) + 256 <= max_lds_bytes();
+        (int64_t)TileLds<PT>::bytes((int)A.width, tile_lanes((int)A.width, n)) + 256 <= max_lds_bytes();
     const bool open = tile_fits && k >= opt.tile_from;  // the number of merges decides
     const bool few = !many_merges(bound, n);            // (of the host's bound; the device may have fewer)
     // what runs: k <= serial_max lane-serial or lane groups, above that tiles
@@ -935,12 +951,13 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
       LevelArgs B = A;
       B.sel = sel_tile;
       const int W = (int)A.width;
-      const int gs = tile_lanes(W);
+      const int gs = tile_lanes(W, n);
+      const int tseg = tile_segment(W, n, opt.seg);
       const int per = gs < 64 ? 64 / gs : 1;
       const dim3 grid(merge_grid(bound, per), 2);
       const size_t lds = per * TileLds<PT>::bytes(W, gs);
 #define HULL_TILE(G) \
-  hipLaunchKernelGGL((k_merge_tile<PT, G>), grid, dim3(G < 64 ? 64 : G), lds, s, B, opt.seg)
+  hipLaunchKernelGGL((k_merge_tile<PT, G>), grid, dim3(G < 64 ? 64 : G), lds, s, B, tseg)
       if (gs == 16) HULL_TILE(16);
       else if (gs == 32) HULL_TILE(32);
       else if (gs == 64) HULL_TILE(64);
@@ -1001,6 +1018,16 @@ struct RunInits {
   }
 };
 
+// Everything before the merges of a single hull.
+template <class InT, class PT>
+static int32_t setup_single(const InT* d_xyz, int64_t n, bool filter, char* ws, const Plan& pl,
+                            const RunInit* runs, hipStream_t s) {
+  if (n <= kSmallMax) return small_setup_and_sort<InT, PT>(d_xyz, n, filter, ws, pl, runs, s);
+  init_call((Header*)(ws + pl.header), (int64_t*)(ws + pl.off1), n, ws, pl, s);
+  const int32_t rc = extent_and_filter<InT>(d_xyz, n, filter, ws, pl, s);
+  return rc ? rc : sort_points<InT, PT>(d_xyz, n, nullptr, 1, ws, pl, runs, filter, s);
+}
+
 template <class InT, class PT>
 static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_t cap,
                            int64_t* d_info, void* d_ws, size_t ws_bytes, hipStream_t s, bool lower,
@@ -1017,8 +1044,8 @@ static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_
   Header* h = (Header*)(ws + pl.header);
   if (ev) (void)hipEventRecord(ev[0], s);
   int64_t* off = (int64_t*)(ws + pl.off1);
-  init_call(h, off, n, ws, pl, s);
   if (n < 3) {
+    init_call(h, off, n, ws, pl, s);
     hipLaunchKernelGGL(k_info_small, dim3(1), dim3(64), 0, s, d_info, h);
     HULL_LAUNCH_CHECK();
     if (ev)
@@ -1030,9 +1057,7 @@ static int32_t hull_runs_t(const InT* d_xyz, int64_t n, int32_t* d_faces, int64_
   S.H = 1;
   const RunInits init(ws, pl, lower, upper);
   filter = filter && n >= kFilterMin;
-  int32_t rc = extent_and_filter<InT>(d_xyz, n, filter, ws, pl, s);
-  if (rc) return rc;
-  rc = sort_points<InT, PT>(d_xyz, n, nullptr, 1, ws, pl, init.r, filter, s);
+  int32_t rc = setup_single<InT, PT>(d_xyz, n, filter, ws, pl, init.r, s);
   if (rc) return rc;
   if (ev) (void)hipEventRecord(ev[1], s);
   rc = run_levels<PT>(n, S, ws, pl, s, lower, upper, L, opt, ev, filter);
@@ -1076,24 +1101,27 @@ int32_t batched(const int32_t* d_xyz, const int64_t* d_off, const int64_t* h_off
   if (ws_bytes < pl.total) return HULL_EWORKSPACE;
   char* ws = (char*)d_ws;
   Header* h = (Header*)(ws + pl.header);
-  init_call(h, (int64_t*)(ws + pl.off1), n, ws, pl, s);
   Sched S{};
   S.off = d_off;
   S.H = H;
+  if (n == 0) init_call(h, nullptr, 0, ws, pl, s);
   if (n > 0) {
     const RunInits init(ws, pl, true, true);
     const bool single = H == 1;
-    bool filter = single ? n >= kFilterMin : longest >= kCloudsFrom && longest <= kCloudMax;
-    int32_t rc = extent_and_filter<int32_t>(d_xyz, n, single && filter, ws, pl, s);
-    if (rc) return rc;
+    const bool filter = single ? n >= kFilterMin : longest >= kCloudsFrom && longest <= kCloudMax;
+    int32_t rc;
     if (single) {
+      rc = setup_single<int32_t, int4>(d_xyz, n, filter, ws, pl, init.r, s);
       S.off = (const int64_t*)(ws + pl.off1);
-    } else if (filter) {
-      rc = filter_clouds(d_xyz, n, d_off, H, longest, ws, pl, s);
-      if (rc) return rc;
-      S.off = (const int64_t*)(ws + pl.off2);
+    } else {
+      init_call(h, nullptr, n, ws, pl, s);
+      rc = extent_and_filter<int32_t>(d_xyz, n, false, ws, pl, s);
+      if (!rc && filter) {
+        rc = filter_clouds(d_xyz, n, d_off, H, longest, ws, pl, s);
+        S.off = (const int64_t*)(ws + pl.off2);
+      }
+      if (!rc) rc = sort_points<int32_t, int4>(d_xyz, n, d_off, H, ws, pl, init.r, filter, s);
     }
-    rc = sort_points<int32_t, int4>(d_xyz, n, single ? nullptr : d_off, H, ws, pl, init.r, filter, s);
     if (rc) return rc;
     // (the bound on a level's merges counts every cloud: the device knows better)
     rc = run_levels<int4>(n, S, ws, pl, s, true, true, L, opt, nullptr, filter || !single);
@@ -1113,15 +1141,11 @@ int32_t movies(const int32_t* d_xyz, int64_t n, int32_t run, int32_t level, int3
   if (ws_bytes < pl.total) return HULL_EWORKSPACE;
   char* ws = (char*)d_ws;
   Header* h = (Header*)(ws + pl.header);
-  int64_t* off = (int64_t*)(ws + pl.off1);
-  init_call(h, off, n, ws, pl, s);
   Sched S{};
-  S.off = off;
+  S.off = (const int64_t*)(ws + pl.off1);
   S.H = 1;
   const RunInits init(ws, pl, run == 0, run == 1);
-  int32_t rc = extent_and_filter<int32_t>(d_xyz, n, false, ws, pl, s);
-  if (rc) return rc;
-  rc = sort_points<int32_t, int4>(d_xyz, n, nullptr, 1, ws, pl, init.r, false, s);
+  int32_t rc = setup_single<int32_t, int4>(d_xyz, n, false, ws, pl, init.r, s);
   if (rc) return rc;
   int L = levels_for(n);
   if (level >= 0 && level < L) L = level;

@@ -28,10 +28,10 @@ struct TileLds {
   LinkPair<short>* lk;   // [W] -inf links
   unsigned short* ent;   // [6W] list entries: positions in ev
   uint2* keep;           // [kTileKeep * GS] bridge events put aside
-  unsigned short* cut;   // [W / 2 + 2] segment bounds in the left movie
+  unsigned short* cut;   // [2 W + 2] segment bounds in the left movie
   __host__ __device__ static constexpr size_t bytes(int W, int GS) {
     const size_t b = (size_t)W * (sizeof(PT) + 16 + 8 + 4 + 12) + 16 +
-                     (size_t)kTileKeep * GS * sizeof(uint2) + (size_t)(W / 2 + 2) * 2;
+                     (size_t)kTileKeep * GS * sizeof(uint2) + (size_t)(2 * W + 2) * 2;
     return (b + 15) & ~(size_t)15;
   }
   __device__ __forceinline__ TileLds(unsigned char* lds, int W, int GS) {

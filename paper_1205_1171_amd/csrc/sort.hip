@@ -169,9 +169,6 @@ __global__ void __launch_bounds__(256) k_hull_ids(const int64_t* __restrict__ of
 // Gather the points in rank order from the buffer of the last executed pass;
 // the index carried with each is the one within the point's hull.  Single
 // points: no links, empty movies.
-struct RunInitPair {
-  RunInit r[2];
-};
 template <class InT, class PT>
 __global__ void __launch_bounds__(256)
     k_gather(const InT* __restrict__ xyz, RadixBufs B, const int32_t* __restrict__ hid,

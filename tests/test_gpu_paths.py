@@ -214,3 +214,24 @@ def test_batch_filter():
         want = validate.canonical(oracle.hull(np.ascontiguousarray(p, dtype=np.int32))) if len(p) >= 3 \
             else np.zeros((0, 3))
         assert got.shape == want.shape and (got == want).all(), (k, len(p))
+
+
+# Setup and sort in one launch: sizes at its changes of block size and chunk, equal
+# x in one chunk and across chunks, the largest size and the first above it; the
+# order itself through the movies' ranks.
+@pytest.mark.parametrize("n", [1, 2, 3, 127, 128, 129, 512, 513, 1023, 4096, 4097, 8192, 8193])
+def test_small_sort(n):
+    import oracle
+    import torch
+    from paper_1205_1171_amd import hull
+    rng = np.random.default_rng(n)
+    for p in (workloads.cube(rng, n, 1 << 29), workloads.lattice(rng, n, 2),
+              np.repeat(workloads.cube(rng, 1, 99), n, axis=0)):
+        say("small sort", n)
+        _, _, order = hull.movies(torch.from_numpy(np.ascontiguousarray(p)).cuda(), 0, 0)
+        assert (order == oracle.sort_order(p)).all()
+    p[n // 2, 1] = (1 << 29) + 1
+    with pytest.raises(hull.HullError) as e:
+        hull.hull_sync(torch.from_numpy(p).cuda()) if n > 2 else hull.movies(
+            torch.from_numpy(p).cuda(), 0, 0)
+    assert e.value.code == hull.HULL_ERANGE
