@@ -399,6 +399,8 @@ struct ParLevel {
   Sched S;
   int64_t n;        // bound on the points
   int sel;
+  bool device_n;    // n is a bound, the device knows the number
+  int ranges;       // ranges of points per merge (lists built in LDS)
   int seg_events;   // child events per walk segment
   int64_t seg_cap;  // bound on the walk segments of a level
   int64_t mcap;     // bound on the merges of a level

@@ -808,6 +808,7 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
   P.h = h;
   P.n = n;
   P.seg_events = opt.seg;
+  P.device_n = device_n;
   P.seg_cap = pl.seg_cap;
   P.mcap = pl.mcap;
   // the call's one-launch scans tell their status words apart by epoch

@@ -14,15 +14,18 @@
 //      the counted steps.  A segment's output is in order, so the level needs
 //      no classification of the child events and no ranks of events in other
 //      lists.
+// Where many points take part, steps 1 and 2 run per range of points in LDS instead
+// (k_list_count, k_list_fill).
 // A level is nine launches.  Claiming lists by events, filling and sorting
 // 16-byte entries, a separate bridge list, survival flags and three more scans
 // took 1.70-2.25 ms a level on the 2^20-point sphere,
-// this 0.70-1.05 ms.
+// this 0.42-0.67 ms.
 #include <algorithm>
 #include <initializer_list>
 
 #include "common.hpp"
 #include "events.hpp"
+#include "merge_tile.hpp"
 #include "walk.hpp"
 
 namespace hull {
@@ -32,6 +35,18 @@ namespace hull {
 // (mean length 3, a few lists of 13-25), 6 with 32.
 constexpr int kParScan = 32;
 constexpr unsigned long long kStepsLost = ~0ull;  // a segment to be walked again
+
+// Lists built range by range in LDS rather than by global atomics: calls of many
+// points, whose changes are enough to be bound by the atomics (they run at about
+// 37 G/s and write one sector each), in blocks of up to 8 ranges (every range reads
+// the child events of its whole merge).  Levels 12 to 16 of the 2^20 sphere took
+// 872, 772, 711, 668 and 644 us by atomics, 567, 475, 433, 424 and 448 by ranges; the
+// 10,000 ragged clouds of 7.3e7 points, 165 and 127 ms a pass.
+constexpr int kRange = 8192;  // points: two counts each, 64 KiB of LDS
+constexpr int64_t kRangesFrom = int64_t(1) << 19;
+constexpr int kRangeThreads = 512;
+constexpr bool lists_by_range(int64_t n, int k) { return n >= kRangesFrom && k >= 12 && k <= 16; }
+static int ranges_of(int k) { return k <= 13 ? 1 : 1 << (k - 13); }
 
 template <class PT>
 struct ParCtx {
@@ -134,7 +149,9 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
   const int64_t merges = selected(P.S, P.sel) ? P.S.merges() : 0, half = int64_t(1) << (P.S.k - 1);
-  const int64_t keys = merges ? 2 * (P.S.off[P.S.H] + 1) : 0;
+  const int64_t n = P.S.off[P.S.H];
+  const int64_t keys = merges ? 2 * (n + 1) : 0;
+  const bool ranges = lists_by_range(n, P.S.k);
   const bool err = P.h->err != 0;
   GRID_STRIDE(g, (int64_t)(err ? 0 : Q.ctr[kCtrSplice + ((P.S.k - 1) & 1)])) {
     const int2 b = Q.uv0[g];
@@ -144,7 +161,8 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
   GRID_STRIDE(g, merges + 1) {
     if (g == 0) {
       Q.ctr[kCtrMerges] = (int)merges;
-      Q.ctr[kCtrKeys] = (int)keys;
+      Q.ctr[kCtrKeys] = ranges ? 0 : (int)keys;
+      Q.ctr[kCtrRanges] = ranges && !err ? (int)(2 * merges * P.ranges) : 0;
       Q.ctr[kCtrSplice + (P.S.k & 1)] = (int)merges;
     }
     if (g < merges && !err) {
@@ -158,7 +176,7 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
       Q.segS[g] = 0;
     }
   }
-  GRID_STRIDE(q, keys) Q.off[q] = 0;
+  if (!ranges) GRID_STRIDE(q, keys) Q.off[q] = 0;
   if (err) return;
   for (int64_t g = blockIdx.x; g < merges; g += gridDim.x) {  // one block per merge
     const int2 se = P.S.merge(g);
@@ -178,9 +196,10 @@ __global__ void __launch_bounds__(256) k_par_enum(ParLevel P) {
   const int merges = Q.ctr[kCtrMerges], E = Q.ctr[kCtrEvents], Sg = Q.ctr[kCtrSegments];
   if (!merges) return;
   const int64_t half = int64_t(1) << (P.S.k - 1), np1 = P.S.off[P.S.H] + 1;
-  GRID_STRIDE(c, (int64_t)E + Sg) {
-    const bool seg = c >= E;
-    const int64_t t = seg ? c - E : c;
+  const int events = Q.ctr[kCtrKeys] ? E : 0;  // (else the lists are built by range)
+  GRID_STRIDE(c, (int64_t)events + Sg) {
+    const bool seg = c >= events;
+    const int64_t t = seg ? c - events : c;
     const int g = find_owner(seg ? Q.segBase : Q.eoff, merges, t);
     const int2 se = P.S.merge(g);
     const int64_t s = se.x, m = s + half, e = se.y;
@@ -239,6 +258,138 @@ __global__ void __launch_bounds__(256) k_par_fill(ParLevel P) {
   }
 }
 
+// One range of points of one merge.
+struct Range {
+  int64_t s, m, e, p0;
+  int pn, nL, N;
+  bool closes;  // the points after it belong to no merge: it ends its lists itself
+  const Event* evL;
+  const Event* evR;
+  __device__ __forceinline__ Range(const ParLevel& P, const RunPtrs& R, int64_t pair, int64_t merges) {
+    const int64_t g = pair / P.ranges;
+    const int r = (int)(pair - g * P.ranges);
+    const int2 se = P.S.merge(g);
+    s = se.x;
+    m = s + (int64_t(1) << (P.S.k - 1));
+    e = se.y;
+    p0 = s + (int64_t)r * kRange;
+    pn = p0 >= e ? 0 : (int)(e - p0 < kRange ? e - p0 : kRange);
+    closes = pn > 0 && p0 + pn == e && (g + 1 == merges || P.S.merge(g + 1).x != e);
+    nL = R.left_len(s);
+    N = nL + R.right_len(m, e);
+    evL = R.left_ev(s);
+    evR = R.ev[(P.S.k - 1) & 1] + 2 * m;
+  }
+  // fn(point within the range, which list, position in the child movie, link
+  // after) for every link that the merge's child events change in the range
+  template <class FN>
+  __device__ __forceinline__ void changes(const FN& fn) const {
+    constexpr int U = 4;  // events in flight per thread
+    for (int c0 = threadIdx.x; c0 < N; c0 += U * kRangeThreads) {
+      int4 x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * kRangeThreads;
+        if (c < N) x[u] = *(const int4*)(c < nL ? evL + c : evR + (c - nL));
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * kRangeThreads;
+        if (c >= N) continue;
+        const int j = c < nL ? c : c - nL, w = x[u].y & 0x7fffffff;
+        const bool ins = x[u].y < 0;
+        const unsigned a = (unsigned)(x[u].x - (int)p0), i = (unsigned)(w - (int)p0),
+                       b = (unsigned)(x[u].z - (int)p0);
+        if (a < (unsigned)pn) fn((int)a, 0, j, ins ? w : x[u].z);
+        if (b < (unsigned)pn) fn((int)b, 1, j, ins ? w : x[u].x);
+        if (ins && i < (unsigned)pn) {
+          fn((int)i, 0, j, x[u].z);
+          fn((int)i, 1, j, x[u].x);
+        }
+      }
+    }
+  }
+};
+
+// Lengths of a range's lists, as offsets within the range, and their totals (next
+// lists of all ranges, then prev lists).
+__global__ void __launch_bounds__(kRangeThreads) k_list_count(ParLevel P) {
+  __shared__ int cnt[2 * kRange];
+  __shared__ int wsum[kRangeThreads / 64];
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!R.pts) return;
+  const int64_t pairs = Q.ctr[kCtrRanges] / 2, merges = Q.ctr[kCtrMerges], np1 = P.S.off[P.S.H] + 1;
+  int* totals = (int*)Q.pos;
+  const BlockGroup<kRangeThreads> g{wsum};
+  for (int64_t pair = blockIdx.x; pair < pairs; pair += gridDim.x) {
+    const Range X(P, R, pair, merges);
+    __syncthreads();
+    for (int q = threadIdx.x; q < 2 * kRange; q += kRangeThreads) cnt[q] = 0;
+    __syncthreads();
+    if (X.pn) X.changes([&](int p, int l, int, int) { atomicAdd(&cnt[l * kRange + p], 1); });
+    __syncthreads();
+    for (int l = 0; l < 2; ++l) {
+      int total = 0;
+      for (int q0 = 0; q0 < X.pn; q0 += 4 * kRangeThreads) {
+        const int q = q0 + 4 * threadIdx.x;
+        int v[4], sum = 0, all;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          v[j] = sum;
+          if (q + j < X.pn) sum += cnt[l * kRange + q + j];
+        }
+        const int before = total + g.scan(sum, all);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (q + j < X.pn) Q.off[l * np1 + X.p0 + q + j] = before + v[j];
+        total += all;
+      }
+      if (threadIdx.x == 0) totals[l * pairs + pair] = total;
+    }
+  }
+}
+
+// The lists' bounds and entries, once the totals are scanned; long lists sorted.
+__global__ void __launch_bounds__(kRangeThreads) k_list_fill(ParLevel P) {
+  __shared__ int cur[2 * kRange];
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!R.pts) return;
+  const int64_t pairs = Q.ctr[kCtrRanges] / 2, merges = Q.ctr[kCtrMerges], np1 = P.S.off[P.S.H] + 1;
+  const int* before = (const int*)Q.pos;
+  if (pairs > 0 && before[2 * pairs] > 6 * P.n) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
+    return;
+  }
+  for (int64_t pair = blockIdx.x; pair < pairs; pair += gridDim.x) {
+    const Range X(P, R, pair, merges);
+    __syncthreads();
+    for (int l = 0; l < 2; ++l) {
+      int* off = Q.off + l * np1 + X.p0;
+      const int base = before[l * pairs + pair];
+      for (int q = threadIdx.x; q < X.pn; q += kRangeThreads) {
+        const int v = off[q] + base;
+        cur[l * kRange + q] = v;
+        off[q] = v;
+      }
+      if (threadIdx.x == 0 && X.closes) off[X.pn] = before[l * pairs + pair + 1];
+    }
+    __syncthreads();
+    if (!X.pn) continue;
+    X.changes([&](int p, int l, int j, int link) {
+      Q.ent[atomicAdd(&cur[l * kRange + p], 1)] = make_int2(j, link);
+    });
+    __syncthreads();  // (also makes the block's entries visible to all of it)
+    for (int l = 0; l < 2; ++l)
+      for (int q = threadIdx.x; q < X.pn; q += kRangeThreads) {
+        const int first = Q.off[l * np1 + X.p0 + q], len = cur[l * kRange + q] - first;
+        if (len > kParScan) sort_entries(Q.ent + first, len);
+      }
+  }
+}
+
+// Sorts the long lists of k_par_fill (lists built by range: no keys).
 __global__ void __launch_bounds__(256) k_par_sort(ParLevel P) {
   const ParRun& Q = P.par[blockIdx.y];
   if (!P.run[blockIdx.y].pts || P.h->err) return;
@@ -391,7 +542,7 @@ __global__ void __launch_bounds__(64) k_par_write(ParLevel P) {
 
 // Scans of the same arrays of both runs in one launch.  kinds: 0 child events
 // and 1 walk segments per merge (their totals are the level's), 2 the lists'
-// lengths by key, 3 events put out per segment.
+// lengths by key, 3 events put out per segment, 4 entries per range.
 static ScanJobs jobs_of(const ParLevel& P, std::initializer_list<int> kinds) {
   ScanJobs J{};
   for (int r = 0; r < 2; ++r) {
@@ -403,6 +554,7 @@ static ScanJobs jobs_of(const ParLevel& P, std::initializer_list<int> kinds) {
         case 0: j = ScanJob{Q.ecnt, Q.eoff, Q.ctr + kCtrMerges, Q.ctr + kCtrEvents}; break;
         case 1: j = ScanJob{Q.segS, Q.segBase, Q.ctr + kCtrMerges, Q.ctr + kCtrSegments}; break;
         case 2: j = ScanJob{Q.off, Q.off, Q.ctr + kCtrKeys, nullptr}; break;
+        case 4: j = ScanJob{(int*)Q.pos, (int*)Q.pos, Q.ctr + kCtrRanges, nullptr}; break;
         default: j = ScanJob{Q.segCnt, Q.segOff, Q.ctr + kCtrSegments, nullptr}; break;
       }
     }
@@ -419,16 +571,29 @@ static int32_t chained(const ParLevel& P, const ScanJobs& J, int slot, int site,
 }
 
 template <class PT>
-int32_t parallel_level(const ParLevel& P, hipStream_t s) {
+int32_t parallel_level(const ParLevel& level, hipStream_t s) {
+  ParLevel P = level;
+  P.ranges = ranges_of(P.S.k);
   const dim3 g2(kStrideBlocks, 2), b256(256);
   hipLaunchKernelGGL(k_par_prep, g2, b256, 0, s, P);
   int32_t rc = chained(P, jobs_of(P, {0, 1}), 0, 1, 1, P.mcap + 1, s);
   if (rc) return rc;
   hipLaunchKernelGGL(k_par_enum<PT>, g2, b256, 0, s, P);
-  rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 2, s);
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_par_fill<PT>, g2, b256, 0, s, P);
-  hipLaunchKernelGGL(k_par_sort, g2, b256, 0, s, P);
+  if (lists_by_range(P.n, P.S.k)) {  // the device's number of points may say otherwise
+    // (a merge at level k has more than 2^(k-1) points)
+    const int64_t pairs = ((P.n >> (P.S.k - 1)) + 1) * P.ranges;
+    const dim3 gr((unsigned)std::min<int64_t>(pairs, 2048), 2);
+    hipLaunchKernelGGL(k_list_count, gr, dim3(kRangeThreads), 0, s, P);
+    rc = chained(P, jobs_of(P, {4}), 8, 4, 1, 2 * pairs + 1, s);
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_list_fill, gr, dim3(kRangeThreads), 0, s, P);
+  }
+  if (!lists_by_range(P.n, P.S.k) || P.device_n) {
+    rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 2, s);
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_par_fill<PT>, g2, b256, 0, s, P);
+    hipLaunchKernelGGL(k_par_sort, g2, b256, 0, s, P);
+  }
   const dim3 gw(16384, 2), b64(64);
   hipLaunchKernelGGL(k_par_walk<PT>, gw, b64, 0, s, P);
   rc = chained(P, jobs_of(P, {3}), 6, 3, 1, P.seg_cap + 1, s);

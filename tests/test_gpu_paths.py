@@ -235,3 +235,37 @@ def test_small_sort(n):
         hull.hull_sync(torch.from_numpy(p).cuda()) if n > 2 else hull.movies(
             torch.from_numpy(p).cuda(), 0, 0)
     assert e.value.code == hull.HULL_ERANGE
+
+
+# Lists built by ranges of points (calls of many points), beside lists by global
+# atomics (the same clouds one by one): blocks of one range, one point more, several
+# ranges and a ragged last one, clouds that end below the level and trailing
+# blocks between others, lists long enough to be sorted (an apex over a circle), and
+# a device-known number of points below and above the line.
+@pytest.mark.parametrize("big", [262144, 180000])
+def test_lists_by_range(big):
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    rng = np.random.default_rng(big)
+    t = np.linspace(0, 2 * np.pi, 9000, endpoint=False)
+    r = 1 << 20
+    cone = np.stack([r - rng.integers(0, 1000, 9000), r * np.cos(t), r * np.sin(t)], 1).astype(np.int32)
+    cone[17] = (-r, 3, 5)
+    parts = [workloads.sphere(rng, 4097, r), cone, workloads.sphere(rng, 8192, r), workloads.sphere(rng, 8193, r),
+             workloads.sphere(rng, 300, r), workloads.sphere(rng, big, r), workloads.cube(rng, 20000, r),
+             workloads.lattice(rng, 5000, 9), workloads.sphere(rng, 245771, r), workloads.sphere(rng, 7, r)]
+    off = np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)
+    x = torch.from_numpy(np.ascontiguousarray(np.concatenate(parts), dtype=np.int32)).cuda()
+    want = []
+    for k, p in enumerate(parts):
+        say("lists by range: cloud", k, len(p))
+        want.append(validate.canonical(hull.hull_sync(
+            torch.from_numpy(np.ascontiguousarray(p, dtype=np.int32)).cuda()).cpu().numpy()))
+    for sched in (None, hull.Schedule(0, 16, 0, -1)):
+        say("lists by range: batch", sched)
+        f, fo = hull.hull_batched_sync(x, off, schedule=sched)
+        f, fo = f.cpu().numpy(), fo.cpu().numpy()
+        for k in range(len(parts)):
+            got = validate.canonical(f[fo[k]:fo[k + 1]])
+            assert got.shape == want[k].shape and (got == want[k]).all(), (k, len(parts[k]))
