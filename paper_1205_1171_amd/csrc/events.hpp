@@ -392,6 +392,7 @@ struct ParRun {
   int2* uv0;      // per merge: the bridge at -inf
 };
 
+constexpr int kRangesFromLevel = 7;  // lists by ranges of points: from this level on
 struct ParLevel {
   RunPtrs run[2];
   ParRun par[2];

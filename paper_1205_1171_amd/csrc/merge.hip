@@ -335,6 +335,12 @@ constexpr int kPtsLdsMerges = 1024;
 // 11 3.5 / 1.9.
 constexpr int kTileFromLevel = 5;  // (one earlier for calls of few points, two for the smallest;
                                    // kTileMerges and kTilePoints: events.hpp)
+// Above the caller's lane-serial levels the parallel strategy competes with tiles too
+// where points are many and its lists are built by ranges (10,000 ragged clouds, up to
+// 1.3e8 points, lane groups up to level 10: 130.9 ms a pass with level 11 by tiles,
+// 122.5 with it by the parallel strategy, 120.4 with levels 10 and 11).  Smaller calls
+// keep tiles, one launch a level (2^20 sphere, level 11: 470 us by a tile, 616).
+constexpr int64_t kTileOpenPoints = int64_t(1) << 23;
 constexpr int kTileLevels = 11;  // kTileMaxWidth
 constexpr int kMaxLevels = 28;
 
@@ -854,7 +860,8 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
     const bool tile_fits =
         k <= opt.tile_levels && A.width <= kTileMaxWidth &&
         (int64_t)TileLds<PT>::bytes((int)A.width, tile_lanes((int)A.width, n)) + 256 <= max_lds_bytes();
-    const bool open = tile_fits && k >= opt.tile_from;  // the number of merges decides
+    // the number of merges decides
+    const bool open = tile_fits && (k >= opt.tile_from || (k > opt.serial_max && k >= kRangesFromLevel && n >= kTileOpenPoints));
     const bool few = !many_merges(bound, n);            // (of the host's bound; the device may have fewer)
     // what runs: k <= serial_max lane-serial or lane groups, above that tiles
     // where they fit, else the parallel strategy; and tiles instead of either

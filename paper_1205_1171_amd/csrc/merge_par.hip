@@ -34,6 +34,7 @@ namespace hull {
 // accesses: with 12, k_par_sort took 170 us a level on the 2^20-point sphere
 // (mean length 3, a few lists of 13-25), 6 with 32.
 constexpr int kParScan = 32;
+constexpr int kWave = 64;
 constexpr unsigned long long kStepsLost = ~0ull;  // a segment to be walked again
 
 // Lists built range by range in LDS rather than by global atomics: calls of many
@@ -41,12 +42,18 @@ constexpr unsigned long long kStepsLost = ~0ull;  // a segment to be walked agai
 // 37 G/s and write one sector each), in blocks of up to 8 ranges (every range reads
 // the child events of its whole merge).  Levels 12 to 16 of the 2^20 sphere took
 // 872, 772, 711, 668 and 644 us by atomics, 567, 475, 433, 424 and 448 by ranges; the
-// 10,000 ragged clouds of 7.3e7 points, 165 and 127 ms a pass.
-constexpr int kRange = 8192;  // points: two counts each, 64 KiB of LDS
+// 10,000 ragged clouds of 1.3e8 points, 165 and 127 ms a pass.
+constexpr int kRangeLog = 13;
+constexpr int kRange = 1 << kRangeLog;  // points: two counts each, 64 KiB of LDS
 constexpr int64_t kRangesFrom = int64_t(1) << 19;
-constexpr int kRangeThreads = 512;
-constexpr bool lists_by_range(int64_t n, int k) { return n >= kRangesFrom && k >= 12 && k <= 16; }
-static int ranges_of(int k) { return k <= 13 ? 1 : 1 << (k - 13); }
+__host__ __device__ constexpr bool lists_by_range(int64_t n, int k) {
+  return n >= kRangesFrom && k >= kRangesFromLevel && k <= kRangeLog + 3;
+}
+__host__ __device__ constexpr int ranges_of(int k) { return k <= kRangeLog ? 1 : 1 << (k - kRangeLog); }
+__host__ __device__ constexpr int range_points(int k) { return k <= kRangeLog ? 1 << k : kRange; }
+// Threads per range: about 8 points each, so that blocks of small merges are many and
+// their barriers cheap.
+static int range_threads(int k) { return std::min(std::max(range_points(k) / 8, 64), 512); }
 
 template <class PT>
 struct ParCtx {
@@ -178,11 +185,26 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
   }
   if (!ranges) GRID_STRIDE(q, keys) Q.off[q] = 0;
   if (err) return;
-  for (int64_t g = blockIdx.x; g < merges; g += gridDim.x) {  // one block per merge
-    const int2 se = P.S.merge(g);
+  if (merges <= gridDim.x) {  // one block per merge
+    if (blockIdx.x >= merges) return;
+    const int2 se = P.S.merge(blockIdx.x);
     const int64_t m = se.x + half, e = se.y;
     if (R.right_waits_in_output(m, e))
       (void)R.settle_right(m, e, R.right_len(m, e), threadIdx.x, blockDim.x);
+    return;
+  }
+  // many merges (so short ones): few have a block to move, a wave looks at 64
+  const int lane = threadIdx.x % kWave;
+  for (int64_t g0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x - lane; g0 < merges;
+       g0 += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t g = g0 + lane < merges ? g0 + lane : merges - 1;
+    const int2 se = P.S.merge(g);
+    unsigned long long todo = __ballot(g0 + lane < merges && R.right_waits_in_output(se.x + half, se.y));
+    for (; todo; todo &= todo - 1) {
+      const int q = __ffsll(todo) - 1;
+      const int64_t m = __shfl(se.x, q) + half, e = __shfl(se.y, q);
+      (void)R.settle_right(m, e, R.right_len(m, e), lane, kWave);
+    }
   }
 }
 
@@ -282,19 +304,19 @@ struct Range {
   }
   // fn(point within the range, which list, position in the child movie, link
   // after) for every link that the merge's child events change in the range
-  template <class FN>
+  template <int T, class FN>
   __device__ __forceinline__ void changes(const FN& fn) const {
     constexpr int U = 4;  // events in flight per thread
-    for (int c0 = threadIdx.x; c0 < N; c0 += U * kRangeThreads) {
+    for (int c0 = threadIdx.x; c0 < N; c0 += U * T) {
       int4 x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int c = c0 + u * kRangeThreads;
+        const int c = c0 + u * T;
         if (c < N) x[u] = *(const int4*)(c < nL ? evL + c : evR + (c - nL));
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int c = c0 + u * kRangeThreads;
+        const int c = c0 + u * T;
         if (c >= N) continue;
         const int j = c < nL ? c : c - nL, w = x[u].y & 0x7fffffff;
         const bool ins = x[u].y < 0;
@@ -313,31 +335,34 @@ struct Range {
 
 // Lengths of a range's lists, as offsets within the range, and their totals (next
 // lists of all ranges, then prev lists).
-__global__ void __launch_bounds__(kRangeThreads) k_list_count(ParLevel P) {
-  __shared__ int cnt[2 * kRange];
-  __shared__ int wsum[kRangeThreads / 64];
+template <int T>
+__global__ void __launch_bounds__(T) k_list_count(ParLevel P) {
+  extern __shared__ int range_lds[];
+  __shared__ int wsum[T / 64];
+  int* cnt = range_lds;
+  const int stride = range_points(P.S.k);
   const RunPtrs& R = P.run[blockIdx.y];
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
   const int64_t pairs = Q.ctr[kCtrRanges] / 2, merges = Q.ctr[kCtrMerges], np1 = P.S.off[P.S.H] + 1;
   int* totals = (int*)Q.pos;
-  const BlockGroup<kRangeThreads> g{wsum};
+  const BlockGroup<T> g{wsum};
   for (int64_t pair = blockIdx.x; pair < pairs; pair += gridDim.x) {
     const Range X(P, R, pair, merges);
     __syncthreads();
-    for (int q = threadIdx.x; q < 2 * kRange; q += kRangeThreads) cnt[q] = 0;
+    for (int q = threadIdx.x; q < 2 * stride; q += T) cnt[q] = 0;
     __syncthreads();
-    if (X.pn) X.changes([&](int p, int l, int, int) { atomicAdd(&cnt[l * kRange + p], 1); });
+    if (X.pn) X.template changes<T>([&](int p, int l, int, int) { atomicAdd(&cnt[l * stride + p], 1); });
     __syncthreads();
     for (int l = 0; l < 2; ++l) {
       int total = 0;
-      for (int q0 = 0; q0 < X.pn; q0 += 4 * kRangeThreads) {
+      for (int q0 = 0; q0 < X.pn; q0 += 4 * T) {
         const int q = q0 + 4 * threadIdx.x;
         int v[4], sum = 0, all;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           v[j] = sum;
-          if (q + j < X.pn) sum += cnt[l * kRange + q + j];
+          if (q + j < X.pn) sum += cnt[l * stride + q + j];
         }
         const int before = total + g.scan(sum, all);
 #pragma unroll
@@ -351,8 +376,11 @@ __global__ void __launch_bounds__(kRangeThreads) k_list_count(ParLevel P) {
 }
 
 // The lists' bounds and entries, once the totals are scanned; long lists sorted.
-__global__ void __launch_bounds__(kRangeThreads) k_list_fill(ParLevel P) {
-  __shared__ int cur[2 * kRange];
+template <int T>
+__global__ void __launch_bounds__(T) k_list_fill(ParLevel P) {
+  extern __shared__ int range_lds[];
+  int* cur = range_lds;
+  const int stride = range_points(P.S.k);
   const RunPtrs& R = P.run[blockIdx.y];
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
@@ -368,22 +396,22 @@ __global__ void __launch_bounds__(kRangeThreads) k_list_fill(ParLevel P) {
     for (int l = 0; l < 2; ++l) {
       int* off = Q.off + l * np1 + X.p0;
       const int base = before[l * pairs + pair];
-      for (int q = threadIdx.x; q < X.pn; q += kRangeThreads) {
+      for (int q = threadIdx.x; q < X.pn; q += T) {
         const int v = off[q] + base;
-        cur[l * kRange + q] = v;
+        cur[l * stride + q] = v;
         off[q] = v;
       }
       if (threadIdx.x == 0 && X.closes) off[X.pn] = before[l * pairs + pair + 1];
     }
     __syncthreads();
     if (!X.pn) continue;
-    X.changes([&](int p, int l, int j, int link) {
-      Q.ent[atomicAdd(&cur[l * kRange + p], 1)] = make_int2(j, link);
+    X.template changes<T>([&](int p, int l, int j, int link) {
+      Q.ent[atomicAdd(&cur[l * stride + p], 1)] = make_int2(j, link);
     });
     __syncthreads();  // (also makes the block's entries visible to all of it)
     for (int l = 0; l < 2; ++l)
-      for (int q = threadIdx.x; q < X.pn; q += kRangeThreads) {
-        const int first = Q.off[l * np1 + X.p0 + q], len = cur[l * kRange + q] - first;
+      for (int q = threadIdx.x; q < X.pn; q += T) {
+        const int first = Q.off[l * np1 + X.p0 + q], len = cur[l * stride + q] - first;
         if (len > kParScan) sort_entries(Q.ent + first, len);
       }
   }
@@ -582,11 +610,19 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
   if (lists_by_range(P.n, P.S.k)) {  // the device's number of points may say otherwise
     // (a merge at level k has more than 2^(k-1) points)
     const int64_t pairs = ((P.n >> (P.S.k - 1)) + 1) * P.ranges;
-    const dim3 gr((unsigned)std::min<int64_t>(pairs, 2048), 2);
-    hipLaunchKernelGGL(k_list_count, gr, dim3(kRangeThreads), 0, s, P);
+    const int T = range_threads(P.S.k);
+    const dim3 gr((unsigned)std::min<int64_t>(pairs, (int64_t)2048 * 512 / T), 2);
+    const size_t lds = 2 * sizeof(int) * range_points(P.S.k);
+#define HULL_RANGES(KERNEL)                                                            \
+  if (T == 512) hipLaunchKernelGGL(KERNEL<512>, gr, dim3(512), lds, s, P);             \
+  else if (T == 256) hipLaunchKernelGGL(KERNEL<256>, gr, dim3(256), lds, s, P);        \
+  else if (T == 128) hipLaunchKernelGGL(KERNEL<128>, gr, dim3(128), lds, s, P);        \
+  else hipLaunchKernelGGL(KERNEL<64>, gr, dim3(64), lds, s, P);
+    HULL_RANGES(k_list_count)
     rc = chained(P, jobs_of(P, {4}), 8, 4, 1, 2 * pairs + 1, s);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_list_fill, gr, dim3(kRangeThreads), 0, s, P);
+    HULL_RANGES(k_list_fill)
+#undef HULL_RANGES
   }
   if (!lists_by_range(P.n, P.S.k) || P.device_n) {
     rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 2, s);

@@ -241,9 +241,11 @@ def test_small_sort(n):
 # atomics (the same clouds one by one): blocks of one range, one point more, several
 # ranges and a ragged last one, clouds that end below the level and trailing
 # blocks between others, lists long enough to be sorted (an apex over a circle), and
-# a device-known number of points below and above the line.
+# a device-known number of points below and above the line; without tiles, also the
+# ranges shorter than the widest, of one wave and more.
 @pytest.mark.parametrize("big", [262144, 180000])
-def test_lists_by_range(big):
+@pytest.mark.parametrize("tile", [None, "0"])
+def test_lists_by_range(big, tile, monkeypatch):
     import torch
     from oracle import validate
     from paper_1205_1171_amd import hull
@@ -262,6 +264,8 @@ def test_lists_by_range(big):
         say("lists by range: cloud", k, len(p))
         want.append(validate.canonical(hull.hull_sync(
             torch.from_numpy(np.ascontiguousarray(p, dtype=np.int32)).cuda()).cpu().numpy()))
+    if tile:
+        monkeypatch.setenv("HULL_TILE_LEVELS", tile)
     for sched in (None, hull.Schedule(0, 16, 0, -1)):
         say("lists by range: batch", sched)
         f, fo = hull.hull_batched_sync(x, off, schedule=sched)
