@@ -33,9 +33,9 @@ constexpr int kWorkBins = 1024;     // child-event counts told apart when orderi
 constexpr int kCtrMerges = 0;    // merges of the level
 constexpr int kCtrEvents = 1;    // child events of the level
 constexpr int kCtrSegments = 2;  // walk segments of the level
-constexpr int kCtrKeys = 3;      // list bounds to scan (two per point and two more; 0: built by range)
+constexpr int kCtrKeys = 3;      // list bounds to scan (two per point and one more; 0: built by range)
 constexpr int kCtrSplice = 4;    // splices pending from the level before, by its parity (2 slots)
-constexpr int kCtrRanges = 6;    // twice the ranges of points whose lists are built in LDS
+constexpr int kCtrRanges = 6;    // ranges of points whose lists are built in LDS
 constexpr int kCtrSlots = 8;     // size of the region (int32 words)
 
 // Device-side status words at the head of every workspace.

@@ -15,11 +15,11 @@
 //      no classification of the child events and no ranks of events in other
 //      lists.
 // Where many points take part, steps 1 and 2 run per range of points in LDS instead
-// (k_list_count, k_list_fill).
+// (k_list_count, k_list_fill; the largest blocks: k_bin, k_bin_lists).
 // A level is nine launches.  Claiming lists by events, filling and sorting
 // 16-byte entries, a separate bridge list, survival flags and three more scans
 // took 1.70-2.25 ms a level on the 2^20-point sphere,
-// this 0.42-0.67 ms.
+// this 0.36-0.55 ms.
 #include <algorithm>
 #include <initializer_list>
 
@@ -41,7 +41,7 @@ constexpr unsigned long long kStepsLost = ~0ull;  // a segment to be walked agai
 // points, whose changes are enough to be bound by the atomics (they run at about
 // 37 G/s and write one sector each), in blocks of up to 8 ranges (every range reads
 // the child events of its whole merge).  Levels 12 to 16 of the 2^20 sphere took
-// 872, 772, 711, 668 and 644 us by atomics, 567, 475, 433, 424 and 448 by ranges; the
+// 872, 772, 711, 668 and 644 us by atomics, 551, 468, 427, 416 and 435 by ranges; the
 // 10,000 ragged clouds of 1.3e8 points, 165 and 127 ms a pass.
 constexpr int kRangeLog = 13;
 constexpr int kRange = 1 << kRangeLog;  // points: two counts each, 64 KiB of LDS
@@ -49,11 +49,25 @@ constexpr int64_t kRangesFrom = int64_t(1) << 19;
 __host__ __device__ constexpr bool lists_by_range(int64_t n, int k) {
   return n >= kRangesFrom && k >= kRangesFromLevel && k <= kRangeLog + 3;
 }
+// Above those levels the changes are first sorted into bins of kRange points (the
+// levels' walk scratch, idle until then, holds them), then a block per bin builds its
+// lists.  Levels 17 to 20 of the 2^20 sphere: 635, 623, 640 and 657 us by atomics,
+// 387, 360, 369 and 373 by bins (counting 5, placing 14, lists 23 us a level, both runs).
+constexpr int64_t kBinsMax = 4096;  // a count of each in LDS
+constexpr int kBinThreads = 512, kBinEvents = 8;
+__host__ __device__ constexpr int64_t bins_of(int64_t n) { return (n + kRange - 1) >> kRangeLog; }
+__host__ __device__ constexpr bool lists_by_bin(int64_t n, int k, bool room) {
+  return room && n >= kRangesFrom && k > kRangeLog + 3;
+}
 __host__ __device__ constexpr int ranges_of(int k) { return k <= kRangeLog ? 1 : 1 << (k - kRangeLog); }
 __host__ __device__ constexpr int range_points(int k) { return k <= kRangeLog ? 1 << k : kRange; }
 // Threads per range: about 8 points each, so that blocks of small merges are many and
 // their barriers cheap.
 static int range_threads(int k) { return std::min(std::max(range_points(k) / 8, 64), 512); }
+
+// A point's two lists lie side by side (their bounds are then one 8-byte load and the
+// word after it, their entries often one cache line).
+__device__ __forceinline__ int64_t key_of(int p, int prev) { return 2 * (int64_t)p + prev; }
 
 template <class PT>
 struct ParCtx {
@@ -64,7 +78,6 @@ struct ParCtx {
   const int2* ent;
   const int* nx0;
   const int* pv0;
-  int64_t np1;  // points + 1: prev lists start there
   int zs;
   __device__ __forceinline__ WalkEv ev(bool left, int i) const {
     const int4 x = *(const int4*)((left ? evL : evR) + i);
@@ -101,14 +114,15 @@ struct ParCtx {
     return l;
   }
   __device__ __forceinline__ int link(int p, bool nx, bool, int cursor) const {
-    const int64_t key = nx ? p : np1 + p;
+    const int64_t key = key_of(p, !nx);
     return last_before(off[key], off[key + 1], cursor, nx ? nx0[p] : pv0[p]);
   }
   __device__ __forceinline__ void links(int p, bool, int cursor, int& nx, int& pv) const {
-    const int n0 = off[p], n1 = off[p + 1], p0 = off[np1 + p], p1 = off[np1 + p + 1];
+    const int2 b = *(const int2*)(off + key_of(p, 0));
+    const int end = off[key_of(p, 2)];
     const int ln = nx0[p], lp = pv0[p];
-    nx = last_before(n0, n1, cursor, ln);
-    pv = last_before(p0, p1, cursor, lp);
+    nx = last_before(b.x, b.y, cursor, ln);
+    pv = last_before(b.y, end, cursor, lp);
   }
 };
 
@@ -123,7 +137,6 @@ __device__ __forceinline__ ParCtx<PT> ctx_of(const ParLevel& P, int r, int64_t s
   X.ent = P.par[r].ent;
   X.nx0 = R.nx0;
   X.pv0 = R.pv0;
-  X.np1 = P.S.off[P.S.H] + 1;
   X.zs = R.zs;
   return X;
 }
@@ -157,8 +170,8 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
   if (!R.pts) return;
   const int64_t merges = selected(P.S, P.sel) ? P.S.merges() : 0, half = int64_t(1) << (P.S.k - 1);
   const int64_t n = P.S.off[P.S.H];
-  const int64_t keys = merges ? 2 * (n + 1) : 0;
-  const bool ranges = lists_by_range(n, P.S.k);
+  const int64_t keys = merges ? 2 * n + 1 : 0;
+  const bool bins = lists_by_bin(n, P.S.k, P.bin_room), ranges = bins || lists_by_range(n, P.S.k);
   const bool err = P.h->err != 0;
   GRID_STRIDE(g, (int64_t)(err ? 0 : Q.ctr[kCtrSplice + ((P.S.k - 1) & 1)])) {
     const int2 b = Q.uv0[g];
@@ -169,7 +182,7 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
     if (g == 0) {
       Q.ctr[kCtrMerges] = (int)merges;
       Q.ctr[kCtrKeys] = ranges ? 0 : (int)keys;
-      Q.ctr[kCtrRanges] = ranges && !err ? (int)(2 * merges * P.ranges) : 0;
+      Q.ctr[kCtrRanges] = err || !ranges || !merges ? 0 : (int)(bins ? bins_of(n) : merges * P.ranges);
       Q.ctr[kCtrSplice + (P.S.k & 1)] = (int)merges;
     }
     if (g < merges && !err) {
@@ -184,6 +197,7 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
     }
   }
   if (!ranges) GRID_STRIDE(q, keys) Q.off[q] = 0;
+  if (bins) GRID_STRIDE(q, bins_of(n)) ((int*)Q.pos)[q] = 0;
   if (err) return;
   if (merges <= gridDim.x) {  // one block per merge
     if (blockIdx.x >= merges) return;
@@ -217,7 +231,7 @@ __global__ void __launch_bounds__(256) k_par_enum(ParLevel P) {
   if (!R.pts) return;
   const int merges = Q.ctr[kCtrMerges], E = Q.ctr[kCtrEvents], Sg = Q.ctr[kCtrSegments];
   if (!merges) return;
-  const int64_t half = int64_t(1) << (P.S.k - 1), np1 = P.S.off[P.S.H] + 1;
+  const int64_t half = int64_t(1) << (P.S.k - 1);
   const int events = Q.ctr[kCtrKeys] ? E : 0;  // (else the lists are built by range)
   GRID_STRIDE(c, (int64_t)events + Sg) {
     const bool seg = c >= events;
@@ -237,11 +251,11 @@ __global__ void __launch_bounds__(256) k_par_enum(ParLevel P) {
     const WalkEv x = X.ev(i < nL, i < nL ? i : i - nL);
     Q.cmerge[c] = g;
     int4 at = make_int4(0, 0, 0, 0);
-    at.x = atomicAdd(&Q.off[x.a], 1);
-    at.y = atomicAdd(&Q.off[np1 + x.b], 1);
+    at.x = atomicAdd(&Q.off[key_of(x.a, 0)], 1);
+    at.y = atomicAdd(&Q.off[key_of(x.b, 1)], 1);
     if (x.kind) {
-      at.z = atomicAdd(&Q.off[x.w], 1);
-      at.w = atomicAdd(&Q.off[np1 + x.w], 1);
+      at.z = atomicAdd(&Q.off[key_of(x.w, 0)], 1);
+      at.w = atomicAdd(&Q.off[key_of(x.w, 1)], 1);
     }
     Q.pos[c] = at;
   }
@@ -255,9 +269,8 @@ __global__ void __launch_bounds__(256) k_par_fill(ParLevel P) {
   if (!R.pts) return;
   const int E = Q.ctr[kCtrEvents], keys = Q.ctr[kCtrKeys];
   if (E <= 0 || keys <= 0) return;
-  const int64_t half = int64_t(1) << (P.S.k - 1), np1 = P.S.off[P.S.H] + 1;
-  // capacity: 6 entries per point (the last bound is the entries of all but
-  // the last key, whose list is empty)
+  const int64_t half = int64_t(1) << (P.S.k - 1);
+  // capacity: 6 entries per point (the last bound is all entries)
   if (Q.off[keys - 1] > 6 * P.n) {
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
     return;
@@ -271,11 +284,11 @@ __global__ void __launch_bounds__(256) k_par_fill(ParLevel P) {
     const int j = i < nL ? i : i - nL;
     const WalkEv x = X.ev(i < nL, j);
     const int4 at = Q.pos[c];
-    Q.ent[Q.off[x.a] + at.x] = make_int2(j, x.kind ? x.w : x.b);
-    Q.ent[Q.off[np1 + x.b] + at.y] = make_int2(j, x.kind ? x.w : x.a);
+    Q.ent[Q.off[key_of(x.a, 0)] + at.x] = make_int2(j, x.kind ? x.w : x.b);
+    Q.ent[Q.off[key_of(x.b, 1)] + at.y] = make_int2(j, x.kind ? x.w : x.a);
     if (x.kind) {
-      Q.ent[Q.off[x.w] + at.z] = make_int2(j, x.b);
-      Q.ent[Q.off[np1 + x.w] + at.w] = make_int2(j, x.a);
+      Q.ent[Q.off[key_of(x.w, 0)] + at.z] = make_int2(j, x.b);
+      Q.ent[Q.off[key_of(x.w, 1)] + at.w] = make_int2(j, x.a);
     }
   }
 }
@@ -333,45 +346,58 @@ struct Range {
   }
 };
 
-// Lengths of a range's lists, as offsets within the range, and their totals (next
-// lists of all ranges, then prev lists).
+// Offsets of the lists of counted lengths in LDS (keys of them), in order from `first`
+// on; returns their total.
+template <int T, class G>
+__device__ __forceinline__ int lists_scan(const G& g, const int* cnt, int keys, int* off, int first) {
+  int total = 0;
+  for (int q0 = 0; q0 < keys; q0 += 4 * T) {
+    const int q = q0 + 4 * threadIdx.x;
+    int v[4], sum = 0, all;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] = sum;
+      if (q + j < keys) sum += cnt[q + j];
+    }
+    const int before = first + total + g.scan(sum, all);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (q + j < keys) off[q + j] = before + v[j];
+    total += all;
+  }
+  return total;
+}
+// Sorts the long lists; cur: where each ends.
+template <int T>
+__device__ __forceinline__ void sort_lists(int2* ent, const int* off, const int* cur, int keys) {
+  for (int q = threadIdx.x; q < keys; q += T) {
+    const int first = off[q], len = cur[q] - first;
+    if (len > kParScan) sort_entries(ent + first, len);
+  }
+}
+
+// Lengths of a range's lists, as offsets within the range, and their total.
 template <int T>
 __global__ void __launch_bounds__(T) k_list_count(ParLevel P) {
   extern __shared__ int range_lds[];
   __shared__ int wsum[T / 64];
   int* cnt = range_lds;
-  const int stride = range_points(P.S.k);
   const RunPtrs& R = P.run[blockIdx.y];
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
-  const int64_t pairs = Q.ctr[kCtrRanges] / 2, merges = Q.ctr[kCtrMerges], np1 = P.S.off[P.S.H] + 1;
+  const int64_t pairs = Q.ctr[kCtrRanges], merges = Q.ctr[kCtrMerges];
   int* totals = (int*)Q.pos;
   const BlockGroup<T> g{wsum};
   for (int64_t pair = blockIdx.x; pair < pairs; pair += gridDim.x) {
     const Range X(P, R, pair, merges);
+    const int keys = 2 * X.pn;
     __syncthreads();
-    for (int q = threadIdx.x; q < 2 * stride; q += T) cnt[q] = 0;
+    for (int q = threadIdx.x; q < keys; q += T) cnt[q] = 0;
     __syncthreads();
-    if (X.pn) X.template changes<T>([&](int p, int l, int, int) { atomicAdd(&cnt[l * stride + p], 1); });
+    if (X.pn) X.template changes<T>([&](int p, int l, int, int) { atomicAdd(&cnt[2 * p + l], 1); });
     __syncthreads();
-    for (int l = 0; l < 2; ++l) {
-      int total = 0;
-      for (int q0 = 0; q0 < X.pn; q0 += 4 * T) {
-        const int q = q0 + 4 * threadIdx.x;
-        int v[4], sum = 0, all;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          v[j] = sum;
-          if (q + j < X.pn) sum += cnt[l * stride + q + j];
-        }
-        const int before = total + g.scan(sum, all);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (q + j < X.pn) Q.off[l * np1 + X.p0 + q + j] = before + v[j];
-        total += all;
-      }
-      if (threadIdx.x == 0) totals[l * pairs + pair] = total;
-    }
+    const int total = lists_scan<T>(g, cnt, keys, Q.off + key_of((int)X.p0, 0), 0);
+    if (threadIdx.x == 0) totals[pair] = total;
   }
 }
 
@@ -380,40 +406,143 @@ template <int T>
 __global__ void __launch_bounds__(T) k_list_fill(ParLevel P) {
   extern __shared__ int range_lds[];
   int* cur = range_lds;
-  const int stride = range_points(P.S.k);
   const RunPtrs& R = P.run[blockIdx.y];
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
-  const int64_t pairs = Q.ctr[kCtrRanges] / 2, merges = Q.ctr[kCtrMerges], np1 = P.S.off[P.S.H] + 1;
+  const int64_t pairs = Q.ctr[kCtrRanges], merges = Q.ctr[kCtrMerges];
   const int* before = (const int*)Q.pos;
-  if (pairs > 0 && before[2 * pairs] > 6 * P.n) {
+  if (pairs > 0 && before[pairs] > 6 * P.n) {
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
     return;
   }
   for (int64_t pair = blockIdx.x; pair < pairs; pair += gridDim.x) {
     const Range X(P, R, pair, merges);
+    int* off = Q.off + key_of((int)X.p0, 0);
+    const int keys = 2 * X.pn, base = before[pair];
     __syncthreads();
-    for (int l = 0; l < 2; ++l) {
-      int* off = Q.off + l * np1 + X.p0;
-      const int base = before[l * pairs + pair];
-      for (int q = threadIdx.x; q < X.pn; q += T) {
-        const int v = off[q] + base;
-        cur[l * stride + q] = v;
-        off[q] = v;
-      }
-      if (threadIdx.x == 0 && X.closes) off[X.pn] = before[l * pairs + pair + 1];
+    for (int q = threadIdx.x; q < keys; q += T) {
+      const int v = off[q] + base;
+      cur[q] = v;
+      off[q] = v;
     }
+    if (threadIdx.x == 0 && X.closes) off[keys] = before[pair + 1];
     __syncthreads();
     if (!X.pn) continue;
     X.template changes<T>([&](int p, int l, int j, int link) {
-      Q.ent[atomicAdd(&cur[l * stride + p], 1)] = make_int2(j, link);
+      Q.ent[atomicAdd(&cur[2 * p + l], 1)] = make_int2(j, link);
     });
     __syncthreads();  // (also makes the block's entries visible to all of it)
-    for (int l = 0; l < 2; ++l)
-      for (int q = threadIdx.x; q < X.pn; q += T) {
-        const int first = Q.off[l * np1 + X.p0 + q], len = cur[l * stride + q] - first;
-        if (len > kParScan) sort_entries(Q.ent + first, len);
-      }
+    sort_lists<T>(Q.ent, off, cur, keys);
+  }
+}
+
+// A link change on its way to its bin: the list (2 x point within the bin + prev),
+// the event's position in its child movie and the link after it.
+struct BinRecords {
+  int2* rec;
+  unsigned short* list;
+  __device__ __forceinline__ BinRecords(const ParLevel& P, const ParRun& Q)
+      : rec((int2*)Q.segKeep), list((unsigned short*)((int2*)Q.segKeep + 6 * P.n)) {}
+};
+
+// fn(point, prev, position, link) for the changes of the events of a block's chunk.
+template <class FN>
+__device__ __forceinline__ void bin_changes(const int4* x, const int* j, const FN& fn) {
+#pragma unroll
+  for (int u = 0; u < kBinEvents; ++u) {
+    if (j[u] < 0) continue;
+    const int w = x[u].y & 0x7fffffff;
+    const bool ins = x[u].y < 0;
+    fn(x[u].x, 0, j[u], ins ? w : x[u].z);
+    fn(x[u].z, 1, j[u], ins ? w : x[u].x);
+    if (ins) {
+      fn(w, 0, j[u], x[u].z);
+      fn(w, 1, j[u], x[u].x);
+    }
+  }
+}
+
+// The bins' counts (PLACE: their records, at the counts scanned), chunk by chunk of
+// the level's child events.
+template <bool PLACE>
+__global__ void __launch_bounds__(kBinThreads) k_bin(ParLevel P) {
+  extern __shared__ int range_lds[];
+  int* cnt = range_lds;
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!R.pts) return;
+  const int bins = Q.ctr[kCtrRanges], merges = Q.ctr[kCtrMerges], E = Q.ctr[kCtrEvents];
+  int* total = (int*)Q.pos;
+  if (!bins || (PLACE && total[bins] > 6 * P.n)) return;  // (k_bin_lists reports it)
+  const BinRecords B(P, Q);
+  constexpr int kChunk = kBinThreads * kBinEvents;
+  for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < E; c0 += (int64_t)gridDim.x * kChunk) {
+    __syncthreads();
+    for (int q = threadIdx.x; q < bins; q += kBinThreads) cnt[q] = 0;
+    __syncthreads();
+    int4 x[kBinEvents];
+    int j[kBinEvents];
+#pragma unroll
+    for (int u = 0; u < kBinEvents; ++u) {
+      const int64_t c = c0 + u * kBinThreads + threadIdx.x;
+      j[u] = -1;
+      if (c >= E) continue;
+      const int g = find_owner(Q.eoff, merges, c);
+      const int64_t s = P.S.merge(g).x, m = s + (int64_t(1) << (P.S.k - 1));
+      const int nL = R.left_len(s), i = (int)(c - Q.eoff[g]);
+      const bool left = i < nL;
+      j[u] = left ? i : i - nL;
+      x[u] = *(const int4*)((left ? R.left_ev(s) : R.ev[(P.S.k - 1) & 1] + 2 * m) + j[u]);
+    }
+    bin_changes(x, j, [&](int p, int, int, int) { atomicAdd(&cnt[p >> kRangeLog], 1); });
+    __syncthreads();
+    for (int q = threadIdx.x; q < bins; q += kBinThreads)
+      if (cnt[q]) cnt[q] = atomicAdd(&total[q], cnt[q]);
+    if (!PLACE) continue;
+    __syncthreads();
+    bin_changes(x, j, [&](int p, int prev, int pos, int link) {
+      const int at = atomicAdd(&cnt[p >> kRangeLog], 1);
+      B.rec[at] = make_int2(pos, link);
+      B.list[at] = (unsigned short)(2 * (p & (kRange - 1)) + prev);
+    });
+  }
+}
+
+// The lists of a bin's points: counted, their bounds, filled, the long ones sorted.
+template <int T>
+__global__ void __launch_bounds__(T) k_bin_lists(ParLevel P) {
+  extern __shared__ int range_lds[];
+  __shared__ int wsum[T / 64];
+  int* cnt = range_lds;
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!P.run[blockIdx.y].pts) return;
+  const int bins = Q.ctr[kCtrRanges];
+  const int* ends = (const int*)Q.pos;  // where k_bin left its cursors
+  if (bins && ends[bins] > 6 * P.n) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
+    return;
+  }
+  const int64_t n = P.S.off[P.S.H];
+  const BinRecords B(P, Q);
+  const BlockGroup<T> g{wsum};
+  for (int b = blockIdx.x; b < bins; b += gridDim.x) {
+    const int first = b ? ends[b - 1] : 0, end = ends[b];
+    const int64_t p0 = (int64_t)b << kRangeLog;
+    const int keys = 2 * (int)(n - p0 < kRange ? n - p0 : kRange);
+    int* off = Q.off + key_of((int)p0, 0);
+    __syncthreads();
+    for (int q = threadIdx.x; q < keys; q += T) cnt[q] = 0;
+    __syncthreads();
+    for (int q = first + threadIdx.x; q < end; q += T) atomicAdd(&cnt[B.list[q]], 1);
+    __syncthreads();
+    (void)lists_scan<T>(g, cnt, keys, off, first);
+    if (threadIdx.x == 0 && b + 1 == bins) off[keys] = end;
+    __syncthreads();
+    for (int q = threadIdx.x; q < keys; q += T) cnt[q] = off[q];
+    __syncthreads();
+    for (int q = first + threadIdx.x; q < end; q += T) Q.ent[atomicAdd(&cnt[B.list[q]], 1)] = B.rec[q];
+    __syncthreads();
+    sort_lists<T>(Q.ent, off, cnt, keys);
   }
 }
 
@@ -570,7 +699,7 @@ __global__ void __launch_bounds__(64) k_par_write(ParLevel P) {
 
 // Scans of the same arrays of both runs in one launch.  kinds: 0 child events
 // and 1 walk segments per merge (their totals are the level's), 2 the lists'
-// lengths by key, 3 events put out per segment, 4 entries per range.
+// lengths by key, 3 events put out per segment, 4 entries per range or bin.
 static ScanJobs jobs_of(const ParLevel& P, std::initializer_list<int> kinds) {
   ScanJobs J{};
   for (int r = 0; r < 2; ++r) {
@@ -602,6 +731,9 @@ template <class PT>
 int32_t parallel_level(const ParLevel& level, hipStream_t s) {
   ParLevel P = level;
   P.ranges = ranges_of(P.S.k);
+  // records of the bins: 8 + 2 bytes each, up to 6 per point
+  P.bin_room = bins_of(P.n) <= kBinsMax &&
+               (P.seg_cap + 1) * kSegKeep * (int64_t)sizeof(Event) >= 60 * P.n;
   const dim3 g2(kStrideBlocks, 2), b256(256);
   hipLaunchKernelGGL(k_par_prep, g2, b256, 0, s, P);
   int32_t rc = chained(P, jobs_of(P, {0, 1}), 0, 1, 1, P.mcap + 1, s);
@@ -619,13 +751,24 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
   else if (T == 128) hipLaunchKernelGGL(KERNEL<128>, gr, dim3(128), lds, s, P);        \
   else hipLaunchKernelGGL(KERNEL<64>, gr, dim3(64), lds, s, P);
     HULL_RANGES(k_list_count)
-    rc = chained(P, jobs_of(P, {4}), 8, 4, 1, 2 * pairs + 1, s);
+    rc = chained(P, jobs_of(P, {4}), 8, 4, 1, pairs + 1, s);
     if (rc) return rc;
     HULL_RANGES(k_list_fill)
 #undef HULL_RANGES
   }
-  if (!lists_by_range(P.n, P.S.k) || P.device_n) {
-    rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 2, s);
+  const bool bins = lists_by_bin(P.n, P.S.k, P.bin_room);
+  if (bins) {
+    const int64_t nb = bins_of(P.n);
+    const size_t lds = nb * sizeof(int);
+    const dim3 gb((unsigned)std::min<int64_t>((2 * P.n) / (kBinThreads * kBinEvents) + 1, 2048), 2);
+    hipLaunchKernelGGL(k_bin<false>, gb, dim3(kBinThreads), lds, s, P);
+    rc = chained(P, jobs_of(P, {4}), 8, 4, 1, nb + 1, s);
+    if (rc) return rc;
+    hipLaunchKernelGGL(k_bin<true>, gb, dim3(kBinThreads), lds, s, P);
+    hipLaunchKernelGGL(k_bin_lists<1024>, dim3((unsigned)nb, 2), dim3(1024), 2 * sizeof(int) * kRange, s, P);
+  }
+  if (!(bins || lists_by_range(P.n, P.S.k)) || P.device_n) {
+    rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 1, s);
     if (rc) return rc;
     hipLaunchKernelGGL(k_par_fill<PT>, g2, b256, 0, s, P);
     hipLaunchKernelGGL(k_par_sort, g2, b256, 0, s, P);

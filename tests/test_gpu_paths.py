@@ -237,7 +237,7 @@ def test_small_sort(n):
     assert e.value.code == hull.HULL_ERANGE
 
 
-# Lists built by ranges of points (calls of many points), beside lists by global
+# Lists built by ranges or bins of points (calls of many points), beside lists by global
 # atomics (the same clouds one by one): blocks of one range, one point more, several
 # ranges and a ragged last one, clouds that end below the level and trailing
 # blocks between others, lists long enough to be sorted (an apex over a circle), and
@@ -266,7 +266,8 @@ def test_lists_by_range(big, tile, monkeypatch):
             torch.from_numpy(np.ascontiguousarray(p, dtype=np.int32)).cuda()).cpu().numpy()))
     if tile:
         monkeypatch.setenv("HULL_TILE_LEVELS", tile)
-    for sched in (None, hull.Schedule(0, 16, 0, -1)):
+    # (segments of 32 events leave no scratch for the bins)
+    for sched in (None, hull.Schedule(0, 16, 0, -1), hull.Schedule(0, 32, 0, -1)):
         say("lists by range: batch", sched)
         f, fo = hull.hull_batched_sync(x, off, schedule=sched)
         f, fo = f.cpu().numpy(), fo.cpu().numpy()
