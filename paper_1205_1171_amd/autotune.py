@@ -3,7 +3,7 @@
 The merge schedule of hull_full_batched -- how many bottom levels run one
 lane per merge, from which of those levels a merge runs on a group of lanes
 (and how many at most, as the groups grow by level), and how many child
-events each walk segment of the parallel levels takes -- changes nothing in
+events each walk segment of the levels above takes -- changes nothing in
 the result, only the time.  The tuner
 times a grid of schedules on the caller's own batch (HIP events on the
 current stream, the same kernels the call would run) and keeps the fastest
@@ -19,9 +19,9 @@ from . import hull
 HERE = os.path.dirname(os.path.abspath(__file__))
 CACHE = os.path.join(HERE, "tuned_schedules.json")
 
-SERIAL_LEVELS = (9, 10, 11, 12, 13, 14, 15, 99)
-WALK_SEGMENTS = (4, 8, 16, 32)
-WAVE_LEVELS = (-1, 5, 6, 7, 8, 9)  # -1: no lane groups
+SERIAL_LEVELS = (4, 5, 7, 8, 9, 10, 11, 12, 99)
+WALK_SEGMENTS = (4, 8, 12, 16)
+WAVE_LEVELS = (-1, 6, 7, 8, 9)  # -1: no lane groups
 WAVE_LANES = 8
 WAVE_LANES_MAX = (8, 64)  # lanes per merge stay at 8, or double per level up to 64
 
