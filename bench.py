@@ -1,25 +1,17 @@
 """Throughput of the MI355X kinetic 3-d hull.
 
-One step = one hull_full call (range check, radix sort by x, every merge
-level of the lower and upper runs, face extraction) on the n = 2^24 workload
+One step = one hull_full call (range check, interior filter, radix sort by x,
+every merge level of the lower and upper runs, face extraction) on the n = 2^24 workload
 (99% Gaussian, 1% sphere), inputs resident in HBM.  Prints one JSON line:
 value = Mpoints/s = n / (time per step).
 
 Also reported on the same line:
-  roofline        the merge kernel with the largest share of the step (the
-                  lane-serial k_merge_level_lk with its links in LDS, or
-                  k_merge_level, the lane-group k_merge_wave or the
-                  LDS-staged k_merge_level_lds, whichever takes the most
-                  time over its levels): algorithmic bytes per launch (from
-                  the oracle's per-level counters: 4 B per event read, 4 B
-                  per event written, 28 B per point touched) over its average
-                  launch time, measured with HIP events recorded around each
-                  of its launches on the library's stream in the timed steps,
-                  and the HBM traffic per launch that rocprofv3's FETCH_SIZE
-                  and WRITE_SIZE counters read for it (profiles/, while the
-                  merge sources are the ones profiled);
-  levels          the same figure for every merge level (the parallel levels
-                  are several kernels each, timed as a whole);
+  roofline        the whole call against HBM: its points read once and its faces
+                  written once over the step's time (most points leave as
+                  interior before the merges, so per-level counts of events
+                  over all points say nothing about the levels' kernels);
+  levels          ms of every merge level (one kernel or, for the parallel
+                  strategy, several);
   other_single_hulls  Mpoints/s and bit-exact flags on n = 4096 and the
                   n = 2^20 sphere and ball;
   delaunay        2-d Delaunay by lifting (lower hull of (x, y, x^2 + y^2)) on
@@ -248,58 +240,14 @@ def single(args, hull, workloads):
     ev.close()
 
     adj_ms = adjacency_ms(hull, faces[:F])
-    roofline = levels = None
-    S = min(sched.serial_levels, L)
-    KL = min(sched.fused_levels, S)  # lowest levels: the LDS-staged kernel
-    W = sched.wave_from if sched.wave_from > 0 else L + 1  # first lane-group level
-    lds_links = os.environ.get("HULL_LDS_LINKS", "1") != "0"
-
-    def kernel_of(k):  # k: 1-based level
-        if k > S:
-            return "parallel strategy (k_par_* kernels, device scans)"
-        if k <= KL:
-            return "k_merge_level_lds"
-        if k >= W:
-            return "k_merge_wave"
-        # lane-serial blocks of up to 128 points keep their links in LDS
-        return "k_merge_level_lk" if lds_links and k <= 7 else "k_merge_level"
-
-    if golden is not None:
-        stats = np.array(golden["level_stats_lower"]) + np.array(golden["level_stats_upper"])
-        Bk = 4.0 * stats[:, 0] + 4.0 * stats[:, 1] + 28.0 * stats[:, 2]  # bytes per level
-        levels = [{"level": k + 1, "kernel": kernel_of(k + 1),
-                   "ms": round(float(lvl[k]), 4), "algorithmic_bytes": float(Bk[k]),
-                   "GBps": round(float(Bk[k]) / (lvl[k] / 1e3) / 1e9, 2),
-                   "frac": round(float(Bk[k]) / (lvl[k] / 1e3) / 1e9 / HBM_PEAK_GBS, 6)}
-                  for k in range(L)]
-        # the dominant kernel: the merge kernel with the most time in the step
-        groups = {}
-        for k in range(L):
-            kn = kernel_of(k + 1)
-            if not kn.startswith("parallel"):
-                groups.setdefault(kn, []).append(k)
-        if groups:
-            kern, ks = max(groups.items(), key=lambda t: float(lvl[t[1]].sum()))
-            per_launch = float(Bk[ks].sum()) / len(ks)
-            avg_ms = float(lvl[ks].mean())
-            achieved = per_launch / (avg_ms / 1e3) / 1e9
-            traffic = None
-            tpath = os.path.join(ROOT, "profiles", f"{kern}_{args.workload}_traffic.json")
-            if os.path.exists(tpath):
-                tr = json.load(open(tpath))
-                src = b"".join(open(os.path.join(ROOT, "paper_1205_1171_amd", "csrc", f), "rb").read()
-                               for f in ("merge.hip", "merge_wave.hpp", "events.hpp",
-                                         "predicates.hpp"))
-                if (tr.get("source_sha256") == hashlib.sha256(src).hexdigest()
-                        and tr.get("levels") == [ks[0] + 1, ks[-1] + 1]):
-                    traffic = tr.get("hbm_bytes_per_launch")
-            roofline = {"bound": "hbm", "achieved": round(achieved, 3), "peak": HBM_PEAK_GBS,
-                        "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 6),
-                        "traffic": traffic, "kernel": kern,
-                        "levels": [ks[0] + 1, ks[-1] + 1], "launches_per_step": len(ks),
-                        "avg_launch_ms": round(avg_ms, 4),
-                        "algorithmic_bytes_per_launch": per_launch,
-                        "all_levels_GBps": round(float(Bk.sum()) / (lvl.sum() / 1e3) / 1e9, 3)}
+    # what the whole call cannot do without: every point read once, every face
+    # written once
+    need = 12.0 * n + 12.0 * F
+    achieved = need / (ms / 1e3) / 1e9
+    roofline = {"bound": "hbm", "achieved": round(achieved, 3), "peak": HBM_PEAK_GBS,
+                "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 6), "traffic": None,
+                "kernel": "hull_full", "algorithmic_bytes_per_step": need}
+    levels = [{"level": k + 1, "ms": round(float(lvl[k]), 4)} for k in range(L)]
 
     out = {
         "metric": "Mpoints/s per hull (n=2^24)",
@@ -326,10 +274,10 @@ def single(args, hull, workloads):
         "bit_exact": bit_exact,
         "phase_ms": {"sort": round(sort_ms, 4), "merge_levels": [round(v, 4) for v in lvl],
                      "extract": round(extract_ms, 4)},
-        # sort: range pass 12 B/pt, 3 radix passes of 16 B/pt (key + index read
-        # and written), gather 12 B/pt read + 16 B/pt written (22-bit keys)
-        "sort": {"ms": round(sort_ms, 4), "algorithmic_bytes": 88.0 * n,
-                 "GBps": round(88.0 * n / (sort_ms / 1e3) / 1e9, 1)},
+        # before the merges: extent and interior filter over all points (12 B each,
+        # read once per pass; the bytes are one read), then the sort of those left
+        "sort": {"ms": round(sort_ms, 4), "algorithmic_bytes": 12.0 * n,
+                 "GBps": round(12.0 * n / (sort_ms / 1e3) / 1e9, 1)},
         "roofline": roofline,
         "levels": levels,
         "adjacency": {"faces": F, "ms": round(adj_ms, 4),
