@@ -145,8 +145,14 @@ int32_t hull_full_noalloc(const int32_t* d_xyz, int64_t n, int32_t* d_faces, int
  * takes the library default):
  *   serial_levels  merge levels 1..serial_levels run one lane per merge (the
  *                  paper's kernel, Sec. 3); the levels above split each merge
- *                  into time segments walked in parallel (default 10)
- *   walk_segment   child events per walk segment, >= 4 (default 4)
+ *                  into time segments walked in parallel, in LDS up to level
+ *                  11 (environment HULL_TILE_LEVELS) or, in calls of 2^23
+ *                  points and more whose levels hold many merges, from level 7
+ *                  on in global memory.  Default: 10, but levels from 5 on (4
+ *                  up to 2^17 points, 3 up to 2^13) are split too where a
+ *                  level holds few merges
+ *   walk_segment   child events per walk segment, >= 4 (default 4; segments
+ *                  in LDS then take 2 to 4 by the size of block and call)
  *   fused_levels   ignored on input (pass 0 or -1); hull_schedule_defaults
  *                  writes the number of LDS-staged lowest levels here
  *   wave_from      lane-serial levels from this one on run one merge per
@@ -190,7 +196,7 @@ int32_t hull_schedule_defaults(hull_schedule_t* out);
 
 /* Bytes of device workspace for hull_full_batched over H hulls of
  * total_points points in all (host, synchronous).  total_points is at most
- * 2^28 (whose workspace, about 924 bytes per point, fits one GPU's memory);
+ * 2^28 (whose workspace, about 672 bytes per point, fits one GPU's memory);
  * more returns HULL_EINVAL, as does hull_full_batched. */
 int32_t hull_workspace_bytes_batched(int64_t total_points, int64_t H, size_t* bytes);
 

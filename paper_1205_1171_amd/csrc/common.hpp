@@ -10,7 +10,7 @@ namespace hull {
 
 constexpr int kNil = -1;
 constexpr int64_t kMaxN = int64_t(1) << 26;      // points of one hull
-// points of a batch: the workspace of 2^28 points (about 924 bytes per
+// points of a batch: the workspace of 2^28 points (about 672 bytes per
 // point) still fits the 288 GB of one MI355X
 constexpr int64_t kMaxTotal = int64_t(1) << 28;
 constexpr int32_t kMaxCoord = 1 << 29;

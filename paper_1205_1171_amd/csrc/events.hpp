@@ -361,19 +361,10 @@ __device__ __forceinline__ int find_owner(const int* off, int count, int64_t x) 
   return lo;
 }
 
-__device__ __forceinline__ Cand cand_of(const Event* ev, int64_t q) {
-  const Event E = ev[q];
-  Cand c;
-  c.t = Tri{E.a, E.w(), E.b};
-  c.kind = E.kind();
-  c.st = (double)E.t;
-  return c;
-}
-
 // Workspace of one run for the parallel strategy (merge_par.hip).
 struct ParRun {
-  int* off;       // [2 (n + 1)] bounds of the link-change lists: next links of point p at
-                  // p, prev links at n + 1 + p
+  int* off;       // [2n + 1] bounds of the link-change lists: next links of point p at 2p,
+                  // prev links at 2p + 1
   int2* ent;      // list entries: (position in the child movie, the link after it)
   int4* pos;      // per child event: its places in the lists of a, b, w, w
   int* cmerge;    // per child event: its merge
