@@ -392,7 +392,7 @@ struct ParLevel {
   int64_t n;        // bound on the points
   int sel;
   bool device_n;    // n is a bound, the device knows the number
-  bool bin_room;    // the segments' scratch holds the changes of a level by bins
+  int bin_log;      // log of the bins' points (0: no lists by bins)
   int ranges;       // ranges of points per merge (lists built in LDS)
   int seg_events;   // child events per walk segment
   int64_t seg_cap;  // bound on the walk segments of a level

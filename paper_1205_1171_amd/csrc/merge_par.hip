@@ -49,15 +49,26 @@ constexpr int64_t kRangesFrom = int64_t(1) << 19;
 __host__ __device__ constexpr bool lists_by_range(int64_t n, int k) {
   return n >= kRangesFrom && k >= kRangesFromLevel && k <= kRangeLog + 3;
 }
-// Above those levels the changes are first sorted into bins of kRange points (the
+// Above those levels, and at every level of calls of fewer points (whose ranges would
+// be too few blocks), the changes are first sorted into bins of points (the
 // levels' walk scratch, idle until then, holds them), then a block per bin builds its
 // lists.  Levels 17 to 20 of the 2^20 sphere: 635, 623, 640 and 657 us by atomics,
 // 387, 360, 369 and 373 by bins (counting 5, placing 14, lists 23 us a level, both runs).
+// Delaunay of 262,139 points (levels 11 to 18, one run): 622 + 157 us a pass by atomics
+// (k_par_enum, k_par_fill), 163 + 491 by bins with the segment table; 5.47 and 5.27 ms.
+constexpr int64_t kBinsFrom = int64_t(1) << 17;
 constexpr int64_t kBinsMax = 4096;  // a count of each in LDS
 constexpr int kBinThreads = 512, kBinEvents = 8;
-__host__ __device__ constexpr int64_t bins_of(int64_t n) { return (n + kRange - 1) >> kRangeLog; }
-__host__ __device__ constexpr bool lists_by_bin(int64_t n, int k, bool room) {
-  return room && n >= kRangesFrom && k > kRangeLog + 3;
+__host__ __device__ constexpr int64_t bins_of(int64_t n, int log) { return (n + (1 << log) - 1) >> log; }
+// The bins' size (log), 0 for none: the host's rule.  The device builds lists by bins
+// where this gives a size and it counts kBinsFrom points.
+static int bin_log(const ParLevel& P) {
+  const int log = P.n >= kRangesFrom ? kRangeLog : kRangeLog - 2, k = P.S.k;
+  // records of the bins: 8 + 2 bytes each, up to 6 per point
+  const bool room = bins_of(P.n, log) <= kBinsMax &&
+                    (P.seg_cap + 1) * kSegKeep * (int64_t)sizeof(Event) >= 60 * P.n;
+  const bool on = P.n >= kRangesFrom ? k > kRangeLog + 3 : P.n >= kBinsFrom && k >= kRangesFromLevel;
+  return room && on ? log : 0;
 }
 __host__ __device__ constexpr int ranges_of(int k) { return k <= kRangeLog ? 1 : 1 << (k - kRangeLog); }
 __host__ __device__ constexpr int range_points(int k) { return k <= kRangeLog ? 1 << k : kRange; }
@@ -171,7 +182,7 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
   const int64_t merges = selected(P.S, P.sel) ? P.S.merges() : 0, half = int64_t(1) << (P.S.k - 1);
   const int64_t n = P.S.off[P.S.H];
   const int64_t keys = merges ? 2 * n + 1 : 0;
-  const bool bins = lists_by_bin(n, P.S.k, P.bin_room), ranges = bins || lists_by_range(n, P.S.k);
+  const bool bins = P.bin_log && n >= kBinsFrom, ranges = bins || lists_by_range(n, P.S.k);
   const bool err = P.h->err != 0;
   GRID_STRIDE(g, (int64_t)(err ? 0 : Q.ctr[kCtrSplice + ((P.S.k - 1) & 1)])) {
     const int2 b = Q.uv0[g];
@@ -182,7 +193,7 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
     if (g == 0) {
       Q.ctr[kCtrMerges] = (int)merges;
       Q.ctr[kCtrKeys] = ranges ? 0 : (int)keys;
-      Q.ctr[kCtrRanges] = err || !ranges || !merges ? 0 : (int)(bins ? bins_of(n) : merges * P.ranges);
+      Q.ctr[kCtrRanges] = err || !ranges || !merges ? 0 : (int)(bins ? bins_of(n, P.bin_log) : merges * P.ranges);
       Q.ctr[kCtrSplice + (P.S.k & 1)] = (int)merges;
     }
     if (g < merges && !err) {
@@ -197,7 +208,7 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
     }
   }
   if (!ranges) GRID_STRIDE(q, keys) Q.off[q] = 0;
-  if (bins) GRID_STRIDE(q, bins_of(n)) ((int*)Q.pos)[q] = 0;
+  if (bins) GRID_STRIDE(q, bins_of(n, P.bin_log)) ((int*)Q.pos)[q] = 0;
   if (err) return;
   if (merges <= gridDim.x) {  // one block per merge
     if (blockIdx.x >= merges) return;
@@ -494,16 +505,16 @@ __global__ void __launch_bounds__(kBinThreads) k_bin(ParLevel P) {
       j[u] = left ? i : i - nL;
       x[u] = *(const int4*)((left ? R.left_ev(s) : R.ev[(P.S.k - 1) & 1] + 2 * m) + j[u]);
     }
-    bin_changes(x, j, [&](int p, int, int, int) { atomicAdd(&cnt[p >> kRangeLog], 1); });
+    bin_changes(x, j, [&](int p, int, int, int) { atomicAdd(&cnt[p >> P.bin_log], 1); });
     __syncthreads();
     for (int q = threadIdx.x; q < bins; q += kBinThreads)
       if (cnt[q]) cnt[q] = atomicAdd(&total[q], cnt[q]);
     if (!PLACE) continue;
     __syncthreads();
     bin_changes(x, j, [&](int p, int prev, int pos, int link) {
-      const int at = atomicAdd(&cnt[p >> kRangeLog], 1);
+      const int at = atomicAdd(&cnt[p >> P.bin_log], 1);
       B.rec[at] = make_int2(pos, link);
-      B.list[at] = (unsigned short)(2 * (p & (kRange - 1)) + prev);
+      B.list[at] = (unsigned short)(2 * (p & ((1 << P.bin_log) - 1)) + prev);
     });
   }
 }
@@ -527,8 +538,9 @@ __global__ void __launch_bounds__(T) k_bin_lists(ParLevel P) {
   const BlockGroup<T> g{wsum};
   for (int b = blockIdx.x; b < bins; b += gridDim.x) {
     const int first = b ? ends[b - 1] : 0, end = ends[b];
-    const int64_t p0 = (int64_t)b << kRangeLog;
-    const int keys = 2 * (int)(n - p0 < kRange ? n - p0 : kRange);
+    const int64_t p0 = (int64_t)b << P.bin_log;
+    const int64_t most = int64_t(1) << P.bin_log;
+    const int keys = 2 * (int)(n - p0 < most ? n - p0 : most);
     int* off = Q.off + key_of((int)p0, 0);
     __syncthreads();
     for (int q = threadIdx.x; q < keys; q += T) cnt[q] = 0;
@@ -653,47 +665,94 @@ __global__ void __launch_bounds__(64) k_par_walk(ParLevel P) {
   }
 }
 
-// Every segment's events to their place in the merged movie.
+// Every counted segment's events to their place in the merged movie.  A lane
+// decodes its segment's steps into references in LDS, then the wave copies the
+// events of its 64 segments in output order, so that writes are whole lines and
+// reads nearly.  10,000 ragged clouds, levels 10 to 16: 3.3 ms
+// a pass, and 1.6 for the segments walked again; a lane writing its own segment's
+// events, in one kernel with the walks (150 VGPRs), took 25.3 over levels 8 to 16.
 template <class PT>
-__global__ void __launch_bounds__(64) k_par_write(ParLevel P) {
+__global__ void __launch_bounds__(kWave) k_par_write(ParLevel P) {
+  __shared__ unsigned short ref[kWave * kWalkSteps];  // lane, source, event of the source
+  __shared__ const int4* src[3][kWave];               // left and right child, bridge events
+  __shared__ int4* dst[kWave];
   const RunPtrs& R = P.run[blockIdx.y];
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts || !Q.ctr[kCtrMerges]) return;
   const bool err = P.h->err != 0;
-  GRID_STRIDE(t, (int64_t)Q.ctr[kCtrSegments]) {
-    const int g = Q.segMerge[t];
-    const int first = Q.segBase[g];
-    if (err) {  // every merge writes its length, also after an error
-      if (t == first) R.out_len(P.S.merge(g).x) = 0;
-      continue;
-    }
-    const ParSeg<PT> Z(P, blockIdx.y, t, g);
-    const int len = Q.segOff[first + Z.S] - Q.segOff[first];
-    const int64_t cap = 2 * (Z.e - Z.s);
-    if (t == first) R.out_len(Z.s) = len <= cap ? len : 0;
-    if (len > cap) {
-      atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
-      continue;
-    }
-    ParWrite wr{R.out_ev(Z.s) + (Q.segOff[t] - Q.segOff[first])};
-    unsigned long long steps = Q.segSteps[t];
-    if (steps == kStepsLost) {
-      const int2 uv = Q.segUV[t];
-      (void)walk<PT>(Z.X, uv.x, uv.y, Z.jL, Z.kL, Z.jR, Z.kR, Z.i + 1 == Z.S, Z.i > 0, Z.T, Z.limit, wr);
-      continue;
-    }
-    int jL = Z.jL, jR = Z.jR;
-    const Event* keep = Q.segKeep + t * kSegKeep;
-    for (; steps; steps >>= 3) {
-      const unsigned code = (unsigned)steps & 7u;
-      if (code == kStepBridge) {
-        *wr.out++ = *keep++;
-      } else {
-        const bool left = code == kStepL || code == kStepHideL;
-        const Event* x = left ? Z.X.evL + jL++ : Z.X.evR + jR++;
-        if (code == kStepL || code == kStepR) *wr.out++ = *x;
+  const int64_t total = Q.ctr[kCtrSegments];
+  const int lane = threadIdx.x;
+  for (int64_t t0 = (int64_t)blockIdx.x * kWave; t0 < total; t0 += (int64_t)gridDim.x * kWave) {
+    const int64_t t = t0 + lane;
+    unsigned long long steps = 0;
+    int count = 0, jL = 0, jR = 0;
+    int64_t s = 0, m = 0;
+    Event* out = nullptr;
+    if (t < total) {
+      const int g = Q.segMerge[t], first = Q.segBase[g], S = Q.segS[g];
+      const int2 se = P.S.merge(g);
+      s = se.x;
+      m = s + (int64_t(1) << (P.S.k - 1));
+      const int before = Q.segOff[first], len = Q.segOff[first + S] - before;
+      const bool fits = !err && len <= 2 * (se.y - s);
+      if (t == first) R.out_len(s) = fits ? len : 0;  // also after an error
+      if (!fits) {
+        if (!err) atomicCAS(&P.h->err, 0, HULL_EINTERNAL);
+      } else if (Q.segSteps[t] != kStepsLost) {
+        steps = Q.segSteps[t];
+        count = Q.segOff[t + 1] - Q.segOff[t];
+        jL = Q.segJ[t];
+        jR = (int)((t - first) * (R.left_len(s) + (int64_t)R.right_len(m, se.y)) / S) - jL;
+        out = R.out_ev(s) + (Q.segOff[t] - before);
       }
     }
+    int end = count;
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(end, o);
+      if (lane >= o) end += y;
+    }
+    const int all = __shfl(end, kWave - 1);
+    int p = end - count;
+    __syncthreads();  // the earlier segments' copies
+    if (count) {
+      src[0][lane] = (const int4*)(R.left_ev(s) + jL);
+      src[1][lane] = (const int4*)(R.ev[(P.S.k - 1) & 1] + 2 * m + jR);
+      src[2][lane] = (const int4*)(Q.segKeep + t * kSegKeep);
+      dst[lane] = (int4*)out - p;
+    }
+    int nL = 0, nR = 0, nB = 0;
+    for (; steps; steps >>= 3) {
+      const int code = (int)steps & 7;
+      const bool left = code == kStepL || code == kStepHideL, bridge = code == kStepBridge;
+      const int i = bridge ? nB : (left ? nL : nR);
+      if (bridge || code == kStepL || code == kStepR)
+        ref[p++] = (unsigned short)(lane | (bridge ? 2 : !left) << 6 | i << 8);
+      nB += bridge;
+      nL += !bridge && left;
+      nR += !bridge && !left;
+    }
+    __syncthreads();
+    for (int q = lane; q < all; q += kWave) {
+      const int r = ref[q], o = r & 63;
+      dst[o][q] = src[(r >> 6) & 3][o][r >> 8];
+    }
+  }
+}
+
+// The segments whose steps were too many to note, walked again.
+template <class PT>
+__global__ void __launch_bounds__(64) k_par_rewalk(ParLevel P) {
+  const RunPtrs& R = P.run[blockIdx.y];
+  const ParRun& Q = P.par[blockIdx.y];
+  if (!R.pts || !Q.ctr[kCtrMerges] || P.h->err) return;
+  GRID_STRIDE(t, (int64_t)Q.ctr[kCtrSegments]) {
+    if (Q.segSteps[t] != kStepsLost) continue;
+    const int g = Q.segMerge[t];
+    const ParSeg<PT> Z(P, blockIdx.y, t, g);
+    const int first = Q.segBase[g];
+    ParWrite wr{R.out_ev(Z.s) + (Q.segOff[t] - Q.segOff[first])};
+    const int2 uv = Q.segUV[t];
+    (void)walk<PT>(Z.X, uv.x, uv.y, Z.jL, Z.kL, Z.jR, Z.kR, Z.i + 1 == Z.S, Z.i > 0, Z.T, Z.limit, wr);
   }
 }
 
@@ -731,9 +790,7 @@ template <class PT>
 int32_t parallel_level(const ParLevel& level, hipStream_t s) {
   ParLevel P = level;
   P.ranges = ranges_of(P.S.k);
-  // records of the bins: 8 + 2 bytes each, up to 6 per point
-  P.bin_room = bins_of(P.n) <= kBinsMax &&
-               (P.seg_cap + 1) * kSegKeep * (int64_t)sizeof(Event) >= 60 * P.n;
+  P.bin_log = bin_log(P);
   const dim3 g2(kStrideBlocks, 2), b256(256);
   hipLaunchKernelGGL(k_par_prep, g2, b256, 0, s, P);
   int32_t rc = chained(P, jobs_of(P, {0, 1}), 0, 1, 1, P.mcap + 1, s);
@@ -756,28 +813,35 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
     HULL_RANGES(k_list_fill)
 #undef HULL_RANGES
   }
-  const bool bins = lists_by_bin(P.n, P.S.k, P.bin_room);
-  if (bins) {
-    const int64_t nb = bins_of(P.n);
+  if (P.bin_log) {
+    const int64_t nb = bins_of(P.n, P.bin_log);
     const size_t lds = nb * sizeof(int);
     const dim3 gb((unsigned)std::min<int64_t>((2 * P.n) / (kBinThreads * kBinEvents) + 1, 2048), 2);
     hipLaunchKernelGGL(k_bin<false>, gb, dim3(kBinThreads), lds, s, P);
     rc = chained(P, jobs_of(P, {4}), 8, 4, 1, nb + 1, s);
     if (rc) return rc;
     hipLaunchKernelGGL(k_bin<true>, gb, dim3(kBinThreads), lds, s, P);
-    hipLaunchKernelGGL(k_bin_lists<1024>, dim3((unsigned)nb, 2), dim3(1024), 2 * sizeof(int) * kRange, s, P);
+    hipLaunchKernelGGL(k_bin_lists<1024>, dim3((unsigned)nb, 2), dim3(1024),
+                       2 * sizeof(int) << P.bin_log, s, P);
   }
-  if (!(bins || lists_by_range(P.n, P.S.k)) || P.device_n) {
+  if (!(P.bin_log || lists_by_range(P.n, P.S.k)) || P.device_n) {
     rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 1, s);
     if (rc) return rc;
     hipLaunchKernelGGL(k_par_fill<PT>, g2, b256, 0, s, P);
     hipLaunchKernelGGL(k_par_sort, g2, b256, 0, s, P);
   }
-  const dim3 gw(16384, 2), b64(64);
+  // The device may have few segments, and an empty block costs its dispatch (2^24
+  // points, 1% on a sphere: 3.14 ms with 16384 blocks a run, 3.06 with 4096; 2^20 sphere:
+  // 7.64 and 7.61, 7.98 with 2048).  Calls of more points keep the finer split, and
+  // enough blocks for their segments walked again (10,000 ragged clouds: 114.2 ms
+  // with 4096, 117.1 with 512).
+  const bool huge = P.n >= int64_t(1) << 25;
+  const dim3 gw((unsigned)std::min<int64_t>(P.seg_cap / 64 + 1, huge ? 16384 : 4096), 2), b64(64);
   hipLaunchKernelGGL(k_par_walk<PT>, gw, b64, 0, s, P);
   rc = chained(P, jobs_of(P, {3}), 6, 3, 1, P.seg_cap + 1, s);
   if (rc) return rc;
   hipLaunchKernelGGL(k_par_write<PT>, gw, b64, 0, s, P);
+  hipLaunchKernelGGL(k_par_rewalk<PT>, dim3(std::min(gw.x, huge ? 4096u : 1024u), 2), b64, 0, s, P);
   HULL_LAUNCH_CHECK();
   return HULL_OK;
 }

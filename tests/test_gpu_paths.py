@@ -238,7 +238,7 @@ def test_small_sort(n):
 
 
 # Lists built by ranges or bins of points (calls of many points), beside lists by global
-# atomics (the same clouds one by one): blocks of one range, one point more, several
+# atomics (the small clouds one by one; the large ones by smaller bins): blocks of one range, one point more, several
 # ranges and a ragged last one, clouds that end below the level and trailing
 # blocks between others, lists long enough to be sorted (an apex over a circle), and
 # a device-known number of points below and above the line; without tiles, also the
@@ -274,3 +274,26 @@ def test_lists_by_range(big, tile, monkeypatch):
         for k in range(len(parts)):
             got = validate.canonical(f[fo[k]:fo[k + 1]])
             assert got.shape == want[k].shape and (got == want[k]).all(), (k, len(parts[k]))
+
+
+# The smaller bins beside lists by global atomics (segments of 32 events leave no
+# scratch for bins; no tiles, so every level's lists differ): the first size that has them, one
+# point fewer, both point types, a size that only the device knows.
+@pytest.mark.parametrize("n", [131071, 131072, 150001])
+def test_lists_by_small_bins(n, monkeypatch):
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    monkeypatch.setenv("HULL_TILE_LEVELS", "0")
+    p = workloads.sphere(np.random.default_rng(n), n, 1 << 20)
+    p[:9] //= 2  # interior points
+    x = torch.from_numpy(p).cuda()
+    off = np.array([0, n], np.int64)
+    say("small bins: atomics", n)
+    want = validate.canonical(hull.hull_batched_sync(x, off, schedule=hull.Schedule(0, 32, 0, -1))[0].cpu().numpy())
+    say("small bins", n)
+    bins = hull.hull_batched_sync(x, off, schedule=hull.Schedule(0, 4, 0, -1))[0]
+    single = hull.hull_sync(x)
+    for f in (bins, single, hull.hull_wide(x.to(torch.int64))):
+        got = validate.canonical(f.cpu().numpy())
+        assert got.shape == want.shape and (got == want).all()
