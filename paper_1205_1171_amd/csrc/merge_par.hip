@@ -791,6 +791,13 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
   ParLevel P = level;
   P.ranges = ranges_of(P.S.k);
   P.bin_log = bin_log(P);
+  // The device may have few segments, and an empty block costs its dispatch (2^24
+  // points, 1% on a sphere: 3.14 ms with 16384 blocks a run, 3.06 with 4096; 2^20 sphere:
+  // 7.64 and 7.61, 7.98 with 2048).  Calls of more points keep the finer split, and
+  // enough blocks for their segments walked again (10,000 ragged clouds: 114.2 ms
+  // with 4096, 117.1 with 512).  The same for the blocks of the lists (2^24: 3.05 and
+  // 3.01 ms).
+  const bool huge = P.n >= int64_t(1) << 25;
   const dim3 g2(kStrideBlocks, 2), b256(256);
   hipLaunchKernelGGL(k_par_prep, g2, b256, 0, s, P);
   int32_t rc = chained(P, jobs_of(P, {0, 1}), 0, 1, 1, P.mcap + 1, s);
@@ -800,7 +807,7 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
     // (a merge at level k has more than 2^(k-1) points)
     const int64_t pairs = ((P.n >> (P.S.k - 1)) + 1) * P.ranges;
     const int T = range_threads(P.S.k);
-    const dim3 gr((unsigned)std::min<int64_t>(pairs, (int64_t)2048 * 512 / T), 2);
+    const dim3 gr((unsigned)std::min<int64_t>(pairs, (int64_t)(huge ? 2048 : 1024) * 512 / T), 2);
     const size_t lds = 2 * sizeof(int) * range_points(P.S.k);
 #define HULL_RANGES(KERNEL)                                                            \
   if (T == 512) hipLaunchKernelGGL(KERNEL<512>, gr, dim3(512), lds, s, P);             \
@@ -816,12 +823,12 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
   if (P.bin_log) {
     const int64_t nb = bins_of(P.n, P.bin_log);
     const size_t lds = nb * sizeof(int);
-    const dim3 gb((unsigned)std::min<int64_t>((2 * P.n) / (kBinThreads * kBinEvents) + 1, 2048), 2);
+    const dim3 gb((unsigned)std::min<int64_t>((2 * P.n) / (kBinThreads * kBinEvents) + 1, 512), 2);
     hipLaunchKernelGGL(k_bin<false>, gb, dim3(kBinThreads), lds, s, P);
     rc = chained(P, jobs_of(P, {4}), 8, 4, 1, nb + 1, s);
     if (rc) return rc;
     hipLaunchKernelGGL(k_bin<true>, gb, dim3(kBinThreads), lds, s, P);
-    hipLaunchKernelGGL(k_bin_lists<1024>, dim3((unsigned)nb, 2), dim3(1024),
+    hipLaunchKernelGGL(k_bin_lists<1024>, dim3((unsigned)std::min<int64_t>(nb, 512), 2), dim3(1024),
                        2 * sizeof(int) << P.bin_log, s, P);
   }
   if (!(P.bin_log || lists_by_range(P.n, P.S.k)) || P.device_n) {
@@ -830,12 +837,6 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
     hipLaunchKernelGGL(k_par_fill<PT>, g2, b256, 0, s, P);
     hipLaunchKernelGGL(k_par_sort, g2, b256, 0, s, P);
   }
-  // The device may have few segments, and an empty block costs its dispatch (2^24
-  // points, 1% on a sphere: 3.14 ms with 16384 blocks a run, 3.06 with 4096; 2^20 sphere:
-  // 7.64 and 7.61, 7.98 with 2048).  Calls of more points keep the finer split, and
-  // enough blocks for their segments walked again (10,000 ragged clouds: 114.2 ms
-  // with 4096, 117.1 with 512).
-  const bool huge = P.n >= int64_t(1) << 25;
   const dim3 gw((unsigned)std::min<int64_t>(P.seg_cap / 64 + 1, huge ? 16384 : 4096), 2), b64(64);
   hipLaunchKernelGGL(k_par_walk<PT>, gw, b64, 0, s, P);
   rc = chained(P, jobs_of(P, {3}), 6, 3, 1, P.seg_cap + 1, s);
