@@ -9,7 +9,6 @@
 namespace hull {
 
 constexpr size_t kScratchBytes = size_t(64) << 20;  // 64 MiB per GPU
-constexpr int64_t kNoallocMax = 72597;               // the entry point's limit (needs 47 MiB)
 
 // The array itself.  Host code never passes this name to a kernel (on the
 // host it only stands for the symbol): the device address comes from
@@ -53,7 +52,7 @@ extern "C" int32_t hull_full_noalloc(const int32_t* d_xyz, int64_t n, int32_t* d
   size_t need = 0;
   int32_t rc = hull_workspace_bytes(n, HULL_WS_STANDARD, &need);
   if (rc) return rc;
-  if (n > hull::kNoallocMax || need > hull::kScratchBytes) return HULL_EWORKSPACE;
+  if (need > hull::kScratchBytes) return HULL_EWORKSPACE;
   void* ws = nullptr;
   rc = hull::scratch_ptr(&ws);
   if (rc) return rc;
