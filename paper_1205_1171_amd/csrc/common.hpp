@@ -36,6 +36,7 @@ constexpr int kCtrSegments = 2;  // walk segments of the level
 constexpr int kCtrKeys = 3;      // list bounds to scan (two per point and one more; 0: built by range)
 constexpr int kCtrSplice = 4;    // splices pending from the level before, by its parity (2 slots)
 constexpr int kCtrRanges = 6;    // ranges of points whose lists are built in LDS
+constexpr int kCtrTotals = 7;    // their entry counts to scan (one per range and one more; 0: none)
 constexpr int kCtrSlots = 8;     // size of the region (int32 words)
 
 // Device-side status words at the head of every workspace.

@@ -193,7 +193,10 @@ __global__ void __launch_bounds__(256) k_par_prep(ParLevel P) {
     if (g == 0) {
       Q.ctr[kCtrMerges] = (int)merges;
       Q.ctr[kCtrKeys] = ranges ? 0 : (int)keys;
-      Q.ctr[kCtrRanges] = err || !ranges || !merges ? 0 : (int)(bins ? bins_of(n, P.bin_log) : merges * P.ranges);
+      const int count = err || !ranges || !merges ? 0 : (int)(bins ? bins_of(n, P.bin_log) : merges * P.ranges);
+      Q.ctr[kCtrRanges] = count;
+      // (no word at all without ranges: pos then holds the events' places)
+      Q.ctr[kCtrTotals] = count ? count + 1 : 0;
       Q.ctr[kCtrSplice + (P.S.k & 1)] = (int)merges;
     }
     if (g < merges && !err) {
@@ -770,7 +773,7 @@ static ScanJobs jobs_of(const ParLevel& P, std::initializer_list<int> kinds) {
         case 0: j = ScanJob{Q.ecnt, Q.eoff, Q.ctr + kCtrMerges, Q.ctr + kCtrEvents}; break;
         case 1: j = ScanJob{Q.segS, Q.segBase, Q.ctr + kCtrMerges, Q.ctr + kCtrSegments}; break;
         case 2: j = ScanJob{Q.off, Q.off, Q.ctr + kCtrKeys, nullptr}; break;
-        case 4: j = ScanJob{(int*)Q.pos, (int*)Q.pos, Q.ctr + kCtrRanges, nullptr}; break;
+        case 4: j = ScanJob{(int*)Q.pos, (int*)Q.pos, Q.ctr + kCtrTotals, nullptr}; break;
         default: j = ScanJob{Q.segCnt, Q.segOff, Q.ctr + kCtrSegments, nullptr}; break;
       }
     }
@@ -815,7 +818,7 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
   else if (T == 128) hipLaunchKernelGGL(KERNEL<128>, gr, dim3(128), lds, s, P);        \
   else hipLaunchKernelGGL(KERNEL<64>, gr, dim3(64), lds, s, P);
     HULL_RANGES(k_list_count)
-    rc = chained(P, jobs_of(P, {4}), 8, 4, 1, pairs + 1, s);
+    rc = chained(P, jobs_of(P, {4}), 8, 4, 0, pairs + 1, s);
     if (rc) return rc;
     HULL_RANGES(k_list_fill)
 #undef HULL_RANGES
@@ -825,7 +828,7 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
     const size_t lds = nb * sizeof(int);
     const dim3 gb((unsigned)std::min<int64_t>((2 * P.n) / (kBinThreads * kBinEvents) + 1, 512), 2);
     hipLaunchKernelGGL(k_bin<false>, gb, dim3(kBinThreads), lds, s, P);
-    rc = chained(P, jobs_of(P, {4}), 8, 4, 1, nb + 1, s);
+    rc = chained(P, jobs_of(P, {4}), 8, 4, 0, nb + 1, s);
     if (rc) return rc;
     hipLaunchKernelGGL(k_bin<true>, gb, dim3(kBinThreads), lds, s, P);
     hipLaunchKernelGGL(k_bin_lists<1024>, dim3((unsigned)std::min<int64_t>(nb, 512), 2), dim3(1024),

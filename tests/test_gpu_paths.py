@@ -297,3 +297,34 @@ def test_lists_by_small_bins(n, monkeypatch):
     for f in (bins, single, hull.hull_wide(x.to(torch.int64))):
         got = validate.canonical(f.cpu().numpy())
         assert got.shape == want.shape and (got == want).all()
+
+
+# Calls whose size on the host says lists by bins or ranges and whose points left
+# after the filter say atomics (a cone whose apex starts the first block and
+# has a long list; the rim's own hull is the hull): single hulls of both point
+# types and a batch.
+@pytest.mark.parametrize("n,rim", [(1 << 17, 4100), (1 << 19, 5000)])
+def test_few_points_left_of_many(n, rim):
+    import oracle
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    from test_kernels_on_host import cone_with_interior
+    rng = np.random.default_rng(rim)
+    p = cone_with_interior(rng, rim, n)
+    want = validate.canonical(oracle.hull(p[:rim + 1]))
+    x = torch.from_numpy(p).cuda()
+    for rep in range(3):
+        for wide in (False, True):
+            say("few points left", n, rep, wide)
+            got = validate.canonical((hull.hull_wide(x.to(torch.int64)) if wide else hull.hull_sync(x)).cpu().numpy())
+            assert got.shape == want.shape and (got == want).all()
+    rims = [rim, 300, 4097, 2500]
+    parts = [cone_with_interior(rng, m, n // 2 if m > 300 else 1000) for m in rims]
+    off = np.cumsum([0] + [len(q) for q in parts]).astype(np.int64)
+    say("few points left: batch", off[-1])
+    f, fo = hull.hull_batched_sync(torch.from_numpy(np.concatenate(parts)).cuda(), off)
+    f, fo = f.cpu().numpy(), fo.cpu().numpy()
+    for k, q in enumerate(parts):
+        got, want = validate.canonical(f[fo[k]:fo[k + 1]]), validate.canonical(oracle.hull(q[:rims[k] + 1]))
+        assert got.shape == want.shape and (got == want).all(), k
