@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(64) k_merge_level_lds(LevelArgs A) {
   __shared__ PT sp[64 * W];
   __shared__ int2 sl[64 * W];
   const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts) return;
+  if (!R.pts || !selected(A.S, A.sel)) return;
   const int64_t M = A.S.merges();
   for (int64_t g = blockIdx.x * (int64_t)64 + threadIdx.x; g < M; g += (int64_t)gridDim.x * 64)
     merge_lds_one<PT, W>(A, R, g, sp + threadIdx.x * W, sl + threadIdx.x * W);
@@ -567,7 +567,7 @@ __global__ void __launch_bounds__(64) k_merge_level_lk(LevelArgs A) {
 // movie.  The same result as the merge loop, without its machinery.
 __global__ void __launch_bounds__(256) k_merge_level1(LevelArgs A) {
   const RunPtrs& R = A.run[blockIdx.y];
-  if (!R.pts) return;
+  if (!R.pts || !selected(A.S, A.sel)) return;
   const int64_t M = A.S.merges();
   for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < M;
        g += (int64_t)gridDim.x * blockDim.x) {
@@ -903,16 +903,16 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
         hipLaunchKernelGGL(k_copy_links, dim3(grid_for(n)), dim3(256), 0, s, R.pv0, R.nx0, R.lk, n);
     }
     if (events) (void)hipEventRecord(events[2 * k], s);
+    LevelArgs B = A;
+    B.sel = sel_other;
     if (serial && k == 1) {
-      hipLaunchKernelGGL(k_merge_level1, dim3(grid_for(bound), 2), dim3(256), 0, s, A);
+      hipLaunchKernelGGL(k_merge_level1, dim3(grid_for(bound), 2), dim3(256), 0, s, B);
     } else if (serial && k <= opt.lds_levels) {
       const dim3 grid(merge_grid(bound, 64), 2);
-      if (k == 2) hipLaunchKernelGGL((k_merge_level_lds<PT, 4>), grid, dim3(64), 0, s, A);
-      else if (k == 3) hipLaunchKernelGGL((k_merge_level_lds<PT, 8>), grid, dim3(64), 0, s, A);
-      else hipLaunchKernelGGL((k_merge_level_lds<PT, 16>), grid, dim3(64), 0, s, A);
+      if (k == 2) hipLaunchKernelGGL((k_merge_level_lds<PT, 4>), grid, dim3(64), 0, s, B);
+      else if (k == 3) hipLaunchKernelGGL((k_merge_level_lds<PT, 8>), grid, dim3(64), 0, s, B);
+      else hipLaunchKernelGGL((k_merge_level_lds<PT, 16>), grid, dim3(64), 0, s, B);
     } else if (serial) {
-      LevelArgs B = A;
-      B.sel = sel_other;
       if (k >= opt.order_from && bound >= opt.order_min) {
         const dim3 grid((unsigned)((bound + 255) / 256), 2);
         for (int r = 0; r < 2; ++r) {
@@ -956,7 +956,7 @@ static int32_t run_levels(int64_t n, const Sched& S0, char* ws, const Plan& pl, 
       if (rc) return rc;
     }
     if (tile) {
-      LevelArgs B = A;
+      B = A;
       B.sel = sel_tile;
       const int W = (int)A.width;
       const int gs = tile_lanes(W, n);

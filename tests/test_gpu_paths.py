@@ -328,3 +328,24 @@ def test_few_points_left_of_many(n, rim):
     for k, q in enumerate(parts):
         got, want = validate.canonical(f[fo[k]:fo[k + 1]]), validate.canonical(oracle.hull(q[:rims[k] + 1]))
         assert got.shape == want.shape and (got == want).all(), k
+
+
+# Level 4 with many merges by the host's bound and few by the device's, LDS-staged or
+# not: many tiny clouds beside some of 50-64 points.
+@pytest.mark.parametrize("lds_levels", ["3", "4"])
+def test_many_tiny_clouds(lds_levels, monkeypatch):
+    import oracle
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    monkeypatch.setenv("HULL_LDS_LEVELS", lds_levels)
+    rng = np.random.default_rng(6)
+    parts = [workloads.sphere(rng, 50 + k % 15, 1 << 20) for k in range(700)]
+    parts += [workloads.sphere(rng, 5, 1 << 20) for _ in range(17000)]
+    off = np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)
+    say("many tiny clouds", lds_levels)
+    f, fo = hull.hull_batched_sync(torch.from_numpy(np.concatenate(parts)).cuda(), off)
+    f, fo = f.cpu().numpy(), fo.cpu().numpy()
+    for k in range(720):
+        got, want = validate.canonical(f[fo[k]:fo[k + 1]]), validate.canonical(oracle.hull(parts[k]))
+        assert got.shape == want.shape and (got == want).all(), k

@@ -34,3 +34,17 @@ def test_first_events_place(n, rim, seed):
     want = oracle.hull(p[:rim + 1])
     for descending in (False, True):
         assert same(hip_on_host.hull(p, descending=descending, fill=0), want), descending
+
+
+# The host's bound counts many merges at level 4, the device few: one of the two
+# kernels launched for the level runs, also where level 4 is an LDS-staged one.
+@pytest.mark.parametrize("lds_levels", ["3", "4"])
+def test_level_runs_one_way(lds_levels, monkeypatch):
+    monkeypatch.setenv("HULL_LDS_LEVELS", lds_levels)
+    monkeypatch.setenv("HULL_WAVE_LEVEL", "-1")  # (lanes in lockstep without barriers)
+    rng = np.random.default_rng(6)
+    parts = [workloads.sphere(rng, 50 + k % 15, 1 << 20) for k in range(600)]
+    parts += [workloads.sphere(rng, 5, 1 << 20) for _ in range(17000)]
+    f, fo = hip_on_host.hull_batched(parts)
+    for k in range(620):
+        assert same(f[fo[k]:fo[k + 1]], oracle.hull(parts[k])), k
