@@ -665,7 +665,8 @@ int32_t extent_and_filter(const InT* d_xyz, int64_t n, bool filter, char* ws, co
   F.quads = (float4*)take((size_t)quads * 8 * sizeof(float4));
   F.mask = (unsigned long long*)take((size_t)tiles * (kFilterTile / 64) * 8);
   F.tcnt = (int32_t*)take((size_t)(tiles + 1) * 4);
-  if (filter && (size_t)(o - (ws + pl.pos[0])) > 2 * (size_t)n * sizeof(int4)) filter = false;
+  // (kFilterMin points have room)
+  if (filter && (size_t)(o - (ws + pl.pos[0])) > 2 * (size_t)n * sizeof(int4)) return HULL_EINTERNAL;
   F.keys = (uint32_t*)(ws + pl.keys1);
   F.vals = (int32_t*)(ws + pl.vals1);
   F.off1 = (int64_t*)(ws + pl.off1);

@@ -31,7 +31,7 @@ def _build(out):
     for s in [os.path.join(csrc, n) for n in SOURCES] + [os.path.join(HERE, "emu.cpp")]:
         obj = os.path.join(out, os.path.basename(s) + ".o")
         objs.append(obj)
-        jobs.append(subprocess.Popen([*flags, "-x", "c++", "-c", s, "-o", obj]))
+        jobs.append(subprocess.Popen([*flags, "-I", csrc, "-x", "c++", "-c", s, "-o", obj]))
     assert all([j.wait() == 0 for j in jobs])
     subprocess.check_call(["g++", "-shared", "-Wl,-Bsymbolic", "-o", so, *objs])
     return so
@@ -55,6 +55,17 @@ def _workspace(size, fill):
     ws = np.full(size + 256, fill, np.uint8)
     at = -ws.ctypes.data % 256
     return ws[at:at + size]
+
+
+def filter_rc(p):
+    """Status of extent_and_filter."""
+    L = lib()
+    n = len(p)
+    size = ctypes.c_size_t()
+    assert L.hull_workspace_bytes(ctypes.c_int64(n), 0, ctypes.byref(size)) == 0
+    ws = _workspace(size.value, 0xA5)
+    L.emu_order(0)
+    return L.emu_filter(_p(p), ctypes.c_int64(n), _p(ws), size)
 
 
 def hull(p, entry="hull_full", descending=False, fill=0xA5):

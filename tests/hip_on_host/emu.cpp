@@ -3,6 +3,8 @@
 
 #include <string>
 
+#include "common.hpp"
+
 namespace hull {
 // dynamic LDS by the names the kernels give it
 __align__(16) unsigned char dyn_lds[163840];
@@ -175,4 +177,12 @@ extern "C" const char* emu_launched() {
   for (const auto& s : emu::launched) text += s + "\n";
   emu::launched.clear();
   return text.c_str();
+}
+
+// Extent and filter, whatever the number of points.
+extern "C" int emu_filter(const int32_t* xyz, int64_t n, char* ws, size_t bytes) {
+  const hull::Plan pl = hull::make_plan(n, 1);
+  if (bytes < pl.total) return HULL_EWORKSPACE;
+  hull::init_call((hull::Header*)(ws + pl.header), (int64_t*)(ws + pl.off1), n, ws, pl, nullptr);
+  return hull::extent_and_filter<int32_t>(xyz, n, true, ws, pl, nullptr);
 }

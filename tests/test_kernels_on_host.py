@@ -48,3 +48,12 @@ def test_level_runs_one_way(lds_levels, monkeypatch):
     f, fo = hip_on_host.hull_batched(parts)
     for k in range(620):
         assert same(f[fo[k]:fo[k + 1]], oracle.hull(parts[k])), k
+
+
+# A filter without room for its grid is an error (the sort would read a list that
+# was never written), and every size that is sent to it has room.
+def test_filter_room():
+    rng = np.random.default_rng(2)
+    assert hip_on_host.filter_rc(workloads.cube(rng, 300, 99)) == -5
+    for n in (1024, 8193, 131071, 131072):
+        assert hip_on_host.filter_rc(workloads.cube(rng, n, 99)) == 0
