@@ -341,6 +341,10 @@ constexpr int kTileFromLevel = 5;  // (one earlier for calls of few points, two 
 // 122.5 with it by the parallel strategy, 120.4 with levels 10 and 11).  Smaller calls
 // keep tiles, one launch a level (2^20 sphere, level 11: 470 us by a tile, 616).
 constexpr int64_t kTileOpenPoints = int64_t(1) << 23;
+// Every level above a parallel one launches the parallel strategy too (which settles
+// the splices of the level below, also where tiles then run): the host counts as
+// many whatever it opens here.
+static_assert(kTileOpenPoints > kTilePoints, "a level by tiles alone would follow a parallel one");
 constexpr int kTileLevels = 11;  // kTileMaxWidth
 constexpr int kMaxLevels = 28;
 
