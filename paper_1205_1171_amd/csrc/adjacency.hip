@@ -79,8 +79,9 @@ __global__ void __launch_bounds__(256) k_adj_match(AdjArgs A) {
       const int64_t h = owner64(A.face_off, A.H, f);
       p0 = A.pt_off[h];
       const int64_t np = A.pt_off[h + 1] - p0;
-      f0 = A.face_off[h];
-      f1 = A.face_off[h + 1];
+      // (owner64 gives rows before or past all offsets to the first or last cloud)
+      if (h > 0) f0 = A.face_off[h];
+      if (h + 1 < A.H) f1 = A.face_off[h + 1];
       ok = ok && v[0] < np && v[1] < np && v[2] < np;
     }
     if (!ok) {

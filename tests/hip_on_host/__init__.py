@@ -103,3 +103,20 @@ def hull_batched(parts, descending=False, fill=0xA5, schedule=None):
                              ctypes.byref(schedule) if schedule is not None else None, None)
     assert rc == 0 and info[0] == 0, (rc, info)
     return faces[:info[1]], face_off
+
+
+def face_adjacency(faces, face_off=None, pt_off=None, descending=False):
+    """(status, adjacency rows, edges without a twin) of face rows."""
+    L = lib()
+    F = len(faces)
+    size = ctypes.c_size_t()
+    assert L.hull_adjacency_workspace_bytes(ctypes.c_int64(F), ctypes.byref(size)) == 0
+    ws = _workspace(size.value, 0xA5)
+    adj = np.full((max(F, 1), 3), -9, np.int32)
+    info = np.full(2, -9, np.int64)
+    L.emu_order(int(descending))
+    H = 1 if face_off is None else len(face_off) - 1
+    assert L.hull_face_adjacency(
+        _p(faces), ctypes.c_int64(F), _p(face_off) if face_off is not None else None,
+        _p(pt_off) if pt_off is not None else None, ctypes.c_int64(H), _p(adj), _p(info), _p(ws), size, None) == 0
+    return int(info[0]), adj[:F], int(info[1])

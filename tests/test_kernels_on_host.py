@@ -57,3 +57,26 @@ def test_filter_room():
     assert hip_on_host.filter_rc(workloads.cube(rng, 300, 99)) == -5
     for n in (1024, 8193, 131071, 131072):
         assert hip_on_host.filter_rc(workloads.cube(rng, n, 99)) == 0
+
+
+# Rows outside every cloud's offsets count to the first or the last cloud (so a
+# batch's last cloud may be given by its first row alone).
+@pytest.mark.parametrize("face_off", [[0, 100, 100], [0, 100, 260], [0, 0, 150], [40, 100, 260], [260, 260, 260]])
+def test_adjacency_rows_past_the_offsets(face_off):
+    rng = np.random.default_rng(7)
+    faces = oracle.hull(workloads.sphere(rng, 132, 1 << 20))
+    F = len(faces)
+    assert F == 260
+    # a cloud's rows are a surface with holes; its points: all for either cloud
+    off = np.asarray(face_off, np.int64)
+    cut = int(off[1])  # rows before it: the first cloud's
+    want = np.full((F, 3), -1, np.int32)
+    for rows in (range(0, cut), range(cut, F)):
+        edge = {(int(faces[f][k]), int(faces[f][(k + 1) % 3])): f for f in rows for k in range(3)}
+        for (a, b), f in edge.items():
+            k = [int(v) for v in faces[f]].index(a)
+            want[f, k] = edge.get((b, a), -1)
+    for descending in (False, True):
+        st, adj, open_edges = hip_on_host.face_adjacency(
+            faces, off, np.array([0, 132, 264], np.int64), descending)
+        assert st == 0 and (adj == want).all() and open_edges == (want < 0).sum()
