@@ -152,7 +152,8 @@ __device__ __forceinline__ ParCtx<PT> ctx_of(const ParLevel& P, int r, int64_t s
   return X;
 }
 
-// Sorts a list by position (Shell's method; only lists above kParScan).
+// Sorts a list by position (Shell's method; only lists above kParScan, up to
+// kParSerial).
 __device__ void sort_entries(int2* a, int k) {
   int gap = 1;
   while (gap < k / 3) gap = 3 * gap + 1;
@@ -166,6 +167,98 @@ __device__ void sort_entries(int2* a, int k) {
       }
       a[j] = x;
     }
+}
+
+// Longer lists (a vertex of high degree has one as long as the movie) are noted in LDS
+// and sorted by the whole workgroup, one after the other.  By one thread each, a cone over
+// 16,384 points took 21 ms, a moment curve 84.
+constexpr int kParSerial = 128;
+constexpr int kParRank = 1024;   // longest list whose entries count the smaller ones
+constexpr int kLongLists = 64;   // noted at a time
+struct LongLists {
+  int count;
+  int2 list[kLongLists];  // first entry, length
+};
+constexpr int sort_words(int T) { return 5 * T; }  // LDS of sort_long, lists above kParRank
+
+// By rank up to kParRank entries.  Above, by windows of 128 T positions: the
+// positions differ, so a bit each says which are there, and an entry's place is the
+// number of bits before its own.  tmp: space for the list; the positions are below
+// `limit`.
+template <int T, class G>
+__device__ void sort_long(const G& g, unsigned* lds, int2* a, int2* tmp, int k, int64_t limit) {
+  const int t = threadIdx.x;
+  if (k <= kParRank) {
+    for (int i = t; i < k; i += T) {
+      const int2 x = a[i];
+      int r = 0;
+#pragma unroll 8
+      for (int j = 0; j < k; ++j) r += a[j].x < x.x;
+      tmp[r] = x;
+    }
+  } else {
+    constexpr int window = 128 * T;
+    unsigned* bits = lds;             // [4 T]
+    int* before = (int*)(lds + 4 * T);  // [T]
+    int done = 0;
+    for (int64_t lo = 0; done < k && lo < limit; lo += window) {
+      for (int q = t; q < 4 * T; q += T) bits[q] = 0;
+      __syncthreads();
+      for (int i = t; i < k; i += T) {
+        const unsigned x = (unsigned)(a[i].x - (int)lo);
+        if (x < (unsigned)window) atomicOr(&bits[x >> 5], 1u << (x & 31));
+      }
+      __syncthreads();
+      int sum = 0, all;
+      for (int q = 0; q < 4; ++q) sum += __popc(bits[4 * t + q]);
+      before[t] = done + g.scan(sum, all);
+      __syncthreads();
+      for (int i = t; i < k; i += T) {
+        const int2 e = a[i];
+        const unsigned x = (unsigned)(e.x - (int)lo);
+        if (x >= (unsigned)window) continue;
+        const int w = x >> 5;
+        int r = before[w >> 2] + __popc(bits[w] & ((1u << (x & 31)) - 1));
+        for (int q = w & ~3; q < w; ++q) r += __popc(bits[q]);
+        tmp[r] = e;
+      }
+      done += all;
+      __syncthreads();
+    }
+  }
+  __syncthreads();
+  for (int i = t; i < k; i += T) a[i] = tmp[i];
+}
+
+// Sorts the lists q, q + step, ... below `keys`: list(q) gives its first entry and its
+// length.  S.count is 0, cleared before a barrier; it is again after the next one.
+// The walk scratch takes the sorted entries (idle until the walks; 6 entries per point
+// fit, and a bin's records there have been read to the end by its own block).
+template <int T, class G, class LIST>
+__device__ __forceinline__ void sort_lists(const G& g, LongLists& S, unsigned* lds, const ParLevel& P,
+                                           const ParRun& Q, int64_t q, int64_t step, int64_t keys,
+                                           const LIST& list) {
+  int2 *ent = Q.ent, *tmp = (int2*)Q.segKeep;
+  for (;;) {
+    for (; q < keys; q += step) {
+      const int2 l = list(q);
+      if (l.y > kParSerial) {
+        const int at = atomicAdd(&S.count, 1);
+        if (at >= kLongLists) break;  // the next round's
+        S.list[at] = l;
+      } else if (l.y > kParScan) {
+        sort_entries(ent + l.x, l.y);
+      }
+    }
+    __syncthreads();
+    const int count = S.count;
+    for (int i = 0; i < count && i < kLongLists; ++i)
+      sort_long<T>(g, lds, ent + S.list[i].x, tmp + S.list[i].x, S.list[i].y, 2 * P.n);
+    __syncthreads();
+    if (threadIdx.x == 0) S.count = 0;
+    if (count <= kLongLists) return;
+    __syncthreads();
+  }
 }
 
 #define GRID_STRIDE(i, n) \
@@ -381,15 +474,6 @@ __device__ __forceinline__ int lists_scan(const G& g, const int* cnt, int keys, 
   }
   return total;
 }
-// Sorts the long lists; cur: where each ends.
-template <int T>
-__device__ __forceinline__ void sort_lists(int2* ent, const int* off, const int* cur, int keys) {
-  for (int q = threadIdx.x; q < keys; q += T) {
-    const int first = off[q], len = cur[q] - first;
-    if (len > kParScan) sort_entries(ent + first, len);
-  }
-}
-
 // Lengths of a range's lists, as offsets within the range, and their total.
 template <int T>
 __global__ void __launch_bounds__(T) k_list_count(ParLevel P) {
@@ -419,7 +503,11 @@ __global__ void __launch_bounds__(T) k_list_count(ParLevel P) {
 template <int T>
 __global__ void __launch_bounds__(T) k_list_fill(ParLevel P) {
   extern __shared__ int range_lds[];
+  __shared__ LongLists S;
+  __shared__ int wsum[T / 64];
   int* cur = range_lds;
+  const BlockGroup<T> g{wsum};
+  if (threadIdx.x == 0) S.count = 0;
   const RunPtrs& R = P.run[blockIdx.y];
   const ParRun& Q = P.par[blockIdx.y];
   if (!R.pts) return;
@@ -446,7 +534,12 @@ __global__ void __launch_bounds__(T) k_list_fill(ParLevel P) {
       Q.ent[atomicAdd(&cur[2 * p + l], 1)] = make_int2(j, link);
     });
     __syncthreads();  // (also makes the block's entries visible to all of it)
-    sort_lists<T>(Q.ent, off, cur, keys);
+    // (longer lists than kParRank come from level 11 on, whose ranges have 16 T words)
+    static_assert(16 * T >= sort_words(T) && kParRank >= 1 << 10, "");
+    const int end = before[pair + 1];
+    sort_lists<T>(g, S, (unsigned*)range_lds, P, Q, threadIdx.x, T, keys, [&](int64_t q) {
+      return make_int2(off[q], (q + 1 < keys ? off[q + 1] : end) - off[q]);
+    });
   }
 }
 
@@ -527,6 +620,8 @@ template <int T>
 __global__ void __launch_bounds__(T) k_bin_lists(ParLevel P) {
   extern __shared__ int range_lds[];
   __shared__ int wsum[T / 64];
+  __shared__ LongLists S;
+  if (threadIdx.x == 0) S.count = 0;
   int* cnt = range_lds;
   const ParRun& Q = P.par[blockIdx.y];
   if (!P.run[blockIdx.y].pts) return;
@@ -557,18 +652,25 @@ __global__ void __launch_bounds__(T) k_bin_lists(ParLevel P) {
     __syncthreads();
     for (int q = first + threadIdx.x; q < end; q += T) Q.ent[atomicAdd(&cnt[B.list[q]], 1)] = B.rec[q];
     __syncthreads();
-    sort_lists<T>(Q.ent, off, cnt, keys);
+    sort_lists<T>(g, S, (unsigned*)range_lds, P, Q, threadIdx.x, T, keys, [&](int64_t q) {
+      return make_int2(off[q], (q + 1 < keys ? off[q + 1] : end) - off[q]);
+    });
   }
 }
 
 // Sorts the long lists of k_par_fill (lists built by range: no keys).
 __global__ void __launch_bounds__(256) k_par_sort(ParLevel P) {
+  __shared__ LongLists S;
+  __shared__ int wsum[4];
+  __shared__ unsigned lds[sort_words(256)];
   const ParRun& Q = P.par[blockIdx.y];
-  if (!P.run[blockIdx.y].pts || P.h->err) return;
-  GRID_STRIDE(q, (int64_t)Q.ctr[kCtrKeys] - 1) {
-    const int first = Q.off[q], k = Q.off[q + 1] - first;
-    if (k > kParScan) sort_entries(Q.ent + first, k);
-  }
+  if (!P.run[blockIdx.y].pts) return;
+  if (threadIdx.x == 0) S.count = P.h->err ? -1 : 0;  // (one reading for the whole block)
+  __syncthreads();
+  if (S.count < 0) return;
+  sort_lists<256>(BlockGroup<256>{wsum}, S, lds, P, Q, blockIdx.x * (int64_t)256 + threadIdx.x,
+                  (int64_t)gridDim.x * 256, (int64_t)Q.ctr[kCtrKeys] - 1,
+                  [&](int64_t q) { return make_int2(Q.off[q], Q.off[q + 1] - Q.off[q]); });
 }
 
 // A counting walk: its steps, and its first kSegKeep bridge events put aside.
@@ -832,7 +934,7 @@ int32_t parallel_level(const ParLevel& level, hipStream_t s) {
     if (rc) return rc;
     hipLaunchKernelGGL(k_bin<true>, gb, dim3(kBinThreads), lds, s, P);
     hipLaunchKernelGGL(k_bin_lists<1024>, dim3((unsigned)std::min<int64_t>(nb, 512), 2), dim3(1024),
-                       2 * sizeof(int) << P.bin_log, s, P);
+                       sizeof(int) * std::max(2 << P.bin_log, sort_words(1024)), s, P);
   }
   if (!(P.bin_log || lists_by_range(P.n, P.S.k)) || P.device_n) {
     rc = chained(P, jobs_of(P, {2}), 4, 2, 0, 2 * P.n + 1, s);

@@ -153,6 +153,10 @@ void launch(dim3 grid, dim3 block, size_t lds, std::function<void()> body, const
     abort();
   }
   launched.push_back(name);
+  // (no kernel uses more dynamic LDS than it was launched with)
+  unsigned char* dyn[] = {hull::dyn_lds, (unsigned char*)hull::range_lds, (unsigned char*)hull::best};
+  const size_t guard = std::min<size_t>(sizeof hull::dyn_lds - lds, 8192);
+  for (auto d : dyn) memset(d + lds, 0x6b, guard);
   g.body = std::move(body);
   g.grid = grid;
   g.block = block;
@@ -165,6 +169,12 @@ void launch(dim3 grid, dim3 block, size_t lds, std::function<void()> body, const
       g.block_idx = dim3(up ? x : grid.x - 1 - x, y);
       run_block(name);
     }
+  for (auto d : dyn)
+    for (size_t q = 0; q < guard; ++q)
+      if (d[lds + q] != 0x6b) {
+        fprintf(stderr, "emu: %s writes past its dynamic LDS\n", name);
+        abort();
+      }
 }
 }  // namespace emu
 

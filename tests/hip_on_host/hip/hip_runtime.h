@@ -202,6 +202,7 @@ inline unsigned __float_as_uint(float x) { return (unsigned)emu::bits(x); }
 inline long long __double_as_longlong(double x) { return (long long)emu::bits(x); }
 inline double __longlong_as_double(long long x) { return emu::value<double>((unsigned long long)x); }
 inline int __popcll(unsigned long long x) { return __builtin_popcountll(x); }
+inline int __popc(unsigned x) { return __builtin_popcount(x); }
 inline int __ffsll(unsigned long long x) { return __builtin_ffsll((long long)x); }
 
 template <class T, class U>

@@ -349,3 +349,46 @@ def test_many_tiny_clouds(lds_levels, monkeypatch):
     for k in range(720):
         got, want = validate.canonical(f[fo[k]:fo[k + 1]]), validate.canonical(oracle.hull(parts[k]))
         assert got.shape == want.shape and (got == want).all(), k
+
+
+# Lists of link changes as long as the movies: in LDS, by atomics, by bins of both
+# sizes and by ranges; the largest beside the lane-serial merges, which have no
+# lists.
+@pytest.mark.parametrize("n", [700, 9000, 140000, (1 << 19) + 5])
+def test_points_of_high_degree(n, monkeypatch):
+    import oracle
+    import torch
+    from oracle import validate
+    from paper_1205_1171_amd import hull
+    from test_kernels_on_host import hubs
+    p = hubs(np.random.default_rng(n), n)
+    x = torch.from_numpy(p).cuda()
+    say("high degree", n)
+    got = [validate.canonical(hull.hull_sync(x).cpu().numpy()),
+           validate.canonical(hull.hull_wide(x.to(torch.int64)).cpu().numpy())]
+    if n <= 9000:
+        want = oracle.hull(p)
+    else:
+        say("high degree: lane-serial", n)
+        monkeypatch.setenv("HULL_SERIAL_LEVELS", "99")
+        monkeypatch.setenv("HULL_WAVE_LEVEL", "-1")
+        want = hull.hull_sync(x).cpu().numpy()
+    want = validate.canonical(want)
+    for f in got:
+        assert f.shape == want.shape and (f == want).all()
+
+
+# The moment curve with exact coordinates: every face joins two neighbours to the
+# first or the last point.
+@pytest.mark.parametrize("half", [100, 1000, 16000])
+def test_moment_curve_wide(half):
+    import torch
+    from paper_1205_1171_amd import hull
+    t = np.arange(-half, half + 1, dtype=np.int64)
+    n = len(t)
+    i = np.arange(n - 1)
+    want = np.sort(np.concatenate([np.stack([np.zeros(n - 2, np.int64), i[1:], i[1:] + 1], 1),
+                                   np.stack([i[:-1], i[:-1] + 1, np.full(n - 2, n - 1)], 1)]), 1)
+    say("moment curve", n)
+    got = np.sort(hull.hull_wide(torch.from_numpy(np.stack([t, t * t, t * t * t], 1)).cuda()).cpu().numpy(), 1)
+    assert (got[np.lexsort(got.T)] == want[np.lexsort(want.T)]).all()

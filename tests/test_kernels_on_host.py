@@ -80,3 +80,25 @@ def test_adjacency_rows_past_the_offsets(face_off):
         st, adj, open_edges = hip_on_host.face_adjacency(
             faces, off, np.array([0, 132, 264], np.int64), descending)
         assert st == 0 and (adj == want).all() and open_edges == (want < 0).sum()
+
+
+def hubs(rng, n):
+    """Two points of high degree side by side over a circle of n - 2 points."""
+    r = 1 << 28
+    t = np.linspace(0, 2 * np.pi, n, endpoint=False)
+    p = np.stack([r - rng.integers(0, 1000, n), r * np.cos(t), r * np.sin(t)], 1)[rng.permutation(n)]
+    p[n // 3], p[n // 2] = (-r, 3, 5), (-r + 9, -7, 11)
+    return p.astype(np.int32)
+
+
+# Lists of link changes as long as the movies, sorted by their workgroup: in LDS, and
+# in global memory below and above the length that is sorted by rank.
+@pytest.mark.parametrize("tile", ["11", "0"])
+@pytest.mark.parametrize("n", [90, 700, 5000])
+def test_points_of_high_degree(n, tile, monkeypatch):
+    monkeypatch.setenv("HULL_TILE_LEVELS", tile)
+    monkeypatch.setenv("HULL_SERIAL_LEVELS", "3")
+    p = hubs(np.random.default_rng(n), n)
+    want = oracle.hull(p)
+    for descending in (False, True):
+        assert same(hip_on_host.hull(p, descending=descending), want)
