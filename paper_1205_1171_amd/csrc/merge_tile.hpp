@@ -390,7 +390,6 @@ __device__ __forceinline__ void tile_merge(const GRP& g, unsigned char* lds, int
   }
 }
 
-#ifndef HULL_HOST_EMULATION
 // GL lanes of a wavefront (GL = 16, 32 or 64).
 template <int GL>
 struct LaneGroup {
@@ -480,6 +479,5 @@ __global__ void __launch_bounds__(GS < 64 ? 64 : GS) k_merge_tile(LevelArgs A, i
     }
   }
 }
-#endif
 
 }  // namespace hull
