@@ -9,14 +9,16 @@
 //   2. list bounds by a scan over the points, then the entries: the event's
 //      position in its child movie and the link after it.  Lists of up to
 //      kParScan entries stay in arrival order (a lookup reads them whole);
-//      longer ones are sorted by position;
+//      longer ones are sorted by position, the longest by a whole workgroup;
 //   3. a counting walk per segment, a scan, and a writing walk that replays
 //      the counted steps.  A segment's output is in order, so the level needs
 //      no classification of the child events and no ranks of events in other
 //      lists.
 // Where many points take part, steps 1 and 2 run per range of points in LDS instead
 // (k_list_count, k_list_fill; the largest blocks: k_bin, k_bin_lists).
-// A level is nine launches.  Claiming lists by events, filling and sorting
+// A level is 10 launches with lists by atomics or by ranges and 11 by bins; where only
+// the device knows the number of points, the last two have those of the atomics (3)
+// as well.  Claiming lists by events, filling and sorting
 // 16-byte entries, a separate bridge list, survival flags and three more scans
 // took 1.70-2.25 ms a level on the 2^20-point sphere,
 // this 0.36-0.55 ms.
@@ -170,8 +172,8 @@ __device__ void sort_entries(int2* a, int k) {
 }
 
 // Longer lists (a vertex of high degree has one as long as the movie) are noted in LDS
-// and sorted by the whole workgroup, one after the other.  By one thread each, a cone over
-// 16,384 points took 21 ms, a moment curve 84.
+// and sorted by the whole workgroup, one after the other: a cone over 16,384 points
+// 1.8 ms, a moment curve 31; by one thread each 21 and 84.
 constexpr int kParSerial = 128;
 constexpr int kParRank = 1024;   // longest list whose entries count the smaller ones
 constexpr int kLongLists = 64;   // noted at a time
@@ -186,7 +188,7 @@ constexpr int sort_words(int T) { return 5 * T; }  // LDS of sort_long, lists ab
 // number of bits before its own.  tmp: space for the list; the positions are below
 // `limit`.
 template <int T, class G>
-__device__ void sort_long(const G& g, unsigned* lds, int2* a, int2* tmp, int k, int64_t limit) {
+__device__ void sort_long(const G& g, unsigned* lds, int2* a, int2* tmp, int k, int limit) {
   const int t = threadIdx.x;
   if (k <= kParRank) {
     for (int i = t; i < k; i += T) {
@@ -201,11 +203,11 @@ __device__ void sort_long(const G& g, unsigned* lds, int2* a, int2* tmp, int k, 
     unsigned* bits = lds;             // [4 T]
     int* before = (int*)(lds + 4 * T);  // [T]
     int done = 0;
-    for (int64_t lo = 0; done < k && lo < limit; lo += window) {
+    for (int lo = 0; done < k && lo < limit; lo += window) {
       for (int q = t; q < 4 * T; q += T) bits[q] = 0;
       __syncthreads();
       for (int i = t; i < k; i += T) {
-        const unsigned x = (unsigned)(a[i].x - (int)lo);
+        const unsigned x = (unsigned)(a[i].x - lo);
         if (x < (unsigned)window) atomicOr(&bits[x >> 5], 1u << (x & 31));
       }
       __syncthreads();
@@ -215,7 +217,7 @@ __device__ void sort_long(const G& g, unsigned* lds, int2* a, int2* tmp, int k, 
       __syncthreads();
       for (int i = t; i < k; i += T) {
         const int2 e = a[i];
-        const unsigned x = (unsigned)(e.x - (int)lo);
+        const unsigned x = (unsigned)(e.x - lo);
         if (x >= (unsigned)window) continue;
         const int w = x >> 5;
         int r = before[w >> 2] + __popc(bits[w] & ((1u << (x & 31)) - 1));
@@ -236,7 +238,7 @@ __device__ void sort_long(const G& g, unsigned* lds, int2* a, int2* tmp, int k, 
 // fit, and a bin's records there have been read to the end by its own block).
 template <int T, class G, class LIST>
 __device__ __forceinline__ void sort_lists(const G& g, LongLists& S, unsigned* lds, const ParLevel& P,
-                                           const ParRun& Q, int64_t q, int64_t step, int64_t keys,
+                                           const ParRun& Q, int q, int step, int keys,
                                            const LIST& list) {
   int2 *ent = Q.ent, *tmp = (int2*)Q.segKeep;
   for (;;) {
@@ -253,7 +255,7 @@ __device__ __forceinline__ void sort_lists(const G& g, LongLists& S, unsigned* l
     __syncthreads();
     const int count = S.count;
     for (int i = 0; i < count && i < kLongLists; ++i)
-      sort_long<T>(g, lds, ent + S.list[i].x, tmp + S.list[i].x, S.list[i].y, 2 * P.n);
+      sort_long<T>(g, lds, ent + S.list[i].x, tmp + S.list[i].x, S.list[i].y, 2 * (int)P.n);
     __syncthreads();
     if (threadIdx.x == 0) S.count = 0;
     if (count <= kLongLists) return;
@@ -537,7 +539,7 @@ __global__ void __launch_bounds__(T) k_list_fill(ParLevel P) {
     // (longer lists than kParRank come from level 11 on, whose ranges have 16 T words)
     static_assert(16 * T >= sort_words(T) && kParRank >= 1 << 10, "");
     const int end = before[pair + 1];
-    sort_lists<T>(g, S, (unsigned*)range_lds, P, Q, threadIdx.x, T, keys, [&](int64_t q) {
+    sort_lists<T>(g, S, (unsigned*)range_lds, P, Q, threadIdx.x, T, keys, [&](int q) {
       return make_int2(off[q], (q + 1 < keys ? off[q + 1] : end) - off[q]);
     });
   }
@@ -652,7 +654,7 @@ __global__ void __launch_bounds__(T) k_bin_lists(ParLevel P) {
     __syncthreads();
     for (int q = first + threadIdx.x; q < end; q += T) Q.ent[atomicAdd(&cnt[B.list[q]], 1)] = B.rec[q];
     __syncthreads();
-    sort_lists<T>(g, S, (unsigned*)range_lds, P, Q, threadIdx.x, T, keys, [&](int64_t q) {
+    sort_lists<T>(g, S, (unsigned*)range_lds, P, Q, threadIdx.x, T, keys, [&](int q) {
       return make_int2(off[q], (q + 1 < keys ? off[q + 1] : end) - off[q]);
     });
   }
@@ -668,9 +670,8 @@ __global__ void __launch_bounds__(256) k_par_sort(ParLevel P) {
   if (threadIdx.x == 0) S.count = P.h->err ? -1 : 0;  // (one reading for the whole block)
   __syncthreads();
   if (S.count < 0) return;
-  sort_lists<256>(BlockGroup<256>{wsum}, S, lds, P, Q, blockIdx.x * (int64_t)256 + threadIdx.x,
-                  (int64_t)gridDim.x * 256, (int64_t)Q.ctr[kCtrKeys] - 1,
-                  [&](int64_t q) { return make_int2(Q.off[q], Q.off[q + 1] - Q.off[q]); });
+  sort_lists<256>(BlockGroup<256>{wsum}, S, lds, P, Q, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256,
+                  Q.ctr[kCtrKeys] - 1, [&](int q) { return make_int2(Q.off[q], Q.off[q + 1] - Q.off[q]); });
 }
 
 // A counting walk: its steps, and its first kSegKeep bridge events put aside.

@@ -170,8 +170,8 @@ __device__ __forceinline__ void sort_positions(unsigned short* a, int k) {
 
 // Sorts a list of up to 4 x the group's size by the whole group (a vertex of high
 // degree has one as long as the movie; the positions differ, so an entry's place is
-// the number of smaller ones).  By one lane, with Shell's method, the two such lists
-// of the moment curve of 1,024 points took 3 ms of its 3.8.
+// the number of smaller ones).  A cone over 1,024 points 0.51 ms, a moment curve of as
+// many 2.5; by one lane, with Shell's method, 0.83 and 3.8.
 template <class GRP>
 __device__ __forceinline__ void sort_positions_by(const GRP& g, unsigned short* a, int k) {
   unsigned short x[4];

@@ -1,8 +1,6 @@
 // The scheduler of hip/hip_runtime.h.
 #include <hip/hip_runtime.h>
 
-#include <string>
-
 #include "common.hpp"
 
 namespace hull {
@@ -14,7 +12,6 @@ __align__(16) unsigned long long best[163840 / 8];
 
 namespace emu {
 State g;
-static std::vector<std::string> launched;
 
 asm(R"(
 .text
@@ -152,7 +149,6 @@ void launch(dim3 grid, dim3 block, size_t lds, std::function<void()> body, const
     fprintf(stderr, "emu: %s cannot be launched\n", name);
     abort();
   }
-  launched.push_back(name);
   // (no kernel uses more dynamic LDS than it was launched with)
   unsigned char* dyn[] = {hull::dyn_lds, (unsigned char*)hull::range_lds, (unsigned char*)hull::best};
   const size_t guard = std::min<size_t>(sizeof hull::dyn_lds - lds, 8192);
@@ -180,15 +176,6 @@ void launch(dim3 grid, dim3 block, size_t lds, std::function<void()> body, const
 
 // 0: threads and workgroups in ascending order, 1: in descending order.
 extern "C" void emu_order(int descending) { emu::g.descending = descending != 0; }
-// The launches since the last call, one name a line.
-extern "C" const char* emu_launched() {
-  static std::string text;
-  text.clear();
-  for (const auto& s : emu::launched) text += s + "\n";
-  emu::launched.clear();
-  return text.c_str();
-}
-
 // Extent and filter, whatever the number of points.
 extern "C" int emu_filter(const int32_t* xyz, int64_t n, char* ws, size_t bytes) {
   const hull::Plan pl = hull::make_plan(n, 1);
