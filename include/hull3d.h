@@ -102,9 +102,9 @@ int32_t hull_full_timed(const int32_t* d_xyz, int64_t n, int32_t* d_faces, int64
 /* The same two calls on the wide coordinate range: int64 rows [n, 3] with
  * |x|, |y| <= 2^30 and |z| <= 2^42 (beyond the standard range of 2^29; for
  * instance lifted points (x, y, x^2 + y^2) with |x|, |y| <= 2^20).  Same
- * method, same perturbation and the same result definition; the orientation
- * products are taken in int128, and exact ties of the double filter go to
- * the full 256-bit cascade.  A coordinate outside the range gives HULL_ERANGE
+ * method, same perturbation and the same result definition.  Near ties of the
+ * filter go to int128 where the leading terms are short enough for their
+ * products, the others to the full 256-bit cascade.  A coordinate outside the range gives HULL_ERANGE
  * in d_info[0].  Workspace: hull_workspace_bytes(n, HULL_WS_WIDE).  The
  * paper keeps float coordinates (Sec. 3, Fig. "point_datatypes"); the wide
  * range is what float input snapped to a 30-bit lattice needs. */
@@ -284,8 +284,9 @@ int32_t hull_adjacency_workspace_bytes(int64_t F, size_t* bytes);
  *   d_ws       workspace of hull_adjacency_workspace_bytes(F) bytes
  * F may be at most (2^31 - 3) / 3 (half-edge ids 3f + k are int32); larger F
  * returns HULL_EINVAL here and from hull_adjacency_workspace_bytes.
- * A hash table of directed edges in the workspace: one insertion pass, one
- * lookup pass (deterministic result). */
+ * Rows before the first or past the last face offset count to the first or the
+ * last cloud.  A hash table of undirected edges in the workspace, matched in one
+ * pass (deterministic result). */
 int32_t hull_face_adjacency(const int32_t* d_faces, int64_t F, const int64_t* d_face_off,
                             const int64_t* d_pt_off, int64_t H, int32_t* d_adj, int64_t* d_info,
                             void* d_ws, size_t ws_bytes, void* stream);
