@@ -172,13 +172,15 @@ struct LevelArgs {
   int sel;
 };
 // Exact (time, rank triple) order of two events (cold path).  Arguments
-// go by value so that callers keep their candidates in registers.
+// go by value so that callers keep their candidates in registers.  lead: what
+// lead_cmp gave (its three coefficients are not taken again where they vanish).
+constexpr int kLeadOpen = 2;
 template <class PT>
-__device__ __noinline__ int tri_cmp_exact(const PT* pts, Tri A, Tri B, int zs) {
+__device__ __noinline__ int tri_cmp_exact(const PT* pts, Tri A, Tri B, int zs, int lead) {
   Coef ca, cb;
   coef_of(pts[A.a], pts[A.w], pts[A.b], zs, ca);
   coef_of(pts[B.a], pts[B.w], pts[B.b], zs, cb);
-  int s = tau_cmp_exact(ca, cb);
+  int s = tau_cmp_exact(ca, cb, lead == 0 ? 3 : 0);
   if (s) return s;
   if (A.a != B.a) return A.a < B.a ? -1 : 1;
   if (A.w != B.w) return A.w < B.w ? -1 : 1;
@@ -212,8 +214,8 @@ __device__ __forceinline__ Lead lead_of(int4 P, int4 Q, int4 R, int zs) {
 // points with equal x (all triples on such a pair share a standard part),
 // with no 256-bit arithmetic; only when all three vanish (or D0 = D1 = 0)
 // does the full cascade run.
-// Sign of tau_A - tau_B from coefficients 1-3 of both leading terms; 0 when
-// they do not decide (all three vanish, or D0 = D1 = 0 on a side).
+// Sign of tau_A - tau_B from coefficients 1-3 of both leading terms; 0 when all
+// three vanish, kLeadOpen when they cannot be taken (D0 = D1 = 0 on a side).
 __device__ __forceinline__ int lead_cmp(const Lead& a, const Lead& b) {
   const int sa = a.d0 ? (a.d0 > 0 ? 1 : -1) : (a.d1 > 0) - (a.d1 < 0);
   const int sb = b.d0 ? (b.d0 > 0 ? 1 : -1) : (b.d1 > 0) - (b.d1 < 0);
@@ -223,15 +225,15 @@ __device__ __forceinline__ int lead_cmp(const Lead& a, const Lead& b) {
       p = (i128)a.n0 * b.d1 + (i128)a.n1 * b.d0 - (i128)b.n0 * a.d1 - (i128)b.n1 * a.d0;
       if (!p) p = (i128)a.n1 * b.d1 - (i128)b.n1 * a.d1;
     }
-    if (p) return (p > 0 ? 1 : -1) * sa * sb;
+    return p ? (p > 0 ? 1 : -1) * sa * sb : 0;
   }
-  return 0;
+  return kLeadOpen;
 }
 
 __device__ __forceinline__ int tri_cmp_mid_body(const int4* pts, Tri A, Tri B, int zs) {
   const int s = lead_cmp(lead_of(pts[A.a], pts[A.w], pts[A.b], zs),
                          lead_of(pts[B.a], pts[B.w], pts[B.b], zs));
-  return s ? s : tri_cmp_exact(pts, A, B, zs);
+  return s == 1 || s == -1 ? s : tri_cmp_exact(pts, A, B, zs, s);
 }
 
 // The same on the wide range, where D0, N0, D1, N1 need int128 and their
@@ -274,15 +276,15 @@ __device__ __forceinline__ int lead_cmp(const WLead& a, const WLead& b) {
       p = a.n0 * b.d1 + a.n1 * b.d0 - b.n0 * a.d1 - b.n1 * a.d0;
       if (!p) p = a.n1 * b.d1 - b.n1 * a.d1;
     }
-    if (p) return (p > 0 ? 1 : -1) * sa * sb;
+    return p ? (p > 0 ? 1 : -1) * sa * sb : 0;
   }
-  return 0;
+  return kLeadOpen;
 }
 
 __device__ __forceinline__ int tri_cmp_mid_body(const WPt* pts, Tri A, Tri B, int zs) {
   const int s = lead_cmp(lead_of(pts[A.a], pts[A.w], pts[A.b], zs),
                          lead_of(pts[B.a], pts[B.w], pts[B.b], zs));
-  return s ? s : tri_cmp_exact(pts, A, B, zs);
+  return s == 1 || s == -1 ? s : tri_cmp_exact(pts, A, B, zs, s);
 }
 
 // Order of two events that the filter on stored times cannot tell apart:
@@ -318,7 +320,7 @@ __device__ __forceinline__ int ev_cmp_half(const PT* pts, const Cand& A, const P
   if (s) return s;
   if (A.t.a == B.t.a && A.t.w == B.t.w && A.t.b == B.t.b) return 0;
   const int m = lead_cmp(lead_of(a0, a1, a2, zs), lead_of(pts[B.t.a], pts[B.t.w], pts[B.t.b], zs));
-  return m ? m : tri_cmp_exact(pts, A.t, B.t, zs);
+  return m == 1 || m == -1 ? m : tri_cmp_exact(pts, A.t, B.t, zs, m);
 }
 
 // Perturbed sign of D when D0 = D1 = 0 (cold path).

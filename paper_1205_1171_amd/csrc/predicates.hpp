@@ -183,13 +183,14 @@ __device__ __noinline__ void coef_of(PT P, PT Q, PT R, int zs, Coef& c) {
 //   e2e3    : N3 D2
 //   e1e2e3  : N3 D12 + N13 D2
 //   e1^2e2e3: N13 D12
-__device__ __noinline__ int tau_cmp_exact(const Coef& A, const Coef& B) {
+// `from`: the first that is not known to vanish.
+__device__ __noinline__ int tau_cmp_exact(const Coef& A, const Coef& B, int from) {
   // index pairs (N term, D term) per monomial; -1 = unused second pair
   const signed char tab[12][4] = {
       {0, 0, -1, -1}, {0, 1, 1, 0}, {1, 1, -1, -1}, {0, 2, -1, -1},
       {0, 3, 1, 2},   {1, 3, -1, -1}, {2, 0, -1, -1}, {2, 1, 3, 0},
       {3, 1, -1, -1}, {2, 2, -1, -1}, {2, 3, 3, 2},   {3, 3, -1, -1}};
-  for (int m = 0; m < 12; ++m) {
+  for (int m = from; m < 12; ++m) {
     W256 acc = w_zero();
     for (int t = 0; t < 2; ++t) {
       int ni = tab[m][2 * t], di = tab[m][2 * t + 1];
