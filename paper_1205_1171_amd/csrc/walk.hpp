@@ -197,17 +197,38 @@ __device__ __forceinline__ bool walk(const CX& X, int u, int v, int i, int iE, i
       nn[k] = zs * det2(q.x, r.z, r.x, q.z);
       st[k] = quotient(nn[k], dd[k]);
     }
+    // What needs a call is gathered first: a wavefront then calls as often as its
+    // lane with the most, not once for each of the four.  Points on lattices, where
+    // ties are everywhere: 300 points of 60^3 911 -> 897 us, flat 30,000 the same,
+    // duplicates 19.5 -> 18.1 ms; 2^20 sphere 7.64 -> 7.60 (four registers fewer).
+    const auto move = [&](int k) {
+      return Tri{k == 1 ? pu : u, k == 0 ? nu : (k == 1 ? u : (k == 2 ? pvv : v)), k == 3 ? nv : v};
+    };
+    unsigned flat = 0, amb = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       ok[k] = lk[k] >= 0;
-      if (ok[k] && dd[k] == 0)
-        st[k] = tau_std_call(pts, tr[k], nn[k], zs);
-      if (haveT) {
+      flat |= (unsigned)(ok[k] && dd[k] == 0) << k;
+    }
+    for (; flat; flat &= flat - 1) {
+      const int f = __builtin_ctz(flat);
+      const double x = tau_std_call(pts, move(f), f == 0 ? nn[0] : (f == 1 ? nn[1] : (f == 2 ? nn[2] : nn[3])), zs);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) st[k] = f == k ? x : st[k];
+    }
+    if (haveT) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
         const int c = std_cmp(st[k], T.st);
         const bool same = T.t.a == tr[k].a && T.t.w == tr[k].w && T.t.b == tr[k].b;
-        const bool amb = ok[k] && c == 0 && !same;
+        amb |= (unsigned)(ok[k] && c == 0 && !same) << k;
         ok[k] = ok[k] && c > 0;
-        if (amb) ok[k] = tri_cmp_near(pts, tr[k], T.t, zs) > 0;
+      }
+      for (; amb; amb &= amb - 1) {
+        const int f = __builtin_ctz(amb);
+        const bool after = tri_cmp_near(pts, move(f), T.t, zs) > 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ok[k] = f == k ? after : ok[k];
       }
     }
     // the earliest valid one
