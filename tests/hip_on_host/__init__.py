@@ -68,7 +68,7 @@ def filter_rc(p):
     return L.emu_filter(_p(p), ctypes.c_int64(n), _p(ws), size)
 
 
-def hull(p, entry="hull_full", descending=False, fill=0xA5):
+def hull(p, entry="hull_full", order=0, fill=0xA5):
     """Faces of int32 (int64: wide) points by an entry point of single hulls."""
     L = lib()
     wide = p.dtype == np.int64
@@ -78,14 +78,14 @@ def hull(p, entry="hull_full", descending=False, fill=0xA5):
     ws = _workspace(size.value, fill)
     faces = np.full((max(2 * n, 1), 3), -9, np.int32)
     info = np.full(2, -9, np.int64)
-    L.emu_order(int(descending))
+    L.emu_order(int(order))
     rc = getattr(L, entry + ("_wide" if wide else ""))(
         _p(p), ctypes.c_int64(n), _p(faces), ctypes.c_int64(2 * n), _p(info), _p(ws), size, None)
     assert rc == 0 and info[0] == 0, (rc, info)
     return faces[:info[1]]
 
 
-def hull_batched(parts, descending=False, fill=0xA5, schedule=None):
+def hull_batched(parts, order=0, fill=0xA5, schedule=None):
     """Faces and face offsets of a batch of int32 clouds."""
     L = lib()
     off = np.cumsum([0] + [len(p) for p in parts]).astype(np.int64)
@@ -97,7 +97,7 @@ def hull_batched(parts, descending=False, fill=0xA5, schedule=None):
     faces = np.full((2 * n, 3), -9, np.int32)
     face_off = np.full(H + 1, -9, np.int64)
     info = np.full(2, -9, np.int64)
-    L.emu_order(int(descending))
+    L.emu_order(int(order))
     rc = L.hull_full_batched(_p(x), _p(off), _p(off), ctypes.c_int64(H), _p(faces), ctypes.c_int64(2 * n),
                              _p(face_off), _p(info), _p(ws), size,
                              ctypes.byref(schedule) if schedule is not None else None, None)
@@ -105,7 +105,7 @@ def hull_batched(parts, descending=False, fill=0xA5, schedule=None):
     return faces[:info[1]], face_off
 
 
-def face_adjacency(faces, face_off=None, pt_off=None, descending=False):
+def face_adjacency(faces, face_off=None, pt_off=None, order=0):
     """(status, adjacency rows, edges without a twin) of face rows."""
     L = lib()
     F = len(faces)
@@ -114,7 +114,7 @@ def face_adjacency(faces, face_off=None, pt_off=None, descending=False):
     ws = _workspace(size.value, 0xA5)
     adj = np.full((max(F, 1), 3), -9, np.int32)
     info = np.full(2, -9, np.int64)
-    L.emu_order(int(descending))
+    L.emu_order(int(order))
     H = 1 if face_off is None else len(face_off) - 1
     assert L.hull_face_adjacency(
         _p(faces), ctypes.c_int64(F), _p(face_off) if face_off is not None else None,

@@ -1,6 +1,9 @@
 // The scheduler of hip/hip_runtime.h.
 #include <hip/hip_runtime.h>
 
+#include <numeric>
+#include <random>
+
 #include "common.hpp"
 
 namespace hull {
@@ -107,7 +110,7 @@ static bool settle_wave(int w0, std::vector<Fiber*>& ready) {
     }
   }
   for (int k = 0; k < 64; ++k) {
-    const int l = g.descending ? 63 - k : k;
+    const int l = g.order ? 63 - k : k;
     if (!((peers >> l) & 1)) continue;
     Fiber* f = g.of[w0 + l];
     f->peers = peers;
@@ -117,8 +120,11 @@ static bool settle_wave(int w0, std::vector<Fiber*>& ready) {
   return true;
 }
 
+static std::mt19937 rng;  // (the same orders in every run)
+
 static void run_block(const char* name) {
   g.next = 0;
+  if (g.order == 2) std::shuffle(g.shuffle.begin(), g.shuffle.end(), rng);
   std::vector<Fiber*> ready;
   for (;;) {
     while (g.next < g.threads) resume(idle_fiber());
@@ -140,6 +146,7 @@ static void run_block(const char* name) {
         abort();
       }
     }
+    if (g.order == 2) std::shuffle(ready.begin(), ready.end(), rng);
     for (Fiber* f : ready) resume(f);
   }
 }
@@ -158,11 +165,17 @@ void launch(dim3 grid, dim3 block, size_t lds, std::function<void()> body, const
   g.block = block;
   g.threads = (int)block.x;
   g.of.assign(block.x, nullptr);
-  // (a chained scan waits for the blocks before its own)
-  const bool up = !g.descending || strstr(name, "scan");
+  g.shuffle.resize(block.x);
+  std::iota(g.shuffle.begin(), g.shuffle.end(), 0);
+  std::vector<unsigned> blocks(grid.x);
+  std::iota(blocks.begin(), blocks.end(), 0u);
+  if (!strstr(name, "scan")) {  // (a chained scan waits for the blocks before its own)
+    if (g.order == 1) std::reverse(blocks.begin(), blocks.end());
+    if (g.order == 2) std::shuffle(blocks.begin(), blocks.end(), rng);
+  }
   for (unsigned y = 0; y < grid.y; ++y)
-    for (unsigned x = 0; x < grid.x; ++x) {
-      g.block_idx = dim3(up ? x : grid.x - 1 - x, y);
+    for (unsigned x : blocks) {
+      g.block_idx = dim3(x, y);
       run_block(name);
     }
   for (auto d : dyn)
@@ -174,8 +187,8 @@ void launch(dim3 grid, dim3 block, size_t lds, std::function<void()> body, const
 }
 }  // namespace emu
 
-// 0: threads and workgroups in ascending order, 1: in descending order.
-extern "C" void emu_order(int descending) { emu::g.descending = descending != 0; }
+// Threads and workgroups in ascending (0), descending (1) or shuffled (2) order.
+extern "C" void emu_order(int order) { emu::g.order = order; }
 // Extent and filter, whatever the number of points.
 extern "C" int emu_filter(const int32_t* xyz, int64_t n, char* ws, size_t bytes) {
   const hull::Plan pl = hull::make_plan(n, 1);

@@ -1,7 +1,7 @@
 // The library's kernels on the CPU, for tests of what a GPU's scheduling may do:
 // every thread of a workgroup is a fiber, and threads and workgroups run in
-// ascending or descending order (emu_order), so that the arrival order of atomics
-// is the test's choice.  A fiber runs until it ends or waits: at __syncthreads for
+// ascending, descending or shuffled order (emu_order), so that the arrival order of
+// atomics is the test's choice.  A fiber runs until it ends or waits: at __syncthreads for
 // every live thread of its workgroup, at a wave operation (shuffle, ballot,
 // wave barrier) for every lane of its wave that can still come to the same place.
 // Only what the library's sources use is here.  x86-64.
@@ -85,9 +85,10 @@ struct State {
   Fiber* cur = nullptr;
   void* main_sp = nullptr;
   int next = 0, threads = 0;  // threads started, of how many
-  bool descending = false;
+  int order = 0;  // 0 ascending, 1 descending, 2 shuffled
+  std::vector<int> shuffle;  // of the workgroup's threads
   dim3 block_idx, grid, block;
-  int thread_of(int k) const { return descending ? threads - 1 - k : k; }
+  int thread_of(int k) const { return order == 2 ? shuffle[k] : (order ? threads - 1 - k : k); }
 };
 extern State g;
 extern "C" void emu_switch(void** save, void* to);

@@ -32,8 +32,8 @@ def cone_with_interior(rng, rim, n):
 def test_first_events_place(n, rim, seed):
     p = cone_with_interior(np.random.default_rng(seed), rim, n)
     want = oracle.hull(p[:rim + 1])
-    for descending in (False, True):
-        assert same(hip_on_host.hull(p, descending=descending, fill=0), want), descending
+    for order in (0, 1, 2):
+        assert same(hip_on_host.hull(p, order=order, fill=0), want), order
 
 
 # The host's bound counts many merges at level 4, the device few: one of the two
@@ -76,9 +76,9 @@ def test_adjacency_rows_past_the_offsets(face_off):
         for (a, b), f in edge.items():
             k = [int(v) for v in faces[f]].index(a)
             want[f, k] = edge.get((b, a), -1)
-    for descending in (False, True):
+    for order in (0, 1, 2):
         st, adj, open_edges = hip_on_host.face_adjacency(
-            faces, off, np.array([0, 132, 264], np.int64), descending)
+            faces, off, np.array([0, 132, 264], np.int64), order)
         assert st == 0 and (adj == want).all() and open_edges == (want < 0).sum()
 
 
@@ -100,5 +100,5 @@ def test_points_of_high_degree(n, tile, monkeypatch):
     monkeypatch.setenv("HULL_SERIAL_LEVELS", "3")
     p = hubs(np.random.default_rng(n), n)
     want = oracle.hull(p)
-    for descending in (False, True):
-        assert same(hip_on_host.hull(p, descending=descending), want)
+    for order in (0, 1, 2):
+        assert same(hip_on_host.hull(p, order=order), want)
