@@ -25,7 +25,7 @@ def _build(out):
             with open(os.path.join(csrc, name), "w") as fh:  # dynamic LDS: one array for all
                 fh.write(text.replace("extern __shared__", "extern"))
     so = os.path.join(out, "libhull3d_host.so")
-    flags = ["g++", "-std=c++17", "-O2", "-g1", "-fPIC", "-ffp-contract=off", "-mfma", "-w", "-fno-strict-aliasing",
+    flags = ["g++", "-std=c++17", "-O2", "-g1", "-fPIC", "-ffp-contract=off", "-w", "-fno-strict-aliasing",
              "-I", HERE]
     objs, jobs = [], []
     for s in [os.path.join(csrc, n) for n in SOURCES] + [os.path.join(HERE, "emu.cpp")]:
